@@ -4,6 +4,8 @@
 
 #include <hip/hip_ext.h>
 
+#include <algorithm>
+
 #include "kv_cache.hpp"
 
 namespace hetis {
@@ -47,6 +49,10 @@ static int check_pool(const hetis_kv_pool *pl, KvChecked *c)
     return HETIS_OK;
 }
 
+// Grid limits of the device: 2^32 threads in x (256 a workgroup), 65535 workgroups in y.
+constexpr int64_t kMaxGridX = (int64_t)1 << 23;
+constexpr int64_t kMaxGridY = 65535;
+
 // Optional events attached to the kernel's dispatch (measurement hook, per host thread):
 // start is stamped when the kernel begins to execute, stop when it has finished.
 static thread_local hipEvent_t t_kv_begin = nullptr;
@@ -62,23 +68,17 @@ static int launch_kv(Kernel kernel, dim3 grid, hipStream_t st, const Params &p)
     return hipGetLastError() == hipSuccess ? HETIS_OK : HETIS_ERR_LAUNCH;
 }
 
-// Threads of one launch of the row kernel are spread over entries (x) and, while the grid
-// is small, over the selected heads (y), so that a decode-step store of a few thousand rows
-// still fills the device.
+// One workgroup per (selected head, group of entries), within the limits of a grid.
 static int launch_rows(bool fetch, const hetis_attn_shape *s, const KvChecked &c, KvRowParams p,
                        hipStream_t st)
 {
     const int D = s->head_dim;
-    const int lanes_per_entry = 2 * D / 8;
-    const int64_t threads = (int64_t)p.n_tokens * lanes_per_entry;
-    const int64_t gx = (threads + 255) / 256;
-    if (gx > 0x7fffffff) return HETIS_ERR_UNSUPPORTED;
-    int64_t gy = (262144 + threads - 1) / threads;
-    if (gy > p.n_sel) gy = p.n_sel;
-    if (gy < 1) gy = 1;
+    const int64_t per_wg = D == 128 ? kKvRowsPerWg<128> : kKvRowsPerWg<64>;
+    const int64_t groups = (p.n_tokens + per_wg - 1) / per_wg;
     p.stride_block = c.stride_block / 8;
     p.stride_head = c.stride_head / 8;
-    const dim3 grid((unsigned)gx, (unsigned)gy);
+    const dim3 grid((unsigned)std::min<int64_t>(p.n_sel, kMaxGridX),
+                    (unsigned)std::min<int64_t>(groups, kMaxGridY));
     if (D == 128)
         return fetch ? launch_kv(kv_rows_kernel<128, true>, grid, st, p)
                      : launch_kv(kv_rows_kernel<128, false>, grid, st, p);

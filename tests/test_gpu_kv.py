@@ -313,3 +313,38 @@ def test_kv_profile_events_bracket_the_launch():
         H.hetis_kv_profile_events(None, None)
     ms = b.elapsed_time(e)
     assert 0.0 < ms < 5.0
+
+
+# ------------------------------------------------------------------ edges of a workgroup's share
+
+@pytest.mark.parametrize("D,n", [(64, 1), (64, 31), (64, 32), (64, 33), (128, 15), (128, 16), (128, 17),
+                                 (128, 16 * 65535 + 5)])
+def test_row_groups(D, n):
+    """Stores and fetches whose entries end around a workgroup's 16 (D = 128) or 32 (D = 64)
+    entries; the last one has more groups than the grid has workgroups in y."""
+    Hkv, heads = 3, [2, 0]
+    lens = [n] if n <= 16384 else [16384] * (n // 16384 + 1)
+    seq = torch.arange(n, device=DEV, dtype=torch.int32) // max(lens)
+    pos = torch.arange(n, device=DEV, dtype=torch.int32) % max(lens)
+    per_seq = (max(lens) + 15) // 16
+    nb = per_seq * len(lens)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(40)
+    table = torch.randperm(nb, generator=gen, device=DEV).int().view(len(lens), per_seq)
+    kn, vn = (torch.randint(-30000, 30000, (n, Hkv, D), generator=gen, device=DEV, dtype=torch.int16)
+              for _ in range(2))
+    shape = H.make_shape(len(lens), Hkv, Hkv, D, per_seq)
+    hid = torch.tensor(heads, device=DEV)
+    k, v = (torch.full((nb, Hkv, 16, D), 77, device=DEV, dtype=torch.int16) for _ in range(2))
+    H.check(H.hetis_kv_store(shape, kn, vn, seq, pos, n, table, hid.int(), len(heads), nb, k, v), "store")
+    blk, slot = table[seq.long(), pos.long() // 16].long(), pos.long() % 16
+    k2, v2 = (torch.full((n, Hkv, D), 77, device=DEV, dtype=torch.int16) for _ in range(2))
+    H.check(H.hetis_kv_fetch(shape, k, v, seq, pos, n, table, hid.int(), len(heads), nb, k2, v2), "fetch")
+    for new, cache, back in ((kn, k, k2), (vn, v, v2)):
+        ref = torch.full_like(cache, 77)
+        for h in heads:
+            ref[blk, h, slot] = new[:, h]
+        assert torch.equal(cache, ref)
+        want = torch.full_like(new, 77)
+        want[:, heads] = new[:, heads]
+        assert torch.equal(back, want)
