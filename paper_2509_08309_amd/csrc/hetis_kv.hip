@@ -58,11 +58,14 @@ constexpr int64_t kMaxGridY = 65535;
 static thread_local hipEvent_t t_kv_begin = nullptr;
 static thread_local hipEvent_t t_kv_end = nullptr;
 
+// `first` / `last`: of the launches of one call.
 template <class Kernel, class Params>
-static int launch_kv(Kernel kernel, dim3 grid, hipStream_t st, const Params &p)
+static int launch_kv(Kernel kernel, dim3 grid, hipStream_t st, const Params &p, bool first = true,
+                     bool last = true)
 {
     if (t_kv_begin)
-        hipExtLaunchKernelGGL(kernel, grid, dim3(256), 0, st, t_kv_begin, t_kv_end, 0, p);
+        hipExtLaunchKernelGGL(kernel, grid, dim3(256), 0, st, first ? t_kv_begin : nullptr,
+                              last ? t_kv_end : nullptr, 0, p);
     else
         kernel<<<grid, 256, 0, st>>>(p);
     return hipGetLastError() == hipSuccess ? HETIS_OK : HETIS_ERR_LAUNCH;
@@ -164,7 +167,6 @@ int hetis_kv_append_pairs(const hetis_attn_shape *shape, const void *k_new, cons
     p.pair_head = pair_head;
     p.stride_tile = stride / 8;
     p.num_tiles = num_tiles;
-    p.n_pairs = n_pairs;
     p.n_kv_heads = shape->n_kv_heads;
     p.batch = shape->batch;
     p.max_blocks_per_seq = shape->max_blocks_per_seq;
@@ -217,8 +219,6 @@ int hetis_kv_copy_tiles(const hetis_kv_pool *src_pool, const void *src_k, const 
     p.src_v = (const uint4 *)src_v;
     p.dst_k = (uint4 *)dst_k;
     p.dst_v = (uint4 *)dst_v;
-    p.src_blocks = src_blocks;
-    p.dst_blocks = dst_blocks;
     p.src_heads = src_heads;
     p.dst_heads = dst_heads;
     p.src_stride_block = sc.stride_block / 8;
@@ -227,18 +227,24 @@ int hetis_kv_copy_tiles(const hetis_kv_pool *src_pool, const void *src_k, const 
     p.dst_stride_head = dc.stride_head / 8;
     p.src_num_blocks = src_pool->num_blocks;
     p.dst_num_blocks = dst_pool->num_blocks;
-    p.n_items = (int64_t)n_pairs * n_sel_heads;
     p.n_sel = n_sel_heads;
     p.src_n_heads = src_pool->n_kv_heads;
     p.dst_n_heads = dst_pool->n_kv_heads;
-    // 4 waves per workgroup, one item per wave and step; enough workgroups to fill every
-    // wave slot of the device, no more than there are items
-    int64_t wgs = (p.n_items + 3) / 4;
-    if (wgs > kKvCopyMaxWorkgroups) wgs = kKvCopyMaxWorkgroups;
+    const int tiles_per_wg = kKvCopyThreads / (kKvBlockTokens * src_pool->head_dim / 8);
+    const unsigned gx = (unsigned)((2 * n_sel_heads + tiles_per_wg - 1) / tiles_per_wg);
     const hipStream_t st = (hipStream_t)stream;
-    if (src_pool->head_dim == 128)
-        return launch_kv(kv_copy_tiles_kernel<128>, dim3((unsigned)wgs), st, p);
-    return launch_kv(kv_copy_tiles_kernel<64>, dim3((unsigned)wgs), st, p);
+    // pairs beyond what the grid can number run as launches of their own
+    for (int64_t i0 = 0; i0 < n_pairs; i0 += kMaxGridY) {
+        p.src_blocks = src_blocks + i0;
+        p.dst_blocks = dst_blocks + i0;
+        const dim3 grid(gx, (unsigned)std::min<int64_t>(n_pairs - i0, kMaxGridY));
+        const bool first = i0 == 0, last = i0 + kMaxGridY >= n_pairs;
+        rc = src_pool->head_dim == 128
+                 ? launch_kv(kv_copy_tiles_kernel<128>, grid, st, p, first, last)
+                 : launch_kv(kv_copy_tiles_kernel<64>, grid, st, p, first, last);
+        if (rc != HETIS_OK) return rc;
+    }
+    return HETIS_OK;
 }
 
 int hetis_kv_profile_events(void *begin, void *end)

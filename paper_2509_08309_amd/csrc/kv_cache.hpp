@@ -11,8 +11,6 @@ namespace hetis {
 typedef unsigned int kv_u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kKvBlockTokens = 16;
-// Workgroups of the tile-copy kernel: 256 CUs x 8 resident workgroups of 4 waves.
-constexpr int kKvCopyMaxWorkgroups = 2048;
 
 struct KvRowParams {
     uint4 *rows_k;              // STORE: source rows [n_tokens, Hkv, D]; FETCH: destination
@@ -124,43 +122,37 @@ struct KvCopyParams {
     const int32_t *src_blocks, *dst_blocks, *src_heads, *dst_heads;
     int64_t src_stride_block, src_stride_head, dst_stride_block, dst_stride_head;   // 16-byte units
     int64_t src_num_blocks, dst_num_blocks;
-    int64_t n_items;            // n_pairs * n_sel
     int32_t n_sel, src_n_heads, dst_n_heads;
 };
 
-// One wave moves the K tile and the V tile of one (pair, head) per step: all loads of the
-// step are issued before the first store, so a wave keeps 2 tiles (8 KB at D = 128) in
-// flight.  Items are numbered pair-major, so neighbouring waves move neighbouring heads of
-// one block.  Grid-stride over items.  Loads and stores are non-temporal: every byte is
-// touched once, and keeping the written lines out of the caches was worth 8 % (measured).
+// Tiles in the order pair, head, K before V; one 16-byte access a thread, so a workgroup moves
+// one tile at D = 128 and two at D = 64, and a wave is always inside one tile (its indices are
+// scalar).  HBM-bound.  As with the rows above the grid is as large as the work: 900 MB of tiles
+// (64 prompts, 13 heads of 128) take 169.7 us this way, 5.4 TB/s read + written, and took 184.8 us
+// with 2048 resident workgroups that strode over the tiles with 8 KB in flight per wave.  Loads
+// and stores are non-temporal: every byte is touched once (cached stores 179 us, cached both ways
+// 186 us).  K and V by the same thread: 180 us.  No loop around the body: with one the compiler
+// fetches the indices by vector loads, because a store may precede them (208 us).
+constexpr int kKvCopyThreads = 256;
+
 template <int D>
-__global__ void __launch_bounds__(256) kv_copy_tiles_kernel(KvCopyParams p)
+__global__ void __launch_bounds__(kKvCopyThreads) kv_copy_tiles_kernel(KvCopyParams p)
 {
-    constexpr int NV = kKvBlockTokens * D * 2 / 1024;     // 1 KB slices per tile
-    const int lane = threadIdx.x & 63;
-    const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int64_t n_waves = (int64_t)gridDim.x * 4;
-    for (int64_t item = wave; item < p.n_items; item += n_waves) {
-        const int64_t i = item / p.n_sel;
-        const int s = (int)(item % p.n_sel);
-        const int64_t sb = p.src_blocks[i], db = p.dst_blocks[i];
-        const int sg = p.src_heads[s], dg = p.dst_heads[s];
-        if (sb < 0 || sb >= p.src_num_blocks || db < 0 || db >= p.dst_num_blocks) continue;
-        if (sg < 0 || sg >= p.src_n_heads || dg < 0 || dg >= p.dst_n_heads) continue;
-        const int64_t so = sb * p.src_stride_block + (int64_t)sg * p.src_stride_head + lane;
-        const int64_t dof = db * p.dst_stride_block + (int64_t)dg * p.dst_stride_head + lane;
-        kv_u32x4 k[NV], v[NV];
-#pragma unroll
-        for (int u = 0; u < NV; ++u) {
-            k[u] = __builtin_nontemporal_load((const kv_u32x4 *)&p.src_k[so + u * 64]);
-            v[u] = __builtin_nontemporal_load((const kv_u32x4 *)&p.src_v[so + u * 64]);
-        }
-#pragma unroll
-        for (int u = 0; u < NV; ++u) {
-            __builtin_nontemporal_store(k[u], (kv_u32x4 *)&p.dst_k[dof + u * 64]);
-            __builtin_nontemporal_store(v[u], (kv_u32x4 *)&p.dst_v[dof + u * 64]);
-        }
-    }
+    constexpr int TV = kKvBlockTokens * D / 8;            // 16-byte units per tile
+    constexpr int TILES = kKvCopyThreads / TV;            // tiles per workgroup
+    const int in_wg = __builtin_amdgcn_readfirstlane((int)threadIdx.x / TV);
+    const int unit = threadIdx.x % TV;
+    const int t = blockIdx.x * TILES + in_wg, s = t >> 1, i = blockIdx.y;
+    if (s >= p.n_sel) return;
+    const int64_t sb = p.src_blocks[i], db = p.dst_blocks[i];
+    const int sg = p.src_heads[s], dg = p.dst_heads[s];
+    if (sb < 0 || sb >= p.src_num_blocks || db < 0 || db >= p.dst_num_blocks) return;
+    if (sg < 0 || sg >= p.src_n_heads || dg < 0 || dg >= p.dst_n_heads) return;
+    const uint4 *src = (t & 1) ? p.src_v : p.src_k;
+    uint4 *dst = (t & 1) ? p.dst_v : p.dst_k;
+    src += sb * p.src_stride_block + sg * p.src_stride_head + unit;
+    dst += db * p.dst_stride_block + dg * p.dst_stride_head + unit;
+    __builtin_nontemporal_store(__builtin_nontemporal_load((const kv_u32x4 *)src), (kv_u32x4 *)dst);
 }
 
 }  // namespace hetis

@@ -348,3 +348,25 @@ def test_row_groups(D, n):
         want = torch.full_like(new, 77)
         want[:, heads] = new[:, heads]
         assert torch.equal(back, want)
+
+
+@pytest.mark.parametrize("D,n,n_sel", [(64, 1, 1), (64, 3, 2), (128, 1, 1), (128, 5, 3), (64, 65535 + 70, 1)])
+def test_tile_groups(D, n, n_sel):
+    """Tile copies with an odd number of tiles a pair, of one pair, and of more pairs than the grid
+    has workgroups in y; the pairs beyond a pool's blocks are skipped."""
+    src_h, dst_h = n_sel + 1, n_sel
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(41)
+    ks, vs = (torch.randint(-30000, 30000, (n, src_h, 16, D), generator=gen, device=DEV, dtype=torch.int16)
+              for _ in range(2))
+    sb, db = (torch.randperm(n, generator=gen, device=DEV).int() for _ in range(2))
+    db[-1:] = n if n > 1 else 0                                  # out of range: skipped
+    sh, dh = list(range(src_h - 1, src_h - 1 - n_sel, -1)), list(range(n_sel))
+    kd, vd = (torch.full((n, dst_h, 16, D), 77, device=DEV, dtype=torch.int16) for _ in range(2))
+    H.check(H.hetis_kv_copy_tiles(H.make_pool(src_h, D, n), ks, vs, H.make_pool(dst_h, D, n), kd, vd, sb, db, n,
+                                  i32(sh), i32(dh), n_sel), "copy")
+    ok = db < n
+    for src, dst in ((ks, kd), (vs, vd)):
+        ref = torch.full_like(dst, 77)
+        ref[db[ok].long()] = src[sb[ok].long()][:, sh]
+        assert torch.equal(dst, ref)
