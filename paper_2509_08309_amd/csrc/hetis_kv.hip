@@ -167,6 +167,7 @@ int hetis_kv_append_pairs(const hetis_attn_shape *shape, const void *k_new, cons
     p.pair_head = pair_head;
     p.stride_tile = stride / 8;
     p.num_tiles = num_tiles;
+    p.n_pairs = n_pairs;
     p.n_kv_heads = shape->n_kv_heads;
     p.batch = shape->batch;
     p.max_blocks_per_seq = shape->max_blocks_per_seq;
