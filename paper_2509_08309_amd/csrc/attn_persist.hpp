@@ -22,7 +22,7 @@
 // ones from the largest class to the smallest (a look-up in the sorted list), so the segments
 // handed out last are the short ones, which keeps the end of the launch short.
 // Work distribution: segment number blockIdx.x belongs to the workgroup without asking (when
-// every segment is a single chunk: two such segments per streaming wave); the rest are tickets
+// every segment is a single chunk: two per streaming wave); the rest are tickets
 // from a device counter, drawn by the workgroup's writer wave, which decodes a segment,
 // reserves a fold slot for it and puts its chunks, ready to use, into an LDS pool; the
 // streaming waves take chunks from the pool with an LDS atomic shortly before they finish the
@@ -33,13 +33,21 @@
 // back to zero for the next launch.
 // Scheduling modes (AttnParams::mode).  kModeSegments is the above.  kModeSplit: seg_tokens =
 // chunk_tokens, every chunk leaves as a partial result for a separate merge launch.
-// kModeSpread, for launches with few rows, where whole segments would leave most workgroups
-// without work: the unit handed out is the chunk (the enumeration counts chunks per row, in
-// row order, no sorting), chunk results go through the partial buffers in global memory, and
-// the wave that stores the last chunk result of a segment folds that segment's chunks with the
-// operations and in the order of the in-LDS fold (fold_coef / fold_weight / fold_elem are
-// shared), so that the mode never shows in a result.  The kernel takes kModeSpread only when
-// some row is longer than two turns of a workgroup's waves.
+// kModeSpread is an offer of the host for launches of few rows, where whole segments would leave
+// most workgroups without work.  If the kernel takes it up, the unit handed out is the chunk (full
+// chunks of all rows first, then the shorter ones), chunk results go through the partial buffers
+// in global memory, and the wave that stores the last chunk result of a segment folds that
+// segment's chunks with the operations and in the order of the in-LDS fold (fold_coef /
+// fold_weight / fold_elem are shared), so that the mode never shows in a result.  These launches
+// are bound by latency, not by HBM: what they pay for is the enumeration ahead of the first load,
+// a second turn of chunks on some waves while others idle, and the round trips of the
+// combination after the last chunk.  Hence: no tables and one barrier (every wave enumerates
+// in registers), one chunk a wave across all compute units with the short ones second, the last
+// chunk of a wave stored and combined by that wave, and partial results loaded many at a time.
+// Measured, before (tables, chunks in row order, the writer wave combining one load at a time)
+// and after: 16 chats of 1088 tokens on average x 13 heads of 128 44.9 -> 32.6 us; two
+// documents of 20k and 27k tokens x 8 heads 70.0 -> 45.5; 144 pairs of 8-head groups 57.5 ->
+// 45.9; 4 chats x 4 heads of 64 14.9 -> 11.2.
 //
 // A workgroup is NW streaming waves plus one writer wave; after the prologue they never
 // meet at a barrier.
@@ -49,7 +57,8 @@
 //     the next chunk before the current one is finished off.  Every global load is issued
 //     unconditionally (indices clamped, tiles that do not exist turned into zero-length
 //     buffer descriptors), so the in-order load counter is known exactly at every wait.
-//     These waves never store to global memory: on gfx9-class hardware loads and stores
+//     These waves do not store to global memory while loads are in flight (only the last chunk
+//     of a wave may be stored by the wave itself): on gfx9-class hardware loads and stores
 //     share one counter that is in order only among loads, so a single pending store would
 //     force every later wait to drain all loads.  A finished chunk (normalised rows and
 //     their base-2 log-sum-exp) is handed over through one of the wave's two LDS mailboxes.
@@ -98,6 +107,7 @@ constexpr int kClasses = kLinClasses + 4;
 static_assert(kClasses + 1 <= 32, "class number + 1 is packed into five bits");
 constexpr int kMaxSegChunks = 32;       // chunks of a segment, at most (one writer lane each)
 constexpr int kPoolSize = 2 * kMaxSegChunks;   // chunk descriptors the LDS pool can hold
+constexpr int kMaxQuickRows = 512;      // rows of a launch that may be handed out by single chunks
 constexpr int kTicketBatch = 8;         // tickets per device atomic while segments are single chunks
 // Segments of at most 1/HETIS_FINE_CHUNK_BELOW of a whole one are cut into chunks of half the
 // size, those of at most a quarter of that into chunks of a quarter of the size.
@@ -124,6 +134,33 @@ constexpr int kTicketBatch = 8;         // tickets per device atomic while segme
 #define HETIS_STATIC_FLAT_X16 14
 #endif
 enum : int { kItemExists = 1 };
+
+// Inclusive scans over the 64 lanes of a wave (DPP, no LDS traffic): sums, and maxima of x >= 0.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_or_zero(int x)
+{
+    return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, true);
+}
+__device__ __forceinline__ int wave_scan_sum(int x)
+{
+    x += dpp_or_zero<0x111, 0xF>(x);    // row_shr 1, 2, 4, 8: inside each row of 16 lanes
+    x += dpp_or_zero<0x112, 0xF>(x);
+    x += dpp_or_zero<0x114, 0xF>(x);
+    x += dpp_or_zero<0x118, 0xF>(x);
+    x += dpp_or_zero<0x142, 0xA>(x);    // row_bcast 15: into rows 1 and 3
+    x += dpp_or_zero<0x143, 0xC>(x);    // row_bcast 31: into rows 2 and 3
+    return x;
+}
+__device__ __forceinline__ int wave_max(int x)
+{
+    x = max(x, dpp_or_zero<0x111, 0xF>(x));
+    x = max(x, dpp_or_zero<0x112, 0xF>(x));
+    x = max(x, dpp_or_zero<0x114, 0xF>(x));
+    x = max(x, dpp_or_zero<0x118, 0xF>(x));
+    x = max(x, dpp_or_zero<0x142, 0xA>(x));
+    x = max(x, dpp_or_zero<0x143, 0xC>(x));
+    return __builtin_amdgcn_readlane(x, 63);
+}
 
 // x / d for x >= 0, d > 0 the same in all lanes: integer division has no instruction of its
 // own and costs about forty; the divisors of the enumeration are powers of two unless a caller
@@ -214,7 +251,6 @@ struct alignas(16) FoldSlot {
     int next;           // chunk to fold next
     int ns;             // chunks of the segment
     int kind, dest;     // where the finished segment goes: kKindOut / kKindPartial
-    int nseg, out_row;  // of the segment's row
 };
 
 template <int R>
@@ -224,7 +260,7 @@ __host__ __device__ constexpr int fold_slots() { return R >= 4 ? 5 : 8; }
 // lane.  `lse2`: base-2 log-sum-exp per row; `w`: when not null, row r is divided by w[r] on
 // the way out (the weight sum of a fold slot).
 template <int D, int R>
-__device__ __forceinline__ void store_result(const float (&o)[R][D], const float *lse2,
+__device__ __forceinline__ void store_result(const float (*o)[D], const float *lse2,
                                              const float *w, int kind, int64_t dest,
                                              const AttnParams &p, int lane)
 {
@@ -260,7 +296,7 @@ __device__ __forceinline__ void store_result(const float (&o)[R][D], const float
 // `base2`: the log-sum-exp is stored as it is (chunk results of kModeSpread), otherwise as a
 // natural logarithm (segment results).
 template <int D, int R>
-__device__ __forceinline__ void store_partial_coherent(const float (&o)[R][D], const float *lse2,
+__device__ __forceinline__ void store_partial_coherent(const float (*o)[D], const float *lse2,
                                                        const float *w, int64_t dest,
                                                        const AttnParams &p, int lane, bool base2)
 {
@@ -268,7 +304,7 @@ __device__ __forceinline__ void store_partial_coherent(const float (&o)[R][D], c
 #pragma unroll
     for (int k = 0; k < R * D / 64; ++k) {
         const int idx = k * 64 + lane;
-        float v = (&o[0][0])[idx];
+        float v = o[0][idx];
         if (w) v *= __builtin_amdgcn_rcpf(w[idx / D]);
         coherent_store(p.o_partial + dest * (R * D) + idx, v);
     }
@@ -276,41 +312,69 @@ __device__ __forceinline__ void store_partial_coherent(const float (&o)[R][D], c
         coherent_store(p.lse_partial + dest * R + lane, base2 ? lse2[lane] : lse2[lane] * kLn2);
 }
 
+// Partial results loaded together by the two functions below.  Their loads are device-coherent
+// (the partial results may come from other XCDs) and the compiler keeps such loads in program
+// order with every use, so a loop that loads and uses one result at a time pays a memory round
+// trip for each: the wave that ends a launch then spends tens of microseconds on a row.
+template <int R>
+constexpr int kPartBatch = R == 1 ? 16 : R == 8 ? 2 : 32 / R;      // at most 64 / R
+
 // Log-sum-exp merge of the n_segs partial results of one row, ascending segment order, by one
 // wave: M = max_c lse_c, w_c = exp(lse_c - M), out = fp16(sum_c w_c o_c / sum_c w_c).  Lane l
 // owns dims l and l + 64 (D = 128) of each of the R query rows.  `first` is the index of
-// segment 0 of the row in the partial buffers, segment c sits `stride` * c slots further.  The
-// partial results may come from other XCDs: they are read with device-coherent loads.
+// segment 0 of the row in the partial buffers, segment c sits `stride` * c slots further.
+// The maximum takes one load a lane per 64 log-sum-exps, the sums one round trip per
+// kPartBatch segments (two rows of 5 to 7 segments per head, one load at a time: 25 us of the 70
+// that launch took).
 template <int D, int R>
 __device__ __forceinline__ void merge_partials(const AttnParams &p, int64_t first, int n_segs,
                                                int stride, int64_t out_row, int lane)
 {
     constexpr int V = D / 64;                        // words per lane and row: 1 or 2
+    constexpr int U = kPartBatch<R>;
     const int64_t step = (int64_t)stride * R;        // rows of the buffers per segment
     const float *lse = p.lse_partial + first * R;    // [segment][r]
     const float *op = p.o_partial + first * (R * D) + lane;
-    float M[R];
+    // lane l looks at segments l / R, l / R + 64 / R, ... of row l % R
+    float mx = -INFINITY;
+#pragma unroll 1
+    for (int c0 = 0; c0 < n_segs; c0 += 64 / R)
+        mx = fmaxf(mx, coherent_load(lse + min(c0 + lane / R, n_segs - 1) * step + lane % R));
 #pragma unroll
-    for (int r = 0; r < R; ++r) M[r] = coherent_load(lse + r);
-    for (int c = 1; c < n_segs; ++c) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) M[r] = fmaxf(M[r], coherent_load(lse + c * step + r));
-    }
-    float W[R], acc[R][V];
+    for (int off = 32; off >= R; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+    float M[R], W[R], acc[R][V];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
+        M[r] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mx), r));
         W[r] = 0.f;
 #pragma unroll
         for (int v = 0; v < V; ++v) acc[r][v] = 0.f;
     }
-    for (int c = 0; c < n_segs; ++c) {
+#pragma unroll 1
+    for (int c0 = 0; c0 < n_segs; c0 += U) {
+        float x[U][R][V];
+        // lane u * R + r: log-sum-exp of segment c0 + u, row r
+        const int lc = __float_as_int(coherent_load(lse + min(c0 + lane / R, n_segs - 1) * step + lane % R));
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const float w = fast_exp2((coherent_load(lse + c * step + r) - M[r]) * kLog2e);
-            W[r] += w;
-            const float *src = op + (c * step + r) * D;
+        for (int u = 0; u < U; ++u) {
+            const int64_t row = min(c0 + u, n_segs - 1) * step;
 #pragma unroll
-            for (int v = 0; v < V; ++v) acc[r][v] = fmaf(w, coherent_load(src + v * 64), acc[r][v]);
+            for (int r = 0; r < R; ++r) {
+#pragma unroll
+                for (int v = 0; v < V; ++v) x[u][r][v] = coherent_load(op + (row + r) * D + v * 64);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (c0 + u >= n_segs) continue;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const float lse_c = __int_as_float(__builtin_amdgcn_readlane(lc, u * R + r));
+                const float w = fast_exp2((lse_c - M[r]) * kLog2e);
+                W[r] += w;
+#pragma unroll
+                for (int v = 0; v < V; ++v) acc[r][v] = fmaf(w, x[u][r][v], acc[r][v]);
+            }
         }
     }
 #pragma unroll
@@ -332,16 +396,19 @@ __device__ __forceinline__ void fold_segment_from_chunks(const AttnParams &p, in
                                                          bool whole_row, int64_t out_row, int lane)
 {
     constexpr int V = D / 64;
-    constexpr int U = 16 / R;                         // chunk results loaded together
+    constexpr int U = kPartBatch<R>;
     float a[R][V], M[R], W[R];
+#pragma unroll 1
     for (int c0 = 0; c0 < ns; c0 += U) {
-        float x[U][R][V], lc[U][R];
+        float x[U][R][V];
+        // lane u * R + r: log-sum-exp of chunk c0 + u, row r
+        const int lc = __float_as_int(
+            coherent_load(p.lse_partial + (slot0 + min(c0 + lane / R, ns - 1)) * R + lane % R));
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t slot = slot0 + min(c0 + u, ns - 1);
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                lc[u][r] = coherent_load(p.lse_partial + slot * R + r);
 #pragma unroll
                 for (int v = 0; v < V; ++v)
                     x[u][r][v] = coherent_load(p.o_partial + (slot * R + r) * D + v * 64 + lane);
@@ -352,13 +419,14 @@ __device__ __forceinline__ void fold_segment_from_chunks(const AttnParams &p, in
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 if (c0 + u >= ns) continue;
+                const float lse_c = __int_as_float(__builtin_amdgcn_readlane(lc, u * R + r));
                 if (c0 + u == 0) {
-                    M[r] = lc[u][r];
+                    M[r] = lse_c;
                     W[r] = 1.f;
 #pragma unroll
                     for (int v = 0; v < V; ++v) a[r][v] = x[u][r][v];
                 } else {
-                    const FoldCoef f = fold_coef(M[r], lc[u][r]);
+                    const FoldCoef f = fold_coef(M[r], lse_c);
                     W[r] = fold_weight(W[r], f);
                     M[r] = f.Mn;
 #pragma unroll
@@ -412,59 +480,72 @@ struct Arrivals {
 // of segment j of that row.  There the wave that completes a segment folds its chunks, which
 // spreads the folding of a long row over as many waves as it has segments, stores the segment
 // result and counts it in for the row in turn.
+__device__ __forceinline__ int64_t arrival_counter(const AttnParams &p, int dest, bool spread, int n_rows)
+{
+    const int64_t row = dest / p.max_segs;           // (enumeration row, head)
+    if (!spread) return row;
+    const int seg_slots = p.max_segs / p.part_stride;
+    return n_rows + row * seg_slots + (dest % p.max_segs) / p.part_stride;
+}
+
+// What follows a count: `before` is the counter's value before this result was counted in.  All
+// arguments are the same in every lane.
+template <int D, int R>
+__device__ __forceinline__ void combine_if_last(const AttnParams &p, int before, int dest, int parts,
+                                                int64_t out_row, int len, bool spread, int n_rows,
+                                                int lane)
+{
+    const int64_t row = dest / p.max_segs;
+    int n_segs = parts;
+    if (spread) {
+        const int j = (dest % p.max_segs) / p.part_stride;
+        const int n_tok = min(p.seg_tokens, len - j * p.seg_tokens);
+        const int ct = chunk_tokens_of(n_tok, p.chunk_tokens, p.seg_tokens);
+        const int ns = (n_tok + ct - 1) / ct;
+        if (before + 1 != ns) return;
+        n_segs = (len + p.seg_tokens - 1) / p.seg_tokens;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        fold_segment_from_chunks<D, R>(p, row * p.max_segs + (int64_t)j * p.part_stride, ns,
+                                       n_segs == 1, out_row, lane);
+        unsigned seen = 0;
+        if (n_segs > 1) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            __builtin_amdgcn_s_waitcnt(0);           // the segment result is stored
+        }
+        if (lane == 0) {
+            __hip_atomic_store(p.arrivals + arrival_counter(p, dest, true, n_rows), 0u, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+            if (n_segs > 1)
+                seen = __hip_atomic_fetch_add(p.arrivals + row, 1u, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (n_segs == 1 || (int)__builtin_amdgcn_readfirstlane(seen) + 1 != n_segs) return;
+    } else if (before + 1 != n_segs) {
+        return;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    merge_partials<D, R>(p, row * p.max_segs, n_segs, spread ? p.part_stride : 1, out_row, lane);
+    if (lane == 0)
+        __hip_atomic_store(p.arrivals + row, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 template <int D, int R, int NW>
 __device__ __forceinline__ void count_in_and_combine(const AttnParams &p, const Arrivals<NW> &arr,
                                                      int n_arr, bool spread, int n_rows, int lane)
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_s_waitcnt(0);                   // every store of this wave has completed
-    const int seg_slots = p.max_segs / p.part_stride;   // segments per row (kModeSpread)
     unsigned old = 0;
-    if (lane < n_arr) {
-        const int d = arr.dest[lane];
-        const int64_t row = d / p.max_segs;          // (enumeration row, head)
-        const int64_t counter = spread ? n_rows + row * seg_slots + (d % p.max_segs) / p.part_stride : row;
-        old = __hip_atomic_fetch_add(p.arrivals + counter, 1u, __ATOMIC_RELAXED,
-                                     __HIP_MEMORY_SCOPE_AGENT);
-    }
-    for (int i = 0; i < n_arr; ++i) {
-        const int before = __builtin_amdgcn_readlane((int)old, i);
-        const int d = __builtin_amdgcn_readfirstlane(arr.dest[i]);
-        const int64_t row = d / p.max_segs;
-        const int64_t out_row = __builtin_amdgcn_readfirstlane(arr.out_row[i]);
-        int n_segs = __builtin_amdgcn_readfirstlane(arr.parts[i]);
-        if (spread) {
-            const int L = __builtin_amdgcn_readfirstlane(arr.len[i]);
-            const int j = (d % p.max_segs) / p.part_stride;
-            const int n_tok = min(p.seg_tokens, L - j * p.seg_tokens);
-            const int ct = chunk_tokens_of(n_tok, p.chunk_tokens, p.seg_tokens);
-            const int ns = (n_tok + ct - 1) / ct;
-            if (before + 1 != ns) continue;
-            n_segs = (L + p.seg_tokens - 1) / p.seg_tokens;
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-            fold_segment_from_chunks<D, R>(p, row * p.max_segs + (int64_t)j * p.part_stride, ns,
-                                           n_segs == 1, out_row, lane);
-            unsigned seen = 0;
-            if (n_segs > 1) {
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                __builtin_amdgcn_s_waitcnt(0);       // the segment result is stored
-            }
-            if (lane == 0) {
-                __hip_atomic_store(p.arrivals + n_rows + row * seg_slots + j, 0u, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-                if (n_segs > 1)
-                    seen = __hip_atomic_fetch_add(p.arrivals + row, 1u, __ATOMIC_RELAXED,
-                                                  __HIP_MEMORY_SCOPE_AGENT);
-            }
-            if (n_segs == 1 || (int)__builtin_amdgcn_readfirstlane(seen) + 1 != n_segs) continue;
-        } else if (before + 1 != n_segs) {
-            continue;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        merge_partials<D, R>(p, row * p.max_segs, n_segs, spread ? p.part_stride : 1, out_row, lane);
-        if (lane == 0)
-            __hip_atomic_store(p.arrivals + row, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    if (lane < n_arr)
+        old = __hip_atomic_fetch_add(p.arrivals + arrival_counter(p, arr.dest[lane], spread, n_rows), 1u,
+                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll 1
+    for (int i = 0; i < n_arr; ++i)
+        combine_if_last<D, R>(p, __builtin_amdgcn_readlane((int)old, i),
+                              __builtin_amdgcn_readfirstlane(arr.dest[i]),
+                              __builtin_amdgcn_readfirstlane(arr.parts[i]),
+                              __builtin_amdgcn_readfirstlane(arr.out_row[i]),
+                              __builtin_amdgcn_readfirstlane(arr.len[i]), spread, n_rows, lane);
 }
 
 struct ItemHdr {
@@ -580,17 +661,92 @@ __global__ __launch_bounds__((NW + 1) * 64)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int seg_tokens = p.seg_tokens;
     const int chunk_tokens = p.chunk_tokens;
-    // kModeSpread is an offer: it is taken up only when some row is long enough to gain from
-    // being worked on by several workgroups (decided below, once the lengths are known)
-    bool spread = MERGE && p.mode == kModeSpread;
     const bool merging = MERGE && p.arrivals != nullptr;
-    // kModeSpread: chunks of a row of L tokens (a row without tokens has one, which writes zeros)
-    auto row_chunks = [&](int L) {
-        if (L <= 0) return 1;
+
+    // ---- launches of few rows (p.mode == kModeSpread: fewer than kMaxQuickRows rows x heads).
+    // Every wave loads all row lengths and works out in registers, without a barrier, how the
+    // launch is handed out, and (streaming waves) its own first item.  One of three ways:
+    //  - spread: single chunks (see the top).  They pay a round trip through global memory per
+    //    chunk result, so only when whole segments would leave workgroups without work although
+    //    there is work to share: fewer segments than workgroups, and some row longer than a
+    //    workgroup's own waves finish in one turn.
+    //  - lone: no more rows than workgroups, and no row longer than a segment: workgroup w takes
+    //    row w as its only segment, and there is nothing to enumerate.
+    //  - otherwise whole segments through the tables, as in every other launch.
+    // The tables cost 3 us of latency (scans over the workgroup, four barriers): a third of what
+    // a launch of a few short rows takes.
+    constexpr int QG = kMaxQuickRows / 64;
+    bool spread = false, lone = false;
+    int q_len[MERGE ? QG : 1], q_seq[MERGE ? QG : 1], q_head[MERGE ? QG : 1];   // lane l: row 64 u + l
+    int qA[MERGE ? QG : 1], qB[MERGE ? QG : 1];     // spread: full / other chunks before the row
+    int totalA = 0, totalB = 0;
+    auto full_chunks = [&](int L, int *others) {    // chunks of chunk_tokens tokens; shorter ones
+        if (L <= 0) {
+            *others = 1;                            // writes zeros
+            return 0;
+        }
         const int nF = udiv(L, seg_tokens), rt = L - nF * seg_tokens;
         const int ct = chunk_tokens_of(rt, chunk_tokens, seg_tokens);
-        return nF * p.part_stride + udiv(rt + ct - 1, ct);
+        const int n = udiv(rt + ct - 1, ct), whole = ct == chunk_tokens ? udiv(rt, ct) : 0;
+        *others = n - whole;
+        return nF * p.part_stride + whole;
     };
+    // value of enumeration row b (the same in all lanes) from the registers of the wave
+    auto of_row = [&](const int (&q)[MERGE ? QG : 1], int b) {
+        int x = 0;
+#pragma unroll
+        for (int u = 0; u < (MERGE ? QG : 1); ++u)
+            if ((b >> 6) == u) x = __builtin_amdgcn_readlane(q[u], b & 63);
+        return x;
+    };
+    int lone_len = 0, lone_head = 0, lone_seq = 0;      // of the workgroup's only row
+    if (tid < 2 * NW) mail[tid].flag = kMailEmpty;
+    if (tid == 0) {
+        pool.next = 0;
+        pool.end = 0;
+    }
+    if (MERGE && p.mode == kModeSpread) {
+#pragma unroll
+        for (int u = 0; u < QG; ++u) {
+            const int i = min(u * 64 + lane, batch - 1);
+            q_seq[u] = PAIRS ? p.pair_seq[i] : i;
+            q_head[u] = PAIRS ? p.pair_head[i] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < QG; ++u) q_len[u] = p.seq_lens[q_seq[u]];
+        __syncthreads();                            // mailboxes and pool are ready
+        int longest = 0, n_segments = 0;
+#pragma unroll
+        for (int u = 0; u < QG; ++u) {
+            if (u * 64 + lane >= batch) continue;
+            longest = max(longest, q_len[u]);
+            n_segments += max(1, udiv(max(q_len[u], 0) + seg_tokens - 1, seg_tokens));
+        }
+        longest = wave_max(longest);
+        n_segments = __builtin_amdgcn_readlane(wave_scan_sum(n_segments), 63);
+        spread = longest > NW * chunk_tokens && (long long)n_segments * n_sel < (long long)gridDim.x;
+        lone = !spread && longest <= seg_tokens && batch * n_sel <= (int)gridDim.x;
+        if (lone) {
+            const int b = min((int)blockIdx.x / n_sel, batch - 1);
+            lone_len = of_row(q_len, b);
+            lone_head = PAIRS ? of_row(q_head, b) : p.head_ids[(int)blockIdx.x % n_sel];
+            lone_seq = PAIRS ? of_row(q_seq, b) : b;
+        }
+        if (spread) {
+#pragma unroll
+            for (int u = 0; u < QG; ++u) {
+                int nB = 0;
+                int nA = full_chunks(q_len[u], &nB);
+                if (u * 64 + lane >= batch) nA = nB = 0;
+                const int inclA = wave_scan_sum(nA), inclB = wave_scan_sum(nB);
+                qA[u] = totalA + inclA - nA;
+                qB[u] = totalB + inclB - nB;
+                totalA += __builtin_amdgcn_readlane(inclA, 63);
+                totalB += __builtin_amdgcn_readlane(inclB, 63);
+            }
+        }
+    }
+    const bool quick = MERGE && (spread || lone);
 
     // ---- work enumeration.  Rows are handled in groups of 64 consecutive rows, one row a lane:
     // group u * (NW + 1) + wave belongs to round u of that wave, so a thread holds up to UR rows
@@ -620,7 +776,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
     __shared__ int scan[E * NT];                        // [class][group] counts, then [group] totals
     __shared__ int wave_tot[2 * (NW + 1)];
     const int n_groups = (batch + 63) / 64;
-    {
+    if (!quick) {
         // The lengths go to LDS at once and the later steps run as loops that are not unrolled:
         // the prologue must not need more registers than the streaming loop, or the register
         // allocation of that loop suffers (measured: 12 % of the kernel's time).
@@ -654,41 +810,8 @@ __global__ __launch_bounds__((NW + 1) * 64)
                 pseq[i] = row[u];
             }
         }
-        if (spread) {
-            // Single chunks pay a round trip through global memory per chunk result.  They are
-            // worth it only when whole segments would leave workgroups without work although
-            // there is work to share: when there are fewer segments than workgroups and some
-            // row is longer than a workgroup's own waves finish in one turn.  Otherwise:
-            // whole segments, folded in LDS, after all.
-            int longest = 0, n_segments = 0;
-#pragma unroll
-            for (int u = 0; u < UR; ++u) {
-                longest = max(longest, L[u]);
-                if (tid + u * NT < batch) n_segments += max(1, udiv(max(L[u], 0) + seg_tokens - 1, seg_tokens));
-            }
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) {
-                longest = max(longest, __shfl_xor(longest, off, 64));
-                n_segments += __shfl_xor(n_segments, off, 64);
-            }
-            if (lane == 0) {
-                wave_tot[wave] = longest;
-                wave_tot[NW + 1 + wave] = n_segments;
-            }
-            __syncthreads();
-            n_segments = 0;
-#pragma unroll
-            for (int w = 0; w < NW + 1; ++w) {
-                longest = max(longest, wave_tot[w]);
-                n_segments += wave_tot[NW + 1 + w];
-            }
-            // (readfirstlane: the compiler must see that the decision is the same in all lanes, or
-            // every branch on it, the streaming loop's included, is compiled as a divergent one;
-            // wave_tot is written again only after the next barrier)
-            spread = __builtin_amdgcn_readfirstlane((int)(longest > NW * chunk_tokens &&
-                                                          (long long)n_segments * n_sel < (long long)gridDim.x)) != 0;
-        }
     }
+    if (!quick) {
     // Per row, kept in the row's firstF entry until step 3:
     // (whole segments of the group's lower rows) << 11 | (rank in its class) << 5 | (class + 1)
 #pragma unroll 1
@@ -701,13 +824,8 @@ __global__ __launch_bounds__((NW + 1) * 64)
             const int L = lens[i];                      // this thread's own write
             nF = L > 0 ? udiv(L, seg_tokens) : 0;
             const int rt = L > 0 ? L - nF * seg_tokens : 0;
-            if (spread) {
-                // chunks are counted instead of whole segments, and no row is listed
-                nF = row_chunks(L);
-            } else {
-                if (rt > 0) cls = size_class(rt);
-                if (L <= 0 && p.direct_single) cls = kClasses - 1;   // the segment that writes the zeros
-            }
+            if (rt > 0) cls = size_class(rt);
+            if (L <= 0 && p.direct_single) cls = kClasses - 1;   // the segment that writes the zeros
         }
         int incl = nF, rank = 0;
 #pragma unroll
@@ -732,11 +850,6 @@ __global__ __launch_bounds__((NW + 1) * 64)
         wave_lds_fence();
         if (cls >= 0 && rank == count - 1) scan[cls * n_groups + g] = count;
         if (lane == 63) scan[kClasses * n_groups + g] = incl;
-    }
-    if (tid < 2 * NW) mail[tid].flag = kMailEmpty;
-    if (tid == 0) {
-        pool.next = 0;
-        pool.end = 0;
     }
     __syncthreads();
     {
@@ -805,13 +918,34 @@ __global__ __launch_bounds__((NW + 1) * 64)
         if (cls >= 0) order[scan[cls * n_groups + g] + rank] = (unsigned short)i;
     }
     __syncthreads();
-    const int totalF = firstF[batch];                         // whole segments of all rows
-    const int total = (totalF + lens[2 * batch + 1]) * n_sel; // segments of this launch
+    }
+    const int totalF = quick ? 0 : firstF[batch];             // whole segments of all rows
+    // segments (spread: chunks) of this launch
+    const int total = (spread ? totalA + totalB : lone ? batch : totalF + lens[2 * batch + 1]) * n_sel;
+    if (spread && wave == NW) {
+        // tables for the writer wave's own use: rows, and chunks before each row
+#pragma unroll
+        for (int u = 0; u < QG; ++u) {
+            const int i = u * 64 + lane;
+            if (i >= batch) continue;
+            lens[i] = q_len[u];
+            firstF[i] = qA[u];
+            scan[i] = qB[u];
+            if (PAIRS) {
+                hids[i] = q_head[u];
+                pseq[i] = q_seq[u];
+            }
+        }
+        if (!PAIRS)
+            for (int i = lane; i < n_ids; i += 64) hids[i] = p.head_ids[i];
+        wave_lds_fence();
+    }
 
     // segment number -> (row, segment, head): whole segments come first (binary search in the
     // running counts), last segments after them by size class (sorted list).  Works per lane.
     auto upper = [&](const int *tab, int key) {               // last b with tab[b] <= key
         int lo = 0, hi = batch - 1;
+#pragma unroll 1
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
             if (tab[mid] <= key)
@@ -831,35 +965,31 @@ __global__ __launch_bounds__((NW + 1) * 64)
         int len;            // tokens of the row
     };
     auto chunk_for = [&](int n_tok) { return chunk_tokens_of(n_tok, chunk_tokens, seg_tokens); };
-    // kModeSpread: item number -> (row, chunk, head); the item is returned as a segment of one chunk
-    auto decode_spread = [&](int itemno) {
+    // kModeSpread: items are numbered full chunks of all rows first, then the shorter ones, heads
+    // fastest; chunk k of those of row b is returned as a segment of one chunk
+    auto spread_segment = [&](int b, int si, bool full, int k, int L, int g, int seq) {
         Segment s;
-        const int w = min(itemno, max(total - 1, 0));
-        const int cg = PAIRS ? w : w / n_sel;
-        const int si = PAIRS ? 0 : w - cg * n_sel;
-        s.b = upper(firstF, cg);
-        const int k = cg - firstF[s.b];                 // chunk of the row
-        const int L = lens[s.b];
         const int gc = p.part_stride;
         const int nF = L > 0 ? udiv(L, seg_tokens) : 0;
+        const int rt = max(L, 0) - nF * seg_tokens;
         int j, c;
-        if (k < nF * gc) {
+        s.ct = chunk_tokens;
+        if (full) {
             j = udiv(k, gc);
             c = k - j * gc;
-            s.ct = chunk_tokens;
             s.n_tok = chunk_tokens;
         } else {
             j = nF;
-            c = k - nF * gc;
-            const int rt = max(L, 0) - nF * seg_tokens;
             s.ct = chunk_for(rt);
+            c = k + (s.ct == chunk_tokens ? udiv(rt, chunk_tokens) : 0);
             s.n_tok = max(0, min(s.ct, rt - c * s.ct));
         }
         s.t0 = j * seg_tokens + c * s.ct;
         s.ns = 1;
-        s.g = hids[PAIRS ? s.b : si];
-        s.seq = PAIRS ? pseq[s.b] : s.b;
-        s.nseg = row_chunks(L);
+        s.b = b;
+        s.g = g;
+        s.seq = seq;
+        s.nseg = nF * gc + udiv(rt + chunk_for(rt) - 1, chunk_for(rt));
         s.out_row = s.seq * p.n_q_heads + s.g * R;
         s.tail = L > 0 && s.t0 + s.n_tok == L;
         s.len = L;
@@ -871,33 +1001,47 @@ __global__ __launch_bounds__((NW + 1) * 64)
             s.dest = s.out_row;
         } else {
             s.kind = kKindPartial;
-            s.dest = (s.b * n_sel + si) * p.max_segs + j * gc + c;
+            s.dest = (b * n_sel + si) * p.max_segs + j * gc + c;
         }
         return s;
     };
-    auto decode = [&](int segno) {
-        if (spread) return decode_spread(segno);
-        Segment s;
-        const int w = min(segno, max(total - 1, 0));
+    auto decode_spread = [&](int itemno) {          // from the writer wave's tables, per lane
+        const int w = min(itemno, max(total - 1, 0));
         const int cg = PAIRS ? w : w / n_sel;
         const int si = PAIRS ? 0 : w - cg * n_sel;
-        int L, j;
-        if (cg < totalF) {
-            s.b = upper(firstF, cg);
-            j = cg - firstF[s.b];
-            L = lens[s.b];
-            s.n_tok = seg_tokens;
-        } else {
-            s.b = order[cg - totalF];
-            L = lens[s.b];
-            j = L > 0 ? udiv(L, seg_tokens) : 0;
-            s.n_tok = L > 0 ? L - j * seg_tokens : 0;
-        }
+        const bool full = cg < totalA;
+        const int key = full ? cg : cg - totalA;
+        const int *tab = full ? firstF : scan;
+        const int b = upper(tab, key);
+        return spread_segment(b, si, full, key - tab[b], lens[b], hids[PAIRS ? b : si],
+                              PAIRS ? pseq[b] : b);
+    };
+    // item -> chunk from the registers of the wave (the item is the same in all lanes)
+    auto quick_spread = [&](int item) {
+        const int cg = PAIRS ? item : item / n_sel;
+        const int si = PAIRS ? 0 : item - cg * n_sel;
+        const bool full = cg < totalA;
+        const int key = full ? cg : cg - totalA;
+        int b = -1;                                 // last row with no more than `key` before it
+#pragma unroll
+        for (int u = 0; u < (MERGE ? QG : 1); ++u)
+            b += __builtin_popcountll(__builtin_amdgcn_ballot_w64(u * 64 + lane < batch &&
+                                                                  (full ? qA[u] : qB[u]) <= key));
+        b = __builtin_amdgcn_readfirstlane(b);
+        const int before = full ? of_row(qA, b) : of_row(qB, b);
+        return spread_segment(b, si, full, key - before, of_row(q_len, b),
+                              PAIRS ? of_row(q_head, b) : p.head_ids[si], PAIRS ? of_row(q_seq, b) : b);
+    };
+    // what of a segment of row b follows from its length
+    auto row_segment = [&](int b, int si, int j, int n_tok, int L, int g, int seq) {
+        Segment s;
+        s.b = b;
+        s.n_tok = n_tok;
         s.t0 = j * seg_tokens;
         s.ct = chunk_for(s.n_tok);
         s.ns = max(1, udiv(s.n_tok + s.ct - 1, s.ct));
-        s.g = hids[PAIRS ? s.b : si];
-        s.seq = PAIRS ? pseq[s.b] : s.b;
+        s.g = g;
+        s.seq = seq;
         const int n_segs = udiv(max(L, 0) + seg_tokens - 1, seg_tokens);
         s.nseg = n_segs;
         s.out_row = s.seq * p.n_q_heads + s.g * R;
@@ -914,6 +1058,26 @@ __global__ __launch_bounds__((NW + 1) * 64)
             s.dest = (s.b * n_sel + si) * p.max_segs + j;
         }
         return s;
+    };
+    auto decode = [&](int segno) {
+        if (spread) return decode_spread(segno);
+        const int w = min(segno, max(total - 1, 0));
+        const int cg = PAIRS ? w : w / n_sel;
+        const int si = PAIRS ? 0 : w - cg * n_sel;
+        if (lone) return row_segment(cg, si, 0, max(lone_len, 0), lone_len, lone_head, lone_seq);
+        int b, L, j, n_tok;
+        if (cg < totalF) {
+            b = upper(firstF, cg);
+            j = cg - firstF[b];
+            L = lens[b];
+            n_tok = seg_tokens;
+        } else {
+            b = order[cg - totalF];
+            L = lens[b];
+            j = L > 0 ? udiv(L, seg_tokens) : 0;
+            n_tok = L > 0 ? L - j * seg_tokens : 0;
+        }
+        return row_segment(b, si, j, n_tok, L, hids[PAIRS ? b : si], PAIRS ? pseq[b] : b);
     };
     // chunk i of a segment; `slot`: the segment's fold slot (segments of several chunks)
     auto chunk_of = [&](const Segment &s, int i, int slot) {
@@ -934,13 +1098,16 @@ __global__ __launch_bounds__((NW + 1) * 64)
     };
     // Work a workgroup has without a ticket.  When segments have several chunks: segment number
     // blockIdx.x, whose first NW chunks the streaming waves take directly (wave v takes chunk
-    // v) and which owns fold slot 0.  When every segment is a single chunk: segments
-    // (blockIdx.x + k gridDim.x) * NW + v, k = 0, 1, two per streaming wave v (the waves of a
-    // workgroup work on neighbouring heads of one chunk position).  Tickets number the segments
-    // after these.
+    // v) and which owns fold slot 0.  When every segment is a single chunk, two per streaming
+    // wave v: kModeSplit: segments (blockIdx.x + k gridDim.x) * NW + v, k = 0, 1 (the waves of a
+    // workgroup work on neighbouring heads of one chunk position).  kModeSpread: item
+    // v gridDim.x + blockIdx.x, so that a launch of fewer items than waves works on every compute
+    // unit, and, through the pool, the items that lie as far from the other end of the first
+    // 2 NW gridDim.x (the shortest items come last: a wave with a full chunk gets a short one or
+    // none).  Tickets number the segments after these.
     const bool single_mode = p.mode == kModeSplit || spread;
     const bool have_first = (int)blockIdx.x < total;
-    const bool step_mode = p.k_new != nullptr;      // never together with single_mode
+    const bool step_mode = p.k_new != nullptr;      // never with kModeSplit
     // chunks of the first segment that are taken without the pool: the first NW, but not the
     // one that holds the row's last position when the new token is stored in this launch
     auto direct_chunks = [&](const Segment &s0) {
@@ -1030,6 +1197,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
                     };
                     const int my = __builtin_amdgcn_readfirstlane(two_sum((int)blockIdx.x));
                     int rank = 0;
+#pragma unroll 1
                     for (int b0 = 0; b0 < Gn; b0 += 64) {
                         const int b = b0 + lane;
                         const int sum_b = two_sum(min(b, Gn - 1));
@@ -1088,6 +1256,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
             r.len = __builtin_amdgcn_readlane(s.len, k);
             return r;
         };
+        bool own_items = spread;          // the workgroup's own items beyond its waves' first ones
         while (done_mask != (1 << NW) - 1 && idle < kSpinLimit) {
             bool progressed = false;
             if (exhausted && !counted_out) count_out();
@@ -1111,7 +1280,12 @@ __global__ __launch_bounds__((NW + 1) * 64)
                 ahead = max(4 * left > (long long)gridDim.x * HETIS_LATE_SEGMENTS_X4 ? HETIS_POOL_AHEAD : 1, n_draw);
             }
             int want = -1;                // segment to decode in this pass (one a lane)
-            if (pend_i == pend_n && q0 >= 0) {
+            if (MERGE && own_items) {
+                want = (NW + lane) * Gn + Gn - 1 - (int)blockIdx.x;          // lanes 0 .. NW - 1
+                pend_n = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < NW && want < total));
+                own_items = false;
+                progressed = true;
+            } else if (pend_i == pend_n && q0 >= 0) {
                 // the next of the workgroup's own segments
                 want = q0;
                 q0 = q1;
@@ -1142,6 +1316,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
                     const int cnt = pend_n - pend_i;
                     if (pool_end + cnt - taken <= kPoolSize) {
                         if (step_mode) {
+#pragma unroll 1
                             for (int e = pend_i; e < pend_n; ++e) {
                                 const Segment sg = bcast(mine, e);
                                 if (sg.tail) store_tail(sg);
@@ -1171,8 +1346,6 @@ __global__ __launch_bounds__((NW + 1) * 64)
                                 fold[slot].ns = seg.ns;
                                 fold[slot].kind = seg.kind;
                                 fold[slot].dest = seg.dest;
-                                fold[slot].nseg = seg.nseg;
-                                fold[slot].out_row = seg.out_row;
                             }
                         }
                         if (step_mode && seg.tail) {
@@ -1223,20 +1396,12 @@ __global__ __launch_bounds__((NW + 1) * 64)
                 if (f != kMailFull) continue;
                 const int kind = __builtin_amdgcn_readfirstlane(mb.kind);
                 const int dest = __builtin_amdgcn_readfirstlane(mb.dest);
-                if (kind != kKindFold) {
-                    if (kind == kKindPartial && merging) {
-                        store_partial_coherent<D, R>(mb.o, mb.lse, nullptr, dest, p, lane, spread);
-                        if (lane == 0) {
-                            arrivals.dest[n_arr] = dest;
-                            arrivals.parts[n_arr] = mb.nseg;
-                            arrivals.out_row[n_arr] = mb.out_row;
-                            arrivals.len[n_arr] = mb.len;
-                        }
-                        ++n_arr;
-                    } else {
-                        store_result<D, R>(mb.o, mb.lse, nullptr, kind, dest, p, lane);
-                    }
-                } else {
+                // a result that leaves the workgroup, if this chunk completes one
+                bool leaves = true;
+                int rkind = kind, rdest = dest;
+                const float(*res)[D] = mb.o;
+                const float *res_lse = mb.lse, *res_w = nullptr;
+                if (kind == kKindFold) {
                     Fold &fs = fold[dest];
                     const int cs = __builtin_amdgcn_readfirstlane(mb.cs);
                     if (cs != __builtin_amdgcn_readfirstlane(fs.next)) continue;   // not its turn yet
@@ -1270,23 +1435,25 @@ __global__ __launch_bounds__((NW + 1) * 64)
                     }
                     if (lane == 0) fs.next = cs + 1;
                     wave_lds_fence();
-                    if (last) {
-                        const int fkind = __builtin_amdgcn_readfirstlane(fs.kind);
-                        const int fdest = __builtin_amdgcn_readfirstlane(fs.dest);
-                        if (fkind == kKindPartial && merging) {
-                            store_partial_coherent<D, R>(fs.acc, fs.M, fs.W, fdest, p, lane, false);
-                            if (lane == 0) {
-                                arrivals.dest[n_arr] = fdest;
-                                arrivals.parts[n_arr] = fs.nseg;
-                                arrivals.out_row[n_arr] = fs.out_row;
-                                arrivals.len[n_arr] = 0;
-                            }
-                            ++n_arr;
-                        } else {
-                            store_result<D, R>(fs.acc, fs.M, fs.W, fkind, fdest, p, lane);
-                        }
-                        busy &= ~(1u << dest);
+                    leaves = last;
+                    rkind = __builtin_amdgcn_readfirstlane(fs.kind);
+                    rdest = __builtin_amdgcn_readfirstlane(fs.dest);
+                    res = fs.acc;
+                    res_lse = fs.M;
+                    res_w = fs.W;
+                    if (last) busy &= ~(1u << dest);
+                }
+                if (leaves && MERGE && rkind == kKindPartial && merging) {
+                    store_partial_coherent<D, R>(res, res_lse, res_w, rdest, p, lane, spread);
+                    if (lane == 0) {
+                        arrivals.dest[n_arr] = rdest;
+                        arrivals.parts[n_arr] = mb.nseg;
+                        arrivals.out_row[n_arr] = mb.out_row;
+                        arrivals.len[n_arr] = mb.len;
                     }
+                    ++n_arr;
+                } else if (leaves) {
+                    store_result<D, R>(res, res_lse, res_w, rkind, rdest, p, lane);
                 }
                 mail_store(&mb.flag, kMailEmpty);
                 next_box[v] ^= 1;
@@ -1362,6 +1529,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
     };
     // bounded wait for a mailbox of this wave to be empty
     auto wait_empty = [&](Mail &mb) {
+#pragma unroll 1
         for (int spin = 0; spin < kSpinLimit; ++spin) {
             if (__builtin_amdgcn_readfirstlane(mail_load(&mb.flag)) == kMailEmpty) return;
             __builtin_amdgcn_s_sleep(2);
@@ -1374,6 +1542,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
         if (lane == 0)
             i = __hip_atomic_fetch_add(&pool.next, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         i = __builtin_amdgcn_readfirstlane(i);
+#pragma unroll 1
         for (int spin = 0; spin < kSpinLimit; ++spin) {
             const int end = __builtin_amdgcn_readfirstlane(
                 __hip_atomic_load(&pool.end, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
@@ -1397,7 +1566,14 @@ __global__ __launch_bounds__((NW + 1) * 64)
         // first chunk: of the work the workgroup has without a ticket, else from the pool
         ChunkDesc d{};
         bool direct = false;
-        if (single_mode) {
+        if (spread) {
+            const int mine = wave * (int)gridDim.x + (int)blockIdx.x;
+            if (mine < total) {
+                const Segment s0 = quick_spread(mine);
+                d = chunk_of(s0, 0, 0);
+                direct = true;
+            }
+        } else if (!MERGE && single_mode) {
             const long long mine = (long long)blockIdx.x * NW + wave;
             if (mine < total) {
                 d = chunk_of(decode((int)mine), 0, 0);
@@ -1447,7 +1623,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
         // out.
         int i = 0;
         for (; i + 4 * RING < lim; i += RING) steady_turn(i);
-        if (single_mode && n == 0) {
+        if (!MERGE && single_mode && n == 0) {
             // the wave's second segment is its own as well
             const long long mine = (long long)(gridDim.x + blockIdx.x) * NW + wave;
             if (mine < total) {
@@ -1474,9 +1650,33 @@ __global__ __launch_bounds__((NW + 1) * 64)
             __builtin_amdgcn_sched_barrier(0);
         }
 
-        // hand the finished chunk to the writer
         Mail &mb = my_mail[n & 1];
         wait_empty(mb);
+        if (MERGE && !nxt.exists && cur.h.kind != kKindFold) {
+            // The wave's last chunk, and a result of its own: no load is in flight that a store
+            // could hold up, so the wave stores, counts and combines it itself instead of
+            // queueing behind the other waves' results at the writer.
+            if (cur.h.kind != kKindZero) Policy::finish(st, mb.o, mb.lse, lane);
+            wave_lds_fence();
+            if (cur.h.kind == kKindPartial && merging) {
+                store_partial_coherent<D, R>(mb.o, mb.lse, nullptr, cur.h.dest, p, lane, spread);
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                __builtin_amdgcn_s_waitcnt(0);      // every store of this wave has completed
+                unsigned old = 0;
+                if (lane == 0)
+                    old = __hip_atomic_fetch_add(
+                        p.arrivals + arrival_counter(p, cur.h.dest, spread, batch * n_sel), 1u,
+                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                mail_store(&mb.flag, kMailDone);
+                combine_if_last<D, R>(p, __builtin_amdgcn_readfirstlane((int)old), cur.h.dest, cur.h.nseg,
+                                      cur.h.out_row, cur.h.len, spread, batch * n_sel, lane);
+            } else {
+                store_result<D, R>(mb.o, mb.lse, nullptr, cur.h.kind, cur.h.dest, p, lane);
+                mail_store(&mb.flag, kMailDone);
+            }
+            return;
+        }
+        // hand the finished chunk to the writer
         if (cur.h.kind != kKindZero) Policy::finish(st, mb.o, mb.lse, lane);
         if (lane == 0) {
             mb.kind = cur.h.kind;

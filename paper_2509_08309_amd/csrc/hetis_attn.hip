@@ -194,7 +194,10 @@ static int launch_persistent(AttnParams p, int batch, hipStream_t st)
     if (cus <= 0) return HETIS_ERR_LAUNCH;
     if (occ > wgs_per_cu_cap()) occ = wgs_per_cu_cap();
     int64_t G = (int64_t)cus * occ;
-    const int64_t most = (int64_t)batch * p.max_segs * p.n_sel;    // segments, at most
+    // Segments (single chunks), at most.  Rows that no launch hands out chunk by chunk, however
+    // long they are here (see `longest` in the kernel), are one segment each.
+    const bool short_rows = p.mode == kModeSpread && p.max_blocks_per_seq * kBlockTokens <= NW * p.chunk_tokens;
+    const int64_t most = (int64_t)batch * (short_rows ? 1 : p.max_segs) * p.n_sel;
     if (G > most) G = most;
     launch_timed(kernel, dim3((unsigned)G), dim3((NW + 1) * 64), lds, st, p, batch);
     return HETIS_OK;
@@ -292,6 +295,7 @@ static void launch_merge(const AttnParams &p, int D, int r, int batch, hipStream
 #ifndef HETIS_SPREAD_BELOW_ROWS
 #define HETIS_SPREAD_BELOW_ROWS 512
 #endif
+static_assert(HETIS_SPREAD_BELOW_ROWS <= kMaxQuickRows, "the kernel keeps these rows in registers");
 struct WsLayout {
     size_t arrivals = 0, o_partial = 0, lse_partial = 0, total = kControlBytes;
     size_t zeroed = kControlBytes;     // leading bytes this shape needs to be zero between launches

@@ -1,0 +1,75 @@
+"""Launches of fewer than 512 rows (sequences x selected heads, or pairs) decide on the device how
+they are handed out: single chunks, one row a workgroup, or whole segments like every other launch.
+At the edges of that decision the results are those of the whole-segment launch, bit for bit: the
+same call with a workspace that holds the control words only."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2509_08309_amd as H
+from paper_2509_08309_amd import workloads as W
+
+from gpu_harness import TOL, Dev, bits, check_rows, no_expired_wait, selected_rows
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def lengths(kind, n, r, rng):
+    turn = 4 * (512 if r >= 4 else 256)             # tokens a workgroup's waves hold in one turn
+    if kind == "short":                             # at most one turn
+        return rng.choice([0, 1, 16, 63, 64, 65, 256, 257, turn - 1, turn], size=n)
+    if kind == "one_long":                          # just beyond a turn: chunks if there are few rows
+        lens = rng.integers(0, 200, size=n)
+        lens[rng.integers(n)] = turn + 1
+        return lens
+    return rng.choice([1, 255, 1025, 2048, 2049, 4095, 4096], size=n)
+
+
+@pytest.mark.parametrize("Hq,Hkv,D", [(1, 1, 64), (2, 1, 128), (8, 1, 128)])
+@pytest.mark.parametrize("kind", ["short", "one_long", "long"])
+def test_ways_of_handing_out_agree(Hq, Hkv, D, kind):
+    r = Hq // Hkv
+    for n in (1, 63, 64, 65, 255, 256, 257, 511, 512):
+        rng = np.random.default_rng(1000 + n)
+        lens = [int(x) for x in lengths(kind, n, r, rng)]
+        w = W.make_custom(lens, Hq, Hkv, D, [0], seed=n, device=DEV)
+        d = Dev(w)
+        out = d.decode([0])
+        small = torch.empty(256, dtype=torch.uint8, device=DEV)
+        H.check(H.hetis_attn_workspace_init(small, 256), "workspace_init")
+        assert w.block_table.shape[1] <= 256        # one segment a row: nothing else in a workspace
+        whole = d.decode_ws([0], small)
+        assert np.array_equal(bits(out), bits(whole)), (kind, n)
+        ws = d.workspace(1)
+        for _ in range(2):                          # the second call finds what the first one left
+            assert np.array_equal(bits(d.decode_ws([0], ws)), bits(whole)), (kind, n)
+        torch.cuda.synchronize()
+        mode = int(ws[:16].view(torch.int32)[3].item())
+        turn = 4 * (512 if r >= 4 else 256)
+        assert mode == (3 if max(lens) > turn and n < 256 else 1), (kind, n, mode)
+        # the same rows as pairs, in another order
+        perm = rng.permutation(n).astype(np.int32)
+        pairs_out = torch.zeros_like(w.q)
+        table = torch.from_numpy(np.ascontiguousarray(w.block_table[perm])).to(DEV)
+        H.check(H.hetis_attn_decode_pairs(d.shape, d.q, d.k.view(-1, 16, D), d.v.view(-1, 16, D), table, d.sl,
+                                          torch.from_numpy(perm).to(DEV), torch.zeros(n, dtype=torch.int32, device=DEV),
+                                          n, d.scale, pairs_out), "pairs")
+        torch.cuda.synchronize()
+        no_expired_wait()
+        assert np.array_equal(bits(pairs_out), bits(whole)), (kind, n)
+
+
+@pytest.mark.parametrize("Hq,D", [(2, 128), (2, 64), (8, 128), (16, 64)])
+def test_rows_of_many_segments(Hq, D):
+    """Two long rows a head: as many segments and chunks a segment as the batched loads of the
+    combination take, and one more."""
+    Hkv = 2
+    lens = [16 * 4096 + 1, 17 * 4096 + 300, 4097]
+    w = W.make_custom(lens, Hq, Hkv, D, [1, 0], seed=77, device=DEV)
+    out = Dev(w).decode([1, 0])
+    ref = oracle.attn_decode(w.q.cpu().numpy(), w.k_cache.cpu().numpy(), w.v_cache.cpu().numpy(),
+                             w.block_table, w.seq_lens, np.asarray([1, 0], dtype=np.int32), w.spec.scale)
+    check_rows(out, ref, selected_rows(w.spec, [1, 0]), TOL, "long rows")
+    no_expired_wait()
