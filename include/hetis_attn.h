@@ -182,9 +182,7 @@ int hetis_attn_decode_ws(const hetis_attn_shape *shape, const void *q, const voi
  *   k_cache, v_cache  read and written
  * The cache ends up as hetis_kv_append leaves it and `out` as hetis_attn_decode computes it on
  * that cache, bit for bit; unlike hetis_kv_append this call does not range-check what it reads
- * from device memory (use hetis_attn_validate).  A call that hands out whole segments stores
- * the rows inside the Attention kernel; one that hands out single chunks enqueues the store as
- * a launch of its own ahead of it.  Workspace rules as for hetis_attn_decode /
+ * from device memory (use hetis_attn_validate).  Workspace rules as for hetis_attn_decode /
  * hetis_attn_decode_ws (same size).  Errors: those of hetis_attn_decode.
  */
 int hetis_attn_decode_step(const hetis_attn_shape *shape, const void *q, const void *k_new,

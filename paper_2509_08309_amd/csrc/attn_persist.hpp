@@ -87,8 +87,9 @@
 // (sequence, head) right before it puts the chunk that contains position L - 1 into the pool,
 // and waits for the stores to complete; the wave that takes the chunk runs on the same
 // compute unit and takes it with an acquire, so it reads the new rows.  That chunk is never
-// one of those taken without the pool.  (kModeSegments only: the host runs the store as a
-// launch of its own when it offers kModeSpread.)
+// one of those taken without the pool, except in launches of few rows, where a streaming wave
+// whose first chunk it is stores the rows itself before its first load (a store as a launch of its
+// own ahead of these cost them 4.7 us and the gap between two launches).
 // Pairs mode (per-request head subsets, Section 4.2 / 5.2.1): the rows of the enumeration are
 // (sequence, KV head) pairs instead of sequences, each with its own block-table row over a
 // pool of single-head tiles; everything else, the arithmetic included, is shared.
@@ -1108,11 +1109,12 @@ __global__ __launch_bounds__((NW + 1) * 64)
     const bool single_mode = p.mode == kModeSplit || spread;
     const bool have_first = (int)blockIdx.x < total;
     const bool step_mode = p.k_new != nullptr;      // never with kModeSplit
-    // chunks of the first segment that are taken without the pool: the first NW, but not the
-    // one that holds the row's last position when the new token is stored in this launch
+    // chunks of the first segment that are taken without the pool: the first NW.  When the new
+    // token is stored in this launch, the one that holds the row's last position is left to the
+    // pool, unless (launches of few rows) the streaming wave that takes it stores the rows itself.
     auto direct_chunks = [&](const Segment &s0) {
         int n = min(NW, s0.ns);
-        if (step_mode && s0.tail && n == s0.ns) --n;
+        if (!MERGE && step_mode && s0.tail && n == s0.ns) --n;
         return n;
     };
     // store of the new token's rows of the segment's (sequence, head), done before the chunk
@@ -1123,6 +1125,12 @@ __global__ __launch_bounds__((NW + 1) * 64)
         const int blk = p.block_table[(int64_t)sg.b * p.max_blocks_per_seq + pos / kBlockTokens];
         const int64_t off = (int64_t)blk * p.stride_block + (PAIRS ? 0 : (int64_t)sg.g * p.stride_head);
         store_new_rows<D>(p, sg.seq, sg.g, off, pos % kBlockTokens, p.n_q_heads / R, lane);
+    };
+    // the same by the streaming wave whose first chunk it is: nothing of it is in flight yet
+    auto store_own_tail = [&](const Segment &sg) {
+        store_tail(sg);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_s_waitcnt(0);
     };
     if (wave == NW) {
         // ------------------------------------------------------------ writer wave
@@ -1348,13 +1356,13 @@ __global__ __launch_bounds__((NW + 1) * 64)
                                 fold[slot].dest = seg.dest;
                             }
                         }
-                        if (step_mode && seg.tail) {
+                        // some chunks of the first segment are taken without the pool
+                        const int skip = first ? direct_chunks(seg) : 0;
+                        if (step_mode && seg.tail && skip < seg.ns) {
                             store_tail(seg);
                             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
                             __builtin_amdgcn_s_waitcnt(0);
                         }
-                        // some chunks of the first segment are taken without the pool
-                        const int skip = first ? direct_chunks(seg) : 0;
                         if (lane >= skip && lane < seg.ns)
                             pool.desc[(pool_end + lane - skip) % kPoolSize] = chunk_of(seg, lane, slot);
                         pool_end += seg.ns - skip;
@@ -1570,6 +1578,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
             const int mine = wave * (int)gridDim.x + (int)blockIdx.x;
             if (mine < total) {
                 const Segment s0 = quick_spread(mine);
+                if (step_mode && s0.tail) store_own_tail(s0);
                 d = chunk_of(s0, 0, 0);
                 direct = true;
             }
@@ -1582,6 +1591,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
         } else if (have_first) {
             const Segment s0 = decode(blockIdx.x);
             if (wave < direct_chunks(s0)) {
+                if (MERGE && step_mode && s0.tail && wave == s0.ns - 1) store_own_tail(s0);
                 d = chunk_of(s0, wave, 0);
                 direct = true;
             }

@@ -2,7 +2,6 @@
 // Every argument error is reported before the first HIP call, so the checks can be
 // exercised on a machine without a GPU.
 #include "../../include/hetis_attn.h"
-#include "../../include/hetis_kv.h"
 
 #include <hip/hip_ext.h>
 
@@ -552,17 +551,8 @@ static int decode_common(const hetis_attn_shape *shape, const void *q, const voi
                                n_sel_heads, scale, out);
     apply_layout(p, lay, c.group, workspace);
     if (step) {
-        if (lay.spread) {
-            // single chunks are handed out without regard to which of them reads the new rows:
-            // the store runs as a launch of its own ahead of the Attention launch
-            rc = hetis_kv_append(shape, k_new, v_new, block_table, seq_lens, head_ids, n_sel_heads,
-                                 INT64_MAX, const_cast<void *>(k_cache), const_cast<void *>(v_cache),
-                                 stream);
-            if (rc != HETIS_OK) return rc;
-        } else {
-            p.k_new = static_cast<const __half *>(k_new);
-            p.v_new = static_cast<const __half *>(v_new);
-        }
+        p.k_new = static_cast<const __half *>(k_new);
+        p.v_new = static_cast<const __half *>(v_new);
     }
     rc = launch_chunks(p, shape->head_dim, c.group, shape->batch, st);
     if (rc != HETIS_OK) return rc;
@@ -704,16 +694,8 @@ static int decode_pairs_common(const hetis_attn_shape *shape, const void *q, con
     p.pair_head = pair_head;
     apply_layout(p, lay, c.group, workspace);
     if (step) {
-        if (lay.spread) {
-            // as in decode_common: the store runs as a launch of its own ahead of the Attention launch
-            rc = hetis_kv_append_pairs(shape, k_new, v_new, block_table, seq_lens, pair_seq, pair_head,
-                                       n_pairs, INT64_MAX, const_cast<void *>(k_tiles),
-                                       const_cast<void *>(v_tiles), stream);
-            if (rc != HETIS_OK) return rc;
-        } else {
-            p.k_new = static_cast<const __half *>(k_new);
-            p.v_new = static_cast<const __half *>(v_new);
-        }
+        p.k_new = static_cast<const __half *>(k_new);
+        p.v_new = static_cast<const __half *>(v_new);
     }
     rc = launch_chunks(p, shape->head_dim, c.group, n_pairs, st);
     if (rc != HETIS_OK) return rc;
