@@ -12,6 +12,32 @@ constexpr float kLog2e = 1.4426950408889634f;
 // Finite stand-in for "no token seen yet": keeps exp2(m_old - m_new) free of inf - inf.
 constexpr float kNegBig = -1.0e30f;
 
+// Cut of the token axis in hetis_attn_decode.  Compile-time constants chosen by the query-group
+// size only: how a row is cut must depend on its length and the model shape alone, or a
+// head-subset call could not reproduce the all-heads call bit for bit.  A chunk is what one
+// wave processes at a time; a segment is what leaves a workgroup as one result (rows of up to
+// one segment never produce partial results in global memory).
+#ifndef HETIS_DECODE_CHUNK_TOKENS
+#define HETIS_DECODE_CHUNK_TOKENS 256
+#endif
+#ifndef HETIS_DECODE_CHUNK_TOKENS_GQA
+#define HETIS_DECODE_CHUNK_TOKENS_GQA 512
+#endif
+#ifndef HETIS_DECODE_SEG_TOKENS
+#define HETIS_DECODE_SEG_TOKENS 4096
+#endif
+#ifndef HETIS_DECODE_SEG_TOKENS_GQA
+#define HETIS_DECODE_SEG_TOKENS_GQA 4096
+#endif
+constexpr int decode_chunk_tokens(int group)
+{
+    return group >= 4 ? HETIS_DECODE_CHUNK_TOKENS_GQA : HETIS_DECODE_CHUNK_TOKENS;
+}
+constexpr int decode_seg_tokens(int group)
+{
+    return group >= 4 ? HETIS_DECODE_SEG_TOKENS_GQA : HETIS_DECODE_SEG_TOKENS;
+}
+
 struct AttnParams {
     const __half *q;            // [B, Hq, D]
     const __half *k_cache;

@@ -168,7 +168,7 @@ __device__ __forceinline__ int wave_max(int x)
 // of the split entry points chooses otherwise.
 __device__ __forceinline__ int udiv(int x, int d)
 {
-    if ((d & (d - 1)) == 0) return x >> __builtin_ctz(d);
+    if (__builtin_expect((d & (d - 1)) == 0, 1)) return x >> __builtin_ctz(d);
     return x / d;
 }
 
@@ -481,12 +481,12 @@ struct Arrivals {
 // of segment j of that row.  There the wave that completes a segment folds its chunks, which
 // spreads the folding of a long row over as many waves as it has segments, stores the segment
 // result and counts it in for the row in turn.
+template <int R>
 __device__ __forceinline__ int64_t arrival_counter(const AttnParams &p, int dest, bool spread, int n_rows)
 {
-    const int64_t row = dest / p.max_segs;           // (enumeration row, head)
-    if (!spread) return row;
-    const int seg_slots = p.max_segs / p.part_stride;
-    return n_rows + row * seg_slots + (dest % p.max_segs) / p.part_stride;
+    constexpr int gc = decode_seg_tokens(R) / decode_chunk_tokens(R);
+    const int row = dest / p.max_segs;               // (enumeration row, head)
+    return spread ? n_rows + (int64_t)row * (p.max_segs / gc) + (dest - row * p.max_segs) / gc : row;
 }
 
 // What follows a count: `before` is the counter's value before this result was counted in.  All
@@ -496,17 +496,18 @@ __device__ __forceinline__ void combine_if_last(const AttnParams &p, int before,
                                                 int64_t out_row, int len, bool spread, int n_rows,
                                                 int lane)
 {
+    constexpr int seg_tokens = decode_seg_tokens(R), gc = seg_tokens / decode_chunk_tokens(R);
     const int64_t row = dest / p.max_segs;
     int n_segs = parts;
     if (spread) {
-        const int j = (dest % p.max_segs) / p.part_stride;
-        const int n_tok = min(p.seg_tokens, len - j * p.seg_tokens);
-        const int ct = chunk_tokens_of(n_tok, p.chunk_tokens, p.seg_tokens);
-        const int ns = (n_tok + ct - 1) / ct;
+        const int j = (dest - (int)row * p.max_segs) / gc;
+        const int n_tok = min(seg_tokens, len - j * seg_tokens);
+        const int ct = chunk_tokens_of(n_tok, decode_chunk_tokens(R), seg_tokens);
+        const int ns = udiv(n_tok + ct - 1, ct);
         if (before + 1 != ns) return;
-        n_segs = (len + p.seg_tokens - 1) / p.seg_tokens;
+        n_segs = (len + seg_tokens - 1) / seg_tokens;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        fold_segment_from_chunks<D, R>(p, row * p.max_segs + (int64_t)j * p.part_stride, ns,
+        fold_segment_from_chunks<D, R>(p, row * p.max_segs + j * gc, ns,
                                        n_segs == 1, out_row, lane);
         unsigned seen = 0;
         if (n_segs > 1) {
@@ -514,7 +515,7 @@ __device__ __forceinline__ void combine_if_last(const AttnParams &p, int before,
             __builtin_amdgcn_s_waitcnt(0);           // the segment result is stored
         }
         if (lane == 0) {
-            __hip_atomic_store(p.arrivals + arrival_counter(p, dest, true, n_rows), 0u, __ATOMIC_RELAXED,
+            __hip_atomic_store(p.arrivals + arrival_counter<R>(p, dest, true, n_rows), 0u, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
             if (n_segs > 1)
                 seen = __hip_atomic_fetch_add(p.arrivals + row, 1u, __ATOMIC_RELAXED,
@@ -525,7 +526,7 @@ __device__ __forceinline__ void combine_if_last(const AttnParams &p, int before,
         return;
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    merge_partials<D, R>(p, row * p.max_segs, n_segs, spread ? p.part_stride : 1, out_row, lane);
+    merge_partials<D, R>(p, row * p.max_segs, n_segs, spread ? gc : 1, out_row, lane);
     if (lane == 0)
         __hip_atomic_store(p.arrivals + row, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -538,7 +539,7 @@ __device__ __forceinline__ void count_in_and_combine(const AttnParams &p, const 
     __builtin_amdgcn_s_waitcnt(0);                   // every store of this wave has completed
     unsigned old = 0;
     if (lane < n_arr)
-        old = __hip_atomic_fetch_add(p.arrivals + arrival_counter(p, arr.dest[lane], spread, n_rows), 1u,
+        old = __hip_atomic_fetch_add(p.arrivals + arrival_counter<R>(p, arr.dest[lane], spread, n_rows), 1u,
                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll 1
     for (int i = 0; i < n_arr; ++i)
@@ -660,8 +661,12 @@ __global__ __launch_bounds__((NW + 1) * 64)
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int seg_tokens = p.seg_tokens;
-    const int chunk_tokens = p.chunk_tokens;
+    // kVariantMerge runs decode calls only, whose cut is fixed: with constants the divisions are
+    // shifts.  Code on the way to the first load is executed once and comes from the instruction
+    // cache's misses, so its length is what it costs.
+    const int seg_tokens = MERGE ? decode_seg_tokens(R) : p.seg_tokens;
+    const int chunk_tokens = MERGE ? decode_chunk_tokens(R) : p.chunk_tokens;
+    constexpr int kSegChunks = decode_seg_tokens(R) / decode_chunk_tokens(R);
     const bool merging = MERGE && p.arrivals != nullptr;
 
     // ---- launches of few rows (p.mode == kModeSpread: fewer than kMaxQuickRows rows x heads).
@@ -690,7 +695,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
         const int ct = chunk_tokens_of(rt, chunk_tokens, seg_tokens);
         const int n = udiv(rt + ct - 1, ct), whole = ct == chunk_tokens ? udiv(rt, ct) : 0;
         *others = n - whole;
-        return nF * p.part_stride + whole;
+        return nF * kSegChunks + whole;
     };
     // value of enumeration row b (the same in all lanes) from the registers of the wave
     auto of_row = [&](const int (&q)[MERGE ? QG : 1], int b) {
@@ -700,6 +705,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
             if ((b >> 6) == u) x = __builtin_amdgcn_readlane(q[u], b & 63);
         return x;
     };
+    int q_first_head = 0;                               // of the wave's first item
     int lone_len = 0, lone_head = 0, lone_seq = 0;      // of the workgroup's only row
     if (tid < 2 * NW) mail[tid].flag = kMailEmpty;
     if (tid == 0) {
@@ -707,35 +713,46 @@ __global__ __launch_bounds__((NW + 1) * 64)
         pool.end = 0;
     }
     if (MERGE && p.mode == kModeSpread) {
+        // heads of the items this wave may start on: spread, lone
+        const int first_item = wave * (int)gridDim.x + (int)blockIdx.x;
+        const int head_spread = PAIRS ? 0 : p.head_ids[first_item % n_sel];
+        const int head_lone = PAIRS ? 0 : p.head_ids[(int)blockIdx.x % n_sel];
+        // (groups beyond the launch's rows are branched over)
 #pragma unroll
         for (int u = 0; u < QG; ++u) {
+            q_len[u] = q_seq[u] = q_head[u] = qA[u] = qB[u] = 0;
+            if (u * 64 >= batch) continue;
             const int i = min(u * 64 + lane, batch - 1);
             q_seq[u] = PAIRS ? p.pair_seq[i] : i;
             q_head[u] = PAIRS ? p.pair_head[i] : 0;
         }
 #pragma unroll
-        for (int u = 0; u < QG; ++u) q_len[u] = p.seq_lens[q_seq[u]];
+        for (int u = 0; u < QG; ++u)
+            if (u * 64 < batch) q_len[u] = p.seq_lens[q_seq[u]];
         __syncthreads();                            // mailboxes and pool are ready
         int longest = 0, n_segments = 0;
 #pragma unroll
         for (int u = 0; u < QG; ++u) {
-            if (u * 64 + lane >= batch) continue;
-            longest = max(longest, q_len[u]);
-            n_segments += max(1, udiv(max(q_len[u], 0) + seg_tokens - 1, seg_tokens));
+            if (u * 64 >= batch) continue;
+            const bool row = u * 64 + lane < batch;
+            longest = max(longest, row ? q_len[u] : 0);
+            n_segments += row ? max(1, udiv(max(q_len[u], 0) + seg_tokens - 1, seg_tokens)) : 0;
         }
         longest = wave_max(longest);
         n_segments = __builtin_amdgcn_readlane(wave_scan_sum(n_segments), 63);
         spread = longest > NW * chunk_tokens && (long long)n_segments * n_sel < (long long)gridDim.x;
         lone = !spread && longest <= seg_tokens && batch * n_sel <= (int)gridDim.x;
+        q_first_head = spread ? head_spread : head_lone;
         if (lone) {
             const int b = min((int)blockIdx.x / n_sel, batch - 1);
             lone_len = of_row(q_len, b);
-            lone_head = PAIRS ? of_row(q_head, b) : p.head_ids[(int)blockIdx.x % n_sel];
+            lone_head = PAIRS ? of_row(q_head, b) : q_first_head;
             lone_seq = PAIRS ? of_row(q_seq, b) : b;
         }
         if (spread) {
 #pragma unroll
             for (int u = 0; u < QG; ++u) {
+                if (u * 64 >= batch) continue;
                 int nB = 0;
                 int nA = full_chunks(q_len[u], &nB);
                 if (u * 64 + lane >= batch) nA = nB = 0;
@@ -828,12 +845,8 @@ __global__ __launch_bounds__((NW + 1) * 64)
             if (rt > 0) cls = size_class(rt);
             if (L <= 0 && p.direct_single) cls = kClasses - 1;   // the segment that writes the zeros
         }
-        int incl = nF, rank = 0;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int up = __shfl_up(incl, off, 64);
-            if (lane >= off) incl += up;
-        }
+        const int incl = wave_scan_sum(nF);
+        int rank = 0;
         // lanes of the same class, from one ballot per bit of the class number
         unsigned long long same = ~0ull;
 #pragma unroll
@@ -866,15 +879,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
             else
                 sumF += v[e];
         }
-        int inclC = sumC, inclF = sumF;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int upC = __shfl_up(inclC, off, 64), upF = __shfl_up(inclF, off, 64);
-            if (lane >= off) {
-                inclC += upC;
-                inclF += upF;
-            }
-        }
+        const int inclC = wave_scan_sum(sumC), inclF = wave_scan_sum(sumF);
         if (lane == 63) {
             wave_tot[wave] = inclC;
             wave_tot[NW + 1 + wave] = inclF;
@@ -927,6 +932,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
         // tables for the writer wave's own use: rows, and chunks before each row
 #pragma unroll
         for (int u = 0; u < QG; ++u) {
+            if (u * 64 >= batch) continue;
             const int i = u * 64 + lane;
             if (i >= batch) continue;
             lens[i] = q_len[u];
@@ -970,7 +976,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
     // fastest; chunk k of those of row b is returned as a segment of one chunk
     auto spread_segment = [&](int b, int si, bool full, int k, int L, int g, int seq) {
         Segment s;
-        const int gc = p.part_stride;
+        constexpr int gc = kSegChunks;
         const int nF = L > 0 ? udiv(L, seg_tokens) : 0;
         const int rt = max(L, 0) - nF * seg_tokens;
         int j, c;
@@ -1017,7 +1023,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
         return spread_segment(b, si, full, key - tab[b], lens[b], hids[PAIRS ? b : si],
                               PAIRS ? pseq[b] : b);
     };
-    // item -> chunk from the registers of the wave (the item is the same in all lanes)
+    // the wave's first item -> chunk, from the registers of the wave
     auto quick_spread = [&](int item) {
         const int cg = PAIRS ? item : item / n_sel;
         const int si = PAIRS ? 0 : item - cg * n_sel;
@@ -1026,12 +1032,13 @@ __global__ __launch_bounds__((NW + 1) * 64)
         int b = -1;                                 // last row with no more than `key` before it
 #pragma unroll
         for (int u = 0; u < (MERGE ? QG : 1); ++u)
-            b += __builtin_popcountll(__builtin_amdgcn_ballot_w64(u * 64 + lane < batch &&
-                                                                  (full ? qA[u] : qB[u]) <= key));
+            if (u * 64 < batch)
+                b += __builtin_popcountll(__builtin_amdgcn_ballot_w64(
+                    u * 64 + lane < batch && (full ? qA[u] : qB[u]) <= key));
         b = __builtin_amdgcn_readfirstlane(b);
         const int before = full ? of_row(qA, b) : of_row(qB, b);
         return spread_segment(b, si, full, key - before, of_row(q_len, b),
-                              PAIRS ? of_row(q_head, b) : p.head_ids[si], PAIRS ? of_row(q_seq, b) : b);
+                              PAIRS ? of_row(q_head, b) : q_first_head, PAIRS ? of_row(q_seq, b) : b);
     };
     // what of a segment of row b follows from its length
     auto row_segment = [&](int b, int si, int j, int n_tok, int L, int g, int seq) {
@@ -1675,7 +1682,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
                 unsigned old = 0;
                 if (lane == 0)
                     old = __hip_atomic_fetch_add(
-                        p.arrivals + arrival_counter(p, cur.h.dest, spread, batch * n_sel), 1u,
+                        p.arrivals + arrival_counter<R>(p, cur.h.dest, spread, batch * n_sel), 1u,
                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 mail_store(&mb.flag, kMailDone);
                 combine_if_last<D, R>(p, __builtin_amdgcn_readfirstlane((int)old), cur.h.dest, cur.h.nseg,
