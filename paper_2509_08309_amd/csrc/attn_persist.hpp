@@ -672,10 +672,16 @@ __global__ __launch_bounds__((NW + 1) * 64)
     // ---- launches of few rows (p.mode == kModeSpread: fewer than kMaxQuickRows rows x heads).
     // Every wave loads all row lengths and works out in registers, without a barrier, how the
     // launch is handed out, and (streaming waves) its own first item.  One of three ways:
-    //  - spread: single chunks (see the top).  They pay a round trip through global memory per
-    //    chunk result, so only when whole segments would leave workgroups without work although
-    //    there is work to share: fewer segments than workgroups, and some row longer than a
-    //    workgroup's own waves finish in one turn.
+    //  - spread: single chunks (see the top), when some row has more than one full chunk and there
+    //    are fewer segments than workgroups, or fewer than two a workgroup and none of a row of
+    //    several.  Whole segments leave a second turn of a few workgroups, or a compute unit with
+    //    one row of four chunks beside an idle one; a wave by itself streams only 10 to 12 KB/us,
+    //    so a chunk on each of many compute units is faster than four on one.  Segments ->
+    //    chunks, rows of L / 4 to L tokens: r = 1, 100 rows of up to 600 18.4 -> 16.5 us, 300 of
+    //    1200 33.5 -> 28.5, 450 of 600 31.5 -> 26.9; r = 8, 64 rows of 2000 36.4 -> 23.6, 300 of
+    //    600 30.5 -> 23.1.  With r >= 4 a partial result is r times as long and the chunk twice:
+    //    more long rows than workgroups stay whole (300 rows of up to 4000: 82 us, as chunks 84 to
+    //    90).  Rows of several segments, more segments than workgroups: already balanced.
     //  - lone: no more rows than workgroups, and no row longer than a segment: workgroup w takes
     //    row w as its only segment, and there is nothing to enumerate.
     //  - otherwise whole segments through the tables, as in every other launch.
@@ -740,7 +746,10 @@ __global__ __launch_bounds__((NW + 1) * 64)
         }
         longest = wave_max(longest);
         n_segments = __builtin_amdgcn_readlane(wave_scan_sum(n_segments), 63);
-        spread = longest > NW * chunk_tokens && (long long)n_segments * n_sel < (long long)gridDim.x;
+        const long long segments = (long long)n_segments * n_sel;
+        spread = longest > chunk_tokens &&
+                 (segments < (long long)gridDim.x ||
+                  (segments < 2ll * gridDim.x && longest <= (R < 4 ? seg_tokens : NW * chunk_tokens)));
         lone = !spread && longest <= seg_tokens && batch * n_sel <= (int)gridDim.x;
         q_first_head = spread ? head_spread : head_lone;
         if (lone) {

@@ -170,7 +170,7 @@ static int launch_persistent(AttnParams p, int batch, hipStream_t st)
     int64_t G = (int64_t)cus * occ;
     // Segments (single chunks), at most.  Rows that no launch hands out chunk by chunk, however
     // long they are here (see `longest` in the kernel), are one segment each.
-    const bool short_rows = p.mode == kModeSpread && p.max_blocks_per_seq * kBlockTokens <= NW * p.chunk_tokens;
+    const bool short_rows = p.mode == kModeSpread && p.max_blocks_per_seq * kBlockTokens <= p.chunk_tokens;
     const int64_t most = (int64_t)batch * (short_rows ? 1 : p.max_segs) * p.n_sel;
     if (G > most) G = most;
     launch_timed(kernel, dim3((unsigned)G), dim3((NW + 1) * 64), lds, st, p, batch);
@@ -263,8 +263,8 @@ static void launch_merge(const AttnParams &p, int D, int r, int batch, hipStream
 // segments of the longest row the block table allows, and a shape whose rows fit one segment
 // needs the control words only.  Spread scheduling (few rows): slots = chunks of the longest
 // row, segment by segment.
-// Launches with fewer rows (enumeration rows x selected heads) than this cut the work into
-// single chunks instead of whole segments: with so few rows whole segments would leave most
+// Launches with fewer rows (enumeration rows x selected heads) than this may cut the work into
+// single chunks instead of whole segments: with so few rows whole segments would leave
 // compute units without work.  Twice the number of compute units of the target.
 #ifndef HETIS_SPREAD_BELOW_ROWS
 #define HETIS_SPREAD_BELOW_ROWS 512

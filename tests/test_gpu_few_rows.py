@@ -18,17 +18,19 @@ DEV = "cuda:0"
 
 def lengths(kind, n, r, rng):
     turn = 4 * (512 if r >= 4 else 256)             # tokens a workgroup's waves hold in one turn
-    if kind == "short":                             # at most one turn
-        return rng.choice([0, 1, 16, 63, 64, 65, 256, 257, turn - 1, turn], size=n)
-    if kind == "one_long":                          # just beyond a turn: chunks if there are few rows
+    if kind == "short":                             # at most one full chunk
+        return rng.choice([0, 1, 16, 63, 64, 65, turn // 4 - 1, turn // 4], size=n)
+    if kind == "turn":                              # at most one turn
+        return rng.choice([0, 1, 63, 256, 257, turn // 4 + 1, turn - 1, turn], size=n)
+    if kind == "one_long":                          # just beyond a chunk
         lens = rng.integers(0, 200, size=n)
-        lens[rng.integers(n)] = turn + 1
+        lens[rng.integers(n)] = turn // 4 + 1
         return lens
     return rng.choice([1, 255, 1025, 2048, 2049, 4095, 4096], size=n)
 
 
 @pytest.mark.parametrize("Hq,Hkv,D", [(1, 1, 64), (2, 1, 128), (8, 1, 128)])
-@pytest.mark.parametrize("kind", ["short", "one_long", "long"])
+@pytest.mark.parametrize("kind", ["short", "turn", "one_long", "long"])
 def test_ways_of_handing_out_agree(Hq, Hkv, D, kind):
     r = Hq // Hkv
     for n in (1, 63, 64, 65, 255, 256, 257, 511, 512):
@@ -48,7 +50,8 @@ def test_ways_of_handing_out_agree(Hq, Hkv, D, kind):
         torch.cuda.synchronize()
         mode = int(ws[:16].view(torch.int32)[3].item())
         turn = 4 * (512 if r >= 4 else 256)
-        assert mode == (3 if max(lens) > turn and n < 256 else 1), (kind, n, mode)
+        chunks = max(lens) > turn // 4 and n < 512 and (r < 4 or max(lens) <= turn or n < 256)
+        assert mode == (3 if chunks else 1), (kind, n, mode)
         # the same rows as pairs, in another order
         perm = rng.permutation(n).astype(np.int32)
         pairs_out = torch.zeros_like(w.q)
