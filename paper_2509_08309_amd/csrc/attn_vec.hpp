@@ -215,21 +215,28 @@ struct VecPolicy {
 };
 
 // Log-sum-exp merge of the partial results of a row's segments: one workgroup of D threads per
-// (sequence, selected query row); in pairs mode per (pair, row of the group).
+// (sequence, selected query row); in pairs mode per (pair, row of the group).  Bound by latency (a
+// row's partial results are a few KB), so what counts is the chain of loads: the log-sum-exps of
+// 64 segments take one load, a lane each, and their weights one exponential a lane; the partial
+// results of kMergeBatch segments are in flight at the same time as the log-sum-exps, which they do
+// not depend on.  The sums keep their order: ascending segments.
+// Before and after, whole split calls: 320 rows of 40 segments 551.5 -> 547.6 us, 32 grouped-query
+// rows of 38 segments 37.6 -> 33.4, 8 rows of 200 segments 35.2 -> 33.8, rows of one segment the same.
+constexpr int kMergeBatch = 32;
 template <int D>
 __global__ __launch_bounds__(D) void attn_merge_kernel(const AttnParams p, int group)
 {
     const int j = blockIdx.x;            // selected row: i*group + rr
     const int b = blockIdx.y;
-    const int d = threadIdx.x;
+    const int d = threadIdx.x, lane = threadIdx.x & 63;
     const bool pairs = p.pair_seq != nullptr;
     const int seq = pairs ? p.pair_seq[b] : b;
     const int n_sel = pairs ? 1 : p.n_sel;
+    const int head = pairs ? p.pair_head[b] : p.head_ids[j / group];
     const int L = p.seq_lens[seq];
     const int n_segs = (L + p.seg_tokens - 1) / p.seg_tokens;
     if (p.direct_single && n_segs <= 1) return;        // already written by the chunk kernel
-    const int h = (pairs ? p.pair_head[b] : p.head_ids[j / group]) * group + j % group;
-    __half *o = p.out + ((int64_t)seq * p.n_q_heads + h) * D;
+    __half *o = p.out + ((int64_t)seq * p.n_q_heads + head * group + j % group) * D;
     if (n_segs <= 0) {
         o[d] = __float2half_rn(0.f);
         return;
@@ -238,16 +245,49 @@ __global__ __launch_bounds__(D) void attn_merge_kernel(const AttnParams p, int g
     const int64_t base = ((int64_t)b * n_sel + j / group) * p.max_segs * group + j % group;
     const float *lse = p.lse_partial + base;
     const float *op = p.o_partial + base * D + d;
-    // (unrolled so that the loads of 16 segments are in flight together; the sums keep their order)
-    float M = lse[0];
-#pragma unroll 16
-    for (int c = 1; c < n_segs; ++c) M = fmaxf(M, lse[(int64_t)c * group]);
+    auto lse_of = [&](int c) { return lse[(int64_t)min(c, n_segs - 1) * group]; };
+    float x[kMergeBatch], next[kMergeBatch];
+    auto load_batch = [&](float (&to)[kMergeBatch], int c0) {
+#pragma unroll
+        for (int g = 0; g < kMergeBatch; g += 8) {
+            if (c0 + g >= n_segs) break;               // rows of few segments: no loads for nothing
+#pragma unroll
+            for (int u = g; u < g + 8; ++u) to[u] = op[(int64_t)min(c0 + u, n_segs - 1) * group * D];
+        }
+    };
+    float l = lse_of(lane);                            // lane: segment c0 + lane of the group of 64
+    load_batch(x, 0);
+    float M = l;
+#pragma unroll 4
+    for (int c0 = 64; c0 < n_segs; c0 += 64) M = fmaxf(M, lse_of(c0 + lane));
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
     float W = 0.f, acc = 0.f;
-#pragma unroll 16
-    for (int c = 0; c < n_segs; ++c) {
-        const float w = fast_exp2((lse[(int64_t)c * group] - M) * kLog2e);
+    int w_lane = 0;
+    auto add = [&](int u, int c) {
+        const float w = __int_as_float(__builtin_amdgcn_readlane(w_lane, c & 63));
         W += w;
-        acc = fmaf(w, op[(int64_t)c * group * D], acc);
+        acc = fmaf(w, x[u], acc);
+    };
+#pragma unroll 1
+    for (int c0 = 0; c0 < n_segs; c0 += kMergeBatch) {
+        if (c0 % 64 == 0) {
+            w_lane = __float_as_int(fast_exp2((l - M) * kLog2e));
+            l = lse_of(c0 + 64 + lane);
+        }
+        if (c0 + kMergeBatch >= n_segs) {
+#pragma unroll
+            for (int u = 0; u < kMergeBatch; ++u) {
+                if (c0 + u >= n_segs) break;
+                add(u, c0 + u);
+            }
+            break;
+        }
+        load_batch(next, c0 + kMergeBatch);
+#pragma unroll
+        for (int u = 0; u < kMergeBatch; ++u) add(u, c0 + u);
+#pragma unroll
+        for (int u = 0; u < kMergeBatch; ++u) x[u] = next[u];
     }
     o[d] = __float2half_rn(acc / W);
 }
