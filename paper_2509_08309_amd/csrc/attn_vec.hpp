@@ -245,6 +245,29 @@ __global__ __launch_bounds__(D) void attn_merge_kernel(const AttnParams p, int g
     const int64_t base = ((int64_t)b * n_sel + j / group) * p.max_segs * group + j % group;
     const float *lse = p.lse_partial + base;
     const float *op = p.o_partial + base * D + d;
+    float W = 0.f, acc = 0.f;
+    if (n_segs <= 4) {
+        // nothing to share between lanes (6600 rows of one segment: 1.5 us less a launch)
+        float lc[4], x4[4], M = -INFINITY;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (u >= n_segs) break;
+            lc[u] = lse[(int64_t)u * group];
+            x4[u] = op[(int64_t)u * group * D];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (u < n_segs) M = fmaxf(M, lc[u]);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (u >= n_segs) break;
+            const float w = fast_exp2((lc[u] - M) * kLog2e);
+            W += w;
+            acc = fmaf(w, x4[u], acc);
+        }
+        o[d] = __float2half_rn(acc / W);
+        return;
+    }
     auto lse_of = [&](int c) { return lse[(int64_t)min(c, n_segs - 1) * group]; };
     float x[kMergeBatch], next[kMergeBatch];
     auto load_batch = [&](float (&to)[kMergeBatch], int c0) {
@@ -262,7 +285,6 @@ __global__ __launch_bounds__(D) void attn_merge_kernel(const AttnParams p, int g
     for (int c0 = 64; c0 < n_segs; c0 += 64) M = fmaxf(M, lse_of(c0 + lane));
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
-    float W = 0.f, acc = 0.f;
     int w_lane = 0;
     auto add = [&](int u, int c) {
         const float w = __int_as_float(__builtin_amdgcn_readlane(w_lane, c & 63));

@@ -11,7 +11,7 @@ DEV = "cuda:0"
 
 @pytest.mark.parametrize("D,r", [(64, 1), (128, 2), (128, 8)])
 def test_merge_segment_counts(D, r):
-    chunk, counts = 16, [1, 2, 7, 8, 9, 31, 32, 33, 40, 63, 64, 65, 96, 97, 128, 129, 200, 0]
+    chunk, counts = 16, [1, 2, 4, 5, 7, 8, 9, 31, 32, 33, 40, 63, 64, 65, 96, 97, 128, 129, 200, 0]
     lens = [16 * n - (n % 3) for n in counts]
     B, Hkv, cmax = len(counts), 2, max(counts)
     shape = H.make_shape(B, Hkv * r, Hkv, D, cmax)
