@@ -206,6 +206,10 @@ static int launch_chunk(const AttnParams &p0, int rows, hipStream_t st)
             p.seq_lens += row0;
             p.q += (int64_t)row0 * p.n_q_heads * D;
             if (p.out) p.out += (int64_t)row0 * p.n_q_heads * D;
+            if (p.k_new) {
+                p.k_new += (int64_t)row0 * (p.n_q_heads / R) * D;
+                p.v_new += (int64_t)row0 * (p.n_q_heads / R) * D;
+            }
         }
         // the leanest instantiation that holds what this launch can need: the in-launch merge
         // when rows can leave partial results; the fixed second and third segments when the

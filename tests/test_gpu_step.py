@@ -96,3 +96,16 @@ def test_step_many_short_rows():
     lens = rng.integers(1, 300, size=1200)
     w = W.make_custom(lens, 4, 4, 128, [0, 1, 3], seed=503, device=DEV)
     check_step(w, [0, 1, 3])
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,B,heads,max_seq_len", [
+    (4, 2, 64, 2 * 2048 + 4, [1], 33),                # three slices of at most 2048 sequences
+    (512, 512, 64, 514, list(range(512)), 4097),      # rows of two segments: 2^18 / 512 sequences a slice
+])
+def test_step_of_more_sequences_than_a_launch_holds(Hq, Hkv, D, B, heads, max_seq_len):
+    """The launches after the first store their own sequences' new rows."""
+    rng = np.random.default_rng(504)
+    lens = rng.integers(1, min(max_seq_len, 8192 // Hkv) + 1, size=B)
+    lens[[0, 5]] = 0
+    w = W.make_custom(lens, Hq, Hkv, D, heads, seed=505, device=DEV, max_seq_len=max_seq_len)
+    check_step(w, heads, use_ws=True)
