@@ -79,9 +79,9 @@
 // into its bound sets a flag in the workspace's error word, which the host reads with
 // hetis_attn_workspace_status (the launch may then have lost a result).
 // Dynamic LDS: int lens[rows], int firstF[rows + 1] (and two spare words), uint16 order[rows],
-// int hids[n_sel] (pairs mode: hids[rows], pseq[rows]); NW x 2 mailboxes; fold slots; NW
-// per-wave staging areas of Policy::kWaveLdsBytes.  Static LDS: the chunk pool and the scan
-// array of the enumeration.
+// uint16 place[rows], int hids[n_sel] (pairs mode: hids[rows], pseq[rows]); NW x 2 mailboxes; fold
+// slots; NW per-wave staging areas of Policy::kWaveLdsBytes.  Static LDS: the chunk pool and the
+// scan array of the enumeration.
 // Decode step with the store folded in (AttnParams::k_new): the new token's K and V rows go
 // to position L - 1 of the cache inside this launch.  The writer wave stores the rows of a
 // (sequence, head) right before it puts the chunk that contains position L - 1 into the pool,
@@ -561,12 +561,12 @@ struct ItemHdr {
 
 __host__ __device__ constexpr size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
 
-// Table bytes: lens, firstF (int), order (uint16), then the selected heads, or in pairs mode
-// the head and the sequence of every pair.
+// Table bytes: lens, firstF (int), order and place (uint16), then the selected heads, or in pairs
+// mode the head and the sequence of every pair.
 __host__ __device__ constexpr size_t persist_table_bytes(int rows, int n_sel, bool pairs)
 {
     return align16((size_t)(2 * rows + 2) * sizeof(int)) +
-           align16((size_t)rows * sizeof(unsigned short)) +
+           align16((size_t)(2 * rows) * sizeof(unsigned short)) +
            align16((size_t)(pairs ? 2 * rows : n_sel) * sizeof(int));
 }
 // Rows of one launch, at most: bounds the static LDS of the enumeration (groups of 64 rows).
@@ -645,9 +645,10 @@ __global__ __launch_bounds__((NW + 1) * 64)
     // by the size class of that segment, largest first
     unsigned short *order =
         reinterpret_cast<unsigned short *>(smem + align16((size_t)(2 * batch + 2) * sizeof(int)));
+    unsigned short *place = order + batch;    // enumeration only: a row's class and rank in it
     // KV head of position si in head_ids / of pair b; pairs mode: then the sequence of pair b
     int *hids = reinterpret_cast<int *>(reinterpret_cast<unsigned char *>(order) +
-                                        align16((size_t)batch * sizeof(unsigned short)));
+                                        align16((size_t)(2 * batch) * sizeof(unsigned short)));
     int *pseq = hids + batch;
     const int n_sel = PAIRS ? 1 : p.n_sel;    // heads per enumeration row
     const int n_ids = PAIRS ? batch : p.n_sel;
@@ -839,8 +840,9 @@ __global__ __launch_bounds__((NW + 1) * 64)
         }
     }
     if (!quick) {
-    // Per row, kept in the row's firstF entry until step 3:
-    // (whole segments of the group's lower rows) << 11 | (rank in its class) << 5 | (class + 1)
+    // Per row, kept until step 3: in its firstF entry the whole segments of the group's lower rows
+    // (a word of its own: a split call over rows of 500k tokens in chunks of 16 has more than 2^21 in
+    // a group), in its place entry (rank in its class) << 5 | (class + 1)
 #pragma unroll 1
     for (int u = 0; u < UR; ++u) {
         const int i = tid + u * NT;
@@ -867,7 +869,10 @@ __global__ __launch_bounds__((NW + 1) * 64)
         rank = __builtin_amdgcn_mbcnt_hi((unsigned)(same >> 32),
                                          __builtin_amdgcn_mbcnt_lo((unsigned)same, 0));
         const int count = __builtin_popcountll(same);
-        if (i < batch) firstF[i] = ((incl - nF) << 11) | (rank << 5) | (cls + 1);
+        if (i < batch) {
+            firstF[i] = incl - nF;
+            place[i] = (unsigned short)((rank << 5) | (cls + 1));
+        }
         // class counts of the group: zero, then the last row of every class present writes its own
         if (lane < kClasses) scan[lane * n_groups + g] = 0;
         wave_lds_fence();
@@ -927,9 +932,9 @@ __global__ __launch_bounds__((NW + 1) * 64)
         const int i = tid + u * NT;
         const int g = u * (NW + 1) + wave;
         if (i >= batch) break;
-        const int info = firstF[i];
-        const int cls = (info & 31) - 1, rank = (info >> 5) & 63;
-        firstF[i] = scan[kClasses * n_groups + g] + (int)((unsigned)info >> 11);
+        const int info = place[i];
+        const int cls = (info & 31) - 1, rank = info >> 5;
+        firstF[i] += scan[kClasses * n_groups + g];
         if (cls >= 0) order[scan[cls * n_groups + g] + rank] = (unsigned short)i;
     }
     __syncthreads();

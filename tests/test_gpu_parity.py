@@ -242,6 +242,33 @@ def test_c4_long_split_512_and_decode():
     check_untouched(out_s, spec, sub_ids)
 
 
+def test_split_of_very_many_chunks():
+    """64 neighbouring rows of the enumeration hold over 2^21 chunks: the last rows' chunks start
+    beyond what 21 bits count.  Every row's partial results are those of a call with the row alone.
+    (The rows' tables name the same few blocks over and over, so that the cache stays small.)"""
+    D, n_rows, n_blk, pool = 64, 65, 34500, 512
+    lens = [n_blk * 16 - (b % 16) for b in range(n_rows)]
+    assert 62 * (lens[15] // 16) > 1 << 21
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(55)
+    k, v = (torch.randn((pool, 1, 16, D), generator=gen, device="cuda:0").half() for _ in range(2))
+    q = torch.randn((n_rows, 1, D), generator=gen, device="cuda:0").half()
+    bt = torch.randint(0, pool, (n_rows, n_blk), generator=gen, device="cuda:0").int()
+    sl, hid = (torch.tensor(x, dtype=torch.int32, device="cuda:0") for x in (lens, [0]))
+    partials = lambda n: (torch.full((n, 1, n_blk, 1, D), float("nan"), device="cuda:0"),
+                          torch.full((n, 1, n_blk, 1), float("nan"), device="cuda:0"))
+    o_all, lse_all = partials(n_rows)
+    H.check(H.hetis_attn_decode_split(H.make_shape(n_rows, 1, 1, D, n_blk), q, k, v, bt, sl, hid, 1, D ** -0.5, 16,
+                                      n_blk * 16, o_all, lse_all), "split")
+    no_expired_wait()
+    for b in range(n_rows):
+        o, lse = partials(1)
+        H.check(H.hetis_attn_decode_split(H.make_shape(1, 1, 1, D, n_blk), q[b:b + 1], k, v, bt[b:b + 1], sl[b:b + 1],
+                                          hid, 1, D ** -0.5, 16, n_blk * 16, o, lse), "split of one row")
+        assert torch.equal(o[0], o_all[b]) and torch.equal(lse[0], lse_all[b]), b
+    no_expired_wait()
+
+
 # ------------------------------------------------------------------ other entry points and paths
 def test_validate_reports_bad_content():
     w = W.make_custom([20, 45], 4, 4, 64, [0, 1], seed=41, max_seq_len=64)
