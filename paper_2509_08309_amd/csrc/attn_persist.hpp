@@ -1139,11 +1139,15 @@ __global__ __launch_bounds__((NW + 1) * 64)
         return n;
     };
     // store of the new token's rows of the segment's (sequence, head), done before the chunk
-    // that reads them becomes visible to the streaming waves
+    // that reads them becomes visible to the streaming waves; like a store on its own it leaves
+    // out a row whose position is past its block table, whose block id is negative or whose head
+    // does not exist
     auto store_tail = [&](const Segment &sg) {
         const int L = sg.t0 + sg.n_tok;             // tail segment: the row's length
         const int pos = L - 1;
+        if (pos / kBlockTokens >= p.max_blocks_per_seq) return;
         const int blk = p.block_table[(int64_t)sg.b * p.max_blocks_per_seq + pos / kBlockTokens];
+        if (blk < 0 || sg.g < 0 || sg.g >= p.n_q_heads / R) return;
         const int64_t off = (int64_t)blk * p.stride_block + (PAIRS ? 0 : (int64_t)sg.g * p.stride_head);
         store_new_rows<D>(p, sg.seq, sg.g, off, pos % kBlockTokens, p.n_q_heads / R, lane);
     };

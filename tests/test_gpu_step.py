@@ -109,3 +109,36 @@ def test_step_of_more_sequences_than_a_launch_holds(Hq, Hkv, D, B, heads, max_se
     lens[[0, 5]] = 0
     w = W.make_custom(lens, Hq, Hkv, D, heads, seed=505, device=DEV, max_seq_len=max_seq_len)
     check_step(w, heads, use_ws=True)
+
+
+@pytest.mark.parametrize("pairs", [False, True])
+@pytest.mark.parametrize("B", [3, 300])                # x 2 heads: few rows, and whole segments
+def test_step_does_not_store_past_the_block_table(B, pairs):
+    """A position past a row's two table entries is not stored, as in hetis_kv_append.  (Attention
+    reads that row's third entry: the first one of the next row, whose block exists.)"""
+    Hkv, D, mb = 2, 64, 2
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(506)
+    bt = torch.randperm(B * mb, generator=gen, device=DEV).int().view(B, mb)
+    lens = torch.randint(17, 33, (B,), generator=gen, device=DEV).int()
+    lens[:-1:7] = 33                                   # never the last row
+    q, kn, vn = (torch.randn((B, Hkv, D), generator=gen, device=DEV).half() for _ in range(3))
+    k, v = (torch.randn((B * mb, Hkv, 16, D), generator=gen, device=DEV).half() for _ in range(2))
+    shape, hid = H.make_shape(B, Hkv, Hkv, D, mb), torch.tensor([0, 1], dtype=torch.int32, device=DEV)
+    ps = torch.arange(B, device=DEV).int().repeat_interleave(Hkv)
+    ph = hid.repeat(B)
+    # tiles of a pair are its sequence's: B * Hkv rows of mb entries, the pairs of the last row last
+    pt = (bt[ps.long()] * Hkv + ph[:, None]).int().contiguous()
+    k2, v2, out, out2 = k.clone(), v.clone(), torch.zeros_like(q), torch.zeros_like(q)
+    H.check(H.hetis_kv_append(shape, kn, vn, bt, lens, hid, Hkv, B * mb, k2, v2), "append")
+    if pairs:
+        H.check(H.hetis_attn_decode_pairs_step(shape, q, kn, vn, k.view(-1, 16, D), v.view(-1, 16, D), pt, lens, ps,
+                                               ph, B * Hkv, D ** -0.5, out), "pairs step")
+    else:
+        H.check(H.hetis_attn_decode_step(shape, q, kn, vn, k, v, bt, lens, hid, Hkv, D ** -0.5, out), "step")
+    H.check(H.hetis_attn_decode(shape, q, k2, v2, bt, lens, hid, Hkv, D ** -0.5, out2), "decode")
+    torch.cuda.synchronize()
+    no_expired_wait()
+    assert torch.equal(k, k2) and torch.equal(v, v2)
+    ok = lens <= 32
+    assert torch.equal(out[ok], out2[ok])
