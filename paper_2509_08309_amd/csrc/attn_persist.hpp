@@ -600,13 +600,14 @@ __device__ __forceinline__ void wave_lds_fence()
 }
 
 // The new token's K row and V row of (sequence, KV head g) -> slot pos % 16 of the tile
-// (block, g); lanes [0, D/8) move the K row, the next D/8 lanes the V row, 16 bytes each.
+// (block, g); lanes [0, D/8) move the K row, the next D/8 lanes the V row, 16 bytes each; nothing
+// is read or written unless `inside`.
 template <int D>
 __device__ __forceinline__ void store_new_rows(const AttnParams &p, int seq, int g, int64_t tile_off,
-                                               int slot, int n_kv_heads, int lane)
+                                               int slot, int n_kv_heads, int lane, bool inside)
 {
     constexpr int LR = D / 8;
-    if (lane < 2 * LR) {
+    if (lane < 2 * LR && inside) {
         const bool is_v = lane >= LR;
         const int c = lane % LR;
         const __half *src = (is_v ? p.v_new : p.k_new) + ((int64_t)seq * n_kv_heads + g) * D + c * 8;
@@ -1145,11 +1146,11 @@ __global__ __launch_bounds__((NW + 1) * 64)
     auto store_tail = [&](const Segment &sg) {
         const int L = sg.t0 + sg.n_tok;             // tail segment: the row's length
         const int pos = L - 1;
-        if (pos / kBlockTokens >= p.max_blocks_per_seq) return;
-        const int blk = p.block_table[(int64_t)sg.b * p.max_blocks_per_seq + pos / kBlockTokens];
-        if (blk < 0 || sg.g < 0 || sg.g >= p.n_q_heads / R) return;
+        const int j = pos / kBlockTokens, n_kv_heads = p.n_q_heads / R;
+        const int blk = p.block_table[(int64_t)sg.b * p.max_blocks_per_seq + min(j, p.max_blocks_per_seq - 1)];
+        const bool inside = (j < p.max_blocks_per_seq) & (blk >= 0) & ((unsigned)sg.g < (unsigned)n_kv_heads);
         const int64_t off = (int64_t)blk * p.stride_block + (PAIRS ? 0 : (int64_t)sg.g * p.stride_head);
-        store_new_rows<D>(p, sg.seq, sg.g, off, pos % kBlockTokens, p.n_q_heads / R, lane);
+        store_new_rows<D>(p, sg.seq, sg.g, off, pos % kBlockTokens, n_kv_heads, lane, inside);
     };
     // the same by the streaming wave whose first chunk it is: nothing of it is in flight yet
     auto store_own_tail = [&](const Segment &sg) {
