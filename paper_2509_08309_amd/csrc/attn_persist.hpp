@@ -616,6 +616,47 @@ __device__ __forceinline__ void store_new_rows(const AttnParams &p, int seq, int
     }
 }
 
+// Launch of fewer than kMaxQuickRows rows of one segment each, the longest of more than one full
+// chunk: are its chunks handed out singly (true), or the rows whole, one or two a workgroup?
+// `rows` rows of `tokens` tokens in all and `longest` at most, `chunks` chunks; G workgroups.
+// Whole rows wait for the longest one, or, with more rows than workgroups, for two in turn, beside
+// idle compute units; but their chunks meet in LDS, where the results of single ones go through
+// global memory, r times as much with r query rows.  Measured, rows whole -> single chunks, in us
+// (r = 1, 128 dims, lengths uniform, unless stated):
+//  - Up to G rows.  What idles is 1 - tokens / (G * longest).  r < 4: chunks, unless less than
+//    three tenths idle and some wave would take a second chunk (128 rows of 4096: 67 -> 50; 255 of
+//    275 to 1100 29.0 -> 27.6; but 230 of 600 23.0 -> 26.0, 255 of 4096 87 -> 97).  r >= 4: a row
+//    of up to NW chunks is one turn of a workgroup; it gains when it is several chunks long, the
+//    more the more idles (r = 8, 200 rows of 500 to 2000: 41.1 -> 37.9; 300 to 1200: 27.7 -> 31.3;
+//    250 to 1000, whose chunks are half as long: 26.2 -> 25.4; 150 to 600: 19.5 -> 20.7).
+//  - More rows.  Chunks for a few long ones among short ones (511 rows, log-normal around 820, up
+//    to 4096: 75 -> 63), where the rows are alike and the workgroups' second turn is mostly empty
+//    (270 of 4096: 134 -> 104), and for up to one (r >= 4) or about two chunks a wave (390 of 1200:
+//    54 -> 47; 511 of 150 to 600: 33 -> 30; r = 2 not if these are quarter chunks: 480 of 75 to 300
+//    27.1 -> 29.3).  Otherwise rows whole: 511 of 500 to 2000 64 -> 71, r = 2 67 -> 78, r = 8 65 ->
+//    77; 511 of 1 to 4096 in seven lengths, r = 2, 93 -> 111.  r >= 4, rows of more than one turn:
+//    whole (r = 8, 360 of 750 to 3000: 75 -> 80).
+template <int R, int NW>
+__device__ __forceinline__ bool spread_pays(int G, int rows, int longest, int tokens, int chunks)
+{
+    constexpr int ct = decode_chunk_tokens(R), turn = NW * ct;      // tokens a workgroup's waves hold
+    const int waves = NW * G, full = G * longest;
+    const bool idle = 10 * tokens < 7 * full;
+    if (rows <= G) {
+        if (R < 4) return idle || chunks <= waves;
+        if (!idle || (rows == G && longest > turn)) return false;
+        // chunks of the longest row are full ones, or half as long
+        const bool halves = chunk_tokens_of(longest, ct, decode_seg_tokens(R)) < ct;
+        return (!halves && 10 * chunks <= 4 * waves) ||
+               200ll * ct * tokens < (halves ? 56ll : 33ll) * longest * full;
+    }
+    const bool even = 20 * tokens >= 17 * full && 16 * rows < (R == 2 ? 24 : 26) * G;
+    if (R < 4)
+        return idle || even || 10 * chunks <= 11 * waves ||
+               (10 * chunks <= (R == 1 ? 25 : 23) * waves && (R == 1 || tokens >= 80 * chunks));
+    return longest <= turn && (chunks <= waves || 20 * tokens < (R == 4 ? 18 : 11) * full || even);
+}
+
 // VARIANT selects what is compiled in besides the common path; code that a launch cannot reach
 // still costs it (launches measured 0.5 to 1.5 % faster without each of the two parts):
 //   kVariantPlain  many rows, none of which can leave partial results
@@ -674,16 +715,8 @@ __global__ __launch_bounds__((NW + 1) * 64)
     // ---- launches of few rows (p.mode == kModeSpread: fewer than kMaxQuickRows rows x heads).
     // Every wave loads all row lengths and works out in registers, without a barrier, how the
     // launch is handed out, and (streaming waves) its own first item.  One of three ways:
-    //  - spread: single chunks (see the top), when some row has more than one full chunk and there
-    //    are fewer segments than workgroups, or fewer than two a workgroup and none of a row of
-    //    several.  Whole segments leave a second turn of a few workgroups, or a compute unit with
-    //    one row of four chunks beside an idle one; a wave by itself streams only 10 to 12 KB/us,
-    //    so a chunk on each of many compute units is faster than four on one.  Segments ->
-    //    chunks, rows of L / 4 to L tokens: r = 1, 100 rows of up to 600 18.4 -> 16.5 us, 300 of
-    //    1200 33.5 -> 28.5, 450 of 600 31.5 -> 26.9; r = 8, 64 rows of 2000 36.4 -> 23.6, 300 of
-    //    600 30.5 -> 23.1.  With r >= 4 a partial result is r times as long and the chunk twice:
-    //    more long rows than workgroups stay whole (300 rows of up to 4000: 82 us, as chunks 84 to
-    //    90).  Rows of several segments, more segments than workgroups: already balanced.
+    //  - spread: single chunks (see the top), when some row has more than one full chunk and
+    //    spread_pays() says so.
     //  - lone: no more rows than workgroups, and no row longer than a segment: workgroup w takes
     //    row w as its only segment, and there is nothing to enumerate.
     //  - otherwise whole segments through the tables, as in every other launch.
@@ -738,20 +771,36 @@ __global__ __launch_bounds__((NW + 1) * 64)
         for (int u = 0; u < QG; ++u)
             if (u * 64 < batch) q_len[u] = p.seq_lens[q_seq[u]];
         __syncthreads();                            // mailboxes and pool are ready
-        int longest = 0, n_segments = 0;
+        int longest = 0;
 #pragma unroll
-        for (int u = 0; u < QG; ++u) {
-            if (u * 64 >= batch) continue;
-            const bool row = u * 64 + lane < batch;
-            longest = max(longest, row ? q_len[u] : 0);
-            n_segments += row ? max(1, udiv(max(q_len[u], 0) + seg_tokens - 1, seg_tokens)) : 0;
-        }
+        for (int u = 0; u < QG; ++u)
+            if (u * 64 < batch) longest = max(longest, u * 64 + lane < batch ? q_len[u] : 0);
         longest = wave_max(longest);
-        n_segments = __builtin_amdgcn_readlane(wave_scan_sum(n_segments), 63);
-        const long long segments = (long long)n_segments * n_sel;
-        spread = longest > chunk_tokens &&
-                 (segments < (long long)gridDim.x ||
-                  (segments < 2ll * gridDim.x && longest <= (R < 4 ? seg_tokens : NW * chunk_tokens)));
+        if (longest > seg_tokens) {
+            int n_segments = 0;
+#pragma unroll
+            for (int u = 0; u < QG; ++u)
+                if (u * 64 + lane < batch)
+                    n_segments += max(1, udiv(max(q_len[u], 0) + seg_tokens - 1, seg_tokens));
+            n_segments = __builtin_amdgcn_readlane(wave_scan_sum(n_segments), 63);
+            spread = (long long)n_segments * n_sel < (long long)gridDim.x;
+        } else if (longest > chunk_tokens) {
+            // blocks and chunks of all rows in one sum: below 2^18 and 2^14
+            static_assert(kMaxQuickRows * kSegChunks <= 1 << 14 &&
+                          kMaxQuickRows * (decode_seg_tokens(R) / kBlockTokens) <= 1 << 17, "sums fit");
+            int sum = 0;
+#pragma unroll
+            for (int u = 0; u < QG; ++u) {
+                if (u * 64 >= batch) continue;
+                const int L = max(q_len[u], 1), ct = chunk_tokens_of(L, chunk_tokens, seg_tokens);
+                const int sh = __builtin_ctz(ct);
+                if (u * 64 + lane < batch)
+                    sum += ((L + kBlockTokens - 1) / kBlockTokens << 14) + ((L + ct - 1) >> sh);
+            }
+            sum = __builtin_amdgcn_readlane(wave_scan_sum(sum), 63);
+            spread = spread_pays<R, NW>((int)gridDim.x, batch * n_sel, longest,
+                                        (sum >> 14) * kBlockTokens * n_sel, (sum & ((1 << 14) - 1)) * n_sel);
+        }
         lone = !spread && longest <= seg_tokens && batch * n_sel <= (int)gridDim.x;
         q_first_head = spread ? head_spread : head_lone;
         if (lone) {

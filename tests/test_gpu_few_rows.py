@@ -51,6 +51,8 @@ def test_ways_of_handing_out_agree(Hq, Hkv, D, kind):
         mode = int(ws[:16].view(torch.int32)[3].item())
         turn = 4 * (512 if r >= 4 else 256)
         chunks = max(lens) > turn // 4 and n < 512 and (r < 4 or max(lens) <= turn or n < 256)
+        if n == 511 and kind == ("long" if r < 4 else "turn"):
+            chunks = False                          # nearly two full segments a workgroup
         assert mode == (3 if chunks else 1), (kind, n, mode)
         # the same rows as pairs, in another order
         perm = rng.permutation(n).astype(np.int32)
@@ -76,3 +78,23 @@ def test_rows_of_many_segments(Hq, D):
                              w.block_table, w.seq_lens, np.asarray([1, 0], dtype=np.int32), w.spec.scale)
     check_rows(out, ref, selected_rows(w.spec, [1, 0]), TOL, "long rows")
     no_expired_wait()
+
+
+@pytest.mark.parametrize("Hq,D,rows,length,mode", [
+    (1, 64, 128, 600, 3), (1, 64, 204, 600, 3), (1, 64, 205, 600, 1), (1, 64, 256, 600, 1), (1, 64, 257, 600, 3),
+    (1, 128, 179, 4096, 3), (1, 128, 180, 4096, 1), (1, 128, 415, 2000, 3), (1, 128, 416, 2000, 1),
+    (1, 64, 511, 300, 3), (1, 64, 511, 600, 3), (1, 128, 426, 700, 3), (1, 128, 427, 700, 1),
+    (2, 128, 383, 2000, 3), (2, 128, 384, 2000, 1), (2, 64, 511, 300, 3),
+    (8, 128, 168, 2048, 3), (8, 128, 169, 2048, 1), (4, 64, 82, 600, 3), (4, 64, 83, 600, 1),
+    (8, 128, 257, 1200, 3), (8, 128, 415, 1200, 3), (8, 128, 416, 1200, 1), (8, 128, 257, 2049, 1),
+])
+def test_rows_whole_or_in_chunks(Hq, D, rows, length, mode):
+    """Both sides of the lines between single chunks (mode 3) and whole rows (mode 1), rows of one
+    length: the same bits as a launch that can only hand out whole rows."""
+    w = W.make_custom([length] * rows, Hq, 1, D, [0], seed=rows, device=DEV)
+    d, ws = Dev(w), torch.empty(256, dtype=torch.uint8, device=DEV)
+    H.check(H.hetis_attn_workspace_init(ws, 256), "workspace_init")
+    whole = d.decode_ws([0], ws)
+    ws = d.workspace(1)
+    assert np.array_equal(bits(d.decode_ws([0], ws)), bits(whole))
+    assert int(ws[:16].view(torch.int32)[3].item()) == mode
