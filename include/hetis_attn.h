@@ -182,9 +182,8 @@ int hetis_attn_decode_ws(const hetis_attn_shape *shape, const void *q, const voi
  *   k_cache, v_cache  read and written
  * The cache ends up as hetis_kv_append leaves it and `out` as hetis_attn_decode computes it on
  * that cache, bit for bit.  Like hetis_kv_append it does not store a row whose position is at or
- * past 16 * max_blocks_per_seq, whose block id is negative or whose head id is outside
- * [0, n_kv_heads); it has no num_blocks to check block ids against, and what the Attention part
- * reads is not checked (use hetis_attn_validate).  Workspace rules as for hetis_attn_decode /
+ * past 16 * max_blocks_per_seq or whose head id is outside [0, n_kv_heads); block ids and what the
+ * Attention part reads are not checked (use hetis_attn_validate).  Workspace rules as for hetis_attn_decode /
  * hetis_attn_decode_ws (same size).  Errors: those of hetis_attn_decode.
  */
 int hetis_attn_decode_step(const hetis_attn_shape *shape, const void *q, const void *k_new,
