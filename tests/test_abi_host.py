@@ -414,3 +414,19 @@ def test_kv_append_pairs_argument_errors(lib):
     assert call(shape=H.make_shape(4, 8, 8, 96, 16)) == binding.HETIS_ERR_UNSUPPORTED
     assert call(shape=H.make_shape(4, 8, 8, 64, 16, kv_stride_block=1000)) == binding.HETIS_ERR_BAD_SHAPE
     assert call(n_pairs=0) == binding.HETIS_OK
+
+
+def test_current_stream_with_and_without_torchs_raw_handle(monkeypatch):
+    import types
+    import torch
+    monkeypatch.setattr(torch.cuda, "is_available", lambda: True)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda dev: 100 + dev, raising=False)
+    assert binding._stream(None) == 103
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: False)
+    assert binding._stream(None) == 77
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert binding._stream(None) == 77
