@@ -98,3 +98,50 @@ def test_rows_whole_or_in_chunks(Hq, D, rows, length, mode):
     ws = d.workspace(1)
     assert np.array_equal(bits(d.decode_ws([0], ws)), bits(whole))
     assert int(ws[:16].view(torch.int32)[3].item()) == mode
+
+
+@pytest.mark.parametrize("r,D,rows,lo,hi,mode,chunks", [
+    (1, 64, 60, 0, 256, 1, None),                # a row a workgroup
+    (8, 128, 300, 0, 512, 1, None),              # whole rows through the tables
+    (1, 128, 511, 1400, 1700, 1, None),          # whole rows of several chunks
+    (8, 64, 280, 0, 600, 3, 1024),               # single chunks: up to one a wave,
+    (2, 64, 300, 200, 700, 3, 2048),             # two a wave: the second through the pool,
+    (8, 128, 300, 1900, 2048, 3, 2048),
+    (1, 128, 410, 1900, 2000, 3, 4096),          # more: the rest by tickets
+    (2, 64, 380, 1900, 2000, 3, 4096),
+    (1, 64, 40, 19000, 24000, 3, 4096),          # the same, rows of several segments
+])
+@pytest.mark.parametrize("pairs", [False, True])
+def test_steps_of_few_rows(r, D, rows, lo, hi, mode, chunks, pairs):
+    """The new rows are stored by whichever wave gets the chunk that reads them: at its first chunk,
+    from the workgroup's pool, or with a ticket.  Cache and outputs are those of the store and the
+    Attention in two calls."""
+    rng = np.random.default_rng(rows)
+    lens = rng.integers(lo, hi + 1, size=rows)
+    lens[rng.integers(rows)] = hi
+    if chunks:                                              # the case is the one that it says it is
+        ct = 512 if r >= 4 else 256
+        fine = lambda n: ct // (4 if n <= 256 else 2 if n <= 1024 else 1)
+        n = sum(L // 4096 * (4096 // ct) + -(-(L % 4096) // fine(L % 4096)) if L else 1 for L in lens.tolist())
+        assert chunks // 2 < n <= chunks
+    w = W.make_custom(lens, 2 * r, 2, D, [1], seed=rows, device=DEV)
+    kn, vn = W.new_token_rows(w)
+    two, one = Dev(w), Dev(w)
+    two.k, two.v = w.k_cache.clone(), w.v_cache.clone()
+    hid, _ = two.heads([1])
+    H.check(H.hetis_kv_append(two.shape, kn, vn, two.bt, two.sl, hid, 1, w.num_blocks, two.k, two.v), "append")
+    want = two.decode([1])
+    out, ws = one.new_out(), one.workspace(1)
+    if pairs:
+        ps, ph = torch.arange(rows, device=DEV).int(), torch.ones(rows, dtype=torch.int32, device=DEV)
+        table = 2 * one.bt + 1
+        H.check(H.hetis_attn_decode_pairs_step_ws(one.shape, one.q, kn, vn, one.k.view(-1, 16, D), one.v.view(-1, 16, D),
+                                                  table, one.sl, ps, ph, rows, one.scale, out, ws, ws.numel()), "step")
+    else:
+        H.check(H.hetis_attn_decode_step_ws(one.shape, one.q, kn, vn, one.k, one.v, one.bt, one.sl, hid, 1, one.scale,
+                                            out, ws, ws.numel()), "step")
+    torch.cuda.synchronize()
+    no_expired_wait(ws)
+    assert int(ws[:16].view(torch.int32)[3].item()) == mode
+    same = lambda a, b: torch.equal(a.view(torch.int16), b.view(torch.int16))
+    assert same(one.k, two.k) and same(one.v, two.v) and same(out, want)

@@ -223,8 +223,8 @@ def test_append_pairs_skips_what_points_outside():
 def test_decode_pairs_step_equals_append_pairs_then_decode_pairs(name):
     """One call for the decode step of the pairs form: pools and outputs bit-identical to
     hetis_kv_append_pairs + hetis_attn_decode_pairs, and within tolerance of the checker on the
-    checker's appended pools.  `few`: a handful of pairs (the store runs as a launch of its own);
-    `many` and the named shapes: the store inside the Attention kernel."""
+    checker's appended pools.  `few`: a handful of pairs, handed out as single chunks; `many` and the
+    named shapes: whole segments."""
     if name in ("few", "many"):
         lens = [1, 16, 17, 255, 256, 300, 0, 1025, 4095, 4096, 4097, 5000]
         if name == "many":
