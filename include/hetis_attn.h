@@ -183,7 +183,10 @@ int hetis_attn_decode_ws(const hetis_attn_shape *shape, const void *q, const voi
  * The cache ends up as hetis_kv_append leaves it and `out` as hetis_attn_decode computes it on
  * that cache, bit for bit.  Like hetis_kv_append it does not store a row whose position is at or
  * past 16 * max_blocks_per_seq or whose head id is outside [0, n_kv_heads); block ids and what the
- * Attention part reads are not checked (use hetis_attn_validate).  Workspace rules as for hetis_attn_decode /
+ * Attention part reads are not checked (use hetis_attn_validate).  Sequences may share blocks, but
+ * not those that receive their new tokens: a row is stored just before its own sequence reads it,
+ * so whether another sequence of the call that names the same block sees it is unspecified (call
+ * hetis_kv_append and hetis_attn_decode for that).  Workspace rules as for hetis_attn_decode /
  * hetis_attn_decode_ws (same size).  Errors: those of hetis_attn_decode.
  */
 int hetis_attn_decode_step(const hetis_attn_shape *shape, const void *q, const void *k_new,
@@ -363,8 +366,8 @@ int hetis_attn_decode_pairs_ws(const hetis_attn_shape *shape, const void *q, con
  * (hetis_kv.h) followed by hetis_attn_decode_pairs.  k_new, v_new fp16 [B, Hkv, D]: pair p
  * stores the rows of (pair_seq[p], pair_head[p]) at position seq_lens[b] - 1 of its own
  * block-table row (length 0 stores nothing); k_tiles, v_tiles are read and written.  Pools
- * and `out` end up as the two calls leave them, bit for bit; checks as for
- * hetis_attn_decode_step (see also hetis_attn_validate_pairs).  A (sequence, head) listed
+ * and `out` end up as the two calls leave them, bit for bit; checks, and what pairs may share, as
+ * for hetis_attn_decode_step (see also hetis_attn_validate_pairs).  A (sequence, head) listed
  * twice with different block-table rows stores the rows through both.  Workspace rules,
  * sizes and errors as for hetis_attn_decode_pairs / hetis_attn_decode_pairs_ws.
  */
