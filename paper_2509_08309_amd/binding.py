@@ -171,11 +171,13 @@ def _stream(stream) -> Optional[int]:
     if stream is None:
         import torch
         # The current stream's handle without a Stream object around it: building one is 3.5 us, of
-        # 9 us that a call takes on the host, and the smallest launches wait for the host.  The name
-        # is torch's own business: without it, the documented way.
-        raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-        if raw_stream is not None and torch.cuda.is_initialized():
-            return raw_stream(torch.cuda.current_device())
+        # 9 us that a call takes on the host, and the smallest launches wait for the host.  The names
+        # are torch's own business: without them, the documented way.
+        if torch.cuda.is_initialized():
+            try:
+                return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            except AttributeError:
+                pass
         return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
     if isinstance(stream, int):
         return stream
