@@ -134,9 +134,9 @@ const char *hetis_attn_status_string(int status);
  * bit of the result: a call with 512 or more (sequence, selected head)
  * combinations hands out whole segments, whose chunks are combined on chip, so
  * that only segment results of sequences longer than 4096 tokens pass through
- * the workspace; a call with fewer hands out single chunks, whose results all
+ * the workspace; a call with fewer may hand out single chunks, whose results all
  * pass through the workspace, so that a few long sequences still occupy the
- * whole device.
+ * whole device (it decides by the lengths, on the device).
  *
  * hetis_attn_decode_ws: the caller's workspace.  hetis_attn_decode_workspace_bytes(shape,
  *   n_sel_heads) is the size with which the call runs as described (it depends on batch,

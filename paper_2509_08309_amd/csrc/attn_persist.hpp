@@ -33,8 +33,8 @@
 // back to zero for the next launch.
 // Scheduling modes (AttnParams::mode).  kModeSegments is the above.  kModeSplit: seg_tokens =
 // chunk_tokens, every chunk leaves as a partial result for a separate merge launch.
-// kModeSpread is an offer of the host for launches of few rows, where whole segments would leave
-// most workgroups without work.  If the kernel takes it up, the unit handed out is the chunk (full
+// kModeSpread is an offer of the host for launches of few rows, where whole segments can leave
+// much of the chip without work.  If the kernel takes it up, the unit handed out is the chunk (full
 // chunks of all rows first, then the shorter ones), chunk results go through the partial buffers
 // in global memory, and the wave that stores the last chunk result of a segment folds that
 // segment's chunks with the operations and in the order of the in-LDS fold (fold_coef /
@@ -44,10 +44,10 @@
 // combination after the last chunk.  Hence: no tables and one barrier (every wave enumerates
 // in registers), one chunk a wave across all compute units with the short ones second, the last
 // chunk of a wave stored and combined by that wave, and partial results loaded many at a time.
-// Measured, before (tables, chunks in row order, the writer wave combining one load at a time)
-// and after: 16 chats of 1088 tokens on average x 13 heads of 128 44.9 -> 32.6 us; two
-// documents of 20k and 27k tokens x 8 heads 70.0 -> 45.5; 144 pairs of 8-head groups 57.5 ->
-// 45.9; 4 chats x 4 heads of 64 14.9 -> 11.2.
+// Measured, before (tables, chunks in row order, the writer wave combining one load at a time, a
+// step's store as a launch of its own) and now: 16 chats of 1088 tokens on average x 13 heads of
+// 128 45.1 -> 28.8 us; two documents of 20k and 27k tokens x 8 heads 70.4 -> 44.2; step of 144 pairs
+// of 8-head groups 58.2 -> 43.4; 4 chats x 4 heads of 64 15.0 -> 11.5.
 //
 // A workgroup is NW streaming waves plus one writer wave; after the prologue they never
 // meet at a barrier.
@@ -832,12 +832,12 @@ __global__ __launch_bounds__((NW + 1) * 64)
     //  1. All threads fetch the lengths of their rows (in pairs mode first the pair's sequence
     //     and head; the loads of all rounds are in flight together) and work out, per row, the
     //     number of whole segments and the size class of the last, shorter one.  Inside each
-    //     group a shuffle scan gives the running count of whole segments, and five ballots
+    //     group a DPP scan gives the running count of whole segments, and five ballots
     //     (one per bit of the class number) give every row the set of rows of its class, hence
     //     its rank among them and the class's count.
     //  2. The per-(class, group) counts, laid out class-major, and the per-group segment
     //     totals go through exclusive scans over the workgroup (three elements a thread, a
-    //     shuffle scan per wave, wave totals through LDS).
+    //     DPP scan per wave, wave totals through LDS).
     //  3. Every thread writes its rows' table entries: firstF[row] = whole segments before
     //     the row; order[position] = row, position = rows of larger classes + rows of the
     //     same class in lower groups + rank.

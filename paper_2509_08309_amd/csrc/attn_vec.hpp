@@ -220,8 +220,9 @@ struct VecPolicy {
 // 64 segments take one load, a lane each, and their weights one exponential a lane; the partial
 // results of kMergeBatch segments are in flight at the same time as the log-sum-exps, which they do
 // not depend on.  The sums keep their order: ascending segments.
-// Before and after, whole split calls: 320 rows of 40 segments 551.5 -> 547.6 us, 32 grouped-query
-// rows of 38 segments 37.6 -> 33.4, 8 rows of 200 segments 35.2 -> 33.8, rows of one segment the same.
+// This launch alone, against one load of each kind after the other: 8 x 40 rows of up to 32 segments
+// 4.7 -> 4.0 us, 200 x 8 of 17 to 33 10.8 -> 7.3, 64 x 13 of up to 4 3.1 -> 2.8, 8 rows of up to 250
+// 10.1 -> 10.3.
 constexpr int kMergeBatch = 32;
 template <int D>
 __global__ __launch_bounds__(D) void attn_merge_kernel(const AttnParams p, int group)
@@ -247,7 +248,8 @@ __global__ __launch_bounds__(D) void attn_merge_kernel(const AttnParams p, int g
     const float *op = p.o_partial + base * D + d;
     float W = 0.f, acc = 0.f;
     if (n_segs <= 4) {
-        // nothing to share between lanes (6600 rows of one segment: 1.5 us less a launch)
+        // nothing to share between lanes (a split call over 6600 rows of one segment: 83.1 us without
+        // this branch, 81.6 with it)
         float lc[4], x4[4], M = -INFINITY;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {

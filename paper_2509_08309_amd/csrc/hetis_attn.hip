@@ -170,7 +170,8 @@ static int launch_persistent(AttnParams p, int batch, hipStream_t st)
     int64_t G = (int64_t)cus * occ;
     // Segments (single chunks), at most.  Rows that no launch hands out chunk by chunk, however
     // long they are here (see `longest` in the kernel), are one segment each.
-    const bool short_rows = p.mode == kModeSpread && p.max_blocks_per_seq * kBlockTokens <= p.chunk_tokens;
+    const bool short_rows =
+        p.mode == kModeSpread && (int64_t)p.max_blocks_per_seq * kBlockTokens <= p.chunk_tokens;
     const int64_t most = (int64_t)batch * (short_rows ? 1 : p.max_segs) * p.n_sel;
     if (G > most) G = most;
     launch_timed(kernel, dim3((unsigned)G), dim3((NW + 1) * 64), lds, st, p, batch);
@@ -278,7 +279,6 @@ struct WsLayout {
     size_t arrivals = 0, o_partial = 0, lse_partial = 0, total = kControlBytes;
     size_t zeroed = kControlBytes;     // leading bytes this shape needs to be zero between launches
     int slots = 1;                     // partial-result slots per row
-    int part_stride = 1;
     bool spread = false;
 };
 constexpr size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -297,8 +297,7 @@ static WsLayout decode_ws_layout(const hetis_attn_shape *s, int64_t rows, int n_
     WsLayout w;
     const int max_segs = decode_max_segs(s, group);
     w.spread = spread;
-    w.part_stride = spread ? decode_seg_tokens(group) / decode_chunk_tokens(group) : 1;
-    w.slots = max_segs * w.part_stride;
+    w.slots = max_segs * (spread ? decode_seg_tokens(group) / decode_chunk_tokens(group) : 1);
     if (w.slots <= 1 || rows <= 0) return w;         // every row is written directly
     const size_t partial_rows = (size_t)rows * n_sel * group * w.slots;
     w.arrivals = kControlBytes;
@@ -461,7 +460,6 @@ static void apply_layout(AttnParams &p, const WsLayout &lay, int group, void *wo
     p.chunk_tokens = decode_chunk_tokens(group);
     p.seg_tokens = decode_seg_tokens(group);
     p.max_segs = lay.slots;
-    p.part_stride = lay.part_stride;
     p.mode = lay.spread ? kModeSpread : kModeSegments;
     p.direct_single = 1;
     unsigned char *base = static_cast<unsigned char *>(workspace);
@@ -838,7 +836,6 @@ static int decode_split_common(const hetis_attn_shape *shape, const void *q, con
     p.chunk_tokens = chunk_tokens;      // every chunk is a segment of its own
     p.seg_tokens = chunk_tokens;
     p.mode = kModeSplit;
-    p.part_stride = 1;
     p.max_segs = hetis_attn_split_num_chunks(max_seq_len, chunk_tokens);
     p.direct_single = 0;
     p.o_partial = o_partial;
