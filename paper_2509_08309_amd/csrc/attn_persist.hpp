@@ -777,6 +777,11 @@ __global__ __launch_bounds__((NW + 1) * 64)
             if (u * 64 < batch) longest = max(longest, u * 64 + lane < batch ? q_len[u] : 0);
         longest = wave_max(longest);
         if (longest > seg_tokens) {
+            // Rows of several segments: chunks while there are fewer segments than workgroups.  Two
+            // rows of 20k and 27k tokens x 8 heads need it (see the top).  Around one segment a
+            // workgroup neither way is always ahead: whole segments -> chunks, 20 rows of 15k to 60k,
+            // r = 1 78 -> 82 us, r = 2 70 -> 63, r = 8 90 -> 105; 20 rows of 60k, r = 1 141 -> 111, r = 8
+            // 152 -> 142; far beyond it whole segments are (500 rows of 5000, r = 2: 150 -> 167).
             int n_segments = 0;
 #pragma unroll
             for (int u = 0; u < QG; ++u)
