@@ -632,11 +632,11 @@ __device__ __forceinline__ void store_new_rows(const AttnParams &p, int seq, int
 //  - More rows.  Chunks for a few long ones among short ones (511 rows, log-normal around 820, up
 //    to 4096: 75 -> 63), where the rows are alike and the workgroups' second turn is mostly empty
 //    (270 of 4096: 134 -> 104), and for up to one (r >= 4) or about two chunks a wave (390 of 1200:
-//    54 -> 47; 511 of 150 to 600: 33 -> 30; r = 2 not if these are quarter chunks: 480 of 75 to 300
-//    27.1 -> 29.3).  Otherwise rows whole: 511 of 500 to 2000 64 -> 71, r = 2 67 -> 78, r = 8 65 ->
-//    77; 511 of 1 to 4096 in seven lengths, r = 2, 93 -> 111.  r >= 4, rows of more than one turn:
-//    whole (r = 8, 360 of 750 to 3000: 75 -> 80).
-template <int R, int NW>
+//    54 -> 47; 511 of 150 to 600: 33 -> 30; r = 2 and 128 dims not if these are quarter chunks: 480
+//    of 75 to 300 27.1 -> 29.3, with 64 dims 25.2 -> 23.9).  Otherwise rows whole: 511 of 500 to
+//    2000 64 -> 71, r = 2 67 -> 78, r = 8 65 -> 77; 511 of 1 to 4096 in seven lengths, r = 2, 93 ->
+//    111.  r >= 4, rows of more than one turn: whole (r = 8, 360 of 750 to 3000: 75 -> 80).
+template <int D, int R, int NW>
 __device__ __forceinline__ bool spread_pays(int G, int rows, int longest, int tokens, int chunks)
 {
     constexpr int ct = decode_chunk_tokens(R), turn = NW * ct;      // tokens a workgroup's waves hold
@@ -648,13 +648,14 @@ __device__ __forceinline__ bool spread_pays(int G, int rows, int longest, int to
         // chunks of the longest row are full ones, or half as long
         const bool halves = chunk_tokens_of(longest, ct, decode_seg_tokens(R)) < ct;
         return (!halves && 10 * chunks <= 4 * waves) ||
-               200ll * ct * tokens < (halves ? 56ll : 33ll) * longest * full;
+               200ll * ct * tokens < (halves ? 60ll : 35ll) * longest * full;
     }
-    const bool even = 20 * tokens >= 17 * full && 16 * rows < (R == 2 ? 24 : 26) * G;
+    constexpr bool wide = R < 4 && R * D > 128;             // a partial result of more than 512 bytes
+    const bool even = 20 * tokens >= 17 * full && 16 * rows < (wide ? 24 : 26) * G;
     if (R < 4)
         return idle || even || 10 * chunks <= 11 * waves ||
-               (10 * chunks <= (R == 1 ? 25 : 23) * waves && (R == 1 || tokens >= 80 * chunks));
-    return longest <= turn && (chunks <= waves || 20 * tokens < (R == 4 ? 18 : 11) * full || even);
+               (10 * chunks <= (wide ? 23 : 25) * waves && (!wide || tokens >= 80 * chunks));
+    return longest <= turn && (chunks <= waves || 20 * tokens < (R * D <= 512 ? 18 : 11) * full || even);
 }
 
 // VARIANT selects what is compiled in besides the common path; code that a launch cannot reach
@@ -790,7 +791,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
             n_segments = __builtin_amdgcn_readlane(wave_scan_sum(n_segments), 63);
             spread = (long long)n_segments * n_sel < (long long)gridDim.x;
         } else if (longest > chunk_tokens) {
-            // blocks and chunks of all rows in one sum: below 2^18 and 2^14
+            // blocks and chunks of all rows, fewer than kMaxQuickRows, in one sum: below 2^17 and 2^14
             static_assert(kMaxQuickRows * kSegChunks <= 1 << 14 &&
                           kMaxQuickRows * (decode_seg_tokens(R) / kBlockTokens) <= 1 << 17, "sums fit");
             int sum = 0;
@@ -803,7 +804,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
                     sum += ((L + kBlockTokens - 1) / kBlockTokens << 14) + ((L + ct - 1) >> sh);
             }
             sum = __builtin_amdgcn_readlane(wave_scan_sum(sum), 63);
-            spread = spread_pays<R, NW>((int)gridDim.x, batch * n_sel, longest,
+            spread = spread_pays<D, R, NW>((int)gridDim.x, batch * n_sel, longest,
                                         (sum >> 14) * kBlockTokens * n_sel, (sum & ((1 << 14) - 1)) * n_sel);
         }
         lone = !spread && longest <= seg_tokens && batch * n_sel <= (int)gridDim.x;

@@ -84,8 +84,8 @@ def test_rows_of_many_segments(Hq, D):
     (1, 64, 128, 600, 3), (1, 64, 204, 600, 3), (1, 64, 205, 600, 1), (1, 64, 256, 600, 1), (1, 64, 257, 600, 3),
     (1, 128, 179, 4096, 3), (1, 128, 180, 4096, 1), (1, 128, 415, 2000, 3), (1, 128, 416, 2000, 1),
     (1, 64, 511, 300, 3), (1, 64, 511, 600, 3), (1, 128, 426, 700, 3), (1, 128, 427, 700, 1),
-    (2, 128, 383, 2000, 3), (2, 128, 384, 2000, 1), (2, 64, 511, 300, 3),
-    (8, 128, 168, 2048, 3), (8, 128, 169, 2048, 1), (4, 64, 82, 600, 3), (4, 64, 83, 600, 1),
+    (2, 128, 383, 2000, 3), (2, 128, 384, 2000, 1), (2, 64, 415, 2000, 3), (2, 64, 416, 2000, 1), (2, 64, 511, 300, 3),
+    (8, 128, 179, 2048, 3), (8, 128, 180, 2048, 1), (4, 64, 88, 600, 3), (4, 64, 89, 600, 1),
     (8, 128, 257, 1200, 3), (8, 128, 415, 1200, 3), (8, 128, 416, 1200, 1), (8, 128, 257, 2049, 1),
 ])
 def test_rows_whole_or_in_chunks(Hq, D, rows, length, mode):
@@ -135,8 +135,9 @@ def test_steps_of_few_rows(r, D, rows, lo, hi, mode, chunks, pairs):
     if pairs:
         ps, ph = torch.arange(rows, device=DEV).int(), torch.ones(rows, dtype=torch.int32, device=DEV)
         table = 2 * one.bt + 1
-        H.check(H.hetis_attn_decode_pairs_step_ws(one.shape, one.q, kn, vn, one.k.view(-1, 16, D), one.v.view(-1, 16, D),
-                                                  table, one.sl, ps, ph, rows, one.scale, out, ws, ws.numel()), "step")
+        k_tiles, v_tiles = one.k.view(-1, 16, D), one.v.view(-1, 16, D)
+        H.check(H.hetis_attn_decode_pairs_step_ws(one.shape, one.q, kn, vn, k_tiles, v_tiles, table, one.sl, ps, ph,
+                                                  rows, one.scale, out, ws, ws.numel()), "step")
     else:
         H.check(H.hetis_attn_decode_step_ws(one.shape, one.q, kn, vn, one.k, one.v, one.bt, one.sl, hid, 1, one.scale,
                                             out, ws, ws.numel()), "step")
