@@ -150,10 +150,9 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 // this chip (measured with the cache rotated over three physical copies, so it is not reuse
 // in the last-level cache).
 constexpr int kStreamingLoad = 2;
-__device__ __forceinline__ uint4 buffer_load_u4(__amdgpu_buffer_rsrc_t r, int byte_offset)
+__device__ __forceinline__ u32x4 buffer_load_u4(__amdgpu_buffer_rsrc_t r, int byte_offset)
 {
-    const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(r, byte_offset, 0, kStreamingLoad);
-    return make_uint4(x.x, x.y, x.z, x.w);
+    return __builtin_amdgcn_raw_buffer_load_b128(r, byte_offset, 0, kStreamingLoad);
 }
 
 // One word to / from device memory, coherent across the whole device (all XCDs): these
@@ -167,11 +166,5 @@ __device__ __forceinline__ float coherent_load(const float *ptr)
 {
     return __hip_atomic_load(ptr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-
-union Pack16 {
-    uint4 u;
-    __half2 h2[4];
-    __half h[8];
-};
 
 }  // namespace hetis

@@ -60,8 +60,8 @@ struct MfmaPolicy {
     static constexpr int kRing = D_ == 64 ? 4 : HETIS_MFMA_RING;   // tile pairs in flight per wave (a third pair at D = 128 was worth 2 % on the grouped-query workloads)
 
     struct Tile {
-        uint4 k[KS];
-        uint4 v[NV];
+        u32x4 k[KS];
+        u32x4 v[NV];
     };
     struct Query {
         f16x8 b[KS];
@@ -109,13 +109,9 @@ struct MfmaPolicy {
             reinterpret_cast<const __half *>(stage + kStageV) + min(j, R - 1) * D + (lane >> 4) * 8;
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
-            union {
-                uint4 u;
-                f16x8 h;
-            } t;
-            t.u = *reinterpret_cast<const uint4 *>(src + s * 32);
-            if (j >= R) t.u = make_uint4(0u, 0u, 0u, 0u);
-            q.b[s] = t.h;
+            u32x4 t = *reinterpret_cast<const u32x4 *>(src + s * 32);
+            if (j >= R) t = u32x4{0u, 0u, 0u, 0u};
+            q.b[s] = __builtin_bit_cast(f16x8, t);
         }
     }
 
@@ -142,20 +138,15 @@ struct MfmaPolicy {
         for (int i = 0; i < NV; ++i) {
             const int pos = i * 1024 + lane * 16;
             const int row = pos / (2 * D), colb = pos % (2 * D);
-            uint4 v = t.v[i];
-            if (row >= n_valid) v = make_uint4(0u, 0u, 0u, 0u);   // slots past the end may hold NaN
-            *reinterpret_cast<uint4 *>(vstage + row * kPitchV + colb) = v;
+            u32x4 v = t.v[i];
+            if (row >= n_valid) v = u32x4{0u, 0u, 0u, 0u};        // slots past the end may hold NaN
+            *reinterpret_cast<u32x4 *>(vstage + row * kPitchV + colb) = v;
         }
         // ---- scores of 16 tokens x 16 (padded) heads
         f32x4 c = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
-            union {
-                uint4 u;
-                f16x8 h;
-            } a;
-            a.u = t.k[s];
-            c = __builtin_amdgcn_mfma_f32_16x16x32_f16(a.h, q.b[s], c, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, t.k[s]), q.b[s], c, 0, 0, 0);
         }
         float s4[4];
 #pragma unroll
