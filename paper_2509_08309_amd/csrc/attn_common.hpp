@@ -145,6 +145,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const __half *tile, 
 }
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 // 16 bytes of a KV tile.  The load is marked non-temporal (cache-policy bit 1): every tile is
 // read exactly once per call, and telling the caches so was worth 9 % of the kernel's time on
 // this chip (measured with the cache rotated over three physical copies, so it is not reuse
@@ -165,6 +167,26 @@ __device__ __forceinline__ void coherent_store(float *ptr, float v)
 __device__ __forceinline__ float coherent_load(const float *ptr)
 {
     return __hip_atomic_load(ptr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The same for sixteen bytes a lane: buffer accesses with the device-scope bit (sc1) of the cache
+// policy, bounded by the descriptor (lanes past its end store nothing).
+constexpr int kDeviceScope = 16;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t coherent_rsrc(float *base, int bytes)
+{
+    const uint64_t a = reinterpret_cast<uint64_t>(base);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc(
+        reinterpret_cast<void *>(((uint64_t)hi << 32) | lo), 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ void coherent_store_b128(__amdgpu_buffer_rsrc_t r, int byte_offset, u32x4 v)
+{
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, byte_offset, 0, kDeviceScope);
+}
+__device__ __forceinline__ u32x4 coherent_load_b128(__amdgpu_buffer_rsrc_t r, int byte_offset, int wave_offset)
+{
+    return __builtin_amdgcn_raw_buffer_load_b128(r, byte_offset, wave_offset, kDeviceScope);
 }
 
 }  // namespace hetis

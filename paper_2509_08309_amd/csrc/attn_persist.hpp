@@ -237,47 +237,62 @@ struct ChunkPool {
 template <int D, int R>
 struct alignas(16) Mailbox {
     float o[R][D];      // normalised output rows
-    float lse[R];       // base-2 log-sum-exp of each row: m + log2(sum_t 2^(s_t - m))
-    int kind, dest, cs; // as in the chunk's descriptor
-    int nseg, out_row, len;
+    int kind, dest, cs, nseg;   // as in the chunk's descriptor (the first four read together)
+    int out_row, len;
     int flag;           // kMailEmpty / kMailFull / kMailDone
+    float lse[R];       // base-2 log-sum-exp of each row: m + log2(sum_t 2^(s_t - m))
 };
 
 // Running combination of the chunks of one segment (writer wave only).
 template <int D, int R>
 struct alignas(16) FoldSlot {
     float acc[R][D];    // sum over folded chunks of o_c 2^(lse_c - M)
-    float M[R];         // running maximum of lse_c (base 2); at the end M + log2 W
-    float W[R];         // sum over folded chunks of 2^(lse_c - M)
     int next;           // chunk to fold next
     int ns;             // chunks of the segment
     int kind, dest;     // where the finished segment goes: kKindOut / kKindPartial
+    float M[R];         // running maximum of lse_c (base 2)
+    float W[R];         // sum over folded chunks of 2^(lse_c - M)
 };
 
 template <int R>
 __host__ __device__ constexpr int fold_slots() { return R >= 4 ? 5 : 8; }
 
-// Result rows in LDS -> `out` (fp16) or the partial buffers (fp32); one wave, four elements a
-// lane.  `lse2`: base-2 log-sum-exp per row; `w`: when not null, row r is divided by w[r] on
-// the way out (the weight sum of a fold slot).
+// The R result rows of one chunk or segment in the registers of a wave: lane l holds elements
+// 4 l + 256 k .. + 3 of the R * D, and with them the row's log-sum-exp.  With fewer than 256 elements
+// the lanes beyond them hold copies of the last ones, which are not stored.
 template <int D, int R>
-__device__ __forceinline__ void store_result(const float (*o)[D], const float *lse2,
-                                             const float *w, int kind, int64_t dest,
+struct RowRegs {
+    static constexpr int K = (R * D + 255) / 256;
+    f32x4 x[K];
+    float lse[K];       // base 2
+    __device__ static __forceinline__ int elem(int lane, int k) { return min(lane * 4 + k * 256, R * D - 4); }
+    __device__ static __forceinline__ bool stored(int lane) { return R * D >= 256 || lane * 4 < R * D; }
+    __device__ __forceinline__ void load(const float (*o)[D], const float *lse2, int lane)
+    {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            x[k] = *reinterpret_cast<const f32x4 *>(&o[0][0] + elem(lane, k));
+            lse[k] = lse2[elem(lane, k) / D];
+        }
+    }
+};
+
+// Result rows -> `out` (fp16) or the partial buffers (fp32, natural-log log-sum-exp).
+template <int D, int R>
+__device__ __forceinline__ void store_result(const RowRegs<D, R> &g, int kind, int64_t dest,
                                              const AttnParams &p, int lane)
 {
+    if (!RowRegs<D, R>::stored(lane)) return;
 #pragma unroll
-    for (int idx = lane * 4; idx < R * D; idx += 256) {
-        const int r = idx / D, d = idx % D;
-        float4 v = *reinterpret_cast<const float4 *>(&o[r][d]);
-        if (w) {
-            const float s = __builtin_amdgcn_rcpf(w[r]);
-            v = make_float4(v.x * s, v.y * s, v.z * s, v.w * s);
-        }
+    for (int k = 0; k < RowRegs<D, R>::K; ++k) {
+        const int idx = lane * 4 + k * 256, r = idx / D, d = idx % D;
+        f32x4 v = g.x[k];
         if (kind == kKindPartial) {
             // the r rows of one (row, head, segment) are contiguous in the partial buffers
-            *reinterpret_cast<float4 *>(p.o_partial + dest * (R * D) + idx) = v;
+            *reinterpret_cast<f32x4 *>(p.o_partial + dest * (R * D) + idx) = v;
+            if (d == 0) p.lse_partial[dest * R + r] = g.lse[k] * kLn2;
         } else {
-            if (kind == kKindZero) v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (kind == kKindZero) v = f32x4{0.f, 0.f, 0.f, 0.f};
             union {
                 __half2 h[2];
                 uint2 u;
@@ -287,43 +302,71 @@ __device__ __forceinline__ void store_result(const float (*o)[D], const float *l
             *reinterpret_cast<uint2 *>(p.out + (dest + r) * D + d) = pk.u;
         }
     }
-    // partial results carry the natural-log log-sum-exp
-    if (kind == kKindPartial && lane < R) p.lse_partial[dest * R + lane] = lse2[lane] * kLn2;
 }
 
 // Partial result of a segment that is merged inside this launch (AttnParams::arrivals): by
 // whichever wave stores the row's last segment, possibly on another XCD, so the words are
-// stored device-coherently, one per lane and step.
+// stored device-coherently, sixteen bytes a lane.
 // `base2`: the log-sum-exp is stored as it is (chunk results of kModeSpread), otherwise as a
 // natural logarithm (segment results).
 template <int D, int R>
-__device__ __forceinline__ void store_partial_coherent(const float (*o)[D], const float *lse2,
-                                                       const float *w, int64_t dest,
+__device__ __forceinline__ void store_partial_coherent(const RowRegs<D, R> &g, int64_t dest,
                                                        const AttnParams &p, int lane, bool base2)
 {
-    static_assert(R * D % 64 == 0, "whole steps of one word a lane");
+    const __amdgpu_buffer_rsrc_t dst = coherent_rsrc(p.o_partial + dest * (R * D), R * D * 4);
 #pragma unroll
-    for (int k = 0; k < R * D / 64; ++k) {
-        const int idx = k * 64 + lane;
-        float v = o[0][idx];
-        if (w) v *= __builtin_amdgcn_rcpf(w[idx / D]);
-        coherent_store(p.o_partial + dest * (R * D) + idx, v);
+    for (int k = 0; k < RowRegs<D, R>::K; ++k) {
+        const int idx = lane * 4 + k * 256;              // (past the R * D elements: not stored)
+        coherent_store_b128(dst, idx * 4, __builtin_bit_cast(u32x4, g.x[k]));
+        if (idx < R * D && idx % D == 0)
+            coherent_store(p.lse_partial + dest * R + idx / D, base2 ? g.lse[k] : g.lse[k] * kLn2);
     }
-    if (lane < R)
-        coherent_store(p.lse_partial + dest * R + lane, base2 ? lse2[lane] : lse2[lane] * kLn2);
 }
 
 // Partial results loaded together by the two functions below.  Their loads are device-coherent
 // (the partial results may come from other XCDs) and the compiler keeps such loads in program
 // order with every use, so a loop that loads and uses one result at a time pays a memory round
 // trip for each: the wave that ends a launch then spends tens of microseconds on a row.
+// With four or eight rows a result (kPartVectors) a lane loads vectors of four words, as many as there
+// are registers for (eight with 8 x 128 words; scratch memory otherwise), and looks its row's weight up;
+// with one or two rows it loads words, the same dims of every row, and weights are the same in all lanes.
+// A step of 144 pairs of 8-head groups: words 44.9 us, vectors 43.4; 16 chats x 13 heads (r = 1) 27.5 and 28.1.
 template <int R>
-constexpr int kPartBatch = R == 1 ? 16 : R == 8 ? 2 : 32 / R;      // at most 64 / R
+constexpr bool kPartVectors = R >= 4;
+template <int D, int R>
+constexpr int kPartBatch =                                         // at most 64 / R
+    !kPartVectors<R> ? 16 : (R * D > 512 ? 8 : 16) / RowRegs<D, R>::K;
+
+// Partial results in slots slot_of(0), slot_of(1), ... of the partial buffers -> x; their
+// log-sum-exps come back with lane u * R + r holding that of result u, row r.
+template <int D, int R, class SlotOf>
+__device__ __forceinline__ float load_partials(const AttnParams &p, f32x4 (&x)[kPartBatch<D, R>][RowRegs<D, R>::K],
+                                               SlotOf slot_of, int lane)
+{
+    const float lc = coherent_load(p.lse_partial + slot_of(min(lane / R, kPartBatch<D, R> - 1)) * R + lane % R);
+    const int64_t s0 = slot_of(0);
+    const __amdgpu_buffer_rsrc_t src = coherent_rsrc(
+        p.o_partial + s0 * (R * D), (int)(slot_of(kPartBatch<D, R> - 1) - s0 + 1) * (R * D * 4));
+#pragma unroll
+    for (int u = 0; u < kPartBatch<D, R>; ++u) {
+        const int from = (int)(slot_of(u) - s0) * (R * D * 4);
+#pragma unroll
+        for (int k = 0; k < RowRegs<D, R>::K; ++k)
+            x[u][k] = __builtin_bit_cast(
+                f32x4, coherent_load_b128(src, RowRegs<D, R>::elem(lane, k) * 4, from));
+    }
+    return lc;
+}
+
+// x of lane `lane + ahead`
+__device__ __forceinline__ float from_lane(float x, int lane, int ahead)
+{
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(4 * lane + 4 * ahead, __float_as_int(x)));
+}
 
 // Log-sum-exp merge of the n_segs partial results of one row, ascending segment order, by one
-// wave: M = max_c lse_c, w_c = exp(lse_c - M), out = fp16(sum_c w_c o_c / sum_c w_c).  Lane l
-// owns dims l and l + 64 (D = 128) of each of the R query rows.  `first` is the index of
-// segment 0 of the row in the partial buffers, segment c sits `stride` * c slots further.
+// wave: M = max_c lse_c, w_c = exp(lse_c - M), out = fp16(sum_c w_c o_c / sum_c w_c).  `first` is the
+// index of segment 0 of the row in the partial buffers, segment c sits `stride` * c slots further.
 // The maximum takes one load a lane per 64 log-sum-exps, the sums one round trip per
 // kPartBatch segments (two rows of 5 to 7 segments per head, one load at a time: 25 us of the 70
 // that launch took).
@@ -331,58 +374,104 @@ template <int D, int R>
 __device__ __forceinline__ void merge_partials(const AttnParams &p, int64_t first, int n_segs,
                                                int stride, int64_t out_row, int lane)
 {
-    constexpr int V = D / 64;                        // words per lane and row: 1 or 2
-    constexpr int U = kPartBatch<R>;
-    const int64_t step = (int64_t)stride * R;        // rows of the buffers per segment
-    const float *lse = p.lse_partial + first * R;    // [segment][r]
-    const float *op = p.o_partial + first * (R * D) + lane;
-    // lane l looks at segments l / R, l / R + 64 / R, ... of row l % R
-    float mx = -INFINITY;
+    if constexpr (kPartVectors<R>) {
+        constexpr int K = RowRegs<D, R>::K, U = kPartBatch<D, R>;
+        const int64_t step = (int64_t)stride * R;        // rows of the buffers per segment
+        const float *lse = p.lse_partial + first * R;    // [segment][r]
+        // lane l looks at segments l / R, l / R + 64 / R, ... of row l % R
+        float mx = -INFINITY;
 #pragma unroll 1
-    for (int c0 = 0; c0 < n_segs; c0 += 64 / R)
-        mx = fmaxf(mx, coherent_load(lse + min(c0 + lane / R, n_segs - 1) * step + lane % R));
+        for (int c0 = 0; c0 < n_segs; c0 += 64 / R)
+            mx = fmaxf(mx, coherent_load(lse + min(c0 + lane / R, n_segs - 1) * step + lane % R));
 #pragma unroll
-    for (int off = 32; off >= R; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-    float M[R], W[R], acc[R][V];
+        for (int off = 32; off >= R; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+        RowRegs<D, R> g;
+        float M[K], W[K];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        M[r] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mx), r));
-        W[r] = 0.f;
-#pragma unroll
-        for (int v = 0; v < V; ++v) acc[r][v] = 0.f;
-    }
+        for (int k = 0; k < K; ++k) {
+            M[k] = __shfl(mx, RowRegs<D, R>::elem(lane, k) / D, 64);
+            W[k] = 0.f;
+            g.x[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+            g.lse[k] = 0.f;
+        }
 #pragma unroll 1
-    for (int c0 = 0; c0 < n_segs; c0 += U) {
-        float x[U][R][V];
-        // lane u * R + r: log-sum-exp of segment c0 + u, row r
-        const int lc = __float_as_int(coherent_load(lse + min(c0 + lane / R, n_segs - 1) * step + lane % R));
+        for (int c0 = 0; c0 < n_segs; c0 += U) {
+            f32x4 x[U][K];
+            const float lc = load_partials<D, R>(
+                p, x, [&](int u) { return first + (int64_t)min(c0 + u, n_segs - 1) * stride; }, lane);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t row = min(c0 + u, n_segs - 1) * step;
+            for (int u = 0; u < U; ++u) {
+                if (c0 + u >= n_segs) continue;
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
+                for (int k = 0; k < K; ++k) {
+                    const float lse_c = from_lane(lc, RowRegs<D, R>::elem(lane, k) / D, u * R);
+                    const float w = fast_exp2((lse_c - M[k]) * kLog2e);
+                    W[k] += w;
 #pragma unroll
-                for (int v = 0; v < V; ++v) x[u][r][v] = coherent_load(op + (row + r) * D + v * 64);
+                    for (int e = 0; e < 4; ++e) g.x[k][e] = fmaf(w, x[u][k][e], g.x[k][e]);
+                }
             }
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (c0 + u >= n_segs) continue;
+        for (int k = 0; k < K; ++k) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const float lse_c = __int_as_float(__builtin_amdgcn_readlane(lc, u * R + r));
-                const float w = fast_exp2((lse_c - M[r]) * kLog2e);
-                W[r] += w;
+            for (int e = 0; e < 4; ++e) g.x[k][e] /= W[k];
+        }
+        store_result<D, R>(g, kKindOut, out_row, p, lane);
+    } else {
+        constexpr int V = D / 64;                        // words per lane and row: 1 or 2
+        constexpr int U = kPartBatch<D, R>;
+        const int64_t step = (int64_t)stride * R;        // rows of the buffers per segment
+        const float *lse = p.lse_partial + first * R;    // [segment][r]
+        const float *op = p.o_partial + first * (R * D) + lane;
+        // lane l looks at segments l / R, l / R + 64 / R, ... of row l % R
+        float mx = -INFINITY;
+#pragma unroll 1
+        for (int c0 = 0; c0 < n_segs; c0 += 64 / R)
+            mx = fmaxf(mx, coherent_load(lse + min(c0 + lane / R, n_segs - 1) * step + lane % R));
 #pragma unroll
-                for (int v = 0; v < V; ++v) acc[r][v] = fmaf(w, x[u][r][v], acc[r][v]);
+        for (int off = 32; off >= R; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+        float M[R], W[R], acc[R][V];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            M[r] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mx), r));
+            W[r] = 0.f;
+#pragma unroll
+            for (int v = 0; v < V; ++v) acc[r][v] = 0.f;
+        }
+#pragma unroll 1
+        for (int c0 = 0; c0 < n_segs; c0 += U) {
+            float x[U][R][V];
+            // lane u * R + r: log-sum-exp of segment c0 + u, row r
+            const int lc = __float_as_int(coherent_load(lse + min(c0 + lane / R, n_segs - 1) * step + lane % R));
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t row = min(c0 + u, n_segs - 1) * step;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+#pragma unroll
+                    for (int v = 0; v < V; ++v) x[u][r][v] = coherent_load(op + (row + r) * D + v * 64);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (c0 + u >= n_segs) continue;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const float lse_c = __int_as_float(__builtin_amdgcn_readlane(lc, u * R + r));
+                    const float w = fast_exp2((lse_c - M[r]) * kLog2e);
+                    W[r] += w;
+#pragma unroll
+                    for (int v = 0; v < V; ++v) acc[r][v] = fmaf(w, x[u][r][v], acc[r][v]);
+                }
             }
         }
-    }
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        __half *dst = p.out + (out_row + r) * D + lane;
+        for (int r = 0; r < R; ++r) {
+            __half *dst = p.out + (out_row + r) * D + lane;
 #pragma unroll
-        for (int v = 0; v < V; ++v) dst[v * 64] = __float2half_rn(acc[r][v] / W[r]);
+            for (int v = 0; v < V; ++v) dst[v * 64] = __float2half_rn(acc[r][v] / W[r]);
+        }
     }
 }
 
@@ -391,71 +480,114 @@ __device__ __forceinline__ void merge_partials(const AttnParams &p, int64_t firs
 // applies to the chunks of a segment in kModeSegments, in the same order: folded in ascending
 // order, then normalised.  `whole_row`: the segment is the whole row and the result goes to
 // `out`; otherwise it replaces the first chunk result in the buffers, as the partial result of
-// the segment (natural-log log-sum-exp) that merge_partials expects.  Lane l owns dims l, l + 64.
+// the segment (natural-log log-sum-exp) that merge_partials expects.
 template <int D, int R>
 __device__ __forceinline__ void fold_segment_from_chunks(const AttnParams &p, int64_t slot0, int ns,
                                                          bool whole_row, int64_t out_row, int lane)
 {
-    constexpr int V = D / 64;
-    constexpr int U = kPartBatch<R>;
-    float a[R][V], M[R], W[R];
+    if constexpr (kPartVectors<R>) {
+        constexpr int K = RowRegs<D, R>::K, U = kPartBatch<D, R>;
+        RowRegs<D, R> g;
+        float W[K];
 #pragma unroll 1
-    for (int c0 = 0; c0 < ns; c0 += U) {
-        float x[U][R][V];
-        // lane u * R + r: log-sum-exp of chunk c0 + u, row r
-        const int lc = __float_as_int(
-            coherent_load(p.lse_partial + (slot0 + min(c0 + lane / R, ns - 1)) * R + lane % R));
+        for (int c0 = 0; c0 < ns; c0 += U) {
+            f32x4 x[U][K];
+            const float lc = load_partials<D, R>(p, x, [&](int u) { return slot0 + min(c0 + u, ns - 1); }, lane);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t slot = slot0 + min(c0 + u, ns - 1);
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-#pragma unroll
-                for (int v = 0; v < V; ++v)
-                    x[u][r][v] = coherent_load(p.o_partial + (slot * R + r) * D + v * 64 + lane);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
+            for (int u = 0; u < U; ++u) {
                 if (c0 + u >= ns) continue;
-                const float lse_c = __int_as_float(__builtin_amdgcn_readlane(lc, u * R + r));
-                if (c0 + u == 0) {
-                    M[r] = lse_c;
-                    W[r] = 1.f;
 #pragma unroll
-                    for (int v = 0; v < V; ++v) a[r][v] = x[u][r][v];
-                } else {
-                    const FoldCoef f = fold_coef(M[r], lse_c);
-                    W[r] = fold_weight(W[r], f);
-                    M[r] = f.Mn;
+                for (int k = 0; k < K; ++k) {
+                    const float lse_c = from_lane(lc, RowRegs<D, R>::elem(lane, k) / D, u * R);
+                    if (c0 + u == 0) {
+                        g.lse[k] = lse_c;
+                        W[k] = 1.f;
+                        g.x[k] = x[u][k];
+                    } else {
+                        const FoldCoef f = fold_coef(g.lse[k], lse_c);
+                        W[k] = fold_weight(W[k], f);
+                        g.lse[k] = f.Mn;
 #pragma unroll
-                    for (int v = 0; v < V; ++v) a[r][v] = fold_elem(a[r][v], x[u][r][v], f);
+                        for (int e = 0; e < 4; ++e) g.x[k][e] = fold_elem(g.x[k][e], x[u][k][e], f);
+                    }
                 }
             }
         }
-    }
-    if (ns > 1) {
+        if (ns > 1) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const float inv = __builtin_amdgcn_rcpf(W[k]);
+                g.lse[k] = g.lse[k] + fast_log2(W[k]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) g.x[k][e] *= inv;
+            }
+        }
+        if (whole_row)
+            store_result<D, R>(g, kKindOut, out_row, p, lane);
+        else
+            store_partial_coherent<D, R>(g, slot0, p, lane, false);
+    } else {
+        constexpr int V = D / 64;
+        constexpr int U = kPartBatch<D, R>;
+        float a[R][V], M[R], W[R];
+#pragma unroll 1
+        for (int c0 = 0; c0 < ns; c0 += U) {
+            float x[U][R][V];
+            // lane u * R + r: log-sum-exp of chunk c0 + u, row r
+            const int lc = __float_as_int(
+                coherent_load(p.lse_partial + (slot0 + min(c0 + lane / R, ns - 1)) * R + lane % R));
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t slot = slot0 + min(c0 + u, ns - 1);
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+#pragma unroll
+                    for (int v = 0; v < V; ++v)
+                        x[u][r][v] = coherent_load(p.o_partial + (slot * R + r) * D + v * 64 + lane);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    if (c0 + u >= ns) continue;
+                    const float lse_c = __int_as_float(__builtin_amdgcn_readlane(lc, u * R + r));
+                    if (c0 + u == 0) {
+                        M[r] = lse_c;
+                        W[r] = 1.f;
+#pragma unroll
+                        for (int v = 0; v < V; ++v) a[r][v] = x[u][r][v];
+                    } else {
+                        const FoldCoef f = fold_coef(M[r], lse_c);
+                        W[r] = fold_weight(W[r], f);
+                        M[r] = f.Mn;
+#pragma unroll
+                        for (int v = 0; v < V; ++v) a[r][v] = fold_elem(a[r][v], x[u][r][v], f);
+                    }
+                }
+            }
+        }
+        if (ns > 1) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const float s = __builtin_amdgcn_rcpf(W[r]);
+                M[r] = M[r] + fast_log2(W[r]);
+#pragma unroll
+                for (int v = 0; v < V; ++v) a[r][v] *= s;
+            }
+        }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const float s = __builtin_amdgcn_rcpf(W[r]);
-            M[r] = M[r] + fast_log2(W[r]);
+            if (whole_row) {
+                __half *dst = p.out + (out_row + r) * D + lane;
 #pragma unroll
-            for (int v = 0; v < V; ++v) a[r][v] *= s;
-        }
-    }
+                for (int v = 0; v < V; ++v) dst[v * 64] = __float2half_rn(a[r][v]);
+            } else {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        if (whole_row) {
-            __half *dst = p.out + (out_row + r) * D + lane;
-#pragma unroll
-            for (int v = 0; v < V; ++v) dst[v * 64] = __float2half_rn(a[r][v]);
-        } else {
-#pragma unroll
-            for (int v = 0; v < V; ++v)
-                coherent_store(p.o_partial + (slot0 * R + r) * D + v * 64 + lane, a[r][v]);
-            if (lane == 0) coherent_store(p.lse_partial + slot0 * R + r, M[r] * kLn2);
+                for (int v = 0; v < V; ++v)
+                    coherent_store(p.o_partial + (slot0 * R + r) * D + v * 64 + lane, a[r][v]);
+                if (lane == 0) coherent_store(p.lse_partial + slot0 * R + r, M[r] * kLn2);
+            }
         }
     }
 }
@@ -496,6 +628,9 @@ __device__ __forceinline__ void combine_if_last(const AttnParams &p, int before,
                                                 int64_t out_row, int len, bool spread, int n_rows,
                                                 int lane)
 {
+    // what follows from the lane's number is worked out here: hoisted out of the writer wave's loop, it
+    // takes more registers than there are
+    asm volatile("" : "+v"(lane));
     constexpr int seg_tokens = decode_seg_tokens(R), gc = seg_tokens / decode_chunk_tokens(R);
     const int64_t row = dest / p.max_segs;
     int n_segs = parts;
@@ -1302,9 +1437,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
                 }
             }
         }
-        int next_box[NW];
-#pragma unroll
-        for (int v = 0; v < NW; ++v) next_box[v] = 0;
+        unsigned boxes = 0;               // bit v: the mailbox of wave v that is read next
         int done_mask = 0;
         int idle = 0;
         int pool_end = 0;                 // entries published so far
@@ -1352,9 +1485,17 @@ __global__ __launch_bounds__((NW + 1) * 64)
         while (done_mask != (1 << NW) - 1 && idle < kSpinLimit) {
             bool progressed = false;
             if (exhausted && !counted_out) count_out();
+            // One look at everything the wave waits for: the pool's counter, and lane v at the flag of
+            // wave v's next mailbox.
+            const int taken_now = __hip_atomic_load(&pool.next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            const int looked = min(lane, NW - 1);
+            const int seen = mail_load(&mail[looked * 2 + (int)((boxes >> looked) & 1u)].flag);
+            const int taken = __builtin_amdgcn_readfirstlane(taken_now);
+            const int done_now = (int)__builtin_amdgcn_ballot_w64(lane < NW && seen == kMailDone);
+            unsigned full = (unsigned)__builtin_amdgcn_ballot_w64(lane < NW && seen == kMailFull);
+            if (done_now != done_mask) progressed = true;
+            done_mask = done_now;
             // ---- keep the chunk pool ahead of the streaming waves
-            const int taken = __builtin_amdgcn_readfirstlane(
-                __hip_atomic_load(&pool.next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
             // Draw.  Work parked in one workgroup's pool cannot be taken by another that has run
             // dry, so little is drawn at a time and late; but a same-address device atomic
             // costs about as much as a short chunk, so short segments are drawn several at a
@@ -1475,80 +1616,82 @@ __global__ __launch_bounds__((NW + 1) * 64)
             // partial results stored in this pass that are merged inside this launch: counted in
             // after the pass, when their mailboxes have been handed back
             int n_arr = 0;
-#pragma unroll
-            for (int v = 0; v < NW; ++v) {
-                if (done_mask & (1 << v)) continue;
-                Mail &mb = mail[v * 2 + next_box[v]];
-                const int f = __builtin_amdgcn_readfirstlane(mail_load(&mb.flag));
-                if (f == kMailDone) {
-                    done_mask |= 1 << v;
-                    progressed = true;
-                    continue;
-                }
-                if (f != kMailFull) continue;
-                const int kind = __builtin_amdgcn_readfirstlane(mb.kind);
-                const int dest = __builtin_amdgcn_readfirstlane(mb.dest);
+            // The values go through registers: the mailbox, its header and then the slot are one LDS
+            // round trip each, and the code is there once, not once per mailbox.
+#pragma unroll 1
+            for (; full != 0; full &= full - 1) {
+                const int v = __builtin_ctz(full);
+                Mail &mb = mail[v * 2 + (int)((boxes >> v) & 1u)];
+                const i32x4 hdr = *reinterpret_cast<const i32x4 *>(&mb.kind);
+                RowRegs<D, R> g;
+                g.load(mb.o, mb.lse, lane);
                 // a result that leaves the workgroup, if this chunk completes one
                 bool leaves = true;
-                int rkind = kind, rdest = dest;
-                const float(*res)[D] = mb.o;
-                const float *res_lse = mb.lse, *res_w = nullptr;
-                if (kind == kKindFold) {
-                    Fold &fs = fold[dest];
-                    const int cs = __builtin_amdgcn_readfirstlane(mb.cs);
-                    if (cs != __builtin_amdgcn_readfirstlane(fs.next)) continue;   // not its turn yet
-                    const bool last = cs + 1 == __builtin_amdgcn_readfirstlane(fs.ns);
-                    // fold chunk cs into the slot; a lane owns the same elements every time
+                int rkind = __builtin_amdgcn_readfirstlane(hdr.x), rdest = __builtin_amdgcn_readfirstlane(hdr.y);
+                if (rkind == kKindFold) {
+                    const int slot = rdest;
+                    Fold &fs = fold[slot];
+                    const i32x4 sh = *reinterpret_cast<const i32x4 *>(&fs.next);
+                    constexpr int K = RowRegs<D, R>::K;
+                    f32x4 y[K];
+                    float Mo[K], Wo[K];                     // of no meaning before the first chunk
 #pragma unroll
-                    for (int idx = lane * 4; idx < R * D; idx += 256) {
-                        const int r = idx / D, d = idx % D;
-                        const float4 x = *reinterpret_cast<const float4 *>(&mb.o[r][d]);
-                        float4 a = x;
-                        if (cs > 0) {
-                            const FoldCoef f = fold_coef(fs.M[r], mb.lse[r]);
-                            const float4 y = *reinterpret_cast<const float4 *>(&fs.acc[r][d]);
-                            a = make_float4(fold_elem(y.x, x.x, f), fold_elem(y.y, x.y, f),
-                                            fold_elem(y.z, x.z, f), fold_elem(y.w, x.w, f));
-                        }
-                        *reinterpret_cast<float4 *>(&fs.acc[r][d]) = a;
+                    for (int k = 0; k < K; ++k) {
+                        const int e = RowRegs<D, R>::elem(lane, k);
+                        y[k] = *reinterpret_cast<const f32x4 *>(&fs.acc[0][0] + e);
+                        Mo[k] = fs.M[e / D];
+                        Wo[k] = fs.W[e / D];
                     }
-                    wave_lds_fence();       // every lane has read M before lane r rewrites it
-                    if (lane < R) {
-                        const float lc = mb.lse[lane];
-                        float Mn = lc, Wn = 1.f;
+                    const int cs = __builtin_amdgcn_readfirstlane(hdr.z);
+                    if (cs != __builtin_amdgcn_readfirstlane(sh.x)) continue;      // not its turn yet
+                    leaves = cs + 1 == __builtin_amdgcn_readfirstlane(sh.y);
+                    // chunk cs into the slot; a lane owns the same elements every time
+#pragma unroll
+                    for (int k = 0; k < K; ++k) {
+                        float Mn = g.lse[k], Wn = 1.f;
                         if (cs > 0) {
-                            const FoldCoef f = fold_coef(fs.M[lane], lc);
+                            const FoldCoef f = fold_coef(Mo[k], g.lse[k]);
                             Mn = f.Mn;
-                            Wn = fold_weight(fs.W[lane], f);
+                            Wn = fold_weight(Wo[k], f);
+                            g.x[k] = f32x4{fold_elem(y[k].x, g.x[k].x, f), fold_elem(y[k].y, g.x[k].y, f),
+                                           fold_elem(y[k].z, g.x[k].z, f), fold_elem(y[k].w, g.x[k].w, f)};
                         }
-                        fs.W[lane] = Wn;
-                        // after the last chunk the slot holds the segment's log-sum-exp
-                        fs.M[lane] = last ? Mn + fast_log2(Wn) : Mn;
+                        if (leaves) {
+                            const float inv = __builtin_amdgcn_rcpf(Wn);
+                            g.x[k] = f32x4{g.x[k].x * inv, g.x[k].y * inv, g.x[k].z * inv, g.x[k].w * inv};
+                            g.lse[k] = Mn + fast_log2(Wn);
+                        } else if (RowRegs<D, R>::stored(lane)) {
+                            const int e = lane * 4 + k * 256;
+                            *reinterpret_cast<f32x4 *>(&fs.acc[0][0] + e) = g.x[k];
+                            if (e % D == 0) {
+                                fs.M[e / D] = Mn;
+                                fs.W[e / D] = Wn;
+                            }
+                        }
                     }
-                    if (lane == 0) fs.next = cs + 1;
+                    if (leaves) {
+                        busy &= ~(1u << slot);
+                        rkind = __builtin_amdgcn_readfirstlane(sh.z);
+                        rdest = __builtin_amdgcn_readfirstlane(sh.w);
+                    } else if (lane == 0) {
+                        fs.next = cs + 1;
+                    }
                     wave_lds_fence();
-                    leaves = last;
-                    rkind = __builtin_amdgcn_readfirstlane(fs.kind);
-                    rdest = __builtin_amdgcn_readfirstlane(fs.dest);
-                    res = fs.acc;
-                    res_lse = fs.M;
-                    res_w = fs.W;
-                    if (last) busy &= ~(1u << dest);
                 }
                 if (leaves && MERGE && rkind == kKindPartial && merging) {
-                    store_partial_coherent<D, R>(res, res_lse, res_w, rdest, p, lane, spread);
+                    store_partial_coherent<D, R>(g, rdest, p, lane, spread);
                     if (lane == 0) {
                         arrivals.dest[n_arr] = rdest;
-                        arrivals.parts[n_arr] = mb.nseg;
+                        arrivals.parts[n_arr] = hdr.w;
                         arrivals.out_row[n_arr] = mb.out_row;
                         arrivals.len[n_arr] = mb.len;
                     }
                     ++n_arr;
                 } else if (leaves) {
-                    store_result<D, R>(res, res_lse, res_w, rkind, rdest, p, lane);
+                    store_result<D, R>(g, rkind, rdest, p, lane);
                 }
                 mail_store(&mb.flag, kMailEmpty);
-                next_box[v] ^= 1;
+                boxes ^= 1u << v;
                 progressed = true;
             }
             if (MERGE && n_arr > 0) {
@@ -1752,8 +1895,10 @@ __global__ __launch_bounds__((NW + 1) * 64)
             // queueing behind the other waves' results at the writer.
             if (cur.h.kind != kKindZero) Policy::finish(st, mb.o, mb.lse, lane);
             wave_lds_fence();
+            RowRegs<D, R> g;
+            g.load(mb.o, mb.lse, lane);
             if (cur.h.kind == kKindPartial && merging) {
-                store_partial_coherent<D, R>(mb.o, mb.lse, nullptr, cur.h.dest, p, lane, spread);
+                store_partial_coherent<D, R>(g, cur.h.dest, p, lane, spread);
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
                 __builtin_amdgcn_s_waitcnt(0);      // every store of this wave has completed
                 unsigned old = 0;
@@ -1765,7 +1910,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
                 combine_if_last<D, R>(p, __builtin_amdgcn_readfirstlane((int)old), cur.h.dest, cur.h.nseg,
                                       cur.h.out_row, cur.h.len, spread, batch * n_sel, lane);
             } else {
-                store_result<D, R>(mb.o, mb.lse, nullptr, cur.h.kind, cur.h.dest, p, lane);
+                store_result<D, R>(g, cur.h.kind, cur.h.dest, p, lane);
                 mail_store(&mb.flag, kMailDone);
             }
             return;
