@@ -53,10 +53,8 @@ struct MfmaPolicy {
     static constexpr int kQBytes = R * D * 2;
     static constexpr int kWaveLdsBytes = kStageV + kQBytes;
     static constexpr int kWavesPerEu = 2;             // register budget: 512 / 2 per lane
-#ifndef HETIS_MFMA_RING
-#define HETIS_MFMA_RING 3
-#endif
-    static constexpr int kRing = D_ == 64 ? 4 : HETIS_MFMA_RING;   // tile pairs in flight per wave (a third pair at D = 128 was worth 2 % on the grouped-query workloads)
+    // tile pairs in flight per wave (a third pair at D = 128 was worth 2 % on the grouped-query workloads)
+    static constexpr int ring(bool) { return D_ == 64 ? 4 : 3; }
 
     struct Tile {
         u32x4 k[KS];

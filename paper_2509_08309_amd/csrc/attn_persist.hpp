@@ -52,8 +52,8 @@
 // A workgroup is NW streaming waves plus one writer wave; after the prologue they never
 // meet at a barrier.
 //   - Streaming waves stream the tiles of their chunk through a register ring of
-//     Policy::kRing slots; a slot is refilled right after it has been consumed, so up to
-//     kRing tile pairs per wave are in flight, and the ring runs on into the first tiles of
+//     Policy::ring slots; a slot is refilled right after it has been consumed, so up to
+//     so many tile pairs per wave are in flight, and the ring runs on into the first tiles of
 //     the next chunk before the current one is finished off.  Every global load is issued
 //     unconditionally (indices clamped, tiles that do not exist turned into zero-length
 //     buffer descriptors), so the in-order load counter is known exactly at every wait.
@@ -135,6 +135,10 @@ constexpr int kTicketBatch = 8;         // tickets per device atomic while segme
 #define HETIS_STATIC_FLAT_X16 14
 #endif
 enum : int { kItemExists = 1 };
+template <int N>
+struct IntTag {
+    static constexpr int value = N;
+};
 
 // Inclusive scans over the 64 lanes of a wave (DPP, no LDS traffic): sums, and maxima of x >= 0.
 template <int CTRL, int ROWS>
@@ -795,7 +799,7 @@ __device__ __forceinline__ bool spread_pays(int G, int rows, int longest, int to
 
 // VARIANT selects what is compiled in besides the common path; code that a launch cannot reach
 // still costs it (launches measured 0.5 to 1.5 % faster without each of the two parts):
-//   kVariantPlain  many rows, none of which can leave partial results
+//   kVariantPlain  many rows, none of which can leave partial results; the split-KV entry points
 //   kVariantFew    also the fixed second and third segments of launches with few segments a
 //                  workgroup
 //   kVariantMerge  also partial results that are combined inside the launch
@@ -1792,146 +1796,157 @@ __global__ __launch_bounds__((NW + 1) * 64)
     unsigned char *my_staging = staging + (size_t)wave * Policy::kWaveLdsBytes;
     Mail *my_mail = mail + wave * 2;
 
-    constexpr int RING = Policy::kRing;             // tile pairs a wave keeps in flight, at most
-    Slot cur, nxt;
-    typename Policy::Query q;
-    typename Policy::QueryPrefetch q_pre;
-    Tile ring[RING];
-    {
-        // first chunk: of the work the workgroup has without a ticket, else from the pool
-        ChunkDesc d{};
-        bool direct = false;
-        if (spread) {
-            const int mine = wave * (int)gridDim.x + (int)blockIdx.x;
-            if (mine < total) {
-                const Segment s0 = quick_spread(mine);
-                if (step_mode && s0.tail) store_own_tail(s0);
-                d = chunk_of(s0, 0, 0);
-                direct = true;
+    // SPLIT: p.mode == kModeSplit
+    auto stream = [&](auto ring_of, auto split) {
+        constexpr int RING = decltype(ring_of)::value;   // tile pairs a wave keeps in flight, at most
+        constexpr bool SPLIT = decltype(split)::value;
+        Slot cur, nxt;
+        typename Policy::Query q;
+        typename Policy::QueryPrefetch q_pre;
+        Tile ring[RING];
+        {
+            // first chunk: of the work the workgroup has without a ticket, else from the pool
+            ChunkDesc d{};
+            bool direct = false;
+            if (spread) {
+                const int mine = wave * (int)gridDim.x + (int)blockIdx.x;
+                if (mine < total) {
+                    const Segment s0 = quick_spread(mine);
+                    if (step_mode && s0.tail) store_own_tail(s0);
+                    d = chunk_of(s0, 0, 0);
+                    direct = true;
+                }
+            } else if (SPLIT) {
+                const long long mine = (long long)blockIdx.x * NW + wave;
+                if (mine < total) {
+                    d = chunk_of(decode((int)mine), 0, 0);
+                    direct = true;
+                }
+            } else if (have_first) {
+                const Segment s0 = decode(blockIdx.x);
+                if (wave < direct_chunks(s0)) {
+                    if (MERGE && step_mode && s0.tail && wave == s0.ns - 1) store_own_tail(s0);
+                    d = chunk_of(s0, wave, 0);
+                    direct = true;
+                }
             }
-        } else if (!MERGE && single_mode) {
-            const long long mine = (long long)blockIdx.x * NW + wave;
-            if (mine < total) {
-                d = chunk_of(decode((int)mine), 0, 0);
-                direct = true;
-            }
-        } else if (have_first) {
-            const Segment s0 = decode(blockIdx.x);
-            if (wave < direct_chunks(s0)) {
-                if (MERGE && step_mode && s0.tail && wave == s0.ns - 1) store_own_tail(s0);
-                d = chunk_of(s0, wave, 0);
-                direct = true;
-            }
+            if (!direct) d = take_chunk();
+            fill(d, cur);
         }
-        if (!direct) d = take_chunk();
-        fill(d, cur);
-    }
-    if (!cur.exists) {
-        mail_store(&my_mail[0].flag, kMailDone);
-        return;
-    }
-    nxt = cur;
-    Policy::q_prefetch(q_pre, q_rows(cur), lane);
-#pragma unroll
-    for (int s = 0; s < RING; ++s) issue(ring[s], cur.ids, s, cur.head_off, s < cur.h.nblk);
-    int n = 0;
-    for (;; ++n) {
-        Policy::q_commit(q, q_pre, my_staging, lane);   // this chunk's query operand
-
-        typename Policy::State st;
-        Policy::reset(st);
-        const int n_my = cur.h.nblk;
-        const int lim = RING * max(1, (n_my + RING - 1) / RING);   // tiles, as whole ring turns
-        // The scheduling fences keep "consume a slot, refill it at once" in program order;
-        // without them the compiler batches the tiles' arithmetic ahead of the refills and
-        // the wave ends up waiting with nothing in flight.
-        auto steady_turn = [&](int i) {                 // whole tiles; refills stay in this chunk
-#pragma unroll
-            for (int s = 0; s < RING; ++s) {
-                Policy::template update<false>(st, ring[s], q, p.scale_log2, lane, kBlockTokens,
-                                               my_staging);
-                __builtin_amdgcn_sched_barrier(0);
-                issue(ring[s], cur.ids, i + RING + s, cur.head_off, i + RING + s < n_my);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        };
-        // The next chunk is taken as late as its block ids allow (three ring turns before
-        // the end of this one), so that little undone work is held back when the work runs
-        // out.
-        int i = 0;
-        for (; i + 4 * RING < lim; i += RING) steady_turn(i);
-        if (!MERGE && single_mode && n == 0) {
-            // the wave's second segment is its own as well
-            const long long mine = (long long)(gridDim.x + blockIdx.x) * NW + wave;
-            if (mine < total) {
-                fill(chunk_of(decode((int)mine), 0, 0), nxt);
-            } else {
-                ChunkDesc none{};
-                fill(none, nxt);
-            }
-        } else {
-            fill(take_chunk(), nxt);
-        }
-        Policy::q_prefetch(q_pre, q_rows(nxt), lane);   // next chunk's query rows
-        for (; i + RING < lim; i += RING) steady_turn(i);
-        // last turn of this chunk (the only place a ragged block can be): its refills are the
-        // first tiles of the next chunk
-#pragma unroll
-        for (int s = 0; s < RING; ++s) {
-            if (i + s < n_my) {
-                const int n_valid = (cur.h.rem != 0 && i + s == n_my - 1) ? cur.h.rem : kBlockTokens;
-                Policy::template update<true>(st, ring[s], q, p.scale_log2, lane, n_valid, my_staging);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            issue(ring[s], nxt.ids, s, nxt.head_off, s < nxt.h.nblk);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-
-        Mail &mb = my_mail[n & 1];
-        wait_empty(mb);
-        if (MERGE && !nxt.exists && cur.h.kind != kKindFold) {
-            // The wave's last chunk, and a result of its own: no load is in flight that a store
-            // could hold up, so the wave stores, counts and combines it itself instead of
-            // queueing behind the other waves' results at the writer.
-            if (cur.h.kind != kKindZero) Policy::finish(st, mb.o, mb.lse, lane);
-            wave_lds_fence();
-            RowRegs<D, R> g;
-            g.load(mb.o, mb.lse, lane);
-            if (cur.h.kind == kKindPartial && merging) {
-                store_partial_coherent<D, R>(g, cur.h.dest, p, lane, spread);
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                __builtin_amdgcn_s_waitcnt(0);      // every store of this wave has completed
-                unsigned old = 0;
-                if (lane == 0)
-                    old = __hip_atomic_fetch_add(
-                        p.arrivals + arrival_counter<R>(p, cur.h.dest, spread, batch * n_sel), 1u,
-                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                mail_store(&mb.flag, kMailDone);
-                combine_if_last<D, R>(p, __builtin_amdgcn_readfirstlane((int)old), cur.h.dest, cur.h.nseg,
-                                      cur.h.out_row, cur.h.len, spread, batch * n_sel, lane);
-            } else {
-                store_result<D, R>(g, cur.h.kind, cur.h.dest, p, lane);
-                mail_store(&mb.flag, kMailDone);
-            }
+        if (!cur.exists) {
+            mail_store(&my_mail[0].flag, kMailDone);
             return;
         }
-        // hand the finished chunk to the writer
-        if (cur.h.kind != kKindZero) Policy::finish(st, mb.o, mb.lse, lane);
-        if (lane == 0) {
-            mb.kind = cur.h.kind;
-            mb.dest = cur.h.dest;
-            mb.cs = cur.h.cs;
-            mb.nseg = cur.h.nseg;
-            mb.out_row = cur.h.out_row;
-            mb.len = cur.h.len;
+        nxt = cur;
+        Policy::q_prefetch(q_pre, q_rows(cur), lane);
+#pragma unroll
+        for (int s = 0; s < RING; ++s) issue(ring[s], cur.ids, s, cur.head_off, s < cur.h.nblk);
+        int n = 0;
+        for (;; ++n) {
+            Policy::q_commit(q, q_pre, my_staging, lane);   // this chunk's query operand
+
+            typename Policy::State st;
+            Policy::reset(st);
+            const int n_my = cur.h.nblk;
+            const int lim = RING * max(1, (n_my + RING - 1) / RING);   // tiles, as whole ring turns
+            // The scheduling fences keep "consume a slot, refill it at once" in program order;
+            // without them the compiler batches the tiles' arithmetic ahead of the refills and
+            // the wave ends up waiting with nothing in flight.
+            auto steady_turn = [&](int i) {                 // whole tiles; refills stay in this chunk
+#pragma unroll
+                for (int s = 0; s < RING; ++s) {
+                    Policy::template update<false>(st, ring[s], q, p.scale_log2, lane, kBlockTokens,
+                                                   my_staging);
+                    __builtin_amdgcn_sched_barrier(0);
+                    issue(ring[s], cur.ids, i + RING + s, cur.head_off, i + RING + s < n_my);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            // The next chunk is taken as late as its block ids allow (three ring turns before
+            // the end of this one), so that little undone work is held back when the work runs
+            // out.
+            int i = 0;
+            for (; i + 4 * RING < lim; i += RING) steady_turn(i);
+            if (SPLIT && n == 0) {
+                // the wave's second segment is its own as well
+                const long long mine = (long long)(gridDim.x + blockIdx.x) * NW + wave;
+                if (mine < total) {
+                    fill(chunk_of(decode((int)mine), 0, 0), nxt);
+                } else {
+                    ChunkDesc none{};
+                    fill(none, nxt);
+                }
+            } else {
+                fill(take_chunk(), nxt);
+            }
+            Policy::q_prefetch(q_pre, q_rows(nxt), lane);   // next chunk's query rows
+            for (; i + RING < lim; i += RING) steady_turn(i);
+            // last turn of this chunk (the only place a ragged block can be): its refills are the
+            // first tiles of the next chunk
+#pragma unroll
+            for (int s = 0; s < RING; ++s) {
+                if (i + s < n_my) {
+                    const int n_valid = (cur.h.rem != 0 && i + s == n_my - 1) ? cur.h.rem : kBlockTokens;
+                    Policy::template update<true>(st, ring[s], q, p.scale_log2, lane, n_valid, my_staging);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                issue(ring[s], nxt.ids, s, nxt.head_off, s < nxt.h.nblk);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+
+            Mail &mb = my_mail[n & 1];
+            wait_empty(mb);
+            if (MERGE && !nxt.exists && cur.h.kind != kKindFold) {
+                // The wave's last chunk, and a result of its own: no load is in flight that a store
+                // could hold up, so the wave stores, counts and combines it itself instead of
+                // queueing behind the other waves' results at the writer.
+                if (cur.h.kind != kKindZero) Policy::finish(st, mb.o, mb.lse, lane);
+                wave_lds_fence();
+                RowRegs<D, R> g;
+                g.load(mb.o, mb.lse, lane);
+                if (cur.h.kind == kKindPartial && merging) {
+                    store_partial_coherent<D, R>(g, cur.h.dest, p, lane, spread);
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                    __builtin_amdgcn_s_waitcnt(0);      // every store of this wave has completed
+                    unsigned old = 0;
+                    if (lane == 0)
+                        old = __hip_atomic_fetch_add(
+                            p.arrivals + arrival_counter<R>(p, cur.h.dest, spread, batch * n_sel), 1u,
+                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    mail_store(&mb.flag, kMailDone);
+                    combine_if_last<D, R>(p, __builtin_amdgcn_readfirstlane((int)old), cur.h.dest, cur.h.nseg,
+                                          cur.h.out_row, cur.h.len, spread, batch * n_sel, lane);
+                } else {
+                    store_result<D, R>(g, cur.h.kind, cur.h.dest, p, lane);
+                    mail_store(&mb.flag, kMailDone);
+                }
+                return;
+            }
+            // hand the finished chunk to the writer
+            if (cur.h.kind != kKindZero) Policy::finish(st, mb.o, mb.lse, lane);
+            if (lane == 0) {
+                mb.kind = cur.h.kind;
+                mb.dest = cur.h.dest;
+                mb.cs = cur.h.cs;
+                mb.nseg = cur.h.nseg;
+                mb.out_row = cur.h.out_row;
+                mb.len = cur.h.len;
+            }
+            mail_store(&mb.flag, kMailFull);
+            if (!nxt.exists) break;
+            cur = nxt;
         }
-        mail_store(&mb.flag, kMailFull);
-        if (!nxt.exists) break;
-        cur = nxt;
+        Mail &last = my_mail[(n + 1) & 1];
+        wait_empty(last);
+        mail_store(&last.flag, kMailDone);
+    };
+    if constexpr (VARIANT == kVariantPlain && !PAIRS) {
+        if (p.mode == kModeSplit) {
+            stream(IntTag<Policy::ring(false)>{}, IntTag<1>{});
+            return;
+        }
     }
-    Mail &last = my_mail[(n + 1) & 1];
-    wait_empty(last);
-    mail_store(&last.flag, kMailDone);
+    stream(IntTag<Policy::ring(!MERGE)>{}, IntTag<0>{});
 }
 
 }  // namespace hetis

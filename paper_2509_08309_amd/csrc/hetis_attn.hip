@@ -214,11 +214,13 @@ static int launch_chunk(const AttnParams &p0, int rows, hipStream_t st)
         }
         // the leanest instantiation that holds what this launch can need: the in-launch merge
         // when rows can leave partial results; the fixed second and third segments when the
-        // launch may have few segments a workgroup (every row has at least one segment)
+        // launch may have few segments a workgroup (every row has at least one segment); split
+        // calls hand out single chunks and have nothing of either
         const int64_t few_rows =
             (int64_t)HETIS_STATIC_SECOND_UPTO * std::max(device_cu_count(), 1) * wgs_per_cu_cap();
         const int variant = p.arrivals ? kVariantMerge
-                                       : ((int64_t)n * n_sel <= few_rows ? kVariantFew : kVariantPlain);
+                            : p.mode != kModeSplit && (int64_t)n * n_sel <= few_rows ? kVariantFew
+                                                                                     : kVariantPlain;
         using Policy = std::conditional_t<(R >= 4), MfmaPolicy<D, R>, VecPolicy<D, R>>;
         int rc;
         if (pairs)
