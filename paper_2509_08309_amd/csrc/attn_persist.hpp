@@ -1454,9 +1454,14 @@ __global__ __launch_bounds__((NW + 1) * 64)
         // safe while others still compute, since none of them draws again.
         bool counted_out = false;
         unsigned gone_before = 0;                     // lane 0: workgroups counted out before this one
+        // (The address passes for one that differs between lanes: of an atomic on one address the
+        // compiler broadcasts the result at once, and the wave waited for it here, in launches of one
+        // turn before the streaming waves had been told that there is no more work.)
         auto count_out = [&]() {
+            int same = 0;
+            asm volatile("" : "+v"(same));
             if (lane == 0)
-                gone_before = __hip_atomic_fetch_add(p.control + kCtlGone, 1u, __ATOMIC_RELAXED,
+                gone_before = __hip_atomic_fetch_add(p.control + kCtlGone + same, 1u, __ATOMIC_RELAXED,
                                                      __HIP_MEMORY_SCOPE_AGENT);
             counted_out = true;
         };
@@ -1488,7 +1493,6 @@ __global__ __launch_bounds__((NW + 1) * 64)
         bool own_items = spread;          // the workgroup's own items beyond its waves' first ones
         while (done_mask != (1 << NW) - 1 && idle < kSpinLimit) {
             bool progressed = false;
-            if (exhausted && !counted_out) count_out();
             // One look at everything the wave waits for: the pool's counter, and lane v at the flag of
             // wave v's next mailbox.
             const int taken_now = __hip_atomic_load(&pool.next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1616,6 +1620,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
                 closed = true;
                 progressed = true;
             }
+            if (exhausted && !counted_out) count_out();
             // ---- results
             // partial results stored in this pass that are merged inside this launch: counted in
             // after the pass, when their mailboxes have been handed back
