@@ -47,7 +47,7 @@
 // Measured, before (tables, chunks in row order, the writer wave combining one load at a time, a
 // step's store as a launch of its own) and now: 16 chats of 1088 tokens on average x 13 heads of
 // 128 45.1 -> 26.8 us; two documents of 20k and 27k tokens x 8 heads 70.4 -> 39.2; step of 144 pairs
-// of 8-head groups 58.2 -> 41.1; 4 chats x 4 heads of 64 15.0 -> 9.6.
+// of 8-head groups 58.2 -> 41.1; 4 chats x 4 heads of 64 15.0 -> 9.4.
 //
 // A workgroup is NW streaming waves plus one writer wave; after the prologue they never
 // meet at a barrier.
@@ -101,6 +101,10 @@ namespace hetis {
 enum : int { kMailEmpty = 0, kMailFull = 1, kMailDone = 2 };
 enum : int { kKindOut = 0, kKindPartial = 1, kKindZero = 2, kKindFold = 3 };
 constexpr int kSpinLimit = 1 << 22;     // polls before a wait gives up (far beyond any real wait)
+// Between two looks of a wait, in units of 64 cycles.  The looks are few (five waves a compute unit); with
+// four units in the writer wave and two in the others 4 chats x 4 heads of 64 dims take 9.7 us
+// instead of 9.4, 15 rows of at most 96 tokens 9.3 instead of 9.1, launches of many rows the same.
+constexpr int kPollSleep = 1;
 // Size classes of a row's last, shorter segment, largest first: fifteen of one sixteenth of a
 // whole segment each, then the last sixteenth split at 1/32, 1/64 and 1/128 of a segment.
 constexpr int kLinClasses = 15;
@@ -1714,7 +1718,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
                 idle = 0;
             } else {
                 ++idle;
-                __builtin_amdgcn_s_sleep(4);
+                __builtin_amdgcn_s_sleep(kPollSleep);
             }
         }
         if (!counted_out) count_out();        // (only after a wait that gave up)
@@ -1779,7 +1783,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
 #pragma unroll 1
         for (int spin = 0; spin < kSpinLimit; ++spin) {
             if (__builtin_amdgcn_readfirstlane(mail_load(&mb.flag)) == kMailEmpty) return;
-            __builtin_amdgcn_s_sleep(2);
+            __builtin_amdgcn_s_sleep(kPollSleep);
         }
         if (lane == 0) report_error(p.control, kErrMailboxWait);
     };
@@ -1794,7 +1798,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
             const int end = __builtin_amdgcn_readfirstlane(
                 __hip_atomic_load(&pool.end, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
             if (end > i) return pool.desc[i % kPoolSize];
-            __builtin_amdgcn_s_sleep(2);
+            __builtin_amdgcn_s_sleep(kPollSleep);
         }
         if (lane == 0) report_error(p.control, kErrTicketWait);
         ChunkDesc none{};
