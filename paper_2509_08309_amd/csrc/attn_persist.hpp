@@ -801,6 +801,29 @@ __device__ __forceinline__ bool spread_pays(int G, int rows, int longest, int to
     return longest <= turn && (chunks <= waves || 20 * tokens < (R * D <= 512 ? 18 : 11) * full || even);
 }
 
+// Depth of the ring of tiles in a decode call of `rows` rows; `short_rows`: how many of 64 rows picked
+// evenly are short as short_row() has it.  The depth follows the rows of the launch alone, whatever
+// variant (see below) the width of the block table asks for.
+//  - Fewer than kMaxQuickRows rows: deep.  Waves run dry before the launch ends, and those at work need
+//    more in flight each (Policy::ring has the figures).
+//  - Many rows, most of them of a few more tiles than the shallow ring holds: deep.  A row is read in one
+//    go only as far as the ring reaches; each turn beyond it waits for memory with little in flight
+//    (shallow -> deep, in us: 2976 rows of 20 to 80 tokens, r = 1, 128 dims 32.0 -> 29.3, 5984 of 40 to
+//    160 76.6 -> 73.7, 3000 pairs of 20 to 80, r = 2 56.9 -> 52.7, 6000 of 64 dims 79.0 -> 75.1; but
+//    5984 rows of 100 to 300 117.0 -> 119.6, r = 2, 64 dims 102.8 -> 105.0, and, one tile each, 6000
+//    pairs of up to 16 62.7 -> 68.3).
+//  - Otherwise shallow.
+template <class Policy>
+__host__ __device__ constexpr bool short_row(int tokens)
+{
+    return tokens > Policy::ring(false) * kBlockTokens && tokens <= 8 * kBlockTokens;
+}
+template <class Policy>
+__host__ __device__ constexpr bool deep_ring(int rows, int short_rows)
+{
+    return rows < kMaxQuickRows || short_rows >= 40;
+}
+
 // VARIANT selects what is compiled in besides the common path; code that a launch cannot reach
 // still costs it (launches measured 0.5 to 1.5 % faster without each of the two parts):
 //   kVariantPlain  many rows, none of which can leave partial results; the split-KV entry points
@@ -1954,11 +1977,19 @@ __global__ __launch_bounds__((NW + 1) * 64)
     };
     if constexpr (VARIANT == kVariantPlain && !PAIRS) {
         if (p.mode == kModeSplit) {
-            stream(IntTag<Policy::ring(false)>{}, IntTag<1>{});
+            stream(IntTag<Policy::ring(true)>{}, IntTag<1>{});
             return;
         }
     }
-    stream(IntTag<Policy::ring(!MERGE)>{}, IntTag<0>{});
+    if constexpr (Policy::ring(true) != Policy::ring(false)) {
+        const int sample = quick ? 0 : lens[(lane * batch) >> 6];
+        const int n_short = __builtin_popcountll(__builtin_amdgcn_ballot_w64(short_row<Policy>(sample)));
+        if (deep_ring<Policy>(batch * n_sel, n_short)) {
+            stream(IntTag<Policy::ring(true)>{}, IntTag<0>{});
+            return;
+        }
+    }
+    stream(IntTag<Policy::ring(false)>{}, IntTag<0>{});
 }
 
 }  // namespace hetis

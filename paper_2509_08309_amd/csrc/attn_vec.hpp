@@ -150,14 +150,16 @@ struct VecPolicy {
     static constexpr int kWaveLdsBytes = 0;      // no per-wave staging area
     static constexpr int kWavesPerEu = 2;        // register budget: 512 / 2 per lane
     // Tile pairs in flight per wave: 8 KB (a tile pair is 8 KB at D = 128, 4 KB at 64) in decode calls of
-    // many rows (`many`), 16 KB in all others.  8 KB in each of 1024 waves already keep HBM busy (random
-    // 4 KB tiles: 6.85 TB/s with one, two or three pairs a wave); more of it only waits longer, and not
-    // equally long on all compute units, which shows at the end of a launch: with 16 and 8 KB 1664 rows of
-    // 1069 tokens 147.4 and 145.0 us, 1024 rows of 1088 97.6 and 96.7, 1600 rows of 900 (r = 2) 126 and 124.
-    // Where waves run dry before the launch ends those at work need more each: 16 chats x 13 heads 27.9 us
-    // with 8 KB and 27.5 with 16, two documents x 8 heads 45.0 and 40.8, 440 rows of 1250 tokens 57.6 and
-    // 55.0.  Split calls have no segments to even out and gain as well (320 long rows 546 and 537).
-    static constexpr int ring(bool many) { return (many ? 1 : 2) * (D_ == 64 ? 2 : 1); }
+    // many rows, 16 KB (`deep`) in those of few or of short rows (deep_ring()) and in split calls.  8 KB in
+    // each of 1024 waves already keep HBM busy (random 4 KB tiles: 6.85 TB/s with one, two or three pairs a
+    // wave); more of it only waits longer, and not equally long on all compute units, which shows at the
+    // end of a launch: with 16 and 8 KB 1664 rows of 1069 tokens 147.4 and 145.0 us (behind a block table
+    // of 32k tokens 148.1 and 146.3), 1024 rows of 1088 97.6 and 96.7, 1600 rows of 900 (r = 2) 126 and
+    // 124, 640 rows of 7000 353 and 350.  Where waves run dry before the launch ends those at work need
+    // more each: 16 chats x 13 heads 27.9 us with 8 KB and 27.5 with 16, two documents x 8 heads 45.0 and
+    // 40.8, 440 rows of 1250 tokens 57.6 and 55.0.  Split calls have no segments to even out and gain as
+    // well (320 long rows 546 and 537).
+    static constexpr int ring(bool deep) { return (deep ? 2 : 1) * (D_ == 64 ? 2 : 1); }
     using Tile = TileRegs<D>;
     using State = VecState<D, R>;
     struct Query {

@@ -1,0 +1,38 @@
+"""Rules of the Attention kernel that do not show in a result, checked at compile time: the headers
+are compiled on the host with the rule as a static_assert."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2509_08309_amd import build
+
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+pytestmark = pytest.mark.skipif(shutil.which(HIPCC) is None, reason="hipcc not found")
+
+
+def assert_compiles(tmp_path, body):
+    src = tmp_path / "rule.hip"
+    src.write_text('#include "attn_mfma.hpp"\n#include "attn_vec.hpp"\nusing namespace hetis;\n' + body)
+    r = subprocess.run([HIPCC, "-std=c++17", "--offload-arch=gfx950", "--cuda-host-only", "-fsyntax-only",
+                        "-I", build.CSRC, str(src)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+
+
+@pytest.mark.parametrize("R", [1, 2])
+@pytest.mark.parametrize("D", [64, 128])
+def test_depth_of_the_ring_follows_the_rows(tmp_path, D, R):
+    """Few rows deep; many rows deep when most are of 2 (64 dims: 3) to 8 tiles.  No other argument:
+    what the block table allows has no say."""
+    ring = 2 if D == 64 else 1
+    P = f"VecPolicy<{D}, {R}>"
+    assert_compiles(tmp_path, f"""
+        static_assert({P}::ring(false) == {ring} && {P}::ring(true) == {2 * ring}, "8 and 16 KB");
+        static_assert(deep_ring<{P}>(1, 0) && deep_ring<{P}>(511, 0), "few rows");
+        static_assert(!deep_ring<{P}>(512, 0) && !deep_ring<{P}>(1 << 21, 39), "many rows");
+        static_assert(deep_ring<{P}>(512, 40) && deep_ring<{P}>(1 << 21, 64), "many short rows");
+        static_assert(!short_row<{P}>(0) && !short_row<{P}>({16 * ring}) && !short_row<{P}>(129) &&
+                      !short_row<{P}>(-5) && !short_row<{P}>(4096) && !short_row<{P}>(1 << 30), "not short");
+        static_assert(short_row<{P}>({16 * ring + 1}) && short_row<{P}>(128), "short");
+    """)
