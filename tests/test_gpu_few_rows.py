@@ -146,3 +146,34 @@ def test_steps_of_few_rows(r, D, rows, lo, hi, mode, chunks, pairs):
     assert int(ws[:16].view(torch.int32)[3].item()) == mode
     same = lambda a, b: torch.equal(a.view(torch.int16), b.view(torch.int16))
     assert same(one.k, two.k) and same(one.v, two.v) and same(out, want)
+
+
+@pytest.mark.parametrize("Hq,Hkv,D", [(2, 2, 64), (2, 1, 128), (8, 2, 64), (16, 2, 128)])
+def test_nobody_counts_where_nobody_draws(Hq, Hkv, D):
+    """Launches whose work is handed out without tickets leave the counter of finished workgroups alone
+    (here: whatever the caller had put there); the others leave it at zero."""
+    rng = np.random.default_rng(Hq + D)
+    sel = list(range(Hkv))
+    for lens in ([33], [17, 100] * 60, [300, 1200, 40] * 12, [20000, 5000], [100, 90] * 64, [0] * 9):
+        w = W.make_custom(lens, Hq, Hkv, D, sel, seed=len(lens), device=DEV)
+        d = Dev(w)
+        ref = d.decode(sel)
+        sizes = [H.hetis_attn_decode_workspace_bytes(d.shape, Hkv)[1]]
+        if w.block_table.shape[1] <= 256 and len(lens) * Hkv <= 256:
+            sizes.append(256)                       # the control words only: one row a workgroup, by table
+        for nbytes in sizes:
+            ws = torch.full((nbytes,), 0xAB, dtype=torch.uint8, device=DEV)
+            H.check(H.hetis_attn_workspace_init(ws, nbytes), "workspace_init")
+            words = ws[:16].view(torch.int32)
+            words[1] = 1000000
+            out = d.decode_ws(sel, ws)
+            assert np.array_equal(bits(out), bits(ref)), (lens[:3], nbytes)
+            assert words[:3].tolist() == [0, 1000000, 0], (lens[:3], nbytes, words.tolist())
+            assert int(words[3]) in (1, 3)
+    lens = [int(x) for x in rng.integers(1, 400, size=1200)]
+    w = W.make_custom(lens, Hq, Hkv, D, sel, seed=5, device=DEV)
+    d = Dev(w)
+    ws = d.workspace(Hkv)
+    out = d.decode_ws(sel, ws)
+    assert ws[:16].view(torch.int32).tolist() == [0, 0, 0, 1]
+    assert np.array_equal(bits(out), bits(d.decode(sel)))
