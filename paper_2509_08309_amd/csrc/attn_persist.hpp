@@ -1548,14 +1548,18 @@ __global__ __launch_bounds__((NW + 1) * 64)
             // runs out.  Otherwise: about one full chunk's worth of tokens per draw, judged by
             // the last segment seen (they come longest first), drawn when fewer than
             // HETIS_POOL_AHEAD chunks (one, near the end) or than a draw's worth are waiting.
-            const long long left = (long long)total - last_base;
-            int n_draw, ahead;
-            if (single_mode) {
-                n_draw = left > 8 * wave_round ? kTicketBatch : (left > 2 * wave_round ? 2 : 1);
-                ahead = n_draw;
-            } else {
-                n_draw = max(1, min(kTicketBatch, chunk_tokens / max(last_tok, 1)));
-                ahead = max(4 * left > (long long)gridDim.x * HETIS_LATE_SEGMENTS_X4 ? HETIS_POOL_AHEAD : 1, n_draw);
+            // (Only in a pass that can draw: the division leaves scratch registers behind that the
+            // compiler takes to be still in use by the counting atomic above, and waits for it.)
+            int n_draw = 0, ahead = 0;
+            if (!exhausted && pend_i == pend_n) {
+                const long long left = (long long)total - last_base;
+                if (single_mode) {
+                    n_draw = left > 8 * wave_round ? kTicketBatch : (left > 2 * wave_round ? 2 : 1);
+                    ahead = n_draw;
+                } else {
+                    n_draw = max(1, min(kTicketBatch, chunk_tokens / max(last_tok, 1)));
+                    ahead = max(4 * left > (long long)gridDim.x * HETIS_LATE_SEGMENTS_X4 ? HETIS_POOL_AHEAD : 1, n_draw);
+                }
             }
             int want = -1;                // segment to decode in this pass (one a lane)
             if (MERGE && own_items) {
