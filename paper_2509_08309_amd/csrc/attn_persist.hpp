@@ -339,11 +339,15 @@ __device__ __forceinline__ void store_partial_coherent(const RowRegs<D, R> &g, i
 // are registers for (eight with 8 x 128 words; scratch memory otherwise), and looks its row's weight up;
 // with one or two rows it loads words, the same dims of every row, and weights are the same in all lanes.
 // A step of 144 pairs of 8-head groups: words 44.9 us, vectors 43.4; 16 chats x 13 heads (r = 1) 27.5 and 28.1.
+// r = 4: vectors too, but half as many: more only fills registers, which are the streaming loop's as well
+// (218 of them against 182 at 64 dims, 256 against 235 at 128).  Words / 16 vectors / 8: 160 rows of 500 to
+// 2000 tokens of 64 dims 21.35 / 21.18 / 20.75 us, 508 of them 39.2 / 40.0 / 39.4; 16 words of 128 dims, 400
+// rows of 300 to 1200 tokens 40.5 / 40.3 / 39.7, 12 rows of 10k to 32k 32.6 / 32.5 / 32.8.
 template <int R>
 constexpr bool kPartVectors = R >= 4;
 template <int D, int R>
 constexpr int kPartBatch =                                         // at most 64 / R
-    !kPartVectors<R> ? 16 : (R * D > 512 ? 8 : 16) / RowRegs<D, R>::K;
+    !kPartVectors<R> ? 16 : (R == 4 ? 8 : R * D > 512 ? 8 : 16) / RowRegs<D, R>::K;
 
 // Partial results in slots slot_of(0), slot_of(1), ... of the partial buffers -> x; their
 // log-sum-exps come back with lane u * R + r holding that of result u, row r.

@@ -41,3 +41,15 @@ def test_no_kernel_uses_scratch_memory(source, expected, tmp_path):
         assert int(f["private_segment_fixed_size"]) == 0, (name, f["private_segment_fixed_size"])
         assert int(f.get("vgpr_spill_count", 0)) == 0, name
         assert int(f["vgpr_count"]) + int(f.get("agpr_count", 0)) <= 256, (name, f["vgpr_count"])
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None, reason="hipcc not found")
+def test_registers_of_the_combination_of_four_rows(tmp_path):
+    """The combination of partial results shares the streaming loop's kernel: with four query rows a
+    batch of them may not take the kernel to the limit of 256 registers."""
+    meta = kernel_metadata("hetis_attn.hip", tmp_path)
+    for dim, limit in ((64, 190), (128, 244)):
+        mine = [f for k, f in meta.items() if re.search(rf"MfmaPolicyILi{dim}ELi4E.*Li2EEEv", k)]
+        assert len(mine) == 2                       # common subset, pairs
+        for f in mine:
+            assert int(f["vgpr_count"]) <= limit, f["vgpr_count"]
