@@ -340,9 +340,9 @@ __device__ __forceinline__ void store_partial_coherent(const RowRegs<D, R> &g, i
 // with one or two rows it loads words, the same dims of every row, and weights are the same in all lanes.
 // A step of 144 pairs of 8-head groups: words 44.9 us, vectors 43.4; 16 chats x 13 heads (r = 1) 27.5 and 28.1.
 // r = 4: vectors too, but half as many: more only fills registers, which are the streaming loop's as well
-// (218 of them against 182 at 64 dims, 256 against 235 at 128).  Words / 16 vectors / 8: 160 rows of 500 to
-// 2000 tokens of 64 dims 21.35 / 21.18 / 20.75 us, 508 of them 39.2 / 40.0 / 39.4; 16 words of 128 dims, 400
-// rows of 300 to 1200 tokens 40.5 / 40.3 / 39.7, 12 rows of 10k to 32k 32.6 / 32.5 / 32.8.
+// (218 of them against 182 at 64 dims, 256 against 235 at 128).  Words / 16 vectors / 8, 64 dims: 160 rows
+// of 500 to 2000 tokens 21.35 / 21.18 / 20.75 us, 508 of them 39.2 / 40.0 / 39.4; words / 16 / 8, 128 dims:
+// 400 of 300 to 1200 40.5 / 40.3 / 39.7, 12 of 10k to 32k 32.6 / 32.5 / 32.8.
 template <int R>
 constexpr bool kPartVectors = R >= 4;
 template <int D, int R>
@@ -768,21 +768,23 @@ __device__ __forceinline__ void store_new_rows(const AttnParams &p, int seq, int
 // `rows` rows of `tokens` tokens in all and `longest` at most, `chunks` chunks; G workgroups.
 // Whole rows wait for the longest one, or, with more rows than workgroups, for two in turn, beside
 // idle compute units; but their chunks meet in LDS, where the results of single ones go through
-// global memory, r times as much with r query rows.  Measured, rows whole -> single chunks, in us
-// (r = 1, 128 dims, lengths uniform, unless stated):
+// global memory, r times as much with r query rows.  Measured with either side forced, rows whole ->
+// single chunks, in us (r = 1, 128 dims, lengths uniform, unless stated):
 //  - Up to G rows.  What idles is 1 - tokens / (G * longest).  r < 4: chunks, unless less than
-//    three tenths idle and some wave would take a second chunk (128 rows of 4096: 67 -> 50; 255 of
-//    275 to 1100 29.0 -> 27.6; but 230 of 600 23.0 -> 26.0, 255 of 4096 87 -> 97).  r >= 4: a row
+//    three tenths idle and some wave would take a second chunk (128 rows of 4096: 52.6 -> 50.6; 255 of
+//    275 to 1100 23.3 -> 22.8; but 230 of 600 17.8 -> 20.4, 255 of 4096 92.7 -> 95.2).  r >= 4: a row
 //    of up to NW chunks is one turn of a workgroup; it gains when it is several chunks long, the
-//    more the more idles (r = 8, 200 rows of 500 to 2000: 41.1 -> 37.9; 300 to 1200: 27.7 -> 31.3;
-//    250 to 1000, whose chunks are half as long: 26.2 -> 25.4; 150 to 600: 19.5 -> 20.7).
+//    more the more idles (r = 8, 200 rows of 500 to 2000: 41.3 -> 36.0; 300 to 1200: 25.8 -> 28.9;
+//    250 to 1000, whose chunks are half as long: 25.0 -> 23.5; 150 to 600: 17.8 -> 17.7).
 //  - More rows.  Chunks for a few long ones among short ones (511 rows, log-normal around 820, up
-//    to 4096: 75 -> 63), where the rows are alike and the workgroups' second turn is mostly empty
-//    (270 of 4096: 134 -> 104), and for up to one (r >= 4) or about two chunks a wave (390 of 1200:
-//    54 -> 47; 511 of 150 to 600: 33 -> 30; r = 2 and 128 dims not if these are quarter chunks: 480
-//    of 75 to 300 27.1 -> 29.3, with 64 dims 25.2 -> 23.9).  Otherwise rows whole: 511 of 500 to
-//    2000 64 -> 71, r = 2 67 -> 78, r = 8 65 -> 77; 511 of 1 to 4096 in seven lengths, r = 2, 93 ->
-//    111.  r >= 4, rows of more than one turn: whole (r = 8, 360 of 750 to 3000: 75 -> 80).
+//    to 4096: 67.5 -> 57.6), where the rows are alike and the workgroups' second turn is mostly empty
+//    (270 of 4096: 120 -> 99), and for up to one (r >= 4) or some 2.4 chunks a wave (390 of 1200: 49.0 ->
+//    45.3; 480 of 75 to 300, r = 2: 19.8 -> 19.5, 480 of up to 290: 23.0 -> 17.6; but around 2.5 a wave 460
+//    of 275 to 1100 34.7 -> 37.6, 64 dims 23.8 -> 29.0).  Otherwise rows whole: 511 of 500 to 2000 57.6 ->
+//    61.9, r = 2 59.2 -> 65.6, r = 8 61.4 -> 68.8; of 150 to 600, r = 8, 26.2 -> 32.4.
+//  - r >= 4 and rows of more than one turn, G or more of them: whole, as when that was the faster way
+//    everywhere.  It no longer is (r = 8, 360 of 750 to 3000: 70.0 -> 70.5, but 270 of 4096 143 -> 114,
+//    256 log-normal around 820 68 -> 40, 511 of these 78.8 -> 64.5).
 template <int D, int R, int NW>
 __device__ __forceinline__ bool spread_pays(int G, int rows, int longest, int tokens, int chunks)
 {
@@ -799,9 +801,7 @@ __device__ __forceinline__ bool spread_pays(int G, int rows, int longest, int to
     }
     constexpr bool wide = R < 4 && R * D > 128;             // a partial result of more than 512 bytes
     const bool even = 20 * tokens >= 17 * full && 16 * rows < (wide ? 24 : 26) * G;
-    if (R < 4)
-        return idle || even || 10 * chunks <= 11 * waves ||
-               (10 * chunks <= (wide ? 23 : 25) * waves && (!wide || tokens >= 80 * chunks));
+    if (R < 4) return idle || even || 10 * chunks <= (wide ? 23 : 25) * waves;
     return longest <= turn && (chunks <= waves || 20 * tokens < (R * D <= 512 ? 18 : 11) * full || even);
 }
 
@@ -951,8 +951,8 @@ __global__ __launch_bounds__((NW + 1) * 64)
             // Rows of several segments: chunks while there are fewer segments than workgroups.  Two
             // rows of 20k and 27k tokens x 8 heads need it (see the top).  Around one segment a
             // workgroup neither way is always ahead: whole segments -> chunks, 20 rows of 15k to 60k,
-            // r = 1 78 -> 82 us, r = 2 70 -> 63, r = 8 90 -> 105; 20 rows of 60k, r = 1 141 -> 111, r = 8
-            // 152 -> 142; far beyond it whole segments are (500 rows of 5000, r = 2: 150 -> 167).
+            // r = 1 67 -> 72 us, r = 2 73 -> 78, r = 8 90 -> 85; 20 rows of 60k, r = 1 129 -> 110, r = 8
+            // 154 -> 141; far beyond it whole segments are (500 rows of 5000, r = 2: 208 -> 234).
             int n_segments = 0;
 #pragma unroll
             for (int u = 0; u < QG; ++u)

@@ -177,3 +177,21 @@ def test_nobody_counts_where_nobody_draws(Hq, Hkv, D):
     out = d.decode_ws(sel, ws)
     assert ws[:16].view(torch.int32).tolist() == [0, 0, 0, 1]
     assert np.array_equal(bits(out), bits(d.decode(sel)))
+
+
+@pytest.mark.parametrize("Hq,D,n,lo,hi,chunks", [
+    (2, 128, 480, 1, 290, True),        # short rows cut into quarter chunks: 1.2 of them a wave
+    (2, 128, 480, 75, 300, True),
+    (2, 128, 460, 275, 1100, False),    # 2.5 chunks a wave
+    (2, 128, 400, 300, 1200, True)])    # 2.2
+def test_chunks_a_wave(Hq, D, n, lo, hi, chunks):
+    """More rows than workgroups, two query rows of 128 dims a head: single chunks up to 2.3 a wave."""
+    lens = [lo + (hi - lo) * ((7 * i) % n) // (n - 1) for i in range(n)]
+    w = W.make_custom(lens, Hq, 1, D, [0], seed=n, device=DEV)
+    d = Dev(w)
+    ws = d.workspace(1)
+    out = d.decode_ws([0], ws)
+    assert int(ws[:16].view(torch.int32)[3]) == (3 if chunks else 1)
+    small = torch.empty(256, dtype=torch.uint8, device=DEV)
+    H.check(H.hetis_attn_workspace_init(small, 256), "workspace_init")
+    assert np.array_equal(bits(out), bits(d.decode_ws([0], small)))
