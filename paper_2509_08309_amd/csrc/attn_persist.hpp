@@ -100,11 +100,13 @@ namespace hetis {
 
 enum : int { kMailEmpty = 0, kMailFull = 1, kMailDone = 2 };
 enum : int { kKindOut = 0, kKindPartial = 1, kKindZero = 2, kKindFold = 3 };
-constexpr int kSpinLimit = 1 << 22;     // polls before a wait gives up (far beyond any real wait)
 // Between two looks of a wait, in units of 64 cycles.  The looks are few (five waves a compute unit); with
 // four units in the writer wave and two in the others 4 chats x 4 heads of 64 dims take 9.7 us
 // instead of 9.4, 15 rows of at most 96 tokens 9.3 instead of 9.1, launches of many rows the same.
 constexpr int kPollSleep = 1;
+// Looks before a wait gives up: 2^30 cycles of sleep, 0.4 s.  The longest real wait is for a chunk of the
+// wave's own workgroup, 1024 tokens at most, some tens of microseconds.
+constexpr int kSpinLimit = (1 << 24) / kPollSleep;
 // Size classes of a row's last, shorter segment, largest first: fifteen of one sixteenth of a
 // whole segment each, then the last sixteenth split at 1/32, 1/64 and 1/128 of a segment.
 constexpr int kLinClasses = 15;

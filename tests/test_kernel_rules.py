@@ -36,3 +36,11 @@ def test_depth_of_the_ring_follows_the_rows(tmp_path, D, R):
                       !short_row<{P}>(-5) && !short_row<{P}>(4096) && !short_row<{P}>(1 << 30), "not short");
         static_assert(short_row<{P}>({16 * ring + 1}) && short_row<{P}>(128), "short");
     """)
+
+
+def test_bound_of_a_wait_is_a_time(tmp_path):
+    """However often a wait looks, it gives up after 2^30 cycles of sleep, not earlier."""
+    assert_compiles(tmp_path, """
+        static_assert(kPollSleep >= 1 && 64ll * kPollSleep * kSpinLimit >= (1ll << 30) - 64ll * kPollSleep &&
+                      64ll * kPollSleep * kSpinLimit <= 1ll << 30, "0.4 s");
+    """)
