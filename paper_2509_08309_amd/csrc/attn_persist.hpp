@@ -838,6 +838,9 @@ __host__ __device__ constexpr bool deep_ring(int rows, int short_rows)
 //   kVariantMerge  also partial results that are combined inside the launch
 //                  (AttnParams::arrivals is set), and single-chunk scheduling
 enum : int { kVariantPlain = 0, kVariantFew = 1, kVariantMerge = 2 };
+// Instantiations that hold the split-KV scheduling (kModeSplit), in the writer wave and in the
+// streaming waves alike; the host refuses such a launch on any other.
+__host__ __device__ constexpr bool holds_split(int variant, bool pairs) { return variant == kVariantPlain && !pairs; }
 template <class Policy, int NW, bool PAIRS, int VARIANT>
 __global__ __launch_bounds__((NW + 1) * 64)
     __attribute__((amdgpu_waves_per_eu(Policy::kWavesPerEu))) void attn_chunk_persistent_kernel(
@@ -847,6 +850,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
     constexpr int R = Policy::R;
     constexpr bool MERGE = VARIANT == kVariantMerge;
     constexpr bool FEW = VARIANT >= kVariantFew;
+    constexpr bool CAN_SPLIT = holds_split(VARIANT, PAIRS);
     constexpr int NT = (NW + 1) * 64;
     constexpr int kTileBytes = kBlockTokens * D * 2;
     constexpr int NS = fold_slots<R>();
@@ -1355,7 +1359,8 @@ __global__ __launch_bounds__((NW + 1) * 64)
     // unit, and, through the pool, the items that lie as far from the other end of the first
     // 2 NW gridDim.x (the shortest items come last: a wave with a full chunk gets a short one or
     // none).  Tickets number the segments after these.
-    const bool single_mode = p.mode == kModeSplit || spread;
+    const bool split_mode = CAN_SPLIT && p.mode == kModeSplit;
+    const bool single_mode = split_mode || spread;
     const bool have_first = (int)blockIdx.x < total;
     const bool step_mode = p.k_new != nullptr;      // never with kModeSplit
     // chunks of the first segment that are taken without the pool: the first NW.  When the new
@@ -1768,7 +1773,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
             if (done_mask != (1 << NW) - 1) report_error(p.control, kErrWriterWait);
             if (draws ? gone_before == gridDim.x - 1 : blockIdx.x == 0)
                 p.control[kCtlLastMode] =
-                    1u + (unsigned)(spread ? kModeSpread : (p.mode == kModeSplit ? kModeSplit : kModeSegments));
+                    1u + (unsigned)(spread ? kModeSpread : (split_mode ? kModeSplit : kModeSegments));
             if (draws && gone_before == gridDim.x - 1) {
                 __hip_atomic_store(p.control + kCtlTickets, 0u, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
@@ -1851,7 +1856,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
     unsigned char *my_staging = staging + (size_t)wave * Policy::kWaveLdsBytes;
     Mail *my_mail = mail + wave * 2;
 
-    // SPLIT: p.mode == kModeSplit
+    // SPLIT: split_mode
     auto stream = [&](auto ring_of, auto split) {
         constexpr int RING = decltype(ring_of)::value;   // tile pairs a wave keeps in flight, at most
         constexpr bool SPLIT = decltype(split)::value;
@@ -1995,8 +2000,8 @@ __global__ __launch_bounds__((NW + 1) * 64)
         wait_empty(last);
         mail_store(&last.flag, kMailDone);
     };
-    if constexpr (VARIANT == kVariantPlain && !PAIRS) {
-        if (p.mode == kModeSplit) {
+    if constexpr (CAN_SPLIT) {
+        if (split_mode) {
             stream(IntTag<Policy::ring(true)>{}, IntTag<1>{});
             return;
         }

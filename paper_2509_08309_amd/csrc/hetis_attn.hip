@@ -221,6 +221,7 @@ static int launch_chunk(const AttnParams &p0, int rows, hipStream_t st)
         const int variant = p.arrivals ? kVariantMerge
                             : p.mode != kModeSplit && (int64_t)n * n_sel <= few_rows ? kVariantFew
                                                                                      : kVariantPlain;
+        if (p.mode == kModeSplit && !holds_split(variant, pairs)) return HETIS_ERR_UNSUPPORTED;
         using Policy = std::conditional_t<(R >= 4), MfmaPolicy<D, R>, VecPolicy<D, R>>;
         int rc;
         if (pairs)

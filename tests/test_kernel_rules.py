@@ -44,3 +44,18 @@ def test_bound_of_a_wait_is_a_time(tmp_path):
         static_assert(kPollSleep >= 1 && 64ll * kPollSleep * kSpinLimit >= (1ll << 30) - 64ll * kPollSleep &&
                       64ll * kPollSleep * kSpinLimit <= 1ll << 30, "0.4 s");
     """)
+
+
+def test_one_instantiation_holds_split_calls(tmp_path):
+    """Both sides of the kernel and the host's check go by the same predicate."""
+    assert_compiles(tmp_path, """
+        static_assert(holds_split(kVariantPlain, false), "split calls run here");
+        static_assert(!holds_split(kVariantPlain, true) && !holds_split(kVariantFew, false) &&
+                      !holds_split(kVariantFew, true) && !holds_split(kVariantMerge, false) &&
+                      !holds_split(kVariantMerge, true), "and nowhere else");
+    """)
+    with open(os.path.join(build.CSRC, "attn_persist.hpp")) as f:
+        kernel = f.read()
+    assert kernel.count("p.mode == kModeSplit") == 1, "one place decides: split_mode"
+    with open(os.path.join(build.CSRC, "hetis_attn.hip")) as f:
+        assert "!holds_split(variant, pairs)) return HETIS_ERR_UNSUPPORTED;" in f.read()
