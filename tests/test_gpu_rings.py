@@ -1,10 +1,14 @@
 """Rows around whole turns of a wave's ring of tiles.  The ring is one tile pair deep (two at 64
-dims) in launches of many rows and twice that in launches of few rows and in split calls; every
-kind of launch gives the same rows the same bits, and all agree with the checker."""
+dims) in launches of many rows, and twice that where rows are few or most of them are of 2 (3) to 8
+tiles, and in split calls; launches of more than three query rows a head have one depth.  Launches of
+each of these kinds, also behind a block table that allows rows of several segments, as pairs and with
+the new rows stored by the launch, give the same rows the same bits, and all agree with the checker."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
+import paper_2509_08309_amd as H
 from paper_2509_08309_amd import workloads as W
 
 from gpu_harness import TOL, Dev, bits, check_rows, no_expired_wait, selected_rows
@@ -15,7 +19,7 @@ LENS = [0, 1, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64, 65, 80, 81, 95, 96, 97
         257, 288, 320, 500, 1023, 1024, 1025, 1100, 2047, 4096]
 
 
-@pytest.mark.parametrize("r,D", [(1, 64), (1, 128), (2, 64), (2, 128), (4, 128), (8, 64)])
+@pytest.mark.parametrize("r,D", [(1, 64), (1, 128), (2, 64), (2, 128), (4, 128), (8, 64), (8, 128)])
 def test_turns_of_the_ring(r, D):
     Hkv, few, some = 32, [30, 2, 17], list(range(1, 21)) + [30]
     w = W.make_custom(LENS, Hkv * r, Hkv, D, few, seed=10 * D + r, device=DEV)
@@ -38,3 +42,69 @@ def test_turns_of_the_ring(r, D):
         assert np.array_equal(o_p.cpu().numpy().view(np.int32), o_m[:, both].cpu().numpy().view(np.int32))
         assert np.array_equal(lse_p.cpu().numpy().view(np.int32), lse_m[:, both].cpu().numpy().view(np.int32))
     no_expired_wait()
+
+
+def on_host(w):
+    return w.q.cpu().numpy(), w.k_cache.cpu().numpy(), w.v_cache.cpu().numpy()
+
+
+def as_pairs(w, d, heads):
+    """Every (sequence, head) as a pair over the same tiles, in one call."""
+    Hkv, D, B = w.spec.n_kv_heads, w.spec.head_dim, len(w.seq_lens)
+    seq = np.tile(np.arange(B, dtype=np.int32), len(heads))
+    head = np.repeat(np.asarray(heads, dtype=np.int32), B)
+    table = np.where(w.block_table[seq] < 0, -1, w.block_table[seq] * Hkv + head[:, None]).astype(np.int32)
+    out = d.new_out()
+    up = lambda x: torch.from_numpy(np.ascontiguousarray(x)).to(DEV)
+    bt, ps, ph = up(table), up(seq), up(head)
+    H.check(H.hetis_attn_decode_pairs(d.shape, d.q, d.k.view(-1, 16, D), d.v.view(-1, 16, D), bt, d.sl, ps, ph,
+                                      len(seq), d.scale, out), "hetis_attn_decode_pairs")
+    torch.cuda.synchronize()
+    no_expired_wait()
+    return out
+
+
+@pytest.mark.parametrize("r,D", [(1, 64), (1, 128), (2, 64), (2, 128), (4, 64), (4, 128), (8, 64), (8, 128)])
+@pytest.mark.parametrize("kind", ["long", "short"])
+def test_kinds_of_launches_agree(r, D, kind):
+    """`long`: many rows of all lengths, the shallow ring.  `short`: many rows of 3 to 8 tiles, the deep
+    one.  Few rows of either: the deep one."""
+    lens = LENS if kind == "long" else [n for n in LENS if 33 <= n <= 128] * 4
+    Hkv = 24
+    every, few = list(range(Hkv)), [11, 0, 20][:max(1, 500 // len(lens) // 4)]
+    make = lambda msl: W.make_custom(lens, Hkv * r, Hkv, D, every, seed=10 * D + r, device=DEV, max_seq_len=msl)
+    w, wide = make(4096), make(3 * 4096)
+    assert len(lens) * Hkv >= 512 > len(lens) * len(few)
+    d, dw = Dev(w), Dev(wide)
+    out = d.decode(every)
+    ref = oracle.attn_decode(*on_host(w), w.block_table, w.seq_lens, np.asarray(every, dtype=np.int32), w.spec.scale)
+    check_rows(out, ref, selected_rows(w.spec, every), TOL, "all rows")
+    assert np.array_equal(bits(dw.decode(every)), bits(out))
+    assert np.array_equal(bits(as_pairs(w, d, every)), bits(out))
+    assert np.array_equal(bits(as_pairs(wide, dw, every)), bits(out))
+    rows = selected_rows(w.spec, few)
+    for one in (d.decode(few), dw.decode(few), as_pairs(w, d, few)):
+        assert np.array_equal(bits(one)[:, rows], bits(out)[:, rows])
+    # the new token's rows stored by the launch itself, over a cache that lacks them
+    last = torch.from_numpy(np.flatnonzero(w.seq_lens > 0)).to(DEV)
+    pos = torch.from_numpy(w.seq_lens[w.seq_lens > 0].astype(np.int64) - 1).to(DEV)
+    for x, dx in ((w, d), (wide, dw)):
+        blk = dx.bt[last, pos // 16].long()
+        kn = torch.zeros((len(lens), Hkv, D), dtype=torch.float16, device=DEV)
+        vn = torch.zeros_like(kn)
+        kn[last], vn[last] = x.k_cache[blk, :, pos % 16], x.v_cache[blk, :, pos % 16]
+        for heads in (every, few):
+            k, v = x.k_cache.clone(), x.v_cache.clone()
+            for h in heads:
+                k[blk, h, pos % 16] = float("nan")
+                v[blk, h, pos % 16] = float("nan")
+            hid, n = dx.heads(heads)
+            got = dx.new_out()
+            H.check(H.hetis_attn_decode_step(dx.shape, dx.q, kn, vn, k, v, dx.bt, dx.sl, hid, n, dx.scale, got),
+                    "hetis_attn_decode_step")
+            torch.cuda.synchronize()
+            no_expired_wait()
+            sel = selected_rows(w.spec, heads)
+            assert np.array_equal(bits(got)[:, sel], bits(out)[:, sel])
+            assert torch.equal(k.view(torch.int16), x.k_cache.view(torch.int16))
+            assert torch.equal(v.view(torch.int16), x.v_cache.view(torch.int16))
