@@ -46,8 +46,8 @@
 // chunk of a wave stored and combined by that wave, and partial results loaded many at a time.
 // Measured, before (tables, chunks in row order, the writer wave combining one load at a time, a
 // step's store as a launch of its own) and now: 16 chats of 1088 tokens on average x 13 heads of
-// 128 45.1 -> 26.8 us; two documents of 20k and 27k tokens x 8 heads 70.4 -> 39.2; step of 144 pairs
-// of 8-head groups 58.2 -> 41.1; 4 chats x 4 heads of 64 15.0 -> 9.4.
+// 128 45.1 -> 26.6 us; two documents of 20k and 27k tokens x 8 heads 70.4 -> 38.4; step of 144 pairs
+// of 8-head groups 58.2 -> 41.0; 4 chats x 4 heads of 64 15.0 -> 9.2.
 //
 // A workgroup is NW streaming waves plus one writer wave; after the prologue they never
 // meet at a barrier.
