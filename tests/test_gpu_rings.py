@@ -2,7 +2,7 @@
 dims) in launches of many rows, and twice that where rows are few or most of them are of 2 (3) to 8
 tiles, and in split calls; launches of more than three query rows a head have one depth.  Launches of
 each of these kinds, also behind a block table that allows rows of several segments, as pairs and with
-the new rows stored by the launch, give the same rows the same bits, and all agree with the checker."""
+the new rows stored by the launch, give the same rows the same bits, and all agree with the oracle."""
 import numpy as np
 import pytest
 import torch
