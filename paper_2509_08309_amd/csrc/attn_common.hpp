@@ -124,6 +124,43 @@ __device__ __forceinline__ float group_sum(float x)
     return x;
 }
 
+// x of this lane's partner 16 or 32 lanes away, as (value of the lower one, value of the upper one),
+// the same pair in both: the swaps of gfx950, which stay in the vector ALU.
+struct LanePair {
+    float lo, hi;
+};
+__device__ __forceinline__ LanePair pair_xor16(float x)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return {__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+__device__ __forceinline__ LanePair pair_xor32(float x)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return {__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+__device__ __forceinline__ float max_xor16(float x)
+{
+    const LanePair p = pair_xor16(x);
+    return fmaxf(p.lo, p.hi);
+}
+__device__ __forceinline__ float max_xor32(float x)
+{
+    const LanePair p = pair_xor32(x);
+    return fmaxf(p.lo, p.hi);
+}
+
+__device__ __forceinline__ float sum_xor16(float x)
+{
+    const LanePair p = pair_xor16(x);
+    return p.lo + p.hi;
+}
+__device__ __forceinline__ float sum_xor32(float x)
+{
+    const LanePair p = pair_xor32(x);
+    return p.lo + p.hi;
+}
+
 // Buffer descriptor covering exactly one (block, head) tile, or nothing.  With valid == false
 // the descriptor spans 0 bytes: the hardware range check then makes every lane of a load
 // return zeros without touching memory, while the instruction still takes its place in the
@@ -144,6 +181,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const __half *tile, 
         reinterpret_cast<void *>(((uint64_t)hi << 32) | lo), 0, nbytes, 0x00020000);
 }
 
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -155,6 +193,11 @@ constexpr int kStreamingLoad = 2;
 __device__ __forceinline__ u32x4 buffer_load_u4(__amdgpu_buffer_rsrc_t r, int byte_offset)
 {
     return __builtin_amdgcn_raw_buffer_load_b128(r, byte_offset, 0, kStreamingLoad);
+}
+
+__device__ __forceinline__ u32x2 buffer_load_u2(__amdgpu_buffer_rsrc_t r, int byte_offset)
+{
+    return __builtin_amdgcn_raw_buffer_load_b64(r, byte_offset, 0, kStreamingLoad);
 }
 
 // One word to / from device memory, coherent across the whole device (all XCDs): these

@@ -13,16 +13,12 @@
 //   O^T += V^T . P     v_mfma_f32_16x16x16_f16, D/16 row blocks
 //         B = P      : lane l holds p[token (l/16)*4 + i][head l%16], i = 0..3: exactly the
 //                      C registers above after exp2 and conversion to fp16
-//         A = V^T    : lane l holds V[token (l/16)*4 + i][dim 16*mb + l%16]: four tokens of
-//                      one dim.  The tile is token-major in memory, so it is staged through a
-//                      wave-private LDS area (coalesced 128-bit loads -> ds_write_b128) and
-//                      read back with the gfx950 transposing read ds_read_b64_tr_b16.
-//         C          : lane l, reg i = O[head l%16][dim 16*mb + (l/16)*4 + i]
-//
-// ds_read_b64_tr_b16, as measured on gfx950: inside each group of 16 lanes, source lane s
-// supplies four consecutive halves X[s][0..3] from its own address, and result lane i
-// receives R[i][e] = X[4e + i/4][i%4].  With source lane s pointing at
-// V[token 4*grp + s/4][dim 16*mb + 4*(s%4)] the result is the A operand above.
+//         A = V^T    : lane l holds V[token (l/16)*4 + i][dim of row l%16], i = 0..3: four tokens of
+//                      one dim.  Lane l loads, of each of its four tokens, the D/16 dims from
+//                      (l%16) * D/16 on (16 lanes a token row) and puts the halves of four tokens
+//                      together in its own registers (v_perm_b32): row l%16 of block e is dim
+//                      (l%16) * D/16 + e, so no lane needs a value that another one has loaded.
+//         C          : lane l, reg i of block e = O[head l%16][dim ((l/16)*4 + i) * D/16 + e]
 //
 // Online softmax state per head lives in the 4 lanes {l%16 == head}: the running maximum is
 // kept identical in all four (two cross-lane maxima per tile), the running sum is kept per
@@ -44,21 +40,18 @@ struct MfmaPolicy {
     static_assert(D % 32 == 0 && R <= 16, "MFMA tiling");
     static constexpr int KS = D / 32;                 // contraction steps of S^T = K.Q^T
     static constexpr int MB = D / 16;                 // 16-dim row blocks of O^T
-    static constexpr int NV = kBlockTokens * D * 2 / 1024;   // 1 KB slices of a V tile
-    // Wave-private LDS: one V tile (token-major rows, pitch padded by 32 bytes so that the
-    // 4 rows x 32 bytes a 16-lane transposing read touches fall into different banks) and
-    // the query rows of the current item.
-    static constexpr int kPitchV = 2 * D + 32;
-    static constexpr int kStageV = kBlockTokens * kPitchV;
+    static constexpr int WV = D / 32;                 // words of V a lane holds of each of its tokens
+    // Wave-private LDS: the query rows of the current item.
     static constexpr int kQBytes = R * D * 2;
-    static constexpr int kWaveLdsBytes = kStageV + kQBytes;
+    static constexpr int kWaveLdsBytes = kQBytes;
     static constexpr int kWavesPerEu = 2;             // register budget: 512 / 2 per lane
     // tile pairs in flight per wave (a third pair at D = 128 was worth 2 % on the grouped-query workloads)
     static constexpr int ring(bool) { return D_ == 64 ? 4 : 3; }
 
+    typedef unsigned int VWords __attribute__((ext_vector_type(WV)));
     struct Tile {
         u32x4 k[KS];
-        u32x4 v[NV];
+        VWords v[4];      // of token (l/16)*4 + i
     };
     struct Query {
         f16x8 b[KS];
@@ -75,9 +68,14 @@ struct MfmaPolicy {
         const int koff = (lane & 15) * (2 * D) + (lane >> 4) * 16;
 #pragma unroll
         for (int s = 0; s < KS; ++s) t.k[s] = buffer_load_u4(rk, koff + s * 64);
-        const int voff = lane * 16;
+        const int voff = (lane >> 4) * (8 * D) + (lane & 15) * (4 * WV);
 #pragma unroll
-        for (int i = 0; i < NV; ++i) t.v[i] = buffer_load_u4(rv, voff + i * 1024);
+        for (int i = 0; i < 4; ++i) {
+            if constexpr (WV == 4)
+                t.v[i] = buffer_load_u4(rv, voff + i * (2 * D));
+            else
+                t.v[i] = buffer_load_u2(rv, voff + i * (2 * D));
+        }
     }
 
     // Query rows: fetched as raw bytes one item ahead (kQBytes over 64 lanes), then passed
@@ -98,12 +96,12 @@ struct MfmaPolicy {
     __device__ static __forceinline__ void q_commit(Query &q, const QueryPrefetch &pre,
                                                     unsigned char *stage, int lane)
     {
-        u32x4 *dst = reinterpret_cast<u32x4 *>(stage + kStageV);
+        u32x4 *dst = reinterpret_cast<u32x4 *>(stage);
         if (lane < kQBytes / 16) dst[lane] = pre.raw0;
         if (kQVec > 1 && lane + 64 < kQBytes / 16) dst[lane + 64] = pre.raw1;
         const int j = lane & 15;
         const __half *src =
-            reinterpret_cast<const __half *>(stage + kStageV) + min(j, R - 1) * D + (lane >> 4) * 8;
+            reinterpret_cast<const __half *>(stage) + min(j, R - 1) * D + (lane >> 4) * 8;
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             u32x4 t = *reinterpret_cast<const u32x4 *>(src + s * 32);
@@ -120,69 +118,69 @@ struct MfmaPolicy {
         for (int mb = 0; mb < MB; ++mb) st.acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 
-    // One code path for full and ragged tiles (n_valid = 16 makes every select a no-op):
-    // two copies of this body would leave the accumulators in different registers on the two
-    // sides of a branch and cost 32 register moves per tile to reconcile.
+    // What bounds a wave is the chain of dependent instructions of a tile, not the matrix cores, so the
+    // chain is kept short: the scores in two chains of products, the maximum over the lane groups by the
+    // swaps of the vector ALU instead of two trips through LDS, V^T put together in registers instead of
+    // written to LDS and read back (the compiler waited for each of the eight reads in turn), the sums
+    // brought to a new maximum only in tiles that have one.  One request of 1000 tokens, 2 groups of 8
+    // heads of 128 dims x 4 20.7 -> 18.1 us, 16 x 4 groups of 4 heads of 128 20.5 -> 18.0, of 64 16.6 ->
+    // 15.2, 16 x 4 of 8 heads, 700 to 2000 tokens, 22.1 -> 20.3; 768 rows of 2176, which wait for HBM,
+    // 139.7 -> 138.6, but 800 rows of 1100 of 64 dims (r = 4; eight bytes a load) 46.0 -> 46.5.  Letting the
+    // maximum lag behind by up to 8 saves another 3 % of the small ones, but the largest weight is then no
+    // longer exactly 1 in fp16: error against 64 bits 2.9e-4 instead of 2.7e-4.
     template <bool MAYBE_RAGGED>
     __device__ static __forceinline__ void update(State &st, const Tile &t, const Query &q,
                                                   float scale_log2, int lane, int n_valid,
-                                                  unsigned char *stage)
+                                                  unsigned char *)
     {
         const int grp = lane >> 4;
-        unsigned char *vstage = stage;
-        // ---- V tile -> wave-private LDS, token-major rows
+        // ---- scores of 16 tokens x 16 (padded) heads, in two chains of products
+        f32x4 c = {0.f, 0.f, 0.f, 0.f}, c2 = c;
 #pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            const int pos = i * 1024 + lane * 16;
-            const int row = pos / (2 * D), colb = pos % (2 * D);
-            u32x4 v = t.v[i];
-            if (row >= n_valid) v = u32x4{0u, 0u, 0u, 0u};        // slots past the end may hold NaN
-            *reinterpret_cast<u32x4 *>(vstage + row * kPitchV + colb) = v;
-        }
-        // ---- scores of 16 tokens x 16 (padded) heads
-        f32x4 c = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
+        for (int s = 0; s < KS; s += 2) {
             c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, t.k[s]), q.b[s], c, 0, 0, 0);
+            c2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, t.k[s + 1]), q.b[s + 1], c2, 0, 0, 0);
         }
+        c += c2;
         float s4[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const bool valid = grp * 4 + i < n_valid;
+            const bool valid = !MAYBE_RAGGED || grp * 4 + i < n_valid;
             s4[i] = valid ? c[i] * scale_log2 : -INFINITY;
         }
         float mt = fmaxf(fmaxf(s4[0], s4[1]), fmaxf(s4[2], s4[3]));
-        mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
-        mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
-        const float m_new = fmaxf(st.m, mt);
-        const float alpha = fast_exp2(st.m - m_new);
-        st.m = m_new;
+        mt = max_xor32(max_xor16(mt));
+        if (__builtin_amdgcn_ballot_w64(mt > st.m) != 0) {
+            const float m_new = fmaxf(st.m, mt);
+            const float alpha = fast_exp2(st.m - m_new);
+            st.m = m_new;
+            st.l *= alpha;
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) st.acc[mb] *= alpha;
+        }
         float p4[4];
         float ps = 0.f;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            p4[i] = fast_exp2(s4[i] - m_new);
+            p4[i] = fast_exp2(s4[i] - st.m);
             ps += p4[i];
         }
-        st.l = st.l * alpha + ps;
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) st.acc[mb] *= alpha;
+        st.l += ps;
         const f16x4 pb = {(_Float16)p4[0], (_Float16)p4[1], (_Float16)p4[2], (_Float16)p4[3]};
-        // ---- O^T += V^T . P, V^T through the transposing LDS read (all reads first, so
-        // that their latencies overlap)
-        const int srow = grp * 4 + ((lane & 15) >> 2);
-        const unsigned char *vsrc = vstage + srow * kPitchV + (lane & 3) * 8;
-        union {
-            i16x4 i;
-            f16x4 h;
-        } vt[MB];
+        // ---- O^T += V^T . P
+        VWords v[4];
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-            vt[mb].i = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                (__attribute__((address_space(3))) i16x4 *)(vsrc + mb * 32));
+        for (int i = 0; i < 4; ++i) {
+            v[i] = t.v[i];
+            if (MAYBE_RAGGED && grp * 4 + i >= n_valid) v[i] = VWords{};     // slots past the end may hold NaN
+        }
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-            st.acc[mb] = __builtin_amdgcn_mfma_f32_16x16x16f16(vt[mb].h, pb, st.acc[mb], 0, 0, 0);
+        for (int e = 0; e < MB; ++e) {
+            const unsigned sel = e % 2 ? 0x07060302u : 0x05040100u;
+            const u32x2 vt = {__builtin_amdgcn_perm(v[1][e / 2], v[0][e / 2], sel),
+                              __builtin_amdgcn_perm(v[3][e / 2], v[2][e / 2], sel)};
+            st.acc[e] = __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4, vt), pb, st.acc[e], 0, 0, 0);
+        }
     }
 
     // normalised rows and their base-2 log-sum-exp -> LDS (the wave's mailbox)
@@ -191,16 +189,17 @@ struct MfmaPolicy {
     {
         const int j = lane & 15, grp = lane >> 4;
         float l = st.l;
-        l += __shfl_xor(l, 16, 64);
-        l += __shfl_xor(l, 32, 64);
+        l = sum_xor32(sum_xor16(l));
         if (j < R) {
             const float inv = __builtin_amdgcn_rcpf(l);
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
-                const float4 v = make_float4(st.acc[mb][0] * inv, st.acc[mb][1] * inv,
-                                             st.acc[mb][2] * inv, st.acc[mb][3] * inv);
-                *reinterpret_cast<float4 *>(&o[j][mb * 16 + grp * 4]) = v;
-            }
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int e = 0; e < MB; e += 4) {
+                    const float4 v = make_float4(st.acc[e][i] * inv, st.acc[e + 1][i] * inv,
+                                                 st.acc[e + 2][i] * inv, st.acc[e + 3][i] * inv);
+                    *reinterpret_cast<float4 *>(&o[j][(grp * 4 + i) * MB + e]) = v;
+                }
             if (grp == 0) lse[j] = st.m + fast_log2(l);
         }
     }
