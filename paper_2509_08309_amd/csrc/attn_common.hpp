@@ -33,10 +33,17 @@ constexpr int decode_chunk_tokens(int group)
 {
     return group >= 4 ? HETIS_DECODE_CHUNK_TOKENS_GQA : HETIS_DECODE_CHUNK_TOKENS;
 }
+// A chunk is computed in PIECES of a quarter of a full chunk, each with sums of its own, which are
+// folded lane by lane in ascending order: one wave after another piece, or (launches of few rows) the
+// waves of a workgroup a piece each, with the same operations.
+constexpr int decode_piece_tokens(int group) { return decode_chunk_tokens(group) / 4; }
 constexpr int decode_seg_tokens(int group)
 {
     return group >= 4 ? HETIS_DECODE_SEG_TOKENS_GQA : HETIS_DECODE_SEG_TOKENS;
 }
+
+// what the arithmetic of a tile may meet: Policy::update<...>
+enum : int { kFullTile = 0, kMaybeRagged = 1, kOneCopy = 2 };
 
 struct AttnParams {
     const __half *q;            // [B, Hq, D]
@@ -161,24 +168,22 @@ __device__ __forceinline__ float sum_xor32(float x)
     return p.lo + p.hi;
 }
 
-// Buffer descriptor covering exactly one (block, head) tile, or nothing.  With valid == false
-// the descriptor spans 0 bytes: the hardware range check then makes every lane of a load
-// return zeros without touching memory, while the instruction still takes its place in the
-// in-order load counter.  This lets the tile ring issue every refill unconditionally, which
-// keeps the compiler's wait counts exact (a load that is issued only on some paths forces
-// full drains).
-// The tile address and the validity flag are the same in every lane; they are passed through
+// Buffer descriptor covering the first `nbytes` bytes of one (block, head) tile, or nothing.  Past
+// its end the hardware range check makes a load return zeros without touching memory, while the
+// instruction still takes its place in the in-order load counter.  This lets the tile ring issue every
+// refill unconditionally, which keeps the compiler's wait counts exact (a load that is issued only on
+// some paths forces full drains), and the rows of a ragged block past the sequence's end, which may
+// hold NaN, arrive as zeros.
+// The tile address and the size are the same in every lane; they are passed through
 // readfirstlane so that the descriptor provably sits in scalar registers (a descriptor the
 // compiler believes to be lane-dependent is handled with a loop around every load).
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const __half *tile, int tile_bytes,
-                                                            bool valid)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const __half *tile, int nbytes)
 {
     const uint64_t a = reinterpret_cast<uint64_t>(tile);
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
     const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-    const int nbytes = __builtin_amdgcn_readfirstlane(valid ? tile_bytes : 0);
     return __builtin_amdgcn_make_buffer_rsrc(
-        reinterpret_cast<void *>(((uint64_t)hi << 32) | lo), 0, nbytes, 0x00020000);
+        reinterpret_cast<void *>(((uint64_t)hi << 32) | lo), 0, __builtin_amdgcn_readfirstlane(nbytes), 0x00020000);
 }
 
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));

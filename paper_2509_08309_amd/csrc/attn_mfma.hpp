@@ -45,9 +45,13 @@ struct MfmaPolicy {
     static constexpr int kQBytes = R * D * 2;
     static constexpr int kWaveLdsBytes = kQBytes;
     static constexpr int kWavesPerEu = 2;             // register budget: 512 / 2 per lane
-    // tile pairs in flight per wave (a third pair at D = 128 was worth 2 % on the grouped-query workloads)
-    static constexpr int ring(bool) { return D_ == 64 ? 4 : 3; }
+    // Tile pairs in flight per wave: 16 KB, a whole part of a piece's eight.  (With 24 KB, possible while a
+    // chunk was one piece, 768 rows of 2176 tokens took 139.0 us instead of 139.8, 768 pairs the same; 4
+    // pairs were slower throughout, 64 rows of 500 to 3000 24.3 -> 25.7.)
+    static constexpr int ring(bool) { return D_ == 64 ? 4 : 2; }
 
+    // of a team's wave: two copies of the arithmetic of a tile (4: 16 rows of 300 to 1200, r = 4, 16.8 -> 17.7)
+    static constexpr int kTeamRing = 2;
     typedef unsigned int VWords __attribute__((ext_vector_type(WV)));
     struct Tile {
         u32x4 k[KS];
@@ -128,11 +132,13 @@ struct MfmaPolicy {
     // 139.7 -> 138.6, but 800 rows of 1100 of 64 dims (r = 4; eight bytes a load) 46.0 -> 46.5.  Letting the
     // maximum lag behind by up to 8 saves another 3 % of the small ones, but the largest weight is then no
     // longer exactly 1 in fp16: error against 64 bits 2.9e-4 instead of 2.7e-4.
-    template <bool MAYBE_RAGGED>
+    template <int MAYBE_RAGGED>
     __device__ static __forceinline__ void update(State &st, const Tile &t, const Query &q,
                                                   float scale_log2, int lane, int n_valid,
                                                   unsigned char *)
     {
+#pragma clang fp contract(off)
+        // (two copies of this code must produce the same bits)
         const int grp = lane >> 4;
         // ---- scores of 16 tokens x 16 (padded) heads, in two chains of products
         f32x4 c = {0.f, 0.f, 0.f, 0.f}, c2 = c;
@@ -168,12 +174,8 @@ struct MfmaPolicy {
         st.l += ps;
         const f16x4 pb = {(_Float16)p4[0], (_Float16)p4[1], (_Float16)p4[2], (_Float16)p4[3]};
         // ---- O^T += V^T . P
-        VWords v[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            v[i] = t.v[i];
-            if (MAYBE_RAGGED && grp * 4 + i >= n_valid) v[i] = VWords{};     // slots past the end may hold NaN
-        }
+        // (rows past n_valid were loaded as zeros: see tile_rsrc)
+        const VWords *v = t.v;
 #pragma unroll
         for (int e = 0; e < MB; ++e) {
             const unsigned sel = e % 2 ? 0x07060302u : 0x05040100u;
@@ -183,6 +185,35 @@ struct MfmaPolicy {
         }
     }
 
+    // state of one piece into the state of the pieces before it, lane by lane
+    __device__ static __forceinline__ void fold(State &tot, const State &st)
+    {
+#pragma clang fp contract(off)
+        const float M = fmaxf(tot.m, st.m);
+        const float a = fast_exp2(tot.m - M), b = fast_exp2(st.m - M);
+        tot.m = M;
+        tot.l = __builtin_fmaf(tot.l, a, st.l * b);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) tot.acc[mb][e] = __builtin_fmaf(tot.acc[mb][e], a, st.acc[mb][e] * b);
+    }
+    // state <-> LDS, sixteen bytes a lane at a time
+    static constexpr int kStateVecs = MB + 1;
+    __device__ static __forceinline__ void deposit(const State &st, f32x4 *to, int lane)
+    {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) to[mb * 64 + lane] = st.acc[mb];
+        to[MB * 64 + lane] = f32x4{st.m, st.l, 0.f, 0.f};
+    }
+    __device__ static __forceinline__ void collect(State &st, const f32x4 *from, int lane)
+    {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) st.acc[mb] = from[mb * 64 + lane];
+        const f32x4 ml = from[MB * 64 + lane];
+        st.m = ml.x;
+        st.l = ml.y;
+    }
     // normalised rows and their base-2 log-sum-exp -> LDS (the wave's mailbox)
     __device__ static __forceinline__ void finish(State &st, float (&o)[R][D], float (&lse)[R],
                                                   int lane)

@@ -34,7 +34,9 @@
 // Scheduling modes (AttnParams::mode).  kModeSegments is the above.  kModeSplit: seg_tokens =
 // chunk_tokens, every chunk leaves as a partial result for a separate merge launch.
 // kModeSpread is an offer of the host for launches of few rows, where whole segments can leave
-// much of the chip without work.  If the kernel takes it up, the unit handed out is the chunk (full
+// much of the chip without work.  If there is no more than one full chunk of work for a workgroup, or a
+// row for each, the waves of a workgroup share it (attn_team.hpp).  If there is more and the kernel takes the
+// offer up, the unit handed out is the chunk (full
 // chunks of all rows first, then the shorter ones), chunk results go through the partial buffers
 // in global memory, and the wave that stores the last chunk result of a segment folds that
 // segment's chunks with the operations and in the order of the in-LDS fold (fold_coef /
@@ -47,7 +49,13 @@
 // Measured, before (tables, chunks in row order, the writer wave combining one load at a time, a
 // step's store as a launch of its own) and now: 16 chats of 1088 tokens on average x 13 heads of
 // 128 45.1 -> 26.6 us; two documents of 20k and 27k tokens x 8 heads 70.4 -> 38.4; step of 144 pairs
-// of 8-head groups 58.2 -> 41.0; 4 chats x 4 heads of 64 15.0 -> 9.2.
+// of 8-head groups 58.2 -> 41.0.
+// Pieces.  A chunk is computed in up to four pieces (decode_piece_tokens) with sums of their own, folded lane
+// by lane in ascending order, so that a chunk gives the same bits whether one wave computes it or four.  A
+// fold costs a wave 0.1 to 0.2 us a piece: nothing in launches of many rows, which wait for HBM (1664 rows of
+// 1069 tokens 146.0 -> 144.8, 768 of 2176 with 8 heads 139.0 -> 139.3), 1 to 2 % in some of 300 to 400 rows
+// (360 rows of 300 to 2000 tokens, r = 2, 45.2 -> 45.9; 400 of 300 to 1600 of 64 dims 28.1 -> 28.6), against 10
+// to 40 % gained where four waves share a chunk.
 //
 // A workgroup is NW streaming waves plus one writer wave; after the prologue they never
 // meet at a barrier.
@@ -94,19 +102,11 @@
 // (sequence, KV head) pairs instead of sequences, each with its own block-table row over a
 // pool of single-head tiles; everything else, the arithmetic included, is shared.
 #pragma once
-#include "attn_common.hpp"
+#include "attn_combine.hpp"
+#include "attn_team.hpp"
 
 namespace hetis {
 
-enum : int { kMailEmpty = 0, kMailFull = 1, kMailDone = 2 };
-enum : int { kKindOut = 0, kKindPartial = 1, kKindZero = 2, kKindFold = 3 };
-// Between two looks of a wait, in units of 64 cycles.  The looks are few (five waves a compute unit); with
-// four units in the writer wave and two in the others 4 chats x 4 heads of 64 dims take 9.7 us
-// instead of 9.4, 15 rows of at most 96 tokens 9.3 instead of 9.1, launches of many rows the same.
-constexpr int kPollSleep = 1;
-// Looks before a wait gives up: 2^30 cycles of sleep, 0.4 s.  The longest real wait is for a chunk of the
-// wave's own workgroup, 1024 tokens at most, some tens of microseconds.
-constexpr int kSpinLimit = (1 << 24) / kPollSleep;
 // Size classes of a row's last, shorter segment, largest first: fifteen of one sixteenth of a
 // whole segment each, then the last sixteenth split at 1/32, 1/64 and 1/128 of a segment.
 constexpr int kLinClasses = 15;
@@ -114,13 +114,7 @@ constexpr int kClasses = kLinClasses + 4;
 static_assert(kClasses + 1 <= 32, "class number + 1 is packed into five bits");
 constexpr int kMaxSegChunks = 32;       // chunks of a segment, at most (one writer lane each)
 constexpr int kPoolSize = 2 * kMaxSegChunks;   // chunk descriptors the LDS pool can hold
-constexpr int kMaxQuickRows = 512;      // rows of a launch that may be handed out by single chunks
 constexpr int kTicketBatch = 8;         // tickets per device atomic while segments are single chunks
-// Segments of at most 1/HETIS_FINE_CHUNK_BELOW of a whole one are cut into chunks of half the
-// size, those of at most a quarter of that into chunks of a quarter of the size.
-#ifndef HETIS_FINE_CHUNK_BELOW
-#define HETIS_FINE_CHUNK_BELOW 4
-#endif
 // Chunks of multi-chunk segments a workgroup keeps waiting in its pool before it draws the
 // next segment.
 #ifndef HETIS_POOL_AHEAD
@@ -141,86 +135,6 @@ constexpr int kTicketBatch = 8;         // tickets per device atomic while segme
 #define HETIS_STATIC_FLAT_X16 14
 #endif
 enum : int { kItemExists = 1 };
-template <int N>
-struct IntTag {
-    static constexpr int value = N;
-};
-
-// Inclusive scans over the 64 lanes of a wave (DPP, no LDS traffic): sums, and maxima of x >= 0.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ int dpp_or_zero(int x)
-{
-    return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, true);
-}
-__device__ __forceinline__ int wave_scan_sum(int x)
-{
-    x += dpp_or_zero<0x111, 0xF>(x);    // row_shr 1, 2, 4, 8: inside each row of 16 lanes
-    x += dpp_or_zero<0x112, 0xF>(x);
-    x += dpp_or_zero<0x114, 0xF>(x);
-    x += dpp_or_zero<0x118, 0xF>(x);
-    x += dpp_or_zero<0x142, 0xA>(x);    // row_bcast 15: into rows 1 and 3
-    x += dpp_or_zero<0x143, 0xC>(x);    // row_bcast 31: into rows 2 and 3
-    return x;
-}
-__device__ __forceinline__ int wave_max(int x)
-{
-    x = max(x, dpp_or_zero<0x111, 0xF>(x));
-    x = max(x, dpp_or_zero<0x112, 0xF>(x));
-    x = max(x, dpp_or_zero<0x114, 0xF>(x));
-    x = max(x, dpp_or_zero<0x118, 0xF>(x));
-    x = max(x, dpp_or_zero<0x142, 0xA>(x));
-    x = max(x, dpp_or_zero<0x143, 0xC>(x));
-    return __builtin_amdgcn_readlane(x, 63);
-}
-
-// x / d for x >= 0, d > 0 the same in all lanes: integer division has no instruction of its
-// own and costs about forty; the divisors of the enumeration are powers of two unless a caller
-// of the split entry points chooses otherwise.
-__device__ __forceinline__ int udiv(int x, int d)
-{
-    if (__builtin_expect((d & (d - 1)) == 0, 1)) return x >> __builtin_ctz(d);
-    return x / d;
-}
-
-// Tokens per chunk of a segment of n_tok tokens: the shorter the segment, the later it is
-// handed out and the finer it is cut, so that the chunks still running when the work runs out
-// are short ones.  A function of the row's length and of constants only, like everything that
-// shapes the arithmetic.
-__device__ __forceinline__ int chunk_tokens_of(int n_tok, int chunk_tokens, int seg_tokens)
-{
-    int ct = chunk_tokens;
-    if (seg_tokens > chunk_tokens) {
-        if (n_tok <= seg_tokens / HETIS_FINE_CHUNK_BELOW) ct = chunk_tokens / 2;
-        if (n_tok <= seg_tokens / (4 * HETIS_FINE_CHUNK_BELOW)) ct = chunk_tokens / 4;
-        ct = max(ct, 2 * kBlockTokens);
-    }
-    return ct;
-}
-
-// One step of the running combination of chunk results (o_c normalised, lse_c base 2) into
-// (A, M, W): M' = max(M, lse_c), A' = A 2^(M-M') + o_c 2^(lse_c-M'), W' = W 2^(M-M') + 2^(lse_c-M').
-// Written once, with explicit fused multiply-adds, because two code paths (the fold in LDS and
-// the fold from the partial buffers) must produce the same bits.
-struct FoldCoef {
-    float Mn, so, sc;
-};
-__device__ __forceinline__ FoldCoef fold_coef(float Mo, float lc)
-{
-    FoldCoef f;
-    f.Mn = fmaxf(Mo, lc);
-    f.so = fast_exp2(Mo - f.Mn);
-    f.sc = fast_exp2(lc - f.Mn);
-    return f;
-}
-__device__ __forceinline__ float fold_weight(float Wo, const FoldCoef &f)
-{
-    return __builtin_fmaf(Wo, f.so, f.sc);
-}
-__device__ __forceinline__ float fold_elem(float y, float x, const FoldCoef &f)
-{
-    return __builtin_fmaf(y, f.so, x * f.sc);
-}
-
 // A chunk, decoded: what a streaming wave needs to start on it and to label its result.
 struct ChunkDesc {
     int b, g, seq;      // enumeration row (sequence, or pair), KV head, sequence of q / out rows
@@ -267,345 +181,6 @@ struct alignas(16) FoldSlot {
 template <int R>
 __host__ __device__ constexpr int fold_slots() { return R >= 4 ? 5 : 8; }
 
-// The R result rows of one chunk or segment in the registers of a wave: lane l holds elements
-// 4 l + 256 k .. + 3 of the R * D, and with them the row's log-sum-exp.  With fewer than 256 elements
-// the lanes beyond them hold copies of the last ones, which are not stored.
-template <int D, int R>
-struct RowRegs {
-    static constexpr int K = (R * D + 255) / 256;
-    f32x4 x[K];
-    float lse[K];       // base 2
-    __device__ static __forceinline__ int elem(int lane, int k) { return min(lane * 4 + k * 256, R * D - 4); }
-    __device__ static __forceinline__ bool stored(int lane) { return R * D >= 256 || lane * 4 < R * D; }
-    __device__ __forceinline__ void load(const float (*o)[D], const float *lse2, int lane)
-    {
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            x[k] = *reinterpret_cast<const f32x4 *>(&o[0][0] + elem(lane, k));
-            lse[k] = lse2[elem(lane, k) / D];
-        }
-    }
-};
-
-// Result rows -> `out` (fp16) or the partial buffers (fp32, natural-log log-sum-exp).
-template <int D, int R>
-__device__ __forceinline__ void store_result(const RowRegs<D, R> &g, int kind, int64_t dest,
-                                             const AttnParams &p, int lane)
-{
-    if (!RowRegs<D, R>::stored(lane)) return;
-#pragma unroll
-    for (int k = 0; k < RowRegs<D, R>::K; ++k) {
-        const int idx = lane * 4 + k * 256, r = idx / D, d = idx % D;
-        f32x4 v = g.x[k];
-        if (kind == kKindPartial) {
-            // the r rows of one (row, head, segment) are contiguous in the partial buffers
-            *reinterpret_cast<f32x4 *>(p.o_partial + dest * (R * D) + idx) = v;
-            if (d == 0) p.lse_partial[dest * R + r] = g.lse[k] * kLn2;
-        } else {
-            if (kind == kKindZero) v = f32x4{0.f, 0.f, 0.f, 0.f};
-            union {
-                __half2 h[2];
-                uint2 u;
-            } pk;
-            pk.h[0] = __floats2half2_rn(v.x, v.y);
-            pk.h[1] = __floats2half2_rn(v.z, v.w);
-            *reinterpret_cast<uint2 *>(p.out + (dest + r) * D + d) = pk.u;
-        }
-    }
-}
-
-// Partial result of a segment that is merged inside this launch (AttnParams::arrivals): by
-// whichever wave stores the row's last segment, possibly on another XCD, so the words are
-// stored device-coherently, sixteen bytes a lane.
-// `base2`: the log-sum-exp is stored as it is (chunk results of kModeSpread), otherwise as a
-// natural logarithm (segment results).
-template <int D, int R>
-__device__ __forceinline__ void store_partial_coherent(const RowRegs<D, R> &g, int64_t dest,
-                                                       const AttnParams &p, int lane, bool base2)
-{
-    const __amdgpu_buffer_rsrc_t dst = coherent_rsrc(p.o_partial + dest * (R * D), R * D * 4);
-#pragma unroll
-    for (int k = 0; k < RowRegs<D, R>::K; ++k) {
-        const int idx = lane * 4 + k * 256;              // (past the R * D elements: not stored)
-        coherent_store_b128(dst, idx * 4, __builtin_bit_cast(u32x4, g.x[k]));
-        if (idx < R * D && idx % D == 0)
-            coherent_store(p.lse_partial + dest * R + idx / D, base2 ? g.lse[k] : g.lse[k] * kLn2);
-    }
-}
-
-// Partial results loaded together by the two functions below.  Their loads are device-coherent
-// (the partial results may come from other XCDs) and the compiler keeps such loads in program
-// order with every use, so a loop that loads and uses one result at a time pays a memory round
-// trip for each: the wave that ends a launch then spends tens of microseconds on a row.
-// With four or eight rows a result (kPartVectors) a lane loads vectors of four words, as many as there
-// are registers for (eight with 8 x 128 words; scratch memory otherwise), and looks its row's weight up;
-// with one or two rows it loads words, the same dims of every row, and weights are the same in all lanes.
-// A step of 144 pairs of 8-head groups: words 44.9 us, vectors 43.4; 16 chats x 13 heads (r = 1) 27.5 and 28.1.
-// r = 4: vectors too, but half as many: more only fills registers, which are the streaming loop's as well
-// (218 of them against 182 at 64 dims, 256 against 235 at 128).  Words / 16 vectors / 8, 64 dims: 160 rows
-// of 500 to 2000 tokens 21.35 / 21.18 / 20.75 us, 508 of them 39.2 / 40.0 / 39.4; words / 16 / 8, 128 dims:
-// 400 of 300 to 1200 40.5 / 40.3 / 39.7, 12 of 10k to 32k 32.6 / 32.5 / 32.8.
-template <int R>
-constexpr bool kPartVectors = R >= 4;
-template <int D, int R>
-constexpr int kPartBatch =                                         // at most 64 / R
-    !kPartVectors<R> ? 16 : (R == 4 ? 8 : R * D > 512 ? 8 : 16) / RowRegs<D, R>::K;
-
-// Partial results in slots slot_of(0), slot_of(1), ... of the partial buffers -> x; their
-// log-sum-exps come back with lane u * R + r holding that of result u, row r.
-template <int D, int R, class SlotOf>
-__device__ __forceinline__ float load_partials(const AttnParams &p, f32x4 (&x)[kPartBatch<D, R>][RowRegs<D, R>::K],
-                                               SlotOf slot_of, int lane)
-{
-    const float lc = coherent_load(p.lse_partial + slot_of(min(lane / R, kPartBatch<D, R> - 1)) * R + lane % R);
-    const int64_t s0 = slot_of(0);
-    const __amdgpu_buffer_rsrc_t src = coherent_rsrc(
-        p.o_partial + s0 * (R * D), (int)(slot_of(kPartBatch<D, R> - 1) - s0 + 1) * (R * D * 4));
-#pragma unroll
-    for (int u = 0; u < kPartBatch<D, R>; ++u) {
-        const int from = (int)(slot_of(u) - s0) * (R * D * 4);
-#pragma unroll
-        for (int k = 0; k < RowRegs<D, R>::K; ++k)
-            x[u][k] = __builtin_bit_cast(
-                f32x4, coherent_load_b128(src, RowRegs<D, R>::elem(lane, k) * 4, from));
-    }
-    return lc;
-}
-
-// x of lane `lane + ahead`
-__device__ __forceinline__ float from_lane(float x, int lane, int ahead)
-{
-    return __int_as_float(__builtin_amdgcn_ds_bpermute(4 * lane + 4 * ahead, __float_as_int(x)));
-}
-
-// Log-sum-exp merge of the n_segs partial results of one row, ascending segment order, by one
-// wave: M = max_c lse_c, w_c = exp(lse_c - M), out = fp16(sum_c w_c o_c / sum_c w_c).  `first` is the
-// index of segment 0 of the row in the partial buffers, segment c sits `stride` * c slots further.
-// The maximum takes one load a lane per 64 log-sum-exps, the sums one round trip per
-// kPartBatch segments (two rows of 5 to 7 segments per head, one load at a time: 25 us of the 70
-// that launch took).
-template <int D, int R>
-__device__ __forceinline__ void merge_partials(const AttnParams &p, int64_t first, int n_segs,
-                                               int stride, int64_t out_row, int lane)
-{
-    if constexpr (kPartVectors<R>) {
-        constexpr int K = RowRegs<D, R>::K, U = kPartBatch<D, R>;
-        const int64_t step = (int64_t)stride * R;        // rows of the buffers per segment
-        const float *lse = p.lse_partial + first * R;    // [segment][r]
-        // lane l looks at segments l / R, l / R + 64 / R, ... of row l % R
-        float mx = -INFINITY;
-#pragma unroll 1
-        for (int c0 = 0; c0 < n_segs; c0 += 64 / R)
-            mx = fmaxf(mx, coherent_load(lse + min(c0 + lane / R, n_segs - 1) * step + lane % R));
-#pragma unroll
-        for (int off = 32; off >= R; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-        RowRegs<D, R> g;
-        float M[K], W[K];
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            M[k] = __shfl(mx, RowRegs<D, R>::elem(lane, k) / D, 64);
-            W[k] = 0.f;
-            g.x[k] = f32x4{0.f, 0.f, 0.f, 0.f};
-            g.lse[k] = 0.f;
-        }
-#pragma unroll 1
-        for (int c0 = 0; c0 < n_segs; c0 += U) {
-            f32x4 x[U][K];
-            const float lc = load_partials<D, R>(
-                p, x, [&](int u) { return first + (int64_t)min(c0 + u, n_segs - 1) * stride; }, lane);
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (c0 + u >= n_segs) continue;
-#pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    const float lse_c = from_lane(lc, RowRegs<D, R>::elem(lane, k) / D, u * R);
-                    const float w = fast_exp2((lse_c - M[k]) * kLog2e);
-                    W[k] += w;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) g.x[k][e] = fmaf(w, x[u][k][e], g.x[k][e]);
-                }
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) g.x[k][e] /= W[k];
-        }
-        store_result<D, R>(g, kKindOut, out_row, p, lane);
-    } else {
-        constexpr int V = D / 64;                        // words per lane and row: 1 or 2
-        constexpr int U = kPartBatch<D, R>;
-        const int64_t step = (int64_t)stride * R;        // rows of the buffers per segment
-        const float *lse = p.lse_partial + first * R;    // [segment][r]
-        const float *op = p.o_partial + first * (R * D) + lane;
-        // lane l looks at segments l / R, l / R + 64 / R, ... of row l % R
-        float mx = -INFINITY;
-#pragma unroll 1
-        for (int c0 = 0; c0 < n_segs; c0 += 64 / R)
-            mx = fmaxf(mx, coherent_load(lse + min(c0 + lane / R, n_segs - 1) * step + lane % R));
-#pragma unroll
-        for (int off = 32; off >= R; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-        float M[R], W[R], acc[R][V];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            M[r] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mx), r));
-            W[r] = 0.f;
-#pragma unroll
-            for (int v = 0; v < V; ++v) acc[r][v] = 0.f;
-        }
-#pragma unroll 1
-        for (int c0 = 0; c0 < n_segs; c0 += U) {
-            float x[U][R][V];
-            // lane u * R + r: log-sum-exp of segment c0 + u, row r
-            const int lc = __float_as_int(coherent_load(lse + min(c0 + lane / R, n_segs - 1) * step + lane % R));
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int64_t row = min(c0 + u, n_segs - 1) * step;
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-#pragma unroll
-                    for (int v = 0; v < V; ++v) x[u][r][v] = coherent_load(op + (row + r) * D + v * 64);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (c0 + u >= n_segs) continue;
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const float lse_c = __int_as_float(__builtin_amdgcn_readlane(lc, u * R + r));
-                    const float w = fast_exp2((lse_c - M[r]) * kLog2e);
-                    W[r] += w;
-#pragma unroll
-                    for (int v = 0; v < V; ++v) acc[r][v] = fmaf(w, x[u][r][v], acc[r][v]);
-                }
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            __half *dst = p.out + (out_row + r) * D + lane;
-#pragma unroll
-            for (int v = 0; v < V; ++v) dst[v * 64] = __float2half_rn(acc[r][v] / W[r]);
-        }
-    }
-}
-
-// kModeSpread: the ns chunk results of one segment lie in the partial buffers (chunk c in slot
-// slot0 + c, log-sum-exp base 2).  One wave combines them with the operations a workgroup
-// applies to the chunks of a segment in kModeSegments, in the same order: folded in ascending
-// order, then normalised.  `whole_row`: the segment is the whole row and the result goes to
-// `out`; otherwise it replaces the first chunk result in the buffers, as the partial result of
-// the segment (natural-log log-sum-exp) that merge_partials expects.
-template <int D, int R>
-__device__ __forceinline__ void fold_segment_from_chunks(const AttnParams &p, int64_t slot0, int ns,
-                                                         bool whole_row, int64_t out_row, int lane)
-{
-    if constexpr (kPartVectors<R>) {
-        constexpr int K = RowRegs<D, R>::K, U = kPartBatch<D, R>;
-        RowRegs<D, R> g;
-        float W[K];
-#pragma unroll 1
-        for (int c0 = 0; c0 < ns; c0 += U) {
-            f32x4 x[U][K];
-            const float lc = load_partials<D, R>(p, x, [&](int u) { return slot0 + min(c0 + u, ns - 1); }, lane);
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (c0 + u >= ns) continue;
-#pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    const float lse_c = from_lane(lc, RowRegs<D, R>::elem(lane, k) / D, u * R);
-                    if (c0 + u == 0) {
-                        g.lse[k] = lse_c;
-                        W[k] = 1.f;
-                        g.x[k] = x[u][k];
-                    } else {
-                        const FoldCoef f = fold_coef(g.lse[k], lse_c);
-                        W[k] = fold_weight(W[k], f);
-                        g.lse[k] = f.Mn;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) g.x[k][e] = fold_elem(g.x[k][e], x[u][k][e], f);
-                    }
-                }
-            }
-        }
-        if (ns > 1) {
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const float inv = __builtin_amdgcn_rcpf(W[k]);
-                g.lse[k] = g.lse[k] + fast_log2(W[k]);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) g.x[k][e] *= inv;
-            }
-        }
-        if (whole_row)
-            store_result<D, R>(g, kKindOut, out_row, p, lane);
-        else
-            store_partial_coherent<D, R>(g, slot0, p, lane, false);
-    } else {
-        constexpr int V = D / 64;
-        constexpr int U = kPartBatch<D, R>;
-        float a[R][V], M[R], W[R];
-#pragma unroll 1
-        for (int c0 = 0; c0 < ns; c0 += U) {
-            float x[U][R][V];
-            // lane u * R + r: log-sum-exp of chunk c0 + u, row r
-            const int lc = __float_as_int(
-                coherent_load(p.lse_partial + (slot0 + min(c0 + lane / R, ns - 1)) * R + lane % R));
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int64_t slot = slot0 + min(c0 + u, ns - 1);
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-#pragma unroll
-                    for (int v = 0; v < V; ++v)
-                        x[u][r][v] = coherent_load(p.o_partial + (slot * R + r) * D + v * 64 + lane);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    if (c0 + u >= ns) continue;
-                    const float lse_c = __int_as_float(__builtin_amdgcn_readlane(lc, u * R + r));
-                    if (c0 + u == 0) {
-                        M[r] = lse_c;
-                        W[r] = 1.f;
-#pragma unroll
-                        for (int v = 0; v < V; ++v) a[r][v] = x[u][r][v];
-                    } else {
-                        const FoldCoef f = fold_coef(M[r], lse_c);
-                        W[r] = fold_weight(W[r], f);
-                        M[r] = f.Mn;
-#pragma unroll
-                        for (int v = 0; v < V; ++v) a[r][v] = fold_elem(a[r][v], x[u][r][v], f);
-                    }
-                }
-            }
-        }
-        if (ns > 1) {
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const float s = __builtin_amdgcn_rcpf(W[r]);
-                M[r] = M[r] + fast_log2(W[r]);
-#pragma unroll
-                for (int v = 0; v < V; ++v) a[r][v] *= s;
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (whole_row) {
-                __half *dst = p.out + (out_row + r) * D + lane;
-#pragma unroll
-                for (int v = 0; v < V; ++v) dst[v * 64] = __float2half_rn(a[r][v]);
-            } else {
-#pragma unroll
-                for (int v = 0; v < V; ++v)
-                    coherent_store(p.o_partial + (slot0 * R + r) * D + v * 64 + lane, a[r][v]);
-                if (lane == 0) coherent_store(p.lse_partial + slot0 * R + r, M[r] * kLn2);
-            }
-        }
-    }
-}
-
 // Partial results (of segments, or in kModeSpread of chunks) that a writer wave has stored in
 // one pass over its mailboxes and that still have to be counted in.  Ordering across waves and
 // XCDs without cache-wide write-backs or invalidations (which were measured to cost several
@@ -621,65 +196,6 @@ struct Arrivals {
     int dest[NW], parts[NW], out_row[NW], len[NW];     // lives in LDS, used by the writer wave only
 };
 
-// Counters (AttnParams::arrivals), n_rows = (enumeration rows) x (selected heads) of the launch:
-// entry row counts the stored segment results of that row; in kModeSpread entry
-// n_rows + row * (segments per row the buffers provide for) + j counts the stored chunk results
-// of segment j of that row.  There the wave that completes a segment folds its chunks, which
-// spreads the folding of a long row over as many waves as it has segments, stores the segment
-// result and counts it in for the row in turn.
-template <int R>
-__device__ __forceinline__ int64_t arrival_counter(const AttnParams &p, int dest, bool spread, int n_rows)
-{
-    constexpr int gc = decode_seg_tokens(R) / decode_chunk_tokens(R);
-    const int row = dest / p.max_segs;               // (enumeration row, head)
-    return spread ? n_rows + (int64_t)row * (p.max_segs / gc) + (dest - row * p.max_segs) / gc : row;
-}
-
-// What follows a count: `before` is the counter's value before this result was counted in.  All
-// arguments are the same in every lane.
-template <int D, int R>
-__device__ __forceinline__ void combine_if_last(const AttnParams &p, int before, int dest, int parts,
-                                                int64_t out_row, int len, bool spread, int n_rows,
-                                                int lane)
-{
-    // what follows from the lane's number is worked out here: hoisted out of the writer wave's loop, it
-    // takes more registers than there are
-    asm volatile("" : "+v"(lane));
-    constexpr int seg_tokens = decode_seg_tokens(R), gc = seg_tokens / decode_chunk_tokens(R);
-    const int64_t row = dest / p.max_segs;
-    int n_segs = parts;
-    if (spread) {
-        const int j = (dest - (int)row * p.max_segs) / gc;
-        const int n_tok = min(seg_tokens, len - j * seg_tokens);
-        const int ct = chunk_tokens_of(n_tok, decode_chunk_tokens(R), seg_tokens);
-        const int ns = udiv(n_tok + ct - 1, ct);
-        if (before + 1 != ns) return;
-        n_segs = (len + seg_tokens - 1) / seg_tokens;
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        fold_segment_from_chunks<D, R>(p, row * p.max_segs + j * gc, ns,
-                                       n_segs == 1, out_row, lane);
-        unsigned seen = 0;
-        if (n_segs > 1) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_s_waitcnt(0);           // the segment result is stored
-        }
-        if (lane == 0) {
-            __hip_atomic_store(p.arrivals + arrival_counter<R>(p, dest, true, n_rows), 0u, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-            if (n_segs > 1)
-                seen = __hip_atomic_fetch_add(p.arrivals + row, 1u, __ATOMIC_RELAXED,
-                                              __HIP_MEMORY_SCOPE_AGENT);
-        }
-        if (n_segs == 1 || (int)__builtin_amdgcn_readfirstlane(seen) + 1 != n_segs) return;
-    } else if (before + 1 != n_segs) {
-        return;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    merge_partials<D, R>(p, row * p.max_segs, n_segs, spread ? gc : 1, out_row, lane);
-    if (lane == 0)
-        __hip_atomic_store(p.arrivals + row, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 template <int D, int R, int NW>
 __device__ __forceinline__ void count_in_and_combine(const AttnParams &p, const Arrivals<NW> &arr,
                                                      int n_arr, bool spread, int n_rows, int lane)
@@ -692,7 +208,7 @@ __device__ __forceinline__ void count_in_and_combine(const AttnParams &p, const 
                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll 1
     for (int i = 0; i < n_arr; ++i)
-        combine_if_last<D, R>(p, __builtin_amdgcn_readlane((int)old, i),
+        combine_if_last<D, R>(p, __builtin_amdgcn_readlane((int)old, i), 1,
                               __builtin_amdgcn_readfirstlane(arr.dest[i]),
                               __builtin_amdgcn_readfirstlane(arr.parts[i]),
                               __builtin_amdgcn_readfirstlane(arr.out_row[i]),
@@ -701,14 +217,11 @@ __device__ __forceinline__ void count_in_and_combine(const AttnParams &p, const 
 
 struct ItemHdr {
     int b, g, seq;  // enumeration row (sequence, or pair), KV head, sequence of q / out rows
-    int nblk;       // blocks of this chunk
-    int rem;        // tokens in the ragged last block (0: none)
+    int n_tok;      // tokens of this chunk
     int t0;         // first token of the chunk
     int kind, dest, cs;
     int nseg, out_row, len;
 };
-
-__host__ __device__ constexpr size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
 
 // Table bytes: lens, firstF (int), order and place (uint16), then the selected heads, or in pairs
 // mode the head and the sequence of every pair.
@@ -729,82 +242,6 @@ __host__ __device__ constexpr size_t persist_lds_bytes(int rows, int n_sel, bool
            2 * NW * sizeof(Mailbox<Policy::D, Policy::R>) +
            fold_slots<Policy::R>() * sizeof(FoldSlot<Policy::D, Policy::R>) +
            (size_t)NW * Policy::kWaveLdsBytes;
-}
-
-__device__ __forceinline__ int mail_load(const int *flag)
-{
-    return __hip_atomic_load(flag, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-__device__ __forceinline__ void mail_store(int *flag, int v)
-{
-    __hip_atomic_store(flag, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-// Orders the LDS accesses of one wave around a point where lanes read what other lanes of
-// the same wave wrote (the hardware keeps a wave's LDS operations in order; this keeps the
-// compiler from moving them).
-__device__ __forceinline__ void wave_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
-// The new token's K row and V row of (sequence, KV head g) -> slot pos % 16 of the tile
-// (block, g); lanes [0, D/8) move the K row, the next D/8 lanes the V row, 16 bytes each; nothing
-// is read or written unless `inside`.
-template <int D>
-__device__ __forceinline__ void store_new_rows(const AttnParams &p, int seq, int g, int64_t tile_off,
-                                               int slot, int n_kv_heads, int lane, bool inside)
-{
-    constexpr int LR = D / 8;
-    if (lane < 2 * LR && inside) {
-        const bool is_v = lane >= LR;
-        const int c = lane % LR;
-        const __half *src = (is_v ? p.v_new : p.k_new) + ((int64_t)seq * n_kv_heads + g) * D + c * 8;
-        __half *dst = const_cast<__half *>(is_v ? p.v_cache : p.k_cache) + tile_off + slot * D + c * 8;
-        *reinterpret_cast<uint4 *>(dst) = *reinterpret_cast<const uint4 *>(src);
-    }
-}
-
-// Launch of fewer than kMaxQuickRows rows of one segment each, the longest of more than one full
-// chunk: are its chunks handed out singly (true), or the rows whole, one or two a workgroup?
-// `rows` rows of `tokens` tokens in all and `longest` at most, `chunks` chunks; G workgroups.
-// Whole rows wait for the longest one, or, with more rows than workgroups, for two in turn, beside
-// idle compute units; but their chunks meet in LDS, where the results of single ones go through
-// global memory, r times as much with r query rows.  Measured with either side forced, rows whole ->
-// single chunks, in us (r = 1, 128 dims, lengths uniform, unless stated):
-//  - Up to G rows.  What idles is 1 - tokens / (G * longest).  r < 4: chunks, unless less than
-//    three tenths idle and some wave would take a second chunk (128 rows of 4096: 52.6 -> 50.6; 255 of
-//    275 to 1100 23.3 -> 22.8; but 230 of 600 17.8 -> 20.4, 255 of 4096 92.7 -> 95.2).  r >= 4: a row
-//    of up to NW chunks is one turn of a workgroup; it gains when it is several chunks long, the
-//    more the more idles (r = 8, 200 rows of 500 to 2000: 41.3 -> 36.0; 300 to 1200: 25.8 -> 28.9;
-//    250 to 1000, whose chunks are half as long: 25.0 -> 23.5; 150 to 600: 17.8 -> 17.7).
-//  - More rows.  Chunks for a few long ones among short ones (511 rows, log-normal around 820, up
-//    to 4096: 67.5 -> 57.6), where the rows are alike and the workgroups' second turn is mostly empty
-//    (270 of 4096: 120 -> 99), and for up to one (r >= 4) or some 2.4 chunks a wave (390 of 1200: 49.0 ->
-//    45.3; 480 of 75 to 300, r = 2: 19.8 -> 19.5, 480 of up to 290: 23.0 -> 17.6; but around 2.5 a wave 460
-//    of 275 to 1100 34.7 -> 37.6, 64 dims 23.8 -> 29.0).  Otherwise rows whole: 511 of 500 to 2000 57.6 ->
-//    61.9, r = 2 59.2 -> 65.6, r = 8 61.4 -> 68.8; of 150 to 600, r = 8, 26.2 -> 32.4.
-//  - r >= 4 and rows of more than one turn, G or more of them: whole, as when that was the faster way
-//    everywhere.  It no longer is (r = 8, 360 of 750 to 3000: 70.0 -> 70.5, but 270 of 4096 143 -> 114,
-//    256 log-normal around 820 68 -> 40, 511 of these 78.8 -> 64.5).
-template <int D, int R, int NW>
-__device__ __forceinline__ bool spread_pays(int G, int rows, int longest, int tokens, int chunks)
-{
-    constexpr int ct = decode_chunk_tokens(R), turn = NW * ct;      // tokens a workgroup's waves hold
-    const int waves = NW * G, full = G * longest;
-    const bool idle = 10 * tokens < 7 * full;
-    if (rows <= G) {
-        if (R < 4) return idle || chunks <= waves;
-        if (!idle || (rows == G && longest > turn)) return false;
-        // chunks of the longest row are full ones, or half as long
-        const bool halves = chunk_tokens_of(longest, ct, decode_seg_tokens(R)) < ct;
-        return (!halves && 10 * chunks <= 4 * waves) ||
-               200ll * ct * tokens < (halves ? 60ll : 35ll) * longest * full;
-    }
-    constexpr bool wide = R < 4 && R * D > 128;             // a partial result of more than 512 bytes
-    const bool even = 20 * tokens >= 17 * full && 16 * rows < (wide ? 24 : 26) * G;
-    if (R < 4) return idle || even || 10 * chunks <= (wide ? 23 : 25) * waves;
-    return longest <= turn && (chunks <= waves || 20 * tokens < (R * D <= 512 ? 18 : 11) * full || even);
 }
 
 // Depth of the ring of tiles in a decode call of `rows` rows; `short_rows`: how many of 64 rows picked
@@ -852,7 +289,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
     constexpr bool FEW = VARIANT >= kVariantFew;
     constexpr bool CAN_SPLIT = holds_split(VARIANT, PAIRS);
     constexpr int NT = (NW + 1) * 64;
-    constexpr int kTileBytes = kBlockTokens * D * 2;
+    constexpr int kRowBytes = D * 2;
     constexpr int NS = fold_slots<R>();
     using Mail = Mailbox<D, R>;
     using Fold = FoldSlot<D, R>;
@@ -891,16 +328,25 @@ __global__ __launch_bounds__((NW + 1) * 64)
 
     // ---- launches of few rows (p.mode == kModeSpread: fewer than kMaxQuickRows rows x heads).
     // Every wave loads all row lengths and works out in registers, without a barrier, how the
-    // launch is handed out, and (streaming waves) its own first item.  One of three ways:
+    // launch is handed out, and (streaming waves) its own first item.  One of four ways:
+    //  - lone: no more rows than workgroups, no row longer than a segment, and spread_pays() (below) says
+    //    no: workgroup w takes row w as a team.
+    //  - team: spread_pays(), and no more items (windows of a full chunk) than workgroups: workgroup w takes item
+    //    w as a team.  A wave's chain of tiles is a quarter of a chunk's, and the chunk's pieces meet in LDS.
+    //    With more items than workgroups the waves are busy with a chunk each, and a team has several
+    //    items, one after the other, and its results pass through one wave: 16 rows of 2000 tokens (r =
+    //    1, 128 items) 13.5 as chunks -> 10.4 us as teams, 64 rows of 500 to 3000 (r = 8, 220) 25.4 -> 19.4, 64
+    //    of 300 to 1200 (r = 4, 64 dims) 16.6 -> 12.3; but 80 pairs of 850 (305 items) 15.3 -> 16.4, 64 rows of
+    //    500 to 1500 (290) 14.9 -> 16.4, 300 of 300 to 1200 (980) 26.9 -> 32.6.  Rows whole: 230 of 600
+    //    tokens 18.3 -> 15.9, 255 of 4096 88.3 -> 86.1, 240 of 1000 of 64 dims 20.1 -> 15.7, 256 of 300 to 900 (r =
+    //    8, 64 dims) 17.3 -> 13.8, 16 of 17 to 255 of 64 dims 9.4 -> 6.9; 250 of 1000 to 4000 (r = 8) 68.0 -> 68.6.
     //  - spread: single chunks (see the top), when some row has more than one full chunk and
     //    spread_pays() says so.
-    //  - lone: no more rows than workgroups, and no row longer than a segment: workgroup w takes
-    //    row w as its only segment, and there is nothing to enumerate.
     //  - otherwise whole segments through the tables, as in every other launch.
     // The tables cost 3 us of latency (scans over the workgroup, four barriers): a third of what
     // a launch of a few short rows takes.
     constexpr int QG = kMaxQuickRows / 64;
-    bool spread = false, lone = false;
+    bool spread = false;
     int q_len[MERGE ? QG : 1], q_seq[MERGE ? QG : 1], q_head[MERGE ? QG : 1];   // lane l: row 64 u + l
     int qA[MERGE ? QG : 1], qB[MERGE ? QG : 1];     // spread: full / other chunks before the row
     int totalA = 0, totalB = 0;
@@ -924,17 +370,17 @@ __global__ __launch_bounds__((NW + 1) * 64)
         return x;
     };
     int q_first_head = 0;                               // of the wave's first item
-    int lone_len = 0, lone_head = 0, lone_seq = 0;      // of the workgroup's only row
-    if (tid < 2 * NW) mail[tid].flag = kMailEmpty;
+    __shared__ int team_full[2 * NW];
+    if (tid < 2 * NW) mail[tid].flag = team_full[tid] = kMailEmpty;
     if (tid == 0) {
         pool.next = 0;
         pool.end = 0;
     }
     if (MERGE && p.mode == kModeSpread) {
-        // heads of the items this wave may start on: spread, lone
+        // heads of the items this wave may start on: spread, team
         const int first_item = wave * (int)gridDim.x + (int)blockIdx.x;
         const int head_spread = PAIRS ? 0 : p.head_ids[first_item % n_sel];
-        const int head_lone = PAIRS ? 0 : p.head_ids[(int)blockIdx.x % n_sel];
+        const int head_team = PAIRS ? 0 : p.head_ids[(int)blockIdx.x % n_sel];
         // (groups beyond the launch's rows are branched over)
 #pragma unroll
         for (int u = 0; u < QG; ++u) {
@@ -949,6 +395,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
             if (u * 64 < batch) q_len[u] = p.seq_lens[q_seq[u]];
         __syncthreads();                            // mailboxes and pool are ready
         int longest = 0;
+        bool full_house = false;
 #pragma unroll
         for (int u = 0; u < QG; ++u)
             if (u * 64 < batch) longest = max(longest, u * 64 + lane < batch ? q_len[u] : 0);
@@ -980,17 +427,60 @@ __global__ __launch_bounds__((NW + 1) * 64)
                     sum += ((L + kBlockTokens - 1) / kBlockTokens << 14) + ((L + ct - 1) >> sh);
             }
             sum = __builtin_amdgcn_readlane(wave_scan_sum(sum), 63);
-            spread = spread_pays<D, R, NW>((int)gridDim.x, batch * n_sel, longest,
-                                        (sum >> 14) * kBlockTokens * n_sel, (sum & ((1 << 14) - 1)) * n_sel);
+            const int tokens = (sum >> 14) * kBlockTokens * n_sel;
+            spread = spread_pays<D, R, NW>((int)gridDim.x, batch * n_sel, longest, tokens,
+                                           (sum & ((1 << 14) - 1)) * n_sel);
+            // more than a full chunk a workgroup, whatever its rows
+            full_house = tokens - batch * n_sel * (kBlockTokens - 1) > (int)gridDim.x * chunk_tokens;
         }
-        lone = !spread && longest <= seg_tokens && batch * n_sel <= (int)gridDim.x;
-        q_first_head = spread ? head_spread : head_lone;
-        if (lone) {
-            const int b = min((int)blockIdx.x / n_sel, batch - 1);
-            lone_len = of_row(q_len, b);
-            lone_head = PAIRS ? of_row(q_head, b) : q_first_head;
-            lone_seq = PAIRS ? of_row(q_seq, b) : b;
+        const bool lone = !spread && longest <= seg_tokens && batch * n_sel <= (int)gridDim.x;
+        // items (windows of a full chunk) of a row, and of all rows, per selected head
+        auto items_of = [&](int L) { return max(1, (L + chunk_tokens - 1) / chunk_tokens); };
+        int n_items = 0;
+        if (spread && !full_house) {
+#pragma unroll
+            for (int u = 0; u < QG; ++u)
+                if (u * 64 + lane < batch) n_items += items_of(q_len[u]);
+            n_items = __builtin_amdgcn_readlane(wave_scan_sum(n_items), 63);
         }
+        const bool team = lone || (spread && !full_house && (long long)n_items * n_sel <= (long long)gridDim.x);
+        if (__builtin_amdgcn_readfirstlane(team)) {
+            if ((int)blockIdx.x >= (lone ? batch : n_items) * n_sel) return;
+            int b = (int)blockIdx.x / n_sel, k = 0;
+            const int si = (int)blockIdx.x - b * n_sel;
+            if (!lone) {
+                // the last row with no more than `left` items before it, group by group
+                int left = b;
+                b = 0;
+#pragma unroll
+                for (int u = 0; u < QG; ++u) {
+                    if (u * 64 >= batch || b != u * 64) continue;
+                    const int mine = u * 64 + lane < batch ? items_of(q_len[u]) : 0;
+                    const int incl = wave_scan_sum(mine), all = __builtin_amdgcn_readlane(incl, 63);
+                    if (left >= all) {
+                        left -= all;
+                        b += 64;
+                    } else {
+                        const int row = __builtin_popcountll(__builtin_amdgcn_ballot_w64(incl <= left));
+                        b += row;
+                        k = left - __builtin_amdgcn_readlane(incl - mine, row);
+                        break;
+                    }
+                }
+                b = __builtin_amdgcn_readfirstlane(b);
+                k = __builtin_amdgcn_readfirstlane(k);
+            }
+            TeamItem it;
+            it.b = b;
+            it.seq = PAIRS ? __builtin_amdgcn_readfirstlane(of_row(q_seq, b)) : b;
+            it.g = PAIRS ? __builtin_amdgcn_readfirstlane(of_row(q_head, b)) : head_team;
+            it.row = b * n_sel + si;
+            it.t0 = k * chunk_tokens;
+            it.len = __builtin_amdgcn_readfirstlane(of_row(q_len, b));
+            team_run<Policy, NW, PAIRS>(p, it, lone, spread, batch * n_sel, team_full, smem);
+            return;
+        }
+        q_first_head = head_spread;
         if (spread) {
 #pragma unroll
             for (int u = 0; u < QG; ++u) {
@@ -1006,7 +496,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
             }
         }
     }
-    const bool quick = MERGE && (spread || lone);
+    const bool quick = MERGE && spread;
 
     // ---- work enumeration.  Rows are handled in groups of 64 consecutive rows, one row a lane:
     // group u * (NW + 1) + wave belongs to round u of that wave, so a thread holds up to UR rows
@@ -1173,7 +663,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
     }
     const int totalF = quick ? 0 : firstF[batch];             // whole segments of all rows
     // segments (spread: chunks) of this launch
-    const int total = (spread ? totalA + totalB : lone ? batch : totalF + lens[2 * batch + 1]) * n_sel;
+    const int total = (spread ? totalA + totalB : totalF + lens[2 * batch + 1]) * n_sel;
     if (spread && wave == NW) {
         // tables for the writer wave's own use: rows, and chunks before each row
 #pragma unroll
@@ -1318,7 +808,6 @@ __global__ __launch_bounds__((NW + 1) * 64)
         const int w = min(segno, max(total - 1, 0));
         const int cg = PAIRS ? w : w / n_sel;
         const int si = PAIRS ? 0 : w - cg * n_sel;
-        if (lone) return row_segment(cg, si, 0, max(lone_len, 0), lone_len, lone_head, lone_seq);
         int b, L, j, n_tok;
         if (cg < totalF) {
             b = upper(firstF, cg);
@@ -1794,9 +1283,9 @@ __global__ __launch_bounds__((NW + 1) * 64)
         int64_t head_off;
         ItemHdr h;
         int ids;            // lane i: physical block of the chunk's i-th tile
-        int exists;
+        int exists, pad;
     };
-    static_assert(sizeof(ItemHdr) == 12 * sizeof(int) && sizeof(Slot) == 8 + sizeof(ItemHdr) + 8,
+    static_assert(sizeof(ItemHdr) == 11 * sizeof(int) && sizeof(Slot) == 8 + sizeof(ItemHdr) + 12,
                   "Slot has no padding");
     // chunk descriptor -> the wave's (uniform) bookkeeping, and the load of its block ids
     auto fill = [&](const ChunkDesc &d, Slot &s) {
@@ -1813,21 +1302,21 @@ __global__ __launch_bounds__((NW + 1) * 64)
         s.h.out_row = __builtin_amdgcn_readfirstlane(d.out_row);
         s.h.len = __builtin_amdgcn_readfirstlane(d.len);
         s.exists = (flags & kItemExists) != 0 ? 1 : 0;
-        s.h.nblk = s.exists ? (n_tok + kBlockTokens - 1) / kBlockTokens : 0;
-        s.h.rem = n_tok & (kBlockTokens - 1);
+        s.h.n_tok = s.exists ? n_tok : 0;
         s.head_off = PAIRS ? 0 : (int64_t)s.h.g * p.stride_head;   // pairs: single-head tiles
         const int32_t *bt =
             p.block_table + (int64_t)s.h.b * p.max_blocks_per_seq + s.h.t0 / kBlockTokens;
-        s.ids = bt[min(lane, max(s.h.nblk - 1, 0))];
+        s.pad = 0;
+        s.ids = bt[min(lane, max((s.h.n_tok + kBlockTokens - 1) / kBlockTokens - 1, 0))];
     };
     auto q_rows = [&](const Slot &s) {
         return p.q + ((int64_t)s.h.seq * p.n_q_heads + s.h.g * R) * D;
     };
-    auto issue = [&](Tile &t, int ids, int idx, int64_t head_off, bool valid) {
+    auto issue = [&](Tile &t, int ids, int idx, int64_t head_off, int n_tok) {     // tile idx of a chunk of n_tok tokens
         const int blk = __builtin_amdgcn_readlane(ids, idx & 63);
         const int64_t base = (int64_t)blk * p.stride_block + head_off;
-        Policy::issue(t, tile_rsrc(p.k_cache + base, kTileBytes, valid),
-                      tile_rsrc(p.v_cache + base, kTileBytes, valid), lane);
+        const int nbytes = min(kBlockTokens, max(0, n_tok - idx * kBlockTokens)) * kRowBytes;
+        Policy::issue(t, tile_rsrc(p.k_cache + base, nbytes), tile_rsrc(p.v_cache + base, nbytes), lane);
     };
     // bounded wait for a mailbox of this wave to be empty
     auto wait_empty = [&](Mail &mb) {
@@ -1903,14 +1392,23 @@ __global__ __launch_bounds__((NW + 1) * 64)
         nxt = cur;
         Policy::q_prefetch(q_pre, q_rows(cur), lane);
 #pragma unroll
-        for (int s = 0; s < RING; ++s) issue(ring[s], cur.ids, s, cur.head_off, s < cur.h.nblk);
+        for (int s = 0; s < RING; ++s) issue(ring[s], cur.ids, s, cur.head_off, cur.h.n_tok);
         int n = 0;
         for (;; ++n) {
             Policy::q_commit(q, q_pre, my_staging, lane);   // this chunk's query operand
 
-            typename Policy::State st;
+            // pieces of a chunk: sums of their own, folded in order (split calls: one piece)
+            constexpr int PT = SPLIT ? 1 << 20 : decode_piece_tokens(R) / kBlockTokens;      // tiles
+            static_assert(PT % RING == 0, "a piece is whole turns of the ring");
+            typename Policy::State st, tot;
             Policy::reset(st);
-            const int n_my = cur.h.nblk;
+            Policy::reset(tot);
+            auto next_piece = [&](int i) {                  // after the turn of tiles [i, i + RING)
+                if (SPLIT || (i + RING) % PT != 0) return;
+                Policy::fold(tot, st);
+                Policy::reset(st);
+            };
+            const int n_tok = cur.h.n_tok, n_my = (n_tok + kBlockTokens - 1) / kBlockTokens;
             const int lim = RING * max(1, (n_my + RING - 1) / RING);   // tiles, as whole ring turns
             // The scheduling fences keep "consume a slot, refill it at once" in program order;
             // without them the compiler batches the tiles' arithmetic ahead of the refills and
@@ -1918,10 +1416,10 @@ __global__ __launch_bounds__((NW + 1) * 64)
             auto steady_turn = [&](int i) {                 // whole tiles; refills stay in this chunk
 #pragma unroll
                 for (int s = 0; s < RING; ++s) {
-                    Policy::template update<false>(st, ring[s], q, p.scale_log2, lane, kBlockTokens,
+                    Policy::template update<kFullTile>(st, ring[s], q, p.scale_log2, lane, kBlockTokens,
                                                    my_staging);
                     __builtin_amdgcn_sched_barrier(0);
-                    issue(ring[s], cur.ids, i + RING + s, cur.head_off, i + RING + s < n_my);
+                    issue(ring[s], cur.ids, i + RING + s, cur.head_off, n_tok);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             };
@@ -1929,7 +1427,10 @@ __global__ __launch_bounds__((NW + 1) * 64)
             // the end of this one), so that little undone work is held back when the work runs
             // out.
             int i = 0;
-            for (; i + 4 * RING < lim; i += RING) steady_turn(i);
+            for (; i + 4 * RING < lim; i += RING) {
+                steady_turn(i);
+                next_piece(i);
+            }
             if (SPLIT && n == 0) {
                 // the wave's second segment is its own as well
                 const long long mine = (long long)(gridDim.x + blockIdx.x) * NW + wave;
@@ -1943,19 +1444,24 @@ __global__ __launch_bounds__((NW + 1) * 64)
                 fill(take_chunk(), nxt);
             }
             Policy::q_prefetch(q_pre, q_rows(nxt), lane);   // next chunk's query rows
-            for (; i + RING < lim; i += RING) steady_turn(i);
+            for (; i + RING < lim; i += RING) {
+                steady_turn(i);
+                next_piece(i);
+            }
             // last turn of this chunk (the only place a ragged block can be): its refills are the
             // first tiles of the next chunk
 #pragma unroll
             for (int s = 0; s < RING; ++s) {
                 if (i + s < n_my) {
-                    const int n_valid = (cur.h.rem != 0 && i + s == n_my - 1) ? cur.h.rem : kBlockTokens;
-                    Policy::template update<true>(st, ring[s], q, p.scale_log2, lane, n_valid, my_staging);
+                    Policy::template update<kMaybeRagged>(st, ring[s], q, p.scale_log2, lane,
+                                                  n_tok - (i + s) * kBlockTokens, my_staging);
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                issue(ring[s], nxt.ids, s, nxt.head_off, s < nxt.h.nblk);
+                issue(ring[s], nxt.ids, s, nxt.head_off, nxt.h.n_tok);
                 __builtin_amdgcn_sched_barrier(0);
             }
+            if (!SPLIT) Policy::fold(tot, st);
+            typename Policy::State &sum = SPLIT ? st : tot;
 
             Mail &mb = my_mail[n & 1];
             wait_empty(mb);
@@ -1963,7 +1469,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
                 // The wave's last chunk, and a result of its own: no load is in flight that a store
                 // could hold up, so the wave stores, counts and combines it itself instead of
                 // queueing behind the other waves' results at the writer.
-                if (cur.h.kind != kKindZero) Policy::finish(st, mb.o, mb.lse, lane);
+                if (cur.h.kind != kKindZero) Policy::finish(sum, mb.o, mb.lse, lane);
                 wave_lds_fence();
                 RowRegs<D, R> g;
                 g.load(mb.o, mb.lse, lane);
@@ -1977,7 +1483,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
                             p.arrivals + arrival_counter<R>(p, cur.h.dest, spread, batch * n_sel), 1u,
                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     mail_store(&mb.flag, kMailDone);
-                    combine_if_last<D, R>(p, __builtin_amdgcn_readfirstlane((int)old), cur.h.dest, cur.h.nseg,
+                    combine_if_last<D, R>(p, __builtin_amdgcn_readfirstlane((int)old), 1, cur.h.dest, cur.h.nseg,
                                           cur.h.out_row, cur.h.len, spread, batch * n_sel, lane);
                 } else {
                     store_result<D, R>(g, cur.h.kind, cur.h.dest, p, lane);
@@ -1986,7 +1492,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
                 return;
             }
             // hand the finished chunk to the writer
-            if (cur.h.kind != kKindZero) Policy::finish(st, mb.o, mb.lse, lane);
+            if (cur.h.kind != kKindZero) Policy::finish(sum, mb.o, mb.lse, lane);
             if (lane == 0) {
                 mb.kind = cur.h.kind;
                 mb.dest = cur.h.dest;

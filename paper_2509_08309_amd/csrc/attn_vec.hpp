@@ -50,12 +50,16 @@ struct TileRegs {
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ f16x2 as_f16x2(unsigned w) { return __builtin_bit_cast(f16x2, w); }
 
-// One tile (16 tokens) of K and V held in registers -> update of the running state.
+// One tile (16 tokens) of K and V held in registers -> update of the running state.  MASKED: only the
+// first n_valid tokens count; the rows past them were loaded as zeros (see tile_rsrc), so their weight
+// of zero meets no NaN.
 template <int D, int R, bool MASKED>
 __device__ __forceinline__ void vec_tile_update(VecState<D, R> &st, const TileRegs<D> &t,
                                                 const f16x2 (&qh)[R][4], float scale_log2,
                                                 int gid, int n_valid)
 {
+#pragma clang fp contract(off)
+    // (every fused operation is written as one: two copies of this code must produce the same bits)
     constexpr int LPR = D / 8;        // lanes per token row
     constexpr int TPI = 64 / LPR;     // tokens per 1 KB slice
     constexpr int NI = 16 / TPI;      // slices per tile
@@ -87,14 +91,13 @@ __device__ __forceinline__ void vec_tile_update(VecState<D, R> &st, const TileRe
             p[i][r] = fast_exp2(s[i][r] - mx);
             ps += p[i][r];
         }
-        st.l[r] = st.l[r] * alpha + ps;
+        st.l[r] = __builtin_fmaf(st.l[r], alpha, ps);
 #pragma unroll
         for (int x = 0; x < 8; ++x) st.o[r][x] *= alpha;
     }
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-        u32x4 vv = t.v[i];
-        if (MASKED && !(i * TPI + gid < n_valid)) vv = u32x4{0u, 0u, 0u, 0u};
+        const u32x4 vv = t.v[i];
 #pragma unroll
         for (int x = 0; x < 8; ++x) {
             const float vf = (float)as_f16x2(vv[x / 2])[x % 2];
@@ -116,28 +119,45 @@ __device__ __forceinline__ void vec_tile_update_any(VecState<D, R> &st, const Ti
         vec_tile_update<D, R, false>(st, t, qh, scale_log2, gid, kBlockTokens);
 }
 
-// Merge the 64/(D/8) lane groups of a wave (xor butterfly over the group index).
+// State of one piece into the state of the pieces before it, lane by lane.
+template <int D, int R>
+__device__ __forceinline__ void vec_fold(VecState<D, R> &tot, const VecState<D, R> &st)
+{
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+#pragma clang fp contract(off)
+        const float M = fmaxf(tot.m[r], st.m[r]);
+        const float a = fast_exp2(tot.m[r] - M), b = fast_exp2(st.m[r] - M);
+        tot.m[r] = M;
+        tot.l[r] = __builtin_fmaf(tot.l[r], a, st.l[r] * b);
+#pragma unroll
+        for (int x = 0; x < 8; ++x) tot.o[r][x] = __builtin_fmaf(tot.o[r][x], a, st.o[r][x] * b);
+    }
+}
+
+// Merge the 64/(D/8) lane groups of a wave, neighbours first; the first group ends up with the sum.
 template <int D, int R>
 __device__ __forceinline__ void vec_wave_merge(VecState<D, R> &st)
 {
-#pragma unroll
-    for (int mask = D / 8; mask < 64; mask <<= 1) {
+#pragma clang fp contract(off)
+    auto merge = [&](auto pair) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const float m2 = __shfl_xor(st.m[r], mask, 64);
-            const float l2 = __shfl_xor(st.l[r], mask, 64);
-            const float M = fmaxf(st.m[r], m2);
-            const float a = fast_exp2(st.m[r] - M);
-            const float a2 = fast_exp2(m2 - M);
+            const LanePair m = pair(st.m[r]), l = pair(st.l[r]);
+            const float M = fmaxf(m.lo, m.hi);
+            const float a = fast_exp2(m.lo - M), b = fast_exp2(m.hi - M);
             st.m[r] = M;
-            st.l[r] = st.l[r] * a + l2 * a2;
+            st.l[r] = __builtin_fmaf(l.lo, a, l.hi * b);
 #pragma unroll
             for (int x = 0; x < 8; ++x) {
-                const float o2 = __shfl_xor(st.o[r][x], mask, 64);
-                st.o[r][x] = st.o[r][x] * a + o2 * a2;
+                const LanePair o = pair(st.o[r][x]);
+                st.o[r][x] = __builtin_fmaf(o.lo, a, o.hi * b);
             }
         }
-    }
+    };
+    if constexpr (D == 64) merge([](float x) { return LanePair{x, dpp_mov<0x128>(x)}; });   // row_ror 8
+    merge([](float x) { return pair_xor16(x); });
+    merge([](float x) { return pair_xor32(x); });
 }
 
 // ---------------------------------------------------------------------------------------
@@ -160,6 +180,9 @@ struct VecPolicy {
     // 40.8, 440 rows of 1250 tokens 57.6 and 55.0.  Split calls have no segments to even out and gain as
     // well (320 long rows 546 and 537).
     static constexpr int ring(bool deep) { return (deep ? 2 : 1) * (D_ == 64 ? 2 : 1); }
+    // of a team's wave, whose piece is four tiles: a second turn costs less than twice the code (4: 32 rows of 600
+    // tokens 11.0 -> 11.5, 16 of 2000 10.7 -> 11.2)
+    static constexpr int kTeamRing = 2;
     using Tile = TileRegs<D>;
     using State = VecState<D, R>;
     struct Query {
@@ -195,21 +218,54 @@ struct VecPolicy {
     __device__ static __forceinline__ void reset(State &st) { st.reset(); }
     // MAYBE_RAGGED: the tile may be the ragged last block of a sequence (n_valid < 16); a
     // separate masked copy of the arithmetic keeps whole tiles free of compares and selects
-    template <bool MAYBE_RAGGED>
+    // kOneCopy: the masked copy for all tiles, where fetching the code costs more than the selects
+    template <int MAYBE_RAGGED>
     __device__ static __forceinline__ void update(State &st, const Tile &t, const Query &q,
                                                   float scale_log2, int lane, int n_valid,
                                                   unsigned char *)
     {
-        if (MAYBE_RAGGED)
+        if (MAYBE_RAGGED == kOneCopy)
+            vec_tile_update<D, R, true>(st, t, q.h, scale_log2, lane / (D / 8), n_valid);
+        else if (MAYBE_RAGGED)
             vec_tile_update_any<D, R>(st, t, q.h, scale_log2, lane / (D / 8), n_valid);
         else
             vec_tile_update<D, R, false>(st, t, q.h, scale_log2, lane / (D / 8), kBlockTokens);
+    }
+    __device__ static __forceinline__ void fold(State &tot, const State &st) { vec_fold<D, R>(tot, st); }
+    // state <-> LDS, sixteen bytes a lane at a time
+    static_assert(R <= 2, "maximum and sum of all rows in one vector");
+    static constexpr int kStateVecs = 2 * R + 1;
+    __device__ static __forceinline__ void deposit(const State &st, f32x4 *to, int lane)
+    {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            to[2 * r * 64 + lane] = f32x4{st.o[r][0], st.o[r][1], st.o[r][2], st.o[r][3]};
+            to[(2 * r + 1) * 64 + lane] = f32x4{st.o[r][4], st.o[r][5], st.o[r][6], st.o[r][7]};
+        }
+        to[2 * R * 64 + lane] = f32x4{st.m[0], st.l[0], st.m[R - 1], st.l[R - 1]};
+    }
+    __device__ static __forceinline__ void collect(State &st, const f32x4 *from, int lane)
+    {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const f32x4 lo = from[2 * r * 64 + lane], hi = from[(2 * r + 1) * 64 + lane];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                st.o[r][x] = lo[x];
+                st.o[r][4 + x] = hi[x];
+            }
+        }
+        const f32x4 ml = from[2 * R * 64 + lane];
+        st.m[0] = ml[0];
+        st.l[0] = ml[1];
+        st.m[R - 1] = ml[2 * (R - 1)];
+        st.l[R - 1] = ml[2 * (R - 1) + 1];
     }
     // normalised rows and their base-2 log-sum-exp -> LDS (the wave's mailbox)
     __device__ static __forceinline__ void finish(State &st, float (&o)[R][D], float (&lse)[R],
                                                   int lane)
     {
-        vec_wave_merge<D, R>(st);                // every lane group now holds the item's totals
+        vec_wave_merge<D, R>(st);                // the first lane group now holds the totals
         const int gid = lane / (D / 8), sub = lane % (D / 8);
         if (gid == 0) {
 #pragma unroll

@@ -161,7 +161,8 @@ static int launch_persistent(AttnParams p, int batch, hipStream_t st)
 {
     constexpr int NW = kVecWaves;
     auto kernel = attn_chunk_persistent_kernel<Policy, NW, PAIRS, VARIANT>;
-    const size_t lds = persist_lds_bytes<Policy, NW>(batch, p.n_sel, PAIRS);
+    size_t lds = persist_lds_bytes<Policy, NW>(batch, p.n_sel, PAIRS);
+    if (VARIANT == kVariantMerge && p.mode == kModeSpread) lds = std::max(lds, sizeof(TeamLds<Policy, NW>));
     int occ = resident_per_cu(kernel, (NW + 1) * 64, lds);
     if (occ < 1) return HETIS_ERR_LAUNCH;
     const int cus = device_cu_count();
