@@ -15,6 +15,7 @@ from typing import Optional
 HERE = os.path.dirname(os.path.abspath(__file__))
 # HETIS_ATTN_LIB (optional) points at another build of the same library, e.g. a tuning variant.
 LIB_PATH = os.environ.get("HETIS_ATTN_LIB") or os.path.join(HERE, "libhetis_attn.so")
+MARSHAL_PATH = os.path.join(HERE, "_marshal.so")
 
 HETIS_OK = 0
 HETIS_ERR_NULL = -1
@@ -64,13 +65,13 @@ def load(build_if_missing: bool = False):
     global _lib
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
+    if not (os.path.exists(LIB_PATH) and os.path.exists(MARSHAL_PATH)):
         if build_if_missing:
             from .build import build
             build()
         else:
             raise FileNotFoundError(
-                f"{LIB_PATH} is not built; run `python -m paper_2509_08309_amd.build` "
+                f"{LIB_PATH} or {MARSHAL_PATH} is not built; run `python -m paper_2509_08309_amd.build` "
                 "(the HIP library is required, there is no fallback)")
     lib = C.CDLL(LIB_PATH)
     vp, i32, i64, f32 = C.c_void_p, C.c_int32, C.c_int64, C.c_float
@@ -152,8 +153,25 @@ def load(build_if_missing: bool = False):
     lib.hetis_kv_copy_tiles.argtypes = [pool, vp, vp, pool, vp, vp, vp, vp, i32, vp, vp, i32, vp]
     lib.hetis_kv_profile_events.restype = C.c_int
     lib.hetis_kv_profile_events.argtypes = [vp, vp]
+    lib.call = _Calls(lib)
     _lib = lib
     return lib
+
+
+class _Calls:
+    """The calls of a decode step (launches, and nothing that waits) with their arguments as the caller has
+    them: tensors, ctypes structures, numbers.  Converted natively (csrc/marshal.cpp)."""
+
+    def __init__(self, lib):
+        from . import _marshal
+        _marshal.structs(hetis_attn_shape, hetis_kv_pool)
+        for name in ("hetis_attn_decode", "hetis_attn_decode_ws", "hetis_attn_decode_step",
+                     "hetis_attn_decode_step_ws", "hetis_attn_decode_pairs", "hetis_attn_decode_pairs_ws",
+                     "hetis_attn_decode_pairs_step", "hetis_attn_decode_pairs_step_ws",
+                     "hetis_attn_decode_split", "hetis_attn_decode_split_ws", "hetis_attn_merge",
+                     "hetis_kv_append", "hetis_kv_append_pairs", "hetis_kv_store", "hetis_kv_fetch",
+                     "hetis_kv_copy_tiles"):
+            setattr(self, name, _marshal.bind(name, C.cast(getattr(lib, name), C.c_void_p).value))
 
 
 def _ptr(t) -> Optional[int]:
@@ -167,9 +185,16 @@ def _ptr(t) -> Optional[int]:
     return t.ctypes.data            # numpy array (host pointer)
 
 
+_torch = None          # torch, once a call has needed it (an import statement costs 0.1 us a call)
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        import torch
+        global _torch
+        if _torch is None:
+            import torch
+            _torch = torch
+        torch = _torch
         # The current stream's handle without a Stream object around it: building one is 3.5 us, of
         # 9 us that a call takes on the host, and the smallest launches wait for the host.  The names
         # are torch's own business: without them, the documented way.
@@ -200,35 +225,28 @@ def hetis_attn_status_string(status: int) -> str:
 
 def hetis_attn_decode(shape, q, k_cache, v_cache, block_table, seq_lens, head_ids, n_sel_heads,
                       scale, out, stream=None) -> int:
-    return load().hetis_attn_decode(C.byref(shape), _ptr(q), _ptr(k_cache), _ptr(v_cache),
-                                    _ptr(block_table), _ptr(seq_lens), _ptr(head_ids),
-                                    int(n_sel_heads), float(scale), _ptr(out), _stream(stream))
+    return (_lib or load()).call.hetis_attn_decode(shape, q, k_cache, v_cache, block_table,
+        seq_lens, head_ids, n_sel_heads, scale, out, _stream(stream))
 
 
 def hetis_attn_decode_ws(shape, q, k_cache, v_cache, block_table, seq_lens, head_ids, n_sel_heads,
                          scale, out, workspace, workspace_bytes, stream=None) -> int:
-    return load().hetis_attn_decode_ws(C.byref(shape), _ptr(q), _ptr(k_cache), _ptr(v_cache),
-                                       _ptr(block_table), _ptr(seq_lens), _ptr(head_ids),
-                                       int(n_sel_heads), float(scale), _ptr(out), _ptr(workspace),
-                                       int(workspace_bytes), _stream(stream))
+    return (_lib or load()).call.hetis_attn_decode_ws(shape, q, k_cache, v_cache, block_table,
+        seq_lens, head_ids, n_sel_heads, scale, out, workspace, workspace_bytes, _stream(stream))
 
 
 def hetis_attn_decode_step(shape, q, k_new, v_new, k_cache, v_cache, block_table, seq_lens, head_ids,
                            n_sel_heads, scale, out, stream=None) -> int:
-    return load().hetis_attn_decode_step(C.byref(shape), _ptr(q), _ptr(k_new), _ptr(v_new),
-                                         _ptr(k_cache), _ptr(v_cache), _ptr(block_table),
-                                         _ptr(seq_lens), _ptr(head_ids), int(n_sel_heads),
-                                         float(scale), _ptr(out), _stream(stream))
+    return (_lib or load()).call.hetis_attn_decode_step(shape, q, k_new, v_new, k_cache, v_cache,
+        block_table, seq_lens, head_ids, n_sel_heads, scale, out, _stream(stream))
 
 
 def hetis_attn_decode_step_ws(shape, q, k_new, v_new, k_cache, v_cache, block_table, seq_lens,
                               head_ids, n_sel_heads, scale, out, workspace, workspace_bytes,
                               stream=None) -> int:
-    return load().hetis_attn_decode_step_ws(C.byref(shape), _ptr(q), _ptr(k_new), _ptr(v_new),
-                                            _ptr(k_cache), _ptr(v_cache), _ptr(block_table),
-                                            _ptr(seq_lens), _ptr(head_ids), int(n_sel_heads),
-                                            float(scale), _ptr(out), _ptr(workspace),
-                                            int(workspace_bytes), _stream(stream))
+    return (_lib or load()).call.hetis_attn_decode_step_ws(shape, q, k_new, v_new, k_cache, v_cache,
+        block_table, seq_lens, head_ids, n_sel_heads, scale, out, workspace, workspace_bytes,
+        _stream(stream))
 
 
 def hetis_attn_decode_static(shape, q, k_cache, v_cache, block_table, seq_lens, head_ids,
@@ -288,29 +306,23 @@ def hetis_attn_split_workspace_bytes(shape, n_sel_heads, max_seq_len, chunk_toke
 def hetis_attn_decode_split(shape, q, k_cache, v_cache, block_table, seq_lens, head_ids,
                             n_sel_heads, scale, chunk_tokens, max_seq_len, o_partial,
                             lse_partial, stream=None) -> int:
-    return load().hetis_attn_decode_split(C.byref(shape), _ptr(q), _ptr(k_cache), _ptr(v_cache),
-                                          _ptr(block_table), _ptr(seq_lens), _ptr(head_ids),
-                                          int(n_sel_heads), float(scale), int(chunk_tokens),
-                                          int(max_seq_len), _ptr(o_partial), _ptr(lse_partial),
-                                          _stream(stream))
+    return (_lib or load()).call.hetis_attn_decode_split(shape, q, k_cache, v_cache, block_table,
+        seq_lens, head_ids, n_sel_heads, scale, chunk_tokens, max_seq_len, o_partial, lse_partial,
+        _stream(stream))
 
 
 def hetis_attn_decode_split_ws(shape, q, k_cache, v_cache, block_table, seq_lens, head_ids,
                                n_sel_heads, scale, chunk_tokens, max_seq_len, o_partial,
                                lse_partial, control, stream=None) -> int:
-    return load().hetis_attn_decode_split_ws(C.byref(shape), _ptr(q), _ptr(k_cache), _ptr(v_cache),
-                                             _ptr(block_table), _ptr(seq_lens), _ptr(head_ids),
-                                             int(n_sel_heads), float(scale), int(chunk_tokens),
-                                             int(max_seq_len), _ptr(o_partial), _ptr(lse_partial),
-                                             _ptr(control), _stream(stream))
+    return (_lib or load()).call.hetis_attn_decode_split_ws(shape, q, k_cache, v_cache, block_table,
+        seq_lens, head_ids, n_sel_heads, scale, chunk_tokens, max_seq_len, o_partial, lse_partial,
+        control, _stream(stream))
 
 
 def hetis_attn_merge(shape, o_partial, lse_partial, seq_lens, head_ids, n_sel_heads,
                      chunk_tokens, max_seq_len, out, stream=None) -> int:
-    return load().hetis_attn_merge(C.byref(shape), _ptr(o_partial), _ptr(lse_partial),
-                                   _ptr(seq_lens), _ptr(head_ids), int(n_sel_heads),
-                                   int(chunk_tokens), int(max_seq_len), _ptr(out),
-                                   _stream(stream))
+    return (_lib or load()).call.hetis_attn_merge(shape, o_partial, lse_partial, seq_lens, head_ids,
+        n_sel_heads, chunk_tokens, max_seq_len, out, _stream(stream))
 
 
 def hetis_attn_profile_events(begin, end) -> int:
@@ -327,39 +339,30 @@ def hetis_attn_validate(shape, block_table, seq_lens, head_ids, n_sel_heads, num
 
 def hetis_attn_decode_pairs(shape, q, k_tiles, v_tiles, block_table, seq_lens, pair_seq, pair_head,
                             n_pairs, scale, out, stream=None) -> int:
-    return load().hetis_attn_decode_pairs(C.byref(shape), _ptr(q), _ptr(k_tiles), _ptr(v_tiles),
-                                          _ptr(block_table), _ptr(seq_lens), _ptr(pair_seq),
-                                          _ptr(pair_head), int(n_pairs), float(scale), _ptr(out),
-                                          _stream(stream))
+    return (_lib or load()).call.hetis_attn_decode_pairs(shape, q, k_tiles, v_tiles, block_table,
+        seq_lens, pair_seq, pair_head, n_pairs, scale, out, _stream(stream))
 
 
 def hetis_attn_decode_pairs_ws(shape, q, k_tiles, v_tiles, block_table, seq_lens, pair_seq,
                                pair_head, n_pairs, scale, out, workspace, workspace_bytes,
                                stream=None) -> int:
-    return load().hetis_attn_decode_pairs_ws(C.byref(shape), _ptr(q), _ptr(k_tiles), _ptr(v_tiles),
-                                             _ptr(block_table), _ptr(seq_lens), _ptr(pair_seq),
-                                             _ptr(pair_head), int(n_pairs), float(scale),
-                                             _ptr(out), _ptr(workspace), int(workspace_bytes),
-                                             _stream(stream))
+    return (_lib or load()).call.hetis_attn_decode_pairs_ws(shape, q, k_tiles, v_tiles, block_table,
+        seq_lens, pair_seq, pair_head, n_pairs, scale, out, workspace, workspace_bytes,
+        _stream(stream))
 
 
 def hetis_attn_decode_pairs_step(shape, q, k_new, v_new, k_tiles, v_tiles, block_table, seq_lens,
                                  pair_seq, pair_head, n_pairs, scale, out, stream=None) -> int:
-    return load().hetis_attn_decode_pairs_step(C.byref(shape), _ptr(q), _ptr(k_new), _ptr(v_new),
-                                               _ptr(k_tiles), _ptr(v_tiles), _ptr(block_table),
-                                               _ptr(seq_lens), _ptr(pair_seq), _ptr(pair_head),
-                                               int(n_pairs), float(scale), _ptr(out), _stream(stream))
+    return (_lib or load()).call.hetis_attn_decode_pairs_step(shape, q, k_new, v_new, k_tiles,
+        v_tiles, block_table, seq_lens, pair_seq, pair_head, n_pairs, scale, out, _stream(stream))
 
 
 def hetis_attn_decode_pairs_step_ws(shape, q, k_new, v_new, k_tiles, v_tiles, block_table,
                                     seq_lens, pair_seq, pair_head, n_pairs, scale, out, workspace,
                                     workspace_bytes, stream=None) -> int:
-    return load().hetis_attn_decode_pairs_step_ws(C.byref(shape), _ptr(q), _ptr(k_new), _ptr(v_new),
-                                                  _ptr(k_tiles), _ptr(v_tiles), _ptr(block_table),
-                                                  _ptr(seq_lens), _ptr(pair_seq), _ptr(pair_head),
-                                                  int(n_pairs), float(scale), _ptr(out),
-                                                  _ptr(workspace), int(workspace_bytes),
-                                                  _stream(stream))
+    return (_lib or load()).call.hetis_attn_decode_pairs_step_ws(shape, q, k_new, v_new, k_tiles,
+        v_tiles, block_table, seq_lens, pair_seq, pair_head, n_pairs, scale, out, workspace,
+        workspace_bytes, _stream(stream))
 
 
 def hetis_attn_validate_pairs(shape, block_table, seq_lens, pair_seq, pair_head, n_pairs,
@@ -377,42 +380,32 @@ def make_pool(n_kv_heads, head_dim, num_blocks, block_size=16, kv_stride_block=0
 
 def hetis_kv_append(shape, k_new, v_new, block_table, seq_lens, head_ids, n_sel_heads,
                     num_blocks, k_cache, v_cache, stream=None) -> int:
-    return load().hetis_kv_append(C.byref(shape), _ptr(k_new), _ptr(v_new), _ptr(block_table),
-                                  _ptr(seq_lens), _ptr(head_ids), int(n_sel_heads),
-                                  int(num_blocks), _ptr(k_cache), _ptr(v_cache), _stream(stream))
+    return (_lib or load()).call.hetis_kv_append(shape, k_new, v_new, block_table, seq_lens,
+        head_ids, n_sel_heads, num_blocks, k_cache, v_cache, _stream(stream))
 
 
 def hetis_kv_append_pairs(shape, k_new, v_new, block_table, seq_lens, pair_seq, pair_head, n_pairs,
                           num_tiles, k_tiles, v_tiles, stream=None) -> int:
-    return load().hetis_kv_append_pairs(C.byref(shape), _ptr(k_new), _ptr(v_new), _ptr(block_table),
-                                        _ptr(seq_lens), _ptr(pair_seq), _ptr(pair_head),
-                                        int(n_pairs), int(num_tiles), _ptr(k_tiles), _ptr(v_tiles),
-                                        _stream(stream))
+    return (_lib or load()).call.hetis_kv_append_pairs(shape, k_new, v_new, block_table, seq_lens,
+        pair_seq, pair_head, n_pairs, num_tiles, k_tiles, v_tiles, _stream(stream))
 
 
 def hetis_kv_store(shape, k_new, v_new, token_seq, token_pos, n_tokens, block_table, head_ids,
                    n_sel_heads, num_blocks, k_cache, v_cache, stream=None) -> int:
-    return load().hetis_kv_store(C.byref(shape), _ptr(k_new), _ptr(v_new), _ptr(token_seq),
-                                 _ptr(token_pos), int(n_tokens), _ptr(block_table),
-                                 _ptr(head_ids), int(n_sel_heads), int(num_blocks),
-                                 _ptr(k_cache), _ptr(v_cache), _stream(stream))
+    return (_lib or load()).call.hetis_kv_store(shape, k_new, v_new, token_seq, token_pos, n_tokens,
+        block_table, head_ids, n_sel_heads, num_blocks, k_cache, v_cache, _stream(stream))
 
 
 def hetis_kv_fetch(shape, k_cache, v_cache, token_seq, token_pos, n_tokens, block_table,
                    head_ids, n_sel_heads, num_blocks, k_out, v_out, stream=None) -> int:
-    return load().hetis_kv_fetch(C.byref(shape), _ptr(k_cache), _ptr(v_cache), _ptr(token_seq),
-                                 _ptr(token_pos), int(n_tokens), _ptr(block_table),
-                                 _ptr(head_ids), int(n_sel_heads), int(num_blocks), _ptr(k_out),
-                                 _ptr(v_out), _stream(stream))
+    return (_lib or load()).call.hetis_kv_fetch(shape, k_cache, v_cache, token_seq, token_pos,
+        n_tokens, block_table, head_ids, n_sel_heads, num_blocks, k_out, v_out, _stream(stream))
 
 
 def hetis_kv_copy_tiles(src_pool, src_k, src_v, dst_pool, dst_k, dst_v, src_blocks, dst_blocks,
                         n_pairs, src_heads, dst_heads, n_sel_heads, stream=None) -> int:
-    return load().hetis_kv_copy_tiles(
-        None if src_pool is None else C.byref(src_pool), _ptr(src_k), _ptr(src_v),
-        None if dst_pool is None else C.byref(dst_pool), _ptr(dst_k), _ptr(dst_v),
-        _ptr(src_blocks), _ptr(dst_blocks), int(n_pairs), _ptr(src_heads), _ptr(dst_heads),
-        int(n_sel_heads), _stream(stream))
+    return (_lib or load()).call.hetis_kv_copy_tiles(src_pool, src_k, src_v, dst_pool, dst_k, dst_v,
+        src_blocks, dst_blocks, n_pairs, src_heads, dst_heads, n_sel_heads, _stream(stream))
 
 
 def hetis_kv_profile_events(begin, end) -> int:
