@@ -182,7 +182,9 @@ __device__ __forceinline__ void store_partial_coherent(const RowRegs<D, R> &g, i
 // order with every use, so a loop that loads and uses one result at a time pays a memory round
 // trip for each: the wave that ends a launch then spends tens of microseconds on a row.
 // With four or eight rows a result (kPartVectors) a lane loads vectors of four words, as many as there
-// are registers for (eight with 8 x 128 words; scratch memory otherwise), and looks its row's weight up;
+// are registers for (sixteen with 8 x 128 words, four results; eight results go to scratch memory), and looks
+// its row's weight up; four results together instead of two: 64 rows of 500 to 3000 tokens 19.4 -> 18.7 us, 8 of
+// 500 to 1500 14.6 -> 14.0, the step of 144 pairs 41.6 -> 40.9, 300 rows of 100 to 600 21.2 -> 21.5;
 // with one or two rows it loads words, the same dims of every row, and weights are the same in all lanes.
 // A step of 144 pairs of 8-head groups: words 44.9 us, vectors 43.4; 16 chats x 13 heads (r = 1) 27.5 and 28.1.
 // r = 4: vectors too, but half as many: more only fills registers, which are the streaming loop's as well
@@ -193,7 +195,7 @@ template <int R>
 constexpr bool kPartVectors = R >= 4;
 template <int D, int R>
 constexpr int kPartBatch =                                         // at most 64 / R
-    !kPartVectors<R> ? 16 : (R == 4 ? 8 : R * D > 512 ? 8 : 16) / RowRegs<D, R>::K;
+    !kPartVectors<R> ? 16 : (R == 4 ? 8 : 16) / RowRegs<D, R>::K;
 
 // Partial results in slots slot_of(0), slot_of(1), ... of the partial buffers -> x; their
 // log-sum-exps come back with lane u * R + r holding that of result u, row r.
