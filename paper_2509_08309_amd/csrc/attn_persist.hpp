@@ -335,11 +335,11 @@ __global__ __launch_bounds__((NW + 1) * 64)
     //    w as a team.  A wave's chain of tiles is a quarter of a chunk's, and the chunk's pieces meet in LDS.
     //    With more items than workgroups the waves are busy with a chunk each, and a team has several
     //    items, one after the other, and its results pass through one wave: 16 rows of 2000 tokens (r =
-    //    1, 128 items) 13.5 as chunks -> 10.4 us as teams, 64 rows of 500 to 3000 (r = 8, 220) 25.4 -> 19.4, 64
+    //    1, 128 items) 13.5 as chunks -> 10.4 us as teams, 64 rows of 500 to 3000 (r = 8, 220) 25.4 -> 18.7, 64
     //    of 300 to 1200 (r = 4, 64 dims) 16.6 -> 12.3; but 80 pairs of 850 (305 items) 15.3 -> 16.4, 64 rows of
     //    500 to 1500 (290) 14.9 -> 16.4, 300 of 300 to 1200 (980) 26.9 -> 32.6.  Rows whole: 230 of 600
     //    tokens 18.3 -> 15.9, 255 of 4096 88.3 -> 86.1, 240 of 1000 of 64 dims 20.1 -> 15.7, 256 of 300 to 900 (r =
-    //    8, 64 dims) 17.3 -> 13.8, 16 of 17 to 255 of 64 dims 9.4 -> 6.9; 250 of 1000 to 4000 (r = 8) 68.0 -> 68.6.
+    //    8, 64 dims) 17.3 -> 13.8, 16 of 17 to 255 of 64 dims 9.4 -> 5.5; 250 of 1000 to 4000 (r = 8) 68.0 -> 68.6.
     //  - spread: single chunks (see the top), when some row has more than one full chunk and
     //    spread_pays() says so.
     //  - otherwise whole segments through the tables, as in every other launch.
