@@ -13,6 +13,7 @@
 
 #include "attn_mfma.hpp"
 #include "attn_vec.hpp"
+#include "attn_rows.hpp"
 
 namespace hetis {
 
@@ -188,8 +189,16 @@ static int launch_persistent(AttnParams p, int batch, hipStream_t st)
 template <int D, int R>
 static int launch_chunk(const AttnParams &p0, int rows, hipStream_t st)
 {
+    using Policy = std::conditional_t<(R >= 4), MfmaPolicy<D, R>, VecPolicy<D, R>>;
     const bool pairs = p0.pair_seq != nullptr;
     const int n_sel = pairs ? 1 : p0.n_sel;
+    const int64_t all = (int64_t)rows * n_sel;          // one wave each: below 2^32 threads
+    if (p0.mode != kModeSplit && all < 1 << 26 &&
+        row_a_wave<D, R>(all, device_cu_count(), (int64_t)p0.max_blocks_per_seq * kBlockTokens)) {
+        auto kernel = pairs ? attn_wave_rows_kernel<Policy, true> : attn_wave_rows_kernel<Policy, false>;
+        launch_timed(kernel, dim3((unsigned)all), dim3(64), 0, st, p0);
+        return HETIS_OK;
+    }
     // the arrival counters are indexed by (row of the slice, head): a slice has no more
     // (row, head) combinations than there are counters
     const int slice = p0.arrivals ? std::min<int64_t>(kMaxPersistBatch, (int64_t)kArrivalSlots / n_sel)
@@ -223,7 +232,6 @@ static int launch_chunk(const AttnParams &p0, int rows, hipStream_t st)
                             : p.mode != kModeSplit && (int64_t)n * n_sel <= few_rows ? kVariantFew
                                                                                      : kVariantPlain;
         if (p.mode == kModeSplit && !holds_split(variant, pairs)) return HETIS_ERR_UNSUPPORTED;
-        using Policy = std::conditional_t<(R >= 4), MfmaPolicy<D, R>, VecPolicy<D, R>>;
         int rc;
         if (pairs)
             rc = variant == kVariantMerge ? launch_persistent<Policy, true, kVariantMerge>(p, n, st)
