@@ -1,4 +1,4 @@
-// Launches of more rows than workgroups, none of them long: a wave a row, a workgroup a wave.
+// Launches of short rows: a wave a row, a workgroup a wave.
 //
 // What the persistent kernel does ahead of the first tile (lengths of all rows, tables, tickets, the pool) and
 // behind the last (mailboxes, the writer wave's folds) pays where a row keeps a workgroup busy.  A row of a few tiles is
@@ -19,7 +19,9 @@ namespace hetis {
 // Whether a launch of `rows` rows on `cus` compute units, of up to `tokens` tokens each (what a row of the block
 // table holds), goes this way.  The persistent kernel is the better one with rows of several hundred tokens, whose
 // order it chooses (longest first) and whose chunks it spreads over the waves of a workgroup:
-//  - no more rows than workgroups: teams (256 of 200 tokens 8.0 us).  Fewer than kMaxQuickRows: a full chunk, beyond which
+//  - no more rows than workgroups: a piece, which leaves the waves of a team nothing to share and saves the wait for
+//    the fifth one (16 rows of 16 to 64 tokens, r = 1 5.5 -> 5.1 us, r = 2 6.3 -> 5.1; 192 of 40 to 128, r = 8 7.5 -> 6.7;
+//    rows of two pieces, r = 1 5.4 -> 5.8, r = 2 6.5 -> 8.1).  Fewer than kMaxQuickRows: a full chunk, beyond which
 //    single chunks may be handed out (496 rows of 150 to 512, r = 8 25.8 -> 21.4 us, 272 27.8 -> 19.2).
 //  - up to 8 rows a compute unit: 512 tokens (r = 1, 520 rows of 100 to 512 25.6 -> 21.5 us, 1280 of 384 to 512 54.9 ->
 //    48.5; r = 8, 512 of 384 to 512 35.6 -> 23.3; of up to 768 tokens 30.4 -> 31.3, 28.9 -> 30.8 with r = 1, 22.5 ->
@@ -30,7 +32,7 @@ namespace hetis {
 template <int D, int R>
 constexpr bool row_a_wave(int64_t rows, int64_t cus, int64_t tokens)
 {
-    if (rows <= cus) return false;
+    if (rows <= cus) return tokens <= decode_piece_tokens(R);
     if (rows < kMaxQuickRows) return tokens <= (R < 4 ? 256 : 512);
     constexpr bool slow = R == 2 || (R == 8 && D == 64);
     return tokens <= (rows > 8 * cus || (slow && rows < 4 * cus) ? 384 : 512);
