@@ -93,7 +93,9 @@ struct AttnParams {
 //                  chunks of one segment run on many workgroups; chunk results then go through
 //                  the partial buffers and the wave that stores a segment's last one folds them
 //                  in the order and with the operations of kModeSegments.  It may as well give
-//                  every workgroup one whole row, or fall back to kModeSegments.
+//                  every workgroup one window or one whole row, shared by its waves (attn_team.hpp),
+//                  or fall back to kModeSegments.
+// (Launches of short rows take neither way: a wave a row, attn_rows.hpp; only kModeSplit keeps them out.)
 enum : int { kModeSegments = 0, kModeSplit = 1, kModeSpread = 2 };
 
 // Control words at the start of a call's workspace.  All are zero between launches: the last
