@@ -185,18 +185,19 @@ struct MfmaPolicy {
         }
     }
 
-    // state of one piece into the state of the pieces before it, lane by lane
+    // state of one piece into the state of the pieces before it, lane by lane (sums that are scaled in place:
+    // with the products the other way round every register took a move as well)
     __device__ static __forceinline__ void fold(State &tot, const State &st)
     {
 #pragma clang fp contract(off)
         const float M = fmaxf(tot.m, st.m);
         const float a = fast_exp2(tot.m - M), b = fast_exp2(st.m - M);
         tot.m = M;
-        tot.l = __builtin_fmaf(tot.l, a, st.l * b);
+        tot.l = __builtin_fmaf(st.l, b, tot.l * a);
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) tot.acc[mb][e] = __builtin_fmaf(tot.acc[mb][e], a, st.acc[mb][e] * b);
+            for (int e = 0; e < 4; ++e) tot.acc[mb][e] = __builtin_fmaf(st.acc[mb][e], b, tot.acc[mb][e] * a);
     }
     // state <-> LDS, sixteen bytes a lane at a time
     static constexpr int kStateVecs = MB + 1;

@@ -119,7 +119,8 @@ __device__ __forceinline__ void vec_tile_update_any(VecState<D, R> &st, const Ti
         vec_tile_update<D, R, false>(st, t, qh, scale_log2, gid, kBlockTokens);
 }
 
-// State of one piece into the state of the pieces before it, lane by lane.
+// State of one piece into the state of the pieces before it, lane by lane (sums that are scaled in place: with
+// the products the other way round every register took a move as well).
 template <int D, int R>
 __device__ __forceinline__ void vec_fold(VecState<D, R> &tot, const VecState<D, R> &st)
 {
@@ -129,9 +130,9 @@ __device__ __forceinline__ void vec_fold(VecState<D, R> &tot, const VecState<D, 
         const float M = fmaxf(tot.m[r], st.m[r]);
         const float a = fast_exp2(tot.m[r] - M), b = fast_exp2(st.m[r] - M);
         tot.m[r] = M;
-        tot.l[r] = __builtin_fmaf(tot.l[r], a, st.l[r] * b);
+        tot.l[r] = __builtin_fmaf(st.l[r], b, tot.l[r] * a);
 #pragma unroll
-        for (int x = 0; x < 8; ++x) tot.o[r][x] = __builtin_fmaf(tot.o[r][x], a, st.o[r][x] * b);
+        for (int x = 0; x < 8; ++x) tot.o[r][x] = __builtin_fmaf(st.o[r][x], b, tot.o[r][x] * a);
     }
 }
 
