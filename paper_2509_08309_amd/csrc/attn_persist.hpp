@@ -274,7 +274,16 @@ __host__ __device__ constexpr bool deep_ring(int rows, int short_rows)
 //                  workgroup
 //   kVariantMerge  also partial results that are combined inside the launch
 //                  (AttnParams::arrivals is set), and single-chunk scheduling
-enum : int { kVariantPlain = 0, kVariantFew = 1, kVariantMerge = 2 };
+//   kVariantTeam   also teams (attn_team.hpp), whose code costs launches that cannot have one up to 1.4 %: it is a quarter
+//                  of the kernel, and the way to the first tile leads past it (with it -> without: 280 rows of 300 to
+//                  1200 tokens, r = 8, 35.0 -> 34.5 us, 480 of 1000 to 1300 of 64 dims, r = 2, 37.1 -> 36.7, 400 of
+//                  300 to 1600 of 64 dims 29.0 -> 28.8)
+enum : int { kVariantPlain = 0, kVariantFew = 1, kVariantMerge = 2, kVariantTeam = 3 };
+// Of the two that combine partial results: teams have a row or an item a workgroup, and a row has one item or more.
+__host__ __device__ constexpr int merge_variant(int mode, int64_t rows, int64_t workgroups)
+{
+    return mode == kModeSpread && rows <= workgroups ? kVariantTeam : kVariantMerge;
+}
 // Instantiations that hold the split-KV scheduling (kModeSplit), in the writer wave and in the
 // streaming waves alike; the host refuses such a launch on any other.
 __host__ __device__ constexpr bool holds_split(int variant, bool pairs) { return variant == kVariantPlain && !pairs; }
@@ -285,7 +294,8 @@ __global__ __launch_bounds__((NW + 1) * 64)
 {
     constexpr int D = Policy::D;
     constexpr int R = Policy::R;
-    constexpr bool MERGE = VARIANT == kVariantMerge;
+    constexpr bool MERGE = VARIANT >= kVariantMerge;
+    constexpr bool TEAM = VARIANT == kVariantTeam;
     constexpr bool FEW = VARIANT >= kVariantFew;
     constexpr bool CAN_SPLIT = holds_split(VARIANT, PAIRS);
     constexpr int NT = (NW + 1) * 64;
@@ -318,7 +328,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // kVariantMerge runs decode calls only, whose cut is fixed: with constants the divisions are
+    // MERGE: decode calls only, whose cut is fixed: with constants the divisions are
     // shifts.  Code on the way to the first load is executed once and comes from the instruction
     // cache's misses, so its length is what it costs.
     const int seg_tokens = MERGE ? decode_seg_tokens(R) : p.seg_tokens;
@@ -444,7 +454,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
             n_items = __builtin_amdgcn_readlane(wave_scan_sum(n_items), 63);
         }
         const bool team = lone || (spread && !full_house && (long long)n_items * n_sel <= (long long)gridDim.x);
-        if (__builtin_amdgcn_readfirstlane(team)) {
+        if (TEAM && __builtin_amdgcn_readfirstlane(team)) {
             if ((int)blockIdx.x >= (lone ? batch : n_items) * n_sel) return;
             int b = (int)blockIdx.x / n_sel, k = 0;
             const int si = (int)blockIdx.x - b * n_sel;

@@ -163,7 +163,7 @@ static int launch_persistent(AttnParams p, int batch, hipStream_t st)
     constexpr int NW = kVecWaves;
     auto kernel = attn_chunk_persistent_kernel<Policy, NW, PAIRS, VARIANT>;
     size_t lds = persist_lds_bytes<Policy, NW>(batch, p.n_sel, PAIRS);
-    if (VARIANT == kVariantMerge && p.mode == kModeSpread) lds = std::max(lds, sizeof(TeamLds<Policy, NW>));
+    if (VARIANT == kVariantTeam) lds = std::max(lds, sizeof(TeamLds<Policy, NW>));
     int occ = resident_per_cu(kernel, (NW + 1) * 64, lds);
     if (occ < 1) return HETIS_ERR_LAUNCH;
     const int cus = device_cu_count();
@@ -223,24 +223,27 @@ static int launch_chunk(const AttnParams &p0, int rows, hipStream_t st)
             }
         }
         // the leanest instantiation that holds what this launch can need: the in-launch merge
-        // when rows can leave partial results; the fixed second and third segments when the
-        // launch may have few segments a workgroup (every row has at least one segment); split
-        // calls hand out single chunks and have nothing of either
-        const int64_t few_rows =
-            (int64_t)HETIS_STATIC_SECOND_UPTO * std::max(device_cu_count(), 1) * wgs_per_cu_cap();
-        const int variant = p.arrivals ? kVariantMerge
-                            : p.mode != kModeSplit && (int64_t)n * n_sel <= few_rows ? kVariantFew
-                                                                                     : kVariantPlain;
+        // when rows can leave partial results, with teams when there is a workgroup for each row; the
+        // fixed second and third segments when the launch may have few segments a workgroup (every
+        // row has at least one segment); split calls hand out single chunks and have nothing of these
+        const int64_t workgroups = (int64_t)std::max(device_cu_count(), 1) * wgs_per_cu_cap();      // at most
+        const int64_t launch_rows = (int64_t)n * n_sel;
+        const int variant = p.arrivals ? merge_variant(p.mode, launch_rows, workgroups)
+                            : p.mode != kModeSplit && launch_rows <= HETIS_STATIC_SECOND_UPTO * workgroups
+                                ? kVariantFew
+                                : kVariantPlain;
         if (p.mode == kModeSplit && !holds_split(variant, pairs)) return HETIS_ERR_UNSUPPORTED;
         int rc;
         if (pairs)
-            rc = variant == kVariantMerge ? launch_persistent<Policy, true, kVariantMerge>(p, n, st)
-                 : variant == kVariantFew ? launch_persistent<Policy, true, kVariantFew>(p, n, st)
-                                          : launch_persistent<Policy, true, kVariantPlain>(p, n, st);
+            rc = variant == kVariantTeam    ? launch_persistent<Policy, true, kVariantTeam>(p, n, st)
+                 : variant == kVariantMerge ? launch_persistent<Policy, true, kVariantMerge>(p, n, st)
+                 : variant == kVariantFew   ? launch_persistent<Policy, true, kVariantFew>(p, n, st)
+                                            : launch_persistent<Policy, true, kVariantPlain>(p, n, st);
         else
-            rc = variant == kVariantMerge ? launch_persistent<Policy, false, kVariantMerge>(p, n, st)
-                 : variant == kVariantFew ? launch_persistent<Policy, false, kVariantFew>(p, n, st)
-                                          : launch_persistent<Policy, false, kVariantPlain>(p, n, st);
+            rc = variant == kVariantTeam    ? launch_persistent<Policy, false, kVariantTeam>(p, n, st)
+                 : variant == kVariantMerge ? launch_persistent<Policy, false, kVariantMerge>(p, n, st)
+                 : variant == kVariantFew   ? launch_persistent<Policy, false, kVariantFew>(p, n, st)
+                                            : launch_persistent<Policy, false, kVariantPlain>(p, n, st);
         if (rc != HETIS_OK) return rc;
     }
     return HETIS_OK;

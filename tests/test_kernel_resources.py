@@ -41,7 +41,7 @@ def kernel_metadata(source):
 
 
 @pytest.mark.skipif(shutil.which(HIPCC) is None, reason="hipcc not found")
-@pytest.mark.parametrize("source,expected", [("hetis_attn.hip", 48), ("hetis_kv.hip", 8)])
+@pytest.mark.parametrize("source,expected", [("hetis_attn.hip", 64), ("hetis_kv.hip", 8)])
 def test_no_kernel_uses_scratch_memory(source, expected):
     meta = kernel_metadata(source)
     main = {k: v for k, v in meta.items() if "persistent_kernel" in k or "kv_" in k}
@@ -98,3 +98,14 @@ def test_a_piece_is_folded_in_place(dim, group):
         moves = sum(x.startswith("v_mov_b32") for x in b)
         scores = sum(x.startswith("buffer_load") for x in b) // 2 * group
         assert moves <= 10 * group + scores + 6, (len(b), moves, scores)
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None, reason="hipcc not found")
+@pytest.mark.parametrize("policy,dim,group", [("Vec", 128, 1), ("Vec", 64, 2), ("Mfma", 128, 8)])
+def test_launches_without_teams_carry_no_team_code(policy, dim, group):
+    """The instantiation for more rows than workgroups is the smaller one by the team's code."""
+    text = assembly("hetis_attn.hip")
+    size = {}
+    for m in re.finditer(rf"^(\S*persistent_kernel\S*{policy}PolicyILi{dim}ELi{group}E\S*Lb0ELi([23])EEEv\S*):", text, re.M):
+        size[m.group(2)] = int(re.search(r"codeLenInByte = (\d+)", text[m.end():]).group(1))
+    assert size["3"] > 1.15 * size["2"], size

@@ -59,3 +59,14 @@ def test_one_instantiation_holds_split_calls(tmp_path):
     assert kernel.count("p.mode == kModeSplit") == 1, "one place decides: split_mode"
     with open(os.path.join(build.CSRC, "hetis_attn.hip")) as f:
         assert "!holds_split(variant, pairs)) return HETIS_ERR_UNSUPPORTED;" in f.read()
+
+
+def test_teams_are_compiled_in_where_they_can_run(tmp_path):
+    """No more rows than workgroups, in a launch that may be handed out singly; its code is in no other
+    instantiation."""
+    assert_compiles(tmp_path, """
+        static_assert(merge_variant(kModeSpread, 1, 256) == kVariantTeam && merge_variant(kModeSpread, 256, 256) == kVariantTeam);
+        static_assert(merge_variant(kModeSpread, 257, 256) == kVariantMerge && merge_variant(kModeSpread, 511, 256) == kVariantMerge);
+        static_assert(merge_variant(kModeSegments, 1, 256) == kVariantMerge && merge_variant(kModeSegments, 4096, 256) == kVariantMerge);
+        static_assert(!holds_split(kVariantTeam, false) && !holds_split(kVariantTeam, true));
+    """)
