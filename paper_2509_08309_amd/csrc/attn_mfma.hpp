@@ -199,6 +199,7 @@ struct MfmaPolicy {
 #pragma unroll
             for (int e = 0; e < 4; ++e) tot.acc[mb][e] = __builtin_fmaf(st.acc[mb][e], b, tot.acc[mb][e] * a);
     }
+    __device__ static __forceinline__ void settle(State &) {}           // (a piece is more than one turn)
     // state <-> LDS, sixteen bytes a lane at a time
     static constexpr int kStateVecs = MB + 1;
     __device__ static __forceinline__ void deposit(const State &st, f32x4 *to, int lane)

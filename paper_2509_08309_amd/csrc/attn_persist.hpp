@@ -1422,12 +1422,20 @@ __global__ __launch_bounds__((NW + 1) * 64)
             const int lim = RING * max(1, (n_my + RING - 1) / RING);   // tiles, as whole ring turns
             // The scheduling fences keep "consume a slot, refill it at once" in program order;
             // without them the compiler batches the tiles' arithmetic ahead of the refills and
-            // the wave ends up waiting with nothing in flight.
+            // the wave ends up waiting with nothing in flight.  Where a turn is a whole piece (64 dims,
+            // deep ring) the sums begin and end in it, and the compiler moves all of the turn's arithmetic
+            // behind its last refill, so that the first refill waits for the whole ring: 480 rows of 1000 to
+            // 1300 tokens, r = 2, 38.0 us, with the sums settled tile by tile 36.7; 400 of 300 to 1600, r = 1,
+            // 29.0 and 28.1.  In launches of no more rows than workgroups, which wait for the way to memory
+            // and not for its width, r = 1 is better off with one wait a turn (20 rows of 10k to 32k 31.0
+            // and 32.7; r = 2, 24 of 6k to 9k 18.8 and 18.7).
+            constexpr bool kSettle = PT == RING && (R == 2 || !TEAM);
             auto steady_turn = [&](int i) {                 // whole tiles; refills stay in this chunk
 #pragma unroll
                 for (int s = 0; s < RING; ++s) {
                     Policy::template update<kFullTile>(st, ring[s], q, p.scale_log2, lane, kBlockTokens,
                                                    my_staging);
+                    if constexpr (kSettle) Policy::settle(st);
                     __builtin_amdgcn_sched_barrier(0);
                     issue(ring[s], cur.ids, i + RING + s, cur.head_off, n_tok);
                     __builtin_amdgcn_sched_barrier(0);

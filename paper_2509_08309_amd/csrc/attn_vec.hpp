@@ -233,6 +233,14 @@ struct VecPolicy {
             vec_tile_update<D, R, false>(st, t, q.h, scale_log2, lane / (D / 8), kBlockTokens);
     }
     __device__ static __forceinline__ void fold(State &tot, const State &st) { vec_fold<D, R>(tot, st); }
+    // The sums as they stand, in registers: no arithmetic on them moves past this point.
+    __device__ static __forceinline__ void settle(State &st)
+    {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            asm volatile("" : "+v"(st.m[r]), "+v"(st.l[r]), "+v"(st.o[r][0]), "+v"(st.o[r][1]), "+v"(st.o[r][2]),
+                         "+v"(st.o[r][3]), "+v"(st.o[r][4]), "+v"(st.o[r][5]), "+v"(st.o[r][6]), "+v"(st.o[r][7]));
+    }
     // state <-> LDS, sixteen bytes a lane at a time
     static_assert(R <= 2, "maximum and sum of all rows in one vector");
     static constexpr int kStateVecs = 2 * R + 1;

@@ -109,3 +109,17 @@ def test_launches_without_teams_carry_no_team_code(policy, dim, group):
     for m in re.finditer(rf"^(\S*persistent_kernel\S*{policy}PolicyILi{dim}ELi{group}E\S*Lb0ELi([23])EEEv\S*):", text, re.M):
         size[m.group(2)] = int(re.search(r"codeLenInByte = (\d+)", text[m.end():]).group(1))
     assert size["3"] > 1.15 * size["2"], size
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None, reason="hipcc not found")
+@pytest.mark.parametrize("dim,group,variant", [(d, g, v) for d in (64, 128) for g in (1, 2) for v in (0, 1, 2, 3)
+                                               if (d, g, v) != (64, 1, 3)])      # drained on purpose
+def test_a_turn_of_the_ring_does_not_drain_it(dim, group, variant):
+    """Vector path: a slot is refilled as soon as its tile is used, so what a turn waits for ahead of its first
+    refill is that tile, not the whole ring."""
+    a_tile = dim // 16                                      # loads of a K tile and a V tile
+    for b in streaming_loops("Vec", dim, group, variant):
+        loads = sum(x.startswith("buffer_load") for x in b)
+        ahead = b[:next(i for i, x in enumerate(b) if x.startswith("buffer_load"))]
+        left = [int(re.search(r"vmcnt\((\d+)\)", x).group(1)) for x in ahead if "vmcnt" in x][-1]
+        assert left >= loads - a_tile, (len(b), loads, left)
