@@ -82,7 +82,16 @@ struct AttnParams {
                                 // zero between launches; nullptr: partial results are left for a
                                 // separate merge (the split-KV entry points)
     float scale_log2;           // scale * log2(e): scores are kept in the base-2 domain
+    unsigned int sel_inverse;   // inverse_of(n_sel)
 };
+
+// x / n as one multiplication, for launches of few rows: n < 512, x < 2^13.  (With i = (2^31 + e) / n, e < n, the
+// product 2 x i / 2^32 is x / n + x e / (n 2^31), too large by less than x / 2^31 <= 1 / n as long as x n < 2^31.)
+__host__ __device__ constexpr unsigned int inverse_of(unsigned int n) { return ((1u << 31) + n - 1) / n; }
+__host__ __device__ constexpr unsigned int divide_by(unsigned int x, unsigned int inverse)
+{
+    return (unsigned int)(((unsigned long long)(2 * x) * inverse) >> 32);
+}
 
 // How the work of a launch is cut for scheduling.  The arithmetic of a row is the same in
 // kModeSegments and kModeSpread.

@@ -380,6 +380,13 @@ __global__ __launch_bounds__((NW + 1) * 64)
         return x;
     };
     int q_first_head = 0;                               // of the wave's first item
+    // `batch`, to be compared with once more: the masks of the row groups, kept from one loop over them to the
+    // next, take 32 scalar registers, and others are spilled for them
+    auto rows_again = [&]() {
+        int n = batch;
+        asm volatile("" : "+s"(n));
+        return n;
+    };
     __shared__ int team_full[2 * NW];
     if (tid < 2 * NW) mail[tid].flag = team_full[tid] = kMailEmpty;
     if (tid == 0) {
@@ -389,8 +396,11 @@ __global__ __launch_bounds__((NW + 1) * 64)
     if (MERGE && p.mode == kModeSpread) {
         // heads of the items this wave may start on: spread, team
         const int first_item = wave * (int)gridDim.x + (int)blockIdx.x;
-        const int head_spread = PAIRS ? 0 : p.head_ids[first_item % n_sel];
-        const int head_team = PAIRS ? 0 : p.head_ids[(int)blockIdx.x % n_sel];
+        const int head_spread =
+            PAIRS ? 0 : p.head_ids[first_item - (int)divide_by(first_item, p.sel_inverse) * n_sel];
+        const int my_b = PAIRS ? (int)blockIdx.x : (int)divide_by(blockIdx.x, p.sel_inverse);
+        const int my_si = (int)blockIdx.x - my_b * n_sel;
+        const int head_team = PAIRS || !TEAM ? 0 : p.head_ids[my_si];
         // (groups beyond the launch's rows are branched over)
 #pragma unroll
         for (int u = 0; u < QG; ++u) {
@@ -404,11 +414,11 @@ __global__ __launch_bounds__((NW + 1) * 64)
         for (int u = 0; u < QG; ++u)
             if (u * 64 < batch) q_len[u] = p.seq_lens[q_seq[u]];
         __syncthreads();                            // mailboxes and pool are ready
-        int longest = 0;
+        int longest = 0, n_rows = rows_again();
         bool full_house = false;
 #pragma unroll
         for (int u = 0; u < QG; ++u)
-            if (u * 64 < batch) longest = max(longest, u * 64 + lane < batch ? q_len[u] : 0);
+            if (u * 64 < n_rows) longest = max(longest, u * 64 + lane < n_rows ? q_len[u] : 0);
         longest = wave_max(longest);
         if (longest > seg_tokens) {
             // Rows of several segments: chunks while there are fewer segments than workgroups.  Two
@@ -417,9 +427,10 @@ __global__ __launch_bounds__((NW + 1) * 64)
             // r = 1 67 -> 72 us, r = 2 73 -> 78, r = 8 90 -> 85; 20 rows of 60k, r = 1 129 -> 110, r = 8
             // 154 -> 141; far beyond it whole segments are (500 rows of 5000, r = 2: 208 -> 234).
             int n_segments = 0;
+            n_rows = rows_again();
 #pragma unroll
             for (int u = 0; u < QG; ++u)
-                if (u * 64 + lane < batch)
+                if (u * 64 + lane < n_rows)
                     n_segments += max(1, udiv(max(q_len[u], 0) + seg_tokens - 1, seg_tokens));
             n_segments = __builtin_amdgcn_readlane(wave_scan_sum(n_segments), 63);
             spread = (long long)n_segments * n_sel < (long long)gridDim.x;
@@ -428,12 +439,13 @@ __global__ __launch_bounds__((NW + 1) * 64)
             static_assert(kMaxQuickRows * kSegChunks <= 1 << 14 &&
                           kMaxQuickRows * (decode_seg_tokens(R) / kBlockTokens) <= 1 << 17, "sums fit");
             int sum = 0;
+            n_rows = rows_again();
 #pragma unroll
             for (int u = 0; u < QG; ++u) {
-                if (u * 64 >= batch) continue;
+                if (u * 64 >= n_rows) continue;
                 const int L = max(q_len[u], 1), ct = chunk_tokens_of(L, chunk_tokens, seg_tokens);
                 const int sh = __builtin_ctz(ct);
-                if (u * 64 + lane < batch)
+                if (u * 64 + lane < n_rows)
                     sum += ((L + kBlockTokens - 1) / kBlockTokens << 14) + ((L + ct - 1) >> sh);
             }
             sum = __builtin_amdgcn_readlane(wave_scan_sum(sum), 63);
@@ -443,29 +455,35 @@ __global__ __launch_bounds__((NW + 1) * 64)
             // more than a full chunk a workgroup, whatever its rows
             full_house = tokens - batch * n_sel * (kBlockTokens - 1) > (int)gridDim.x * chunk_tokens;
         }
-        const bool lone = !spread && longest <= seg_tokens && batch * n_sel <= (int)gridDim.x;
+        const bool fits = TEAM && batch * n_sel <= (int)gridDim.x;          // a workgroup for each row
+        const bool lone = fits && !spread && longest <= seg_tokens;
         // items (windows of a full chunk) of a row, and of all rows, per selected head
         auto items_of = [&](int L) { return max(1, (L + chunk_tokens - 1) / chunk_tokens); };
-        int n_items = 0;
-        if (spread && !full_house) {
+        int n_items = (int)gridDim.x + 1;
+        // (counted only where the longest row's, with one for each other row, leave it open)
+        if (fits && spread && !full_house &&
+            (long long)(batch - 1 + items_of(longest)) * n_sel <= (long long)gridDim.x) {
+            n_items = 0;
+            n_rows = rows_again();
 #pragma unroll
             for (int u = 0; u < QG; ++u)
-                if (u * 64 + lane < batch) n_items += items_of(q_len[u]);
+                if (u * 64 + lane < n_rows) n_items += items_of(q_len[u]);
             n_items = __builtin_amdgcn_readlane(wave_scan_sum(n_items), 63);
         }
-        const bool team = lone || (spread && !full_house && (long long)n_items * n_sel <= (long long)gridDim.x);
+        const bool team = lone || (long long)n_items * n_sel <= (long long)gridDim.x;
         if (TEAM && __builtin_amdgcn_readfirstlane(team)) {
             if ((int)blockIdx.x >= (lone ? batch : n_items) * n_sel) return;
-            int b = (int)blockIdx.x / n_sel, k = 0;
-            const int si = (int)blockIdx.x - b * n_sel;
+            int b = my_b, k = 0;
+            const int si = my_si;
             if (!lone) {
                 // the last row with no more than `left` items before it, group by group
                 int left = b;
                 b = 0;
+                n_rows = rows_again();
 #pragma unroll
                 for (int u = 0; u < QG; ++u) {
-                    if (u * 64 >= batch || b != u * 64) continue;
-                    const int mine = u * 64 + lane < batch ? items_of(q_len[u]) : 0;
+                    if (u * 64 >= n_rows || b != u * 64) continue;
+                    const int mine = u * 64 + lane < n_rows ? items_of(q_len[u]) : 0;
                     const int incl = wave_scan_sum(mine), all = __builtin_amdgcn_readlane(incl, 63);
                     if (left >= all) {
                         left -= all;
@@ -492,12 +510,13 @@ __global__ __launch_bounds__((NW + 1) * 64)
         }
         q_first_head = head_spread;
         if (spread) {
+            n_rows = rows_again();
 #pragma unroll
             for (int u = 0; u < QG; ++u) {
-                if (u * 64 >= batch) continue;
+                if (u * 64 >= n_rows) continue;
                 int nB = 0;
                 int nA = full_chunks(q_len[u], &nB);
-                if (u * 64 + lane >= batch) nA = nB = 0;
+                if (u * 64 + lane >= n_rows) nA = nB = 0;
                 const int inclA = wave_scan_sum(nA), inclB = wave_scan_sum(nB);
                 qA[u] = totalA + inclA - nA;
                 qB[u] = totalB + inclB - nB;
@@ -771,7 +790,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
     };
     // the wave's first item -> chunk, from the registers of the wave
     auto quick_spread = [&](int item) {
-        const int cg = PAIRS ? item : item / n_sel;
+        const int cg = PAIRS ? item : (int)divide_by(item, p.sel_inverse);
         const int si = PAIRS ? 0 : item - cg * n_sel;
         const bool full = cg < totalA;
         const int key = full ? cg : cg - totalA;

@@ -176,6 +176,8 @@ static int launch_persistent(AttnParams p, int batch, hipStream_t st)
         p.mode == kModeSpread && (int64_t)p.max_blocks_per_seq * kBlockTokens <= p.chunk_tokens;
     const int64_t most = (int64_t)batch * (short_rows ? 1 : p.max_segs) * p.n_sel;
     if (G > most) G = most;
+    if (VARIANT >= kVariantMerge && p.mode == kModeSpread) G = std::min<int64_t>(G, 8192 / (NW + 1));     // divide_by
+    p.sel_inverse = inverse_of((unsigned)p.n_sel);
     launch_timed(kernel, dim3((unsigned)G), dim3((NW + 1) * 64), lds, st, p, batch);
     return HETIS_OK;
 }

@@ -70,3 +70,21 @@ def test_teams_are_compiled_in_where_they_can_run(tmp_path):
         static_assert(merge_variant(kModeSegments, 1, 256) == kVariantMerge && merge_variant(kModeSegments, 4096, 256) == kVariantMerge);
         static_assert(!holds_split(kVariantTeam, false) && !holds_split(kVariantTeam, true));
     """)
+
+
+@pytest.mark.parametrize("first,last", [(1, 8), (8, 64), (64, 200), (200, 350), (350, 512)])
+def test_division_by_a_multiplication(tmp_path, first, last):
+    """divide_by over every divisor of a launch of few rows: the quotient changes at the multiples and nowhere
+    else, up to the largest item number."""
+    assert_compiles(tmp_path, f"""
+        constexpr bool exact() {{
+            for (unsigned n = {first}; n < {last}; ++n) {{
+                const unsigned i = inverse_of(n);
+                for (unsigned q = 0; q * n < 8192; ++q)
+                    if (divide_by(q * n, i) != q || divide_by(q * n + n - 1, i) != q) return false;
+                if (divide_by(8191, i) != 8191 / n) return false;
+            }}
+            return true;
+        }}
+        static_assert(exact(), "as / has it");
+    """)
