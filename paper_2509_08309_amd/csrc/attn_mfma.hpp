@@ -45,10 +45,11 @@ struct MfmaPolicy {
     static constexpr int kQBytes = R * D * 2;
     static constexpr int kWaveLdsBytes = kQBytes;
     static constexpr int kWavesPerEu = 2;             // register budget: 512 / 2 per lane
-    // Tile pairs in flight per wave: 16 KB, a whole part of a piece's eight.  (With 24 KB, possible while a
-    // chunk was one piece, 768 rows of 2176 tokens took 139.0 us instead of 139.8, 768 pairs the same; 4
-    // pairs were slower throughout, 64 rows of 500 to 3000 24.3 -> 25.7.)
-    static constexpr int ring(bool) { return D_ == 64 ? 4 : 2; }
+    // Tile pairs in flight per wave: 16 KB at 64 dims, 24 KB at 128 (a piece of eight tiles then ends inside a turn).
+    // 16 KB -> 24 KB at 128 dims: 160 rows of 300 to 1200 tokens, r = 8, 25.6 -> 24.0 us, r = 4 24.7 -> 23.0, 26 of
+    // 150 to 18 700, r = 4, 26.5 -> 24.4, 768 of 2176, r = 8, 139.7 -> 138.6; but 12 of 10k to 32k, r = 8, 32.5 -> 32.9,
+    // 300 of 100 to 600 20.9 -> 21.3.  (32 KB, while a chunk was one piece: slower throughout.)
+    static constexpr int ring(bool) { return D_ == 64 ? 4 : 3; }
 
     // of a team's wave: two copies of the arithmetic of a tile (4: 16 rows of 300 to 1200, r = 4, 16.8 -> 17.7)
     static constexpr int kTeamRing = 2;
@@ -199,7 +200,7 @@ struct MfmaPolicy {
 #pragma unroll
             for (int e = 0; e < 4; ++e) tot.acc[mb][e] = __builtin_fmaf(st.acc[mb][e], b, tot.acc[mb][e] * a);
     }
-    __device__ static __forceinline__ void settle(State &) {}           // (a piece is more than one turn)
+    __device__ static __forceinline__ void settle(State &) {}           // (no piece is one turn)
     // state <-> LDS, sixteen bytes a lane at a time
     static constexpr int kStateVecs = MB + 1;
     __device__ static __forceinline__ void deposit(const State &st, f32x4 *to, int lane)

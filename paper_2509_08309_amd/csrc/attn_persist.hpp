@@ -1374,6 +1374,13 @@ __global__ __launch_bounds__((NW + 1) * 64)
         return none;
     };
 
+    // The lane's number for what runs once a chunk: addresses that follow from it would be worked out ahead of the
+    // streaming loop and kept, in 18 of the registers that the tiles of the MFMA path need.
+    auto lane_again = [&]() {
+        int l = lane;
+        if constexpr (R >= 4) asm volatile("" : "+v"(l));
+        return l;
+    };
     unsigned char *my_staging = staging + (size_t)wave * Policy::kWaveLdsBytes;
     Mail *my_mail = mail + wave * 2;
 
@@ -1428,12 +1435,14 @@ __global__ __launch_bounds__((NW + 1) * 64)
 
             // pieces of a chunk: sums of their own, folded in order (split calls: one piece)
             constexpr int PT = SPLIT ? 1 << 20 : decode_piece_tokens(R) / kBlockTokens;      // tiles
-            static_assert(PT % RING == 0, "a piece is whole turns of the ring");
+            // a piece is whole turns of the ring and folded behind the last one's refills, or (MFMA path, 128
+            // dims) it ends anywhere in a turn and is folded behind its last tile
+            constexpr bool kAnywhere = !SPLIT && PT % RING != 0;
             typename Policy::State st, tot;
             Policy::reset(st);
             Policy::reset(tot);
-            auto next_piece = [&](int i) {                  // after the turn of tiles [i, i + RING)
-                if (SPLIT || (i + RING) % PT != 0) return;
+            auto next_piece = [&](int n_tiles) {            // after so many tiles of the chunk
+                if (SPLIT || n_tiles % PT != 0) return;
                 Policy::fold(tot, st);
                 Policy::reset(st);
             };
@@ -1455,6 +1464,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
                     Policy::template update<kFullTile>(st, ring[s], q, p.scale_log2, lane, kBlockTokens,
                                                    my_staging);
                     if constexpr (kSettle) Policy::settle(st);
+                    if (kAnywhere) next_piece(i + s + 1);
                     __builtin_amdgcn_sched_barrier(0);
                     issue(ring[s], cur.ids, i + RING + s, cur.head_off, n_tok);
                     __builtin_amdgcn_sched_barrier(0);
@@ -1466,7 +1476,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
             int i = 0;
             for (; i + 4 * RING < lim; i += RING) {
                 steady_turn(i);
-                next_piece(i);
+                if (!kAnywhere) next_piece(i + RING);
             }
             if (SPLIT && n == 0) {
                 // the wave's second segment is its own as well
@@ -1483,7 +1493,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
             Policy::q_prefetch(q_pre, q_rows(nxt), lane);   // next chunk's query rows
             for (; i + RING < lim; i += RING) {
                 steady_turn(i);
-                next_piece(i);
+                if (!kAnywhere) next_piece(i + RING);
             }
             // last turn of this chunk (the only place a ragged block can be): its refills are the
             // first tiles of the next chunk
@@ -1492,6 +1502,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
                 if (i + s < n_my) {
                     Policy::template update<kMaybeRagged>(st, ring[s], q, p.scale_log2, lane,
                                                   n_tok - (i + s) * kBlockTokens, my_staging);
+                    if (kAnywhere && i + s + 1 < n_my) next_piece(i + s + 1);
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 issue(ring[s], nxt.ids, s, nxt.head_off, nxt.h.n_tok);
@@ -1506,12 +1517,13 @@ __global__ __launch_bounds__((NW + 1) * 64)
                 // The wave's last chunk, and a result of its own: no load is in flight that a store
                 // could hold up, so the wave stores, counts and combines it itself instead of
                 // queueing behind the other waves' results at the writer.
-                if (cur.h.kind != kKindZero) Policy::finish(sum, mb.o, mb.lse, lane);
+                const int lane_now = lane_again();
+                if (cur.h.kind != kKindZero) Policy::finish(sum, mb.o, mb.lse, lane_now);
                 wave_lds_fence();
                 RowRegs<D, R> g;
-                g.load(mb.o, mb.lse, lane);
+                g.load(mb.o, mb.lse, lane_now);
                 if (cur.h.kind == kKindPartial && merging) {
-                    store_partial_coherent<D, R>(g, cur.h.dest, p, lane, spread);
+                    store_partial_coherent<D, R>(g, cur.h.dest, p, lane_now, spread);
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
                     __builtin_amdgcn_s_waitcnt(0);      // every store of this wave has completed
                     unsigned old = 0;
@@ -1523,13 +1535,13 @@ __global__ __launch_bounds__((NW + 1) * 64)
                     combine_if_last<D, R>(p, __builtin_amdgcn_readfirstlane((int)old), 1, cur.h.dest, cur.h.nseg,
                                           cur.h.out_row, cur.h.len, spread, batch * n_sel, lane);
                 } else {
-                    store_result<D, R>(g, cur.h.kind, cur.h.dest, p, lane);
+                    store_result<D, R>(g, cur.h.kind, cur.h.dest, p, lane_now);
                     mail_store(&mb.flag, kMailDone);
                 }
                 return;
             }
             // hand the finished chunk to the writer
-            if (cur.h.kind != kKindZero) Policy::finish(sum, mb.o, mb.lse, lane);
+            if (cur.h.kind != kKindZero) Policy::finish(sum, mb.o, mb.lse, lane_again());
             if (lane == 0) {
                 mb.kind = cur.h.kind;
                 mb.dest = cur.h.dest;

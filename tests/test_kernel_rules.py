@@ -88,3 +88,12 @@ def test_division_by_a_multiplication(tmp_path, first, last):
         }}
         static_assert(exact(), "as / has it");
     """)
+
+
+@pytest.mark.parametrize("R", [4, 8])
+def test_depth_of_the_ring_on_the_mfma_path(tmp_path, R):
+    """16 KB of tiles a wave with 64 dims, 24 KB with 128, in every launch."""
+    assert_compiles(tmp_path, f"""
+        static_assert(MfmaPolicy<64, {R}>::ring(true) == 4 && MfmaPolicy<64, {R}>::ring(false) == 4, "16 KB");
+        static_assert(MfmaPolicy<128, {R}>::ring(true) == 3 && MfmaPolicy<128, {R}>::ring(false) == 3, "24 KB");
+    """)
