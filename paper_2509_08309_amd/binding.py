@@ -10,12 +10,13 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import sysconfig
 from typing import Optional
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 # HETIS_ATTN_LIB (optional) points at another build of the same library, e.g. a tuning variant.
 LIB_PATH = os.environ.get("HETIS_ATTN_LIB") or os.path.join(HERE, "libhetis_attn.so")
-MARSHAL_PATH = os.path.join(HERE, "_marshal.so")
+MARSHAL_PATH = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))    # (build.MARSHAL)
 
 HETIS_OK = 0
 HETIS_ERR_NULL = -1
@@ -65,13 +66,13 @@ def load(build_if_missing: bool = False):
     global _lib
     if _lib is not None:
         return _lib
-    if not (os.path.exists(LIB_PATH) and os.path.exists(MARSHAL_PATH)):
+    if not os.path.exists(LIB_PATH):
         if build_if_missing:
             from .build import build
             build()
         else:
             raise FileNotFoundError(
-                f"{LIB_PATH} or {MARSHAL_PATH} is not built; run `python -m paper_2509_08309_amd.build` "
+                f"{LIB_PATH} is not built; run `python -m paper_2509_08309_amd.build` "
                 "(the HIP library is required, there is no fallback)")
     lib = C.CDLL(LIB_PATH)
     vp, i32, i64, f32 = C.c_void_p, C.c_int32, C.c_int64, C.c_float
@@ -160,18 +161,41 @@ def load(build_if_missing: bool = False):
 
 class _Calls:
     """The calls of a decode step (launches, and nothing that waits) with their arguments as the caller has
-    them: tensors, ctypes structures, numbers.  Converted natively (csrc/marshal.cpp)."""
+    them: tensors, ctypes structures, numbers.  Converted natively (csrc/marshal.cpp), or through ctypes (some
+    1.5 us a call more) where the extension is not built for this interpreter."""
 
     def __init__(self, lib):
-        from . import _marshal
-        _marshal.structs(hetis_attn_shape, hetis_kv_pool)
+        native = os.path.exists(MARSHAL_PATH)
+        if native:
+            from . import _marshal
+            _marshal.structs(hetis_attn_shape, hetis_kv_pool)
         for name in ("hetis_attn_decode", "hetis_attn_decode_ws", "hetis_attn_decode_step",
                      "hetis_attn_decode_step_ws", "hetis_attn_decode_pairs", "hetis_attn_decode_pairs_ws",
                      "hetis_attn_decode_pairs_step", "hetis_attn_decode_pairs_step_ws",
                      "hetis_attn_decode_split", "hetis_attn_decode_split_ws", "hetis_attn_merge",
                      "hetis_kv_append", "hetis_kv_append_pairs", "hetis_kv_store", "hetis_kv_fetch",
                      "hetis_kv_copy_tiles"):
-            setattr(self, name, _marshal.bind(name, C.cast(getattr(lib, name), C.c_void_p).value))
+            fn = getattr(lib, name)
+            setattr(self, name, _marshal.bind(name, C.cast(fn, C.c_void_p).value) if native else _by_ctypes(fn))
+
+
+def _by_ctypes(fn):
+    """`fn` with its arguments converted as csrc/marshal.cpp converts them."""
+    def struct(o):
+        return None if o is None else C.byref(o)
+
+    convert = []
+    for t in fn.argtypes:
+        if hasattr(t, "contents"):                                       # (a shape has to be one)
+            convert.append(C.byref if t._type_ is hetis_attn_shape else struct)
+        else:
+            convert.append(_ptr if t is C.c_void_p else float if t is C.c_float else int)
+
+    def call(*args):
+        if len(args) != len(convert):
+            raise TypeError(f"{len(convert)} arguments expected, {len(args)} given")
+        return fn(*[c(a) for c, a in zip(convert, args)])
+    return call
 
 
 def _ptr(t) -> Optional[int]:

@@ -1,6 +1,7 @@
-"""Build libhetis_attn.so for gfx950 with hipcc and the binding's argument marshalling (_marshal.so, host
-code), in-tree (next to this file)."""
+"""Build libhetis_attn.so for gfx950 with hipcc and the binding's argument marshalling (host code, an extension
+of the interpreter that runs this), in-tree (next to this file)."""
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -8,7 +9,8 @@ import sysconfig
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhetis_attn.so")
-MARSHAL = os.path.join(HERE, "_marshal.so")
+# (the name carries the interpreter's version: another one does not pick up what it cannot load)
+MARSHAL = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
 SOURCES = ["hetis_attn.hip", "hetis_kv.hip", "hetis_profiler.hip", "hetis_dispatch.hip"]
 
 HIPCC_FLAGS = [
@@ -27,10 +29,19 @@ def sources():
     return out
 
 
+def marshal_compiler():
+    """The C++ compiler of the marshalling extension; None where it or Python's headers are missing, and the
+    binding then converts arguments through ctypes."""
+    if not os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h")):
+        return None
+    return os.environ.get("CXX") or shutil.which("g++")
+
+
 def is_current() -> bool:
-    if not (os.path.exists(LIB) and os.path.exists(MARSHAL)):
+    built = [LIB, MARSHAL] if marshal_compiler() else [LIB]
+    if not all(os.path.exists(b) for b in built):
         return False
-    t = min(os.path.getmtime(LIB), os.path.getmtime(MARSHAL))
+    t = min(os.path.getmtime(b) for b in built)
     return all(os.path.getmtime(s) <= t for s in sources())
 
 
@@ -40,9 +51,12 @@ def build(force: bool = True, extra_flags=()) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     cmd = [hipcc] + HIPCC_FLAGS + list(extra_flags) + \
           [os.path.join(CSRC, s) for s in SOURCES] + ["-o", LIB]
-    subprocess.run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
-                    "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL],
-                   check=True)
+    if marshal_compiler():
+        subprocess.run([marshal_compiler(), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+                        "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL],
+                       check=True)
+    else:
+        print("no C++ compiler or no Python headers: the binding converts arguments through ctypes", file=sys.stderr)
     subprocess.run(cmd, check=True)
     return LIB
 
