@@ -162,7 +162,7 @@ def load(build_if_missing: bool = False):
 class _Calls:
     """The calls of a decode step (launches, and nothing that waits) with their arguments as the caller has
     them: tensors, ctypes structures, numbers.  Converted natively (csrc/marshal.cpp), or through ctypes (some
-    1.5 us a call more) where the extension is not built for this interpreter."""
+    2.5 us a call more) where the extension is not built for this interpreter."""
 
     def __init__(self, lib):
         native = os.path.exists(MARSHAL_PATH)
@@ -180,22 +180,17 @@ class _Calls:
 
 
 def _by_ctypes(fn):
-    """`fn` with its arguments converted as csrc/marshal.cpp converts them."""
-    def struct(o):
-        return None if o is None else C.byref(o)
-
-    convert = []
-    for t in fn.argtypes:
+    """`fn` with its arguments converted as csrc/marshal.cpp converts them (spelled out argument by argument: a
+    loop over them is 1.2 us a call)."""
+    def kind(t):
         if hasattr(t, "contents"):                                       # (a shape has to be one)
-            convert.append(C.byref if t._type_ is hetis_attn_shape else struct)
-        else:
-            convert.append(_ptr if t is C.c_void_p else float if t is C.c_float else int)
+            return "byref" if t._type_ is hetis_attn_shape else "struct"
+        return "_ptr" if t is C.c_void_p else "float" if t is C.c_float else "int"
 
-    def call(*args):
-        if len(args) != len(convert):
-            raise TypeError(f"{len(convert)} arguments expected, {len(args)} given")
-        return fn(*[c(a) for c, a in zip(convert, args)])
-    return call
+    names = [f"a{i}" for i in range(len(fn.argtypes))]
+    converted = [f"{kind(t)}({a})" for t, a in zip(fn.argtypes, names)]
+    return eval(f"lambda {', '.join(names)}: fn({', '.join(converted)})",
+                {"fn": fn, "_ptr": _ptr, "byref": C.byref, "struct": lambda o: None if o is None else C.byref(o)})
 
 
 def _ptr(t) -> Optional[int]:
