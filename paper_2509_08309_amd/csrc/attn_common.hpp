@@ -112,7 +112,14 @@ enum : int { kModeSegments = 0, kModeSplit = 1, kModeSpread = 2 };
 // clears it) and records that a bounded wait inside a kernel expired, which means that the
 // launch may have dropped or overwritten a result.  kCtlLastMode: 1 + the scheduling mode the
 // last launch ran in (a statistic for tests and tuning; nothing reads it on the device).
-enum : int { kCtlTickets = 0, kCtlGone = 1, kCtlError = 2, kCtlLastMode = 3 };
+// kCtlLastWay: how the last launch handed its work out, whatever the mode is called (statistics as well).
+enum : int { kCtlTickets = 0, kCtlGone = 1, kCtlError = 2, kCtlLastMode = 3, kCtlLastWay = 4 };
+enum : unsigned { kWaySegments = 1, kWayChunks = 2, kWaySplit = 3, kWayTeamRows = 4, kWayTeamItems = 5, kWayWaveRows = 6 };
+__device__ __forceinline__ void record_way(unsigned int *control, int mode, unsigned way)
+{
+    control[kCtlLastMode] = 1u + (unsigned)mode;
+    control[kCtlLastWay] = way;
+}
 enum : unsigned { kErrWriterWait = 1u, kErrMailboxWait = 2u, kErrTicketWait = 4u };
 constexpr int kControlBytes = 256;
 

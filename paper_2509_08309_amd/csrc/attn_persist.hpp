@@ -1293,8 +1293,8 @@ __global__ __launch_bounds__((NW + 1) * 64)
         if (lane == 0) {
             if (done_mask != (1 << NW) - 1) report_error(p.control, kErrWriterWait);
             if (draws ? gone_before == gridDim.x - 1 : blockIdx.x == 0)
-                p.control[kCtlLastMode] =
-                    1u + (unsigned)(spread ? kModeSpread : (split_mode ? kModeSplit : kModeSegments));
+                record_way(p.control, spread ? kModeSpread : split_mode ? kModeSplit : kModeSegments,
+                           spread ? kWayChunks : split_mode ? kWaySplit : kWaySegments);
             if (draws && gone_before == gridDim.x - 1) {
                 __hip_atomic_store(p.control + kCtlTickets, 0u, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);

@@ -48,7 +48,7 @@ __global__ __launch_bounds__(64, 2) void attn_wave_rows_kernel(const AttnParams 
         unsigned char staging[Policy::kWaveLdsBytes ? Policy::kWaveLdsBytes : 16];
     } l;
     const int lane = threadIdx.x;
-    if (blockIdx.x == 0 && lane == 0) p.control[kCtlLastMode] = 1u + (unsigned)kModeSegments;
+    if (blockIdx.x == 0 && lane == 0) record_way(p.control, kModeSegments, kWayWaveRows);
     TeamItem it;
     it.row = (int)blockIdx.x;
     it.b = PAIRS ? it.row : udiv(it.row, p.n_sel);

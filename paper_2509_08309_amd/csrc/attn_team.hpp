@@ -208,7 +208,7 @@ __device__ __forceinline__ void team_run(const AttnParams &p, const TeamItem &fi
         // ------------------------------------------------------------ merger
         const int64_t out_row = (int64_t)first.seq * p.n_q_heads + first.g * R;
         if (blockIdx.x == 0 && lane == 0)
-            p.control[kCtlLastMode] = 1u + (unsigned)(spread ? kModeSpread : kModeSegments);
+            record_way(p.control, spread ? kModeSpread : kModeSegments, whole ? kWayTeamRows : kWayTeamItems);
         RowFold<D, R> y;                            // the row's own workgroup: fold so far
         if (len <= 0) {
             store_result<D, R>(y.y, kKindZero, out_row, p, lane);

@@ -101,6 +101,14 @@ class Dev:
         return out
 
 
+SEGMENTS, CHUNKS, SPLIT, TEAM_ROWS, TEAM_ITEMS, WAVE_ROWS = 1, 2, 3, 4, 5, 6
+
+
+def way(ws) -> int:
+    """How the last launch on a workspace handed its work out (one of the above)."""
+    return int(ws[:20].view(torch.int32)[4])
+
+
 def no_expired_wait(ws=None):
     """The workspace's error word is zero: no bounded wait inside a kernel gave up (ws None: the
     library-owned workspace)."""
