@@ -10,7 +10,7 @@ import oracle
 import paper_2509_08309_amd as H
 from paper_2509_08309_amd import workloads as W
 
-from gpu_harness import TOL, Dev, bits, check_rows, no_expired_wait, selected_rows
+from gpu_harness import SEGMENTS, TOL, WAVE_ROWS, Dev, bits, check_rows, no_expired_wait, selected_rows, way
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -100,19 +100,20 @@ def test_rows_whole_or_in_chunks(Hq, D, rows, length, mode):
     assert int(ws[:16].view(torch.int32)[3].item()) == mode
 
 
-@pytest.mark.parametrize("r,D,rows,lo,hi,mode,chunks", [
-    (1, 64, 60, 0, 256, 1, None),                # a row a workgroup
-    (8, 128, 300, 0, 512, 1, None),              # whole rows through the tables
-    (1, 128, 511, 1400, 1700, 1, None),          # whole rows of several chunks
-    (8, 64, 280, 0, 600, 3, 1024),               # single chunks: up to one a wave,
-    (2, 64, 300, 200, 700, 3, 2048),             # two a wave: the second through the pool,
-    (8, 128, 300, 1900, 2048, 3, 2048),
-    (1, 128, 410, 1900, 2000, 3, 4096),          # more: the rest by tickets
-    (2, 64, 380, 1900, 2000, 3, 4096),
-    (1, 64, 40, 19000, 24000, 3, 4096),          # the same, rows of several segments
+@pytest.mark.parametrize("r,D,rows,lo,hi,mode,chunks,tokens", [       # (tokens a row of the block table holds, or as needed)
+    (1, 64, 60, 0, 256, 1, None, None),          # a row a workgroup
+    (8, 128, 300, 0, 512, 1, None, None),        # a wave a row;
+    (8, 128, 300, 0, 512, 1, None, 1024),        # behind a wider block table whole rows through the tables
+    (1, 128, 511, 1400, 1700, 1, None, None),    # whole rows of several chunks
+    (8, 64, 280, 0, 600, 3, 1024, None),         # single chunks: up to one a wave,
+    (2, 64, 300, 200, 700, 3, 2048, None),       # two a wave: the second through the pool,
+    (8, 128, 300, 1900, 2048, 3, 2048, None),
+    (1, 128, 410, 1900, 2000, 3, 4096, None),    # more: the rest by tickets
+    (2, 64, 380, 1900, 2000, 3, 4096, None),
+    (1, 64, 40, 19000, 24000, 3, 4096, None),    # the same, rows of several segments
 ])
 @pytest.mark.parametrize("pairs", [False, True])
-def test_steps_of_few_rows(r, D, rows, lo, hi, mode, chunks, pairs):
+def test_steps_of_few_rows(r, D, rows, lo, hi, mode, chunks, tokens, pairs):
     """The new rows are stored by whichever wave gets the chunk that reads them: at its first chunk,
     from the workgroup's pool, or with a ticket.  Cache and outputs are those of the store and the
     Attention in two calls."""
@@ -124,7 +125,7 @@ def test_steps_of_few_rows(r, D, rows, lo, hi, mode, chunks, pairs):
         fine = lambda n: ct // (4 if n <= 256 else 2 if n <= 1024 else 1)
         n = sum(L // 4096 * (4096 // ct) + -(-(L % 4096) // fine(L % 4096)) if L else 1 for L in lens.tolist())
         assert chunks // 2 < n <= chunks
-    w = W.make_custom(lens, 2 * r, 2, D, [1], seed=rows, device=DEV)
+    w = W.make_custom(lens, 2 * r, 2, D, [1], seed=rows, device=DEV, max_seq_len=tokens)
     kn, vn = W.new_token_rows(w)
     two, one = Dev(w), Dev(w)
     two.k, two.v = w.k_cache.clone(), w.v_cache.clone()
@@ -144,6 +145,8 @@ def test_steps_of_few_rows(r, D, rows, lo, hi, mode, chunks, pairs):
     torch.cuda.synchronize()
     no_expired_wait(ws)
     assert int(ws[:16].view(torch.int32)[3].item()) == mode
+    if rows > 256 and hi <= 512:
+        assert way(ws) == (SEGMENTS if tokens else WAVE_ROWS)
     same = lambda a, b: torch.equal(a.view(torch.int16), b.view(torch.int16))
     assert same(one.k, two.k) and same(one.v, two.v) and same(out, want)
 
@@ -171,11 +174,11 @@ def test_nobody_counts_where_nobody_draws(Hq, Hkv, D):
             assert words[:3].tolist() == [0, 1000000, 0], (lens[:3], nbytes, words.tolist())
             assert int(words[3]) in (1, 3)
     lens = [int(x) for x in rng.integers(1, 400, size=1200)]
-    w = W.make_custom(lens, Hq, Hkv, D, sel, seed=5, device=DEV)
+    w = W.make_custom(lens, Hq, Hkv, D, sel, seed=5, device=DEV, max_seq_len=1024)
     d = Dev(w)
     ws = d.workspace(Hkv)
     out = d.decode_ws(sel, ws)
-    assert ws[:16].view(torch.int32).tolist() == [0, 0, 0, 1]
+    assert ws[:20].view(torch.int32).tolist() == [0, 0, 0, 1, SEGMENTS]
     assert np.array_equal(bits(out), bits(d.decode(sel)))
 
 

@@ -11,8 +11,8 @@ import oracle
 import paper_2509_08309_amd as H
 from paper_2509_08309_amd import workloads as W
 
-from gpu_harness import (SENTINEL, TOL, Dev, as_f64, bits, check_rows, host_copy, no_expired_wait, partials_as_rows,
-                         rows_as_partials, selected_rows, unselected_rows)
+from gpu_harness import (SEGMENTS, SENTINEL, TOL, WAVE_ROWS, Dev, as_f64, bits, check_rows, host_copy, no_expired_wait,
+                         partials_as_rows, rows_as_partials, selected_rows, unselected_rows, way)
 
 pytestmark = pytest.mark.gpu
 
@@ -301,13 +301,18 @@ def test_profile_events_bracket_the_chunk_kernel():
     assert np.array_equal(bits(out), bits(ref))
 
 
-def test_batch_beyond_the_persistent_kernel_limit():
-    # more than 2048 sequences: several launches over slices of the sequences
+@pytest.mark.parametrize("table,ways", [(1024, (SEGMENTS, SEGMENTS)), (304, (WAVE_ROWS, WAVE_ROWS))])
+def test_batch_beyond_the_persistent_kernel_limit(table, ways):
+    # more than 2048 sequences: several launches over slices of the sequences (behind a narrow block
+    # table: one launch, a wave a sequence)
     rng = np.random.default_rng(43)
     lens = rng.integers(0, 300, size=4100).tolist()
-    w = W.make_custom(lens, 2, 2, 64, [1], seed=43, max_seq_len=304)
+    w = W.make_custom(lens, 2, 2, 64, [1], seed=43, max_seq_len=table)
     d = Dev(w)
     out = d.decode([1])
+    for heads, expected in zip(([1], [0, 1]), ways):
+        ws = d.workspace(len(heads))
+        assert np.array_equal(bits(d.decode_ws(heads, ws))[:, 1], bits(out)[:, 1]) and way(ws) == expected
     ref = oracle_of(w, [1])
     check_against_oracle(out, ref, w.spec, [1])
     check_untouched(out, w.spec, [1])
@@ -315,18 +320,22 @@ def test_batch_beyond_the_persistent_kernel_limit():
     assert np.array_equal(bits(full)[:, 1], bits(out)[:, 1])
 
 
-def test_many_short_sequences_and_repeat_calls():
+@pytest.mark.parametrize("table,expected", [(1024, SEGMENTS), (48, WAVE_ROWS)])
+def test_many_short_sequences_and_repeat_calls(table, expected):
     # thousands of tiny items exercise the ticket pool; repeated calls must leave its counters
-    # ready (identical bits every time)
+    # ready (identical bits every time).  Behind a narrow block table: a wave each, no counters
     rng = np.random.default_rng(44)
     lens = rng.integers(1, 40, size=1500).tolist()
-    w = W.make_custom(lens, 4, 4, 128, [0, 2, 3], seed=44, max_seq_len=48)
+    w = W.make_custom(lens, 4, 4, 128, [0, 2, 3], seed=44, max_seq_len=table)
     d = Dev(w)
     first = d.decode([0, 2, 3])
     ref = oracle_of(w, [0, 2, 3])
     check_against_oracle(first, ref, w.spec, [0, 2, 3])
+    ws = d.workspace(3)
     for _ in range(5):
         assert np.array_equal(bits(d.decode([0, 2, 3])), bits(first))
+        assert np.array_equal(bits(d.decode_ws([0, 2, 3], ws)), bits(first))
+        assert ws[:12].view(torch.int32).tolist() == [0, 0, 0] and way(ws) == expected
 
 
 # ------------------------------------------------------------------ graphs and streams
@@ -448,14 +457,18 @@ def test_split_with_the_largest_chunk():
     assert C == 3 and np.isnan(lse[0, :, 1:]).all() and not np.isnan(lse[1, :, :2]).any()
 
 
-def test_batch_at_the_persistent_kernel_limit():
-    """Exactly 2048 sequences: the largest batch the persistent kernel's tables hold."""
+@pytest.mark.parametrize("table,expected", [(1024, SEGMENTS), (208, WAVE_ROWS)])
+def test_batch_at_the_persistent_kernel_limit(table, expected):
+    """Exactly 2048 sequences: the largest batch the persistent kernel's tables hold (behind a narrow
+    block table: a wave a sequence)."""
     rng = np.random.default_rng(98)
     lens = rng.integers(1, 200, size=2048)
     hid = [1]
-    w = W.make_custom(lens, 2, 2, 64, hid, seed=99, device="cuda:0")
+    w = W.make_custom(lens, 2, 2, 64, hid, seed=99, device="cuda:0", max_seq_len=table)
     d = Dev(w)
-    out = d.decode(hid)
+    ws = d.workspace(1)
+    out = d.decode_ws(hid, ws)
+    assert way(ws) == expected
     ref = oracle_of(host_copy(w), hid)
     check_against_oracle(out, ref, w.spec, hid)
     check_untouched(out, w.spec, hid)

@@ -10,7 +10,7 @@ import oracle
 import paper_2509_08309_amd as H
 from paper_2509_08309_amd import workloads as W
 
-from gpu_harness import SENTINEL, TOL, Dev, bits, check_rows, no_expired_wait, selected_rows
+from gpu_harness import SEGMENTS, SENTINEL, TOL, WAVE_ROWS, Dev, bits, check_rows, no_expired_wait, selected_rows, way
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -30,7 +30,7 @@ def run_step(d, heads, kn, vn, ws=None):
     return out
 
 
-def check_step(w, heads, use_ws=False):
+def check_step(w, heads, use_ws=False, expected=None):
     spec = w.spec
     kn, vn = W.new_token_rows(w)
     ref_k, ref_v = oracle.kv_append(bits(w.k_cache), bits(w.v_cache), bits(kn), bits(vn),
@@ -48,6 +48,7 @@ def check_step(w, heads, use_ws=False):
     one = Dev(w)
     ws = one.workspace(len(heads)) if use_ws else None
     out_one = run_step(one, heads, kn, vn, ws)
+    assert expected is None or way(ws) == expected
     same = lambda t, r: bool(torch.equal(t.view(torch.int16).reshape(-1),
                                          torch.from_numpy(r.view(np.int16)).to(DEV).reshape(-1)))
     assert same(one.k, ref_k) and same(one.v, ref_v), "cache differs from the checker's append"
@@ -88,27 +89,29 @@ def test_step_full_size(name):
     check_step(w, list(spec.head_ids), use_ws=(name == "c3_13b_subset"))
 
 
-def test_step_many_short_rows():
+@pytest.mark.parametrize("table,expected", [(1024, SEGMENTS), (304, WAVE_ROWS)])
+def test_step_many_short_rows(table, expected):
     """Thousands of one-chunk rows: the new row is stored by the wave that publishes the chunk,
     also when chunks are published in batches and when a workgroup's first chunk is the one
-    that holds the new token."""
+    that holds the new token (behind a narrow block table: by the row's own wave)."""
     rng = np.random.default_rng(502)
     lens = rng.integers(1, 300, size=1200)
-    w = W.make_custom(lens, 4, 4, 128, [0, 1, 3], seed=503, device=DEV)
-    check_step(w, [0, 1, 3])
+    w = W.make_custom(lens, 4, 4, 128, [0, 1, 3], seed=503, device=DEV, max_seq_len=table)
+    check_step(w, [0, 1, 3], use_ws=True, expected=expected)
 
 
-@pytest.mark.parametrize("Hq,Hkv,D,B,heads,max_seq_len", [
-    (4, 2, 64, 2 * 2048 + 4, [1], 33),                # three slices of at most 2048 sequences
-    (512, 512, 64, 514, list(range(512)), 4097),      # rows of two segments: 2^18 / 512 sequences a slice
+@pytest.mark.parametrize("Hq,Hkv,D,B,heads,max_seq_len,expected", [
+    (4, 2, 64, 2 * 2048 + 4, [1], 1024, SEGMENTS),    # three slices of at most 2048 sequences
+    (4, 2, 64, 2 * 2048 + 4, [1], 33, WAVE_ROWS),     # one launch, a wave a sequence
+    (512, 512, 64, 514, list(range(512)), 4097, SEGMENTS),      # rows of two segments: 2^18 / 512 sequences a slice
 ])
-def test_step_of_more_sequences_than_a_launch_holds(Hq, Hkv, D, B, heads, max_seq_len):
+def test_step_of_more_sequences_than_a_launch_holds(Hq, Hkv, D, B, heads, max_seq_len, expected):
     """The launches after the first store their own sequences' new rows."""
     rng = np.random.default_rng(504)
-    lens = rng.integers(1, min(max_seq_len, 8192 // Hkv) + 1, size=B)
+    lens = rng.integers(1, min(max_seq_len, 48 if Hkv == 2 else 8192 // Hkv) + 1, size=B)
     lens[[0, 5]] = 0
     w = W.make_custom(lens, Hq, Hkv, D, heads, seed=505, device=DEV, max_seq_len=max_seq_len)
-    check_step(w, heads, use_ws=True)
+    check_step(w, heads, use_ws=True, expected=expected)
 
 
 @pytest.mark.parametrize("pairs", [False, True])
