@@ -1333,10 +1333,11 @@ __global__ __launch_bounds__((NW + 1) * 64)
         s.exists = (flags & kItemExists) != 0 ? 1 : 0;
         s.h.n_tok = s.exists ? n_tok : 0;
         s.head_off = PAIRS ? 0 : (int64_t)s.h.g * p.stride_head;   // pairs: single-head tiles
-        const int32_t *bt =
-            p.block_table + (int64_t)s.h.b * p.max_blocks_per_seq + s.h.t0 / kBlockTokens;
+        const int32_t *bt = p.block_table + (int64_t)s.h.b * p.max_blocks_per_seq;
+        const int last = s.h.t0 / kBlockTokens + max((s.h.n_tok + kBlockTokens - 1) / kBlockTokens - 1, 0);
         s.pad = 0;
-        s.ids = bt[min(lane, max((s.h.n_tok + kBlockTokens - 1) / kBlockTokens - 1, 0))];
+        // (a length past the block table, the caller's error, reads the table's last entry again, as in a team)
+        s.ids = bt[min(min(s.h.t0 / kBlockTokens + lane, last), p.max_blocks_per_seq - 1)];
     };
     auto q_rows = [&](const Slot &s) {
         return p.q + ((int64_t)s.h.seq * p.n_q_heads + s.h.g * R) * D;

@@ -10,7 +10,8 @@ import oracle
 import paper_2509_08309_amd as H
 from paper_2509_08309_amd import workloads as W
 
-from gpu_harness import SEGMENTS, SENTINEL, TOL, WAVE_ROWS, Dev, bits, check_rows, no_expired_wait, selected_rows, way
+from gpu_harness import (SEGMENTS, SENTINEL, TEAM_ITEMS, TEAM_ROWS, TOL, WAVE_ROWS, Dev, bits, check_rows, no_expired_wait,
+                         selected_rows, way)
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -116,15 +117,18 @@ def test_step_of_more_sequences_than_a_launch_holds(Hq, Hkv, D, B, heads, max_se
 
 @pytest.mark.parametrize("pairs", [False, True])
 @pytest.mark.parametrize("B", [3, 300])                # x 2 heads: few rows, and whole segments
-def test_step_does_not_store_past_the_block_table(B, pairs):
-    """A position past a row's two table entries is not stored, as in hetis_kv_append.  (Attention
-    reads that row's third entry: the first one of the next row, whose block exists.)"""
-    Hkv, D, mb = 2, 64, 2
+@pytest.mark.parametrize("mb,expected", [(2, (WAVE_ROWS, WAVE_ROWS)), (5, (TEAM_ROWS, WAVE_ROWS)),
+                                         (40, (TEAM_ITEMS, SEGMENTS))])
+def test_step_does_not_store_past_the_block_table(B, mb, expected, pairs):
+    """A position past a row's mb table entries is not stored, as in hetis_kv_append, and whichever way the
+    launch goes Attention reads the row's last entry once more for it, and nothing outside the table."""
+    Hkv, D, full = 2, 64, 16 * mb
     gen = torch.Generator(device=DEV)
     gen.manual_seed(506)
     bt = torch.randperm(B * mb, generator=gen, device=DEV).int().view(B, mb)
-    lens = torch.randint(17, 33, (B,), generator=gen, device=DEV).int()
-    lens[:-1:7] = 33                                   # never the last row
+    lens = torch.randint(full - 15, full + 1, (B,), generator=gen, device=DEV).int()
+    lens[::7] = full + 1
+    lens[-1] = full + 1                                # the table ends with this row
     q, kn, vn = (torch.randn((B, Hkv, D), generator=gen, device=DEV).half() for _ in range(3))
     k, v = (torch.randn((B * mb, Hkv, 16, D), generator=gen, device=DEV).half() for _ in range(2))
     shape, hid = H.make_shape(B, Hkv, Hkv, D, mb), torch.tensor([0, 1], dtype=torch.int32, device=DEV)
@@ -134,14 +138,22 @@ def test_step_does_not_store_past_the_block_table(B, pairs):
     pt = (bt[ps.long()] * Hkv + ph[:, None]).int().contiguous()
     k2, v2, out, out2 = k.clone(), v.clone(), torch.zeros_like(q), torch.zeros_like(q)
     H.check(H.hetis_kv_append(shape, kn, vn, bt, lens, hid, Hkv, B * mb, k2, v2), "append")
+    rc, need = H.hetis_attn_decode_pairs_workspace_bytes(shape, B * Hkv) if pairs else \
+        H.hetis_attn_decode_workspace_bytes(shape, Hkv)
+    H.check(rc)
+    ws = torch.zeros(need, dtype=torch.uint8, device=DEV)
     if pairs:
-        H.check(H.hetis_attn_decode_pairs_step(shape, q, kn, vn, k.view(-1, 16, D), v.view(-1, 16, D), pt, lens, ps,
-                                               ph, B * Hkv, D ** -0.5, out), "pairs step")
+        H.check(H.hetis_attn_decode_pairs_step_ws(shape, q, kn, vn, k.view(-1, 16, D), v.view(-1, 16, D), pt, lens, ps,
+                                                  ph, B * Hkv, D ** -0.5, out, ws, need), "pairs step")
     else:
-        H.check(H.hetis_attn_decode_step(shape, q, kn, vn, k, v, bt, lens, hid, Hkv, D ** -0.5, out), "step")
-    H.check(H.hetis_attn_decode(shape, q, k2, v2, bt, lens, hid, Hkv, D ** -0.5, out2), "decode")
+        H.check(H.hetis_attn_decode_step_ws(shape, q, kn, vn, k, v, bt, lens, hid, Hkv, D ** -0.5, out, ws, need), "step")
+    # the same rows behind a table that has the entry, twice
+    longer = torch.cat([bt, bt[:, -1:]], 1).contiguous()
+    H.check(H.hetis_attn_decode(H.make_shape(B, Hkv, Hkv, D, mb + 1), q, k2, v2, longer, lens, hid, Hkv, D ** -0.5, out2),
+            "decode")
     torch.cuda.synchronize()
+    no_expired_wait(ws)
     no_expired_wait()
+    assert way(ws) == expected[B > 3]
     assert torch.equal(k, k2) and torch.equal(v, v2)
-    ok = lens <= 32
-    assert torch.equal(out[ok], out2[ok])
+    assert torch.equal(out, out2)
