@@ -28,7 +28,7 @@
  *   - block_table: int32 [batch, max_blocks_per_seq]; entry j of row b is the
  *     physical block of tokens [16 j, 16 j + 16).  Entries at or beyond
  *     ceil(seq_lens[b] / 16) are never read.  Slots past the end of a sequence
- *     inside its last block are loaded but never enter a result (they may hold
+ *     inside its last block never enter a result (they may hold
  *     NaN).
  *   - seq_lens: int32 [batch], number of cached tokens including the current
  *     one; 0 <= seq_lens[b] <= 16 * max_blocks_per_seq.  Length 0 gives zeros.

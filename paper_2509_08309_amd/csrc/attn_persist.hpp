@@ -138,7 +138,7 @@ enum : int { kItemExists = 1 };
 // A chunk, decoded: what a streaming wave needs to start on it and to label its result.
 struct ChunkDesc {
     int b, g, seq;      // enumeration row (sequence, or pair), KV head, sequence of q / out rows
-    int t0;             // first token of the chunk in its sequence
+    int t0;             // first token of the chunk in its sequence, or of its last block in the table
     int n_tok;          // tokens of the chunk
     int flags;          // kItemExists, or 0: no work is left, the wave may finish
     int kind;           // kKindOut / kKindPartial / kKindZero (whole segment) or kKindFold
@@ -857,7 +857,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
         d.b = s.b;
         d.g = s.g;
         d.seq = s.seq;
-        d.t0 = s.t0 + i * s.ct;
+        d.t0 = min((s.t0 + i * s.ct) / kBlockTokens, p.max_blocks_per_seq - 1) * kBlockTokens;       // (see fill)
         d.n_tok = max(0, min(s.ct, s.n_tok - i * s.ct));
         d.flags = kItemExists;
         d.kind = s.ns > 1 ? (int)kKindFold : s.kind;
@@ -1333,11 +1333,14 @@ __global__ __launch_bounds__((NW + 1) * 64)
         s.exists = (flags & kItemExists) != 0 ? 1 : 0;
         s.h.n_tok = s.exists ? n_tok : 0;
         s.head_off = PAIRS ? 0 : (int64_t)s.h.g * p.stride_head;   // pairs: single-head tiles
-        const int32_t *bt = p.block_table + (int64_t)s.h.b * p.max_blocks_per_seq;
-        const int last = s.h.t0 / kBlockTokens + max((s.h.n_tok + kBlockTokens - 1) / kBlockTokens - 1, 0);
+        // (a length past the block table, the caller's error, reads the row's last entry again, as in a team;
+        // bounded per chunk: with a second bound in each lane, or the first entry's bound here, 240 rows of
+        // 1000 tokens of 64 dims took 15.2 us instead of 14.9, two documents x 8 heads 39.0 instead of 38.8)
+        const int j0 = s.h.t0 / kBlockTokens;
+        const int n_ids = min((s.h.n_tok + kBlockTokens - 1) / kBlockTokens, p.max_blocks_per_seq - j0);
+        const int32_t *bt = p.block_table + (int64_t)s.h.b * p.max_blocks_per_seq + j0;
         s.pad = 0;
-        // (a length past the block table, the caller's error, reads the table's last entry again, as in a team)
-        s.ids = bt[min(min(s.h.t0 / kBlockTokens + lane, last), p.max_blocks_per_seq - 1)];
+        s.ids = bt[min(lane, max(n_ids - 1, 0))];
     };
     auto q_rows = [&](const Slot &s) {
         return p.q + ((int64_t)s.h.seq * p.n_q_heads + s.h.g * R) * D;
