@@ -13,6 +13,7 @@ constexpr int kMaxQuickRows = 512;      // rows of a launch that may be handed o
 #ifndef HETIS_FINE_CHUNK_BELOW
 #define HETIS_FINE_CHUNK_BELOW 4
 #endif
+static_assert(HETIS_FINE_CHUNK_BELOW >= 4, "a segment in quarter chunks is one item of a team");
 // Between two looks of a wait, in units of 64 cycles.  The looks are few (five waves a compute unit); with
 // four units in the writer wave and two in the others 4 chats x 4 heads of 64 dims take 9.7 us
 // instead of 9.4, 15 rows of at most 96 tokens 9.3 instead of 9.1, launches of many rows the same.

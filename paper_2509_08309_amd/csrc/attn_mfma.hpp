@@ -135,8 +135,7 @@ struct MfmaPolicy {
     // longer exactly 1 in fp16: error against 64 bits 2.9e-4 instead of 2.7e-4.
     template <int MAYBE_RAGGED>
     __device__ static __forceinline__ void update(State &st, const Tile &t, const Query &q,
-                                                  float scale_log2, int lane, int n_valid,
-                                                  unsigned char *)
+                                                  float scale_log2, int lane, int n_valid)
     {
 #pragma clang fp contract(off)
         // (two copies of this code must produce the same bits)

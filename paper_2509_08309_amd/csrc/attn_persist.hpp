@@ -339,7 +339,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
     // ---- launches of few rows (p.mode == kModeSpread: fewer than kMaxQuickRows rows x heads).
     // Every wave loads all row lengths and works out in registers, without a barrier, how the
     // launch is handed out, and (streaming waves) its own first item.  One of four ways:
-    //  - lone: no more rows than workgroups, no row longer than a segment, and spread_pays() (below) says
+    //  - lone: no more rows than workgroups, no row longer than a segment, and spread_pays() (attn_combine.hpp) says
     //    no: workgroup w takes row w as a team.
     //  - team: spread_pays(), and no more items (windows of a full chunk) than workgroups: workgroup w takes item
     //    w as a team.  A wave's chain of tiles is a quarter of a chunk's, and the chunk's pieces meet in LDS.
@@ -1465,8 +1465,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
             auto steady_turn = [&](int i) {                 // whole tiles; refills stay in this chunk
 #pragma unroll
                 for (int s = 0; s < RING; ++s) {
-                    Policy::template update<kFullTile>(st, ring[s], q, p.scale_log2, lane, kBlockTokens,
-                                                   my_staging);
+                    Policy::template update<kFullTile>(st, ring[s], q, p.scale_log2, lane, kBlockTokens);
                     if constexpr (kSettle) Policy::settle(st);
                     if (kAnywhere) next_piece(i + s + 1);
                     __builtin_amdgcn_sched_barrier(0);
@@ -1505,7 +1504,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
             for (int s = 0; s < RING; ++s) {
                 if (i + s < n_my) {
                     Policy::template update<kMaybeRagged>(st, ring[s], q, p.scale_log2, lane,
-                                                  n_tok - (i + s) * kBlockTokens, my_staging);
+                                                  n_tok - (i + s) * kBlockTokens);
                     if (kAnywhere && i + s + 1 < n_my) next_piece(i + s + 1);
                 }
                 __builtin_amdgcn_sched_barrier(0);

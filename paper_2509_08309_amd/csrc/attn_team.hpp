@@ -150,8 +150,7 @@ __device__ __forceinline__ void run_pieces(const AttnParams &p, const TeamItem &
         for (; PT > RING && i + RING < lim; i += RING) {
 #pragma unroll
             for (int s = 0; s < RING; ++s) {
-                Policy::template update<kOneCopy>(st, ring[s], q, p.scale_log2, lane, n_tok - (i + s) * kBlockTokens,
-                                              staging);
+                Policy::template update<kOneCopy>(st, ring[s], q, p.scale_log2, lane, n_tok - (i + s) * kBlockTokens);
                 __builtin_amdgcn_sched_barrier(0);
                 issue(ring[s], ids[RING + s], i + RING + s, n_tok);
                 __builtin_amdgcn_sched_barrier(0);
@@ -162,8 +161,7 @@ __device__ __forceinline__ void run_pieces(const AttnParams &p, const TeamItem &
 #pragma unroll
         for (int s = 0; s < RING; ++s) {
             if (i + s < n_my)
-                Policy::template update<kOneCopy>(st, ring[s], q, p.scale_log2, lane, n_tok - (i + s) * kBlockTokens,
-                                              staging);
+                Policy::template update<kOneCopy>(st, ring[s], q, p.scale_log2, lane, n_tok - (i + s) * kBlockTokens);
             __builtin_amdgcn_sched_barrier(0);
             issue(ring[s], next_ids[s], s, n_next);
             __builtin_amdgcn_sched_barrier(0);

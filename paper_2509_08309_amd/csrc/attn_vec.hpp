@@ -222,8 +222,7 @@ struct VecPolicy {
     // kOneCopy: the masked copy for all tiles, where fetching the code costs more than the selects
     template <int MAYBE_RAGGED>
     __device__ static __forceinline__ void update(State &st, const Tile &t, const Query &q,
-                                                  float scale_log2, int lane, int n_valid,
-                                                  unsigned char *)
+                                                  float scale_log2, int lane, int n_valid)
     {
         if (MAYBE_RAGGED == kOneCopy)
             vec_tile_update<D, R, true>(st, t, q.h, scale_log2, lane / (D / 8), n_valid);

@@ -25,10 +25,7 @@ static_assert(HETIS_DECODE_SEG_TOKENS % HETIS_DECODE_CHUNK_TOKENS == 0 &&
 static_assert(HETIS_DECODE_SEG_TOKENS > HETIS_DECODE_CHUNK_TOKENS &&
               HETIS_DECODE_SEG_TOKENS_GQA > HETIS_DECODE_CHUNK_TOKENS_GQA,
               "the decode path folds chunks inside a workgroup (the folded-in store relies on it)");
-#ifndef HETIS_STREAM_WAVES
-#define HETIS_STREAM_WAVES 4
-#endif
-constexpr int kVecWaves = HETIS_STREAM_WAVES;
+constexpr int kVecWaves = 4;    // streaming waves of a workgroup: a chunk has as many pieces (attn_team.hpp)
 constexpr int kWgsPerCu = 1;    // persistent workgroups per compute unit
 // Rows (sequences, or pairs) per launch: what the persistent kernel's LDS tables hold.  Larger
 // batches run as several launches over slices of the rows.
