@@ -134,13 +134,12 @@ constexpr int kTicketBatch = 8;         // tickets per device atomic while segme
 #ifndef HETIS_STATIC_FLAT_X16
 #define HETIS_STATIC_FLAT_X16 14
 #endif
-enum : int { kItemExists = 1 };
 // A chunk, decoded: what a streaming wave needs to start on it and to label its result.
 struct ChunkDesc {
     int b, g, seq;      // enumeration row (sequence, or pair), KV head, sequence of q / out rows
     int t0;             // first token of the chunk in its sequence, or of its last block in the table
     int n_tok;          // tokens of the chunk
-    int flags;          // kItemExists, or 0: no work is left, the wave may finish
+    int n_ids;          // its entries of the block table, one or more, or 0: no work is left, the wave may finish
     int kind;           // kKindOut / kKindPartial / kKindZero (whole segment) or kKindFold
     int dest;           // Out / Zero: first of the R rows in `out`; Partial: slot in the partial
                         // buffers; Fold: the segment's fold slot
@@ -857,9 +856,12 @@ __global__ __launch_bounds__((NW + 1) * 64)
         d.b = s.b;
         d.g = s.g;
         d.seq = s.seq;
-        d.t0 = min((s.t0 + i * s.ct) / kBlockTokens, p.max_blocks_per_seq - 1) * kBlockTokens;       // (see fill)
+        // (a length past the block table, the caller's error, reads the row's last entry again, as in a team.
+        // Bounded here: with the bounds where the ids are loaded the step of 145 pairs, r = 8, took 40.1 us
+        // instead of 39.8, with one in each lane 240 rows of 1000 tokens of 64 dims 15.2 instead of 14.9.)
+        d.t0 = min((s.t0 + i * s.ct) / kBlockTokens, p.max_blocks_per_seq - 1) * kBlockTokens;
         d.n_tok = max(0, min(s.ct, s.n_tok - i * s.ct));
-        d.flags = kItemExists;
+        d.n_ids = max(1, min((d.n_tok + kBlockTokens - 1) / kBlockTokens, p.max_blocks_per_seq - d.t0 / kBlockTokens));
         d.kind = s.ns > 1 ? (int)kKindFold : s.kind;
         d.dest = s.ns > 1 ? slot : s.dest;
         d.cs = i;
@@ -1318,7 +1320,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
                   "Slot has no padding");
     // chunk descriptor -> the wave's (uniform) bookkeeping, and the load of its block ids
     auto fill = [&](const ChunkDesc &d, Slot &s) {
-        const int flags = __builtin_amdgcn_readfirstlane(d.flags);
+        const int n_ids = __builtin_amdgcn_readfirstlane(d.n_ids);
         const int n_tok = __builtin_amdgcn_readfirstlane(d.n_tok);
         s.h.b = __builtin_amdgcn_readfirstlane(d.b);
         s.h.g = __builtin_amdgcn_readfirstlane(d.g);
@@ -1330,17 +1332,13 @@ __global__ __launch_bounds__((NW + 1) * 64)
         s.h.nseg = __builtin_amdgcn_readfirstlane(d.nseg);
         s.h.out_row = __builtin_amdgcn_readfirstlane(d.out_row);
         s.h.len = __builtin_amdgcn_readfirstlane(d.len);
-        s.exists = (flags & kItemExists) != 0 ? 1 : 0;
+        s.exists = n_ids > 0 ? 1 : 0;
         s.h.n_tok = s.exists ? n_tok : 0;
         s.head_off = PAIRS ? 0 : (int64_t)s.h.g * p.stride_head;   // pairs: single-head tiles
-        // (a length past the block table, the caller's error, reads the row's last entry again, as in a team;
-        // bounded per chunk: with a second bound in each lane, or the first entry's bound here, 240 rows of
-        // 1000 tokens of 64 dims took 15.2 us instead of 14.9, two documents x 8 heads 39.0 instead of 38.8)
-        const int j0 = s.h.t0 / kBlockTokens;
-        const int n_ids = min((s.h.n_tok + kBlockTokens - 1) / kBlockTokens, p.max_blocks_per_seq - j0);
-        const int32_t *bt = p.block_table + (int64_t)s.h.b * p.max_blocks_per_seq + j0;
+        const int32_t *bt =
+            p.block_table + (int64_t)s.h.b * p.max_blocks_per_seq + s.h.t0 / kBlockTokens;
         s.pad = 0;
-        s.ids = bt[min(lane, max(n_ids - 1, 0))];
+        s.ids = bt[min(lane, max(n_ids, 1) - 1)];
     };
     auto q_rows = [&](const Slot &s) {
         return p.q + ((int64_t)s.h.seq * p.n_q_heads + s.h.g * R) * D;
@@ -1360,7 +1358,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
         }
         if (lane == 0) report_error(p.control, kErrMailboxWait);
     };
-    // next chunk from the workgroup's pool (flags 0 = none left)
+    // next chunk from the workgroup's pool (no ids: none left)
     auto take_chunk = [&]() {
         int i = 0;
         if (lane == 0)
