@@ -50,6 +50,11 @@ struct MfmaPolicy {
     // 150 to 18 700, r = 4, 26.5 -> 24.4, 768 of 2176, r = 8, 139.7 -> 138.6; but 12 of 10k to 32k, r = 8, 32.5 -> 32.9,
     // 300 of 100 to 600 20.9 -> 21.3.  (32 KB, while a chunk was one piece: slower throughout.)
     static constexpr int ring(bool) { return D_ == 64 ? 4 : 3; }
+    // In split calls, whose chunks are one piece, short loops count for more: 24 rows of up to 26 tokens of 64 dims
+    // (r = 4) 10.6 us with four pairs, 9.9 with three, 9.7 with two; 240 of up to 200 15.1, 14.2, 14.1; 24 of 300 to
+    // 900 21.1, 20.6, 20.4; but 160 of 4k to 16k 81.0, 80.7, 83.3.  128 dims, three and two: 24 of up to 26 10.9 and
+    // 10.5, of 300 to 900 34.1 and 33.6; 160 of 4k to 16k 141.2 and 143.9 (r = 8 149.8 and 150.3).
+    static constexpr int ring_split = D_ == 64 ? 3 : 2;
 
     // of a team's wave: two copies of the arithmetic of a tile (4: 16 rows of 300 to 1200, r = 4, 16.8 -> 17.7)
     static constexpr int kTeamRing = 2;

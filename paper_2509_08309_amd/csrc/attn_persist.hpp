@@ -1561,7 +1561,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
     };
     if constexpr (CAN_SPLIT) {
         if (split_mode) {
-            stream(IntTag<Policy::ring(true)>{}, IntTag<1>{});
+            stream(IntTag<Policy::ring_split>{}, IntTag<1>{});
             return;
         }
     }

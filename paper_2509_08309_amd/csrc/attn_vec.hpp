@@ -184,6 +184,7 @@ struct VecPolicy {
     // of a team's wave, whose piece is four tiles: a second turn costs less than twice the code (4: 32 rows of 600
     // tokens 11.0 -> 11.5, 16 of 2000 10.7 -> 11.2)
     static constexpr int kTeamRing = 2;
+    static constexpr int ring_split = ring(true);
     using Tile = TileRegs<D>;
     using State = VecState<D, R>;
     struct Query {

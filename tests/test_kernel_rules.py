@@ -92,8 +92,11 @@ def test_division_by_a_multiplication(tmp_path, first, last):
 
 @pytest.mark.parametrize("R", [4, 8])
 def test_depth_of_the_ring_on_the_mfma_path(tmp_path, R):
-    """16 KB of tiles a wave with 64 dims, 24 KB with 128, in every launch."""
+    """16 KB of tiles a wave with 64 dims, 24 KB with 128, in decode calls of every size; less in split calls."""
     assert_compiles(tmp_path, f"""
         static_assert(MfmaPolicy<64, {R}>::ring(true) == 4 && MfmaPolicy<64, {R}>::ring(false) == 4, "16 KB");
         static_assert(MfmaPolicy<128, {R}>::ring(true) == 3 && MfmaPolicy<128, {R}>::ring(false) == 3, "24 KB");
+        static_assert(MfmaPolicy<64, {R}>::ring_split == 3 && MfmaPolicy<128, {R}>::ring_split == 2, "12 and 16 KB");
+        static_assert(VecPolicy<64, 1>::ring_split == VecPolicy<64, 1>::ring(true) &&
+                      VecPolicy<128, 2>::ring_split == VecPolicy<128, 2>::ring(true), "the deep one");
     """)
