@@ -135,7 +135,7 @@ struct MfmaPolicy {
     // brought to a new maximum only in tiles that have one.  One request of 1000 tokens, 2 groups of 8
     // heads of 128 dims x 4 20.7 -> 18.1 us, 16 x 4 groups of 4 heads of 128 20.5 -> 18.0, of 64 16.6 ->
     // 15.2, 16 x 4 of 8 heads, 700 to 2000 tokens, 22.1 -> 20.3; 768 rows of 2176, which wait for HBM,
-    // 139.7 -> 138.6, but 800 rows of 1100 of 64 dims (r = 4; eight bytes a load) 46.0 -> 46.5.  Letting the
+    // within 1 %, but 800 rows of 1100 of 64 dims (r = 4; eight bytes a load) 46.0 -> 46.5.  Letting the
     // maximum lag behind by up to 8 saves another 3 % of the small ones, but the largest weight is then no
     // longer exactly 1 in fp16: error against 64 bits 2.9e-4 instead of 2.7e-4.
     template <int MAYBE_RAGGED>

@@ -53,9 +53,10 @@
 // Pieces.  A chunk is computed in up to four pieces (decode_piece_tokens) with sums of their own, folded lane
 // by lane in ascending order, so that a chunk gives the same bits whether one wave computes it or four.  A
 // fold costs a wave 0.1 to 0.2 us a piece: nothing in launches of many rows, which wait for HBM (1664 rows of
-// 1069 tokens 146.0 -> 144.8, 768 of 2176 with 8 heads 139.0 -> 139.3), 1 to 2 % in some of 300 to 400 rows
-// (360 rows of 300 to 2000 tokens, r = 2, 45.2 -> 45.9; 400 of 300 to 1600 of 64 dims 28.1 -> 28.6), against 10
-// to 40 % gained where four waves share a chunk.
+// 1069 tokens, 768 of 2176 with 8 heads: within 0.5 %), 1 to 3 % in some of 100 to 500 rows, a wave a chunk (252 of
+// 100 to 400 tokens, r = 2, 64 dims 12.0 -> 12.2; 400 of 300 to 1600 of 64 dims 28.4 -> 28.7), against 10 to 40 %
+// gained where four waves share a chunk.  (The first piece's fold changes nothing, but taking its state over as
+// it is takes as many instructions as that fold: 28 launches 1.132 times as fast as before pieces, not 1.136.)
 //
 // A workgroup is NW streaming waves plus one writer wave; after the prologue they never
 // meet at a barrier.

@@ -7,8 +7,7 @@
 //   - q.k is a v_dot2 chain per lane followed by a DPP sum over the D/8 lanes of a row;
 //   - each group of D/8 lanes runs its own online softmax over the tokens it sees
 //     (exp2 domain, fp32), so p never leaves registers between q.k and p.v;
-//   - the lane groups of a wave are merged once per chunk, in a fixed order, through
-//     shuffles.
+//   - the lane groups of a wave are merged once per chunk, in a fixed order, by lane swaps.
 // Nothing depends on how many heads were selected: the result for one (sequence, head)
 // is a function of that sequence's length alone.
 #pragma once
