@@ -1377,8 +1377,10 @@ __global__ __launch_bounds__((NW + 1) * 64)
         return none;
     };
 
-    // The lane's number for what runs once a chunk: addresses that follow from it would be worked out ahead of the
-    // streaming loop and kept, in 18 of the registers that the tiles of the MFMA path need.
+    // The lane's number for the wave's last chunk, which it stores itself: addresses that follow from it would be worked
+    // out ahead of the streaming loop and kept, in 16 of the registers that the tiles of the MFMA path need.  (For
+    // the hand-over of the others as well: the step of 145 pairs, r = 8, 40.1 us instead of 40.0, 8 rows of 500 to
+    // 1500 15.6 instead of 15.3.)
     auto lane_again = [&]() {
         int l = lane;
         if constexpr (R >= 4) asm volatile("" : "+v"(l));
@@ -1543,7 +1545,7 @@ __global__ __launch_bounds__((NW + 1) * 64)
                 return;
             }
             // hand the finished chunk to the writer
-            if (cur.h.kind != kKindZero) Policy::finish(sum, mb.o, mb.lse, lane_again());
+            if (cur.h.kind != kKindZero) Policy::finish(sum, mb.o, mb.lse, lane);
             if (lane == 0) {
                 mb.kind = cur.h.kind;
                 mb.dest = cur.h.dest;
